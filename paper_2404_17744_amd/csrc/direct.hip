@@ -36,7 +36,41 @@ __global__ __launch_bounds__(NT) void hadamard64_kernel(const double* W, const d
     H[i] = W[i] * Gt[i];
 }
 
+// A <- W o A and B <- W^T o B (either may be null), one 32 x 32 tile per workgroup: W
+// is read once along its rows, its transpose goes through LDS
+__global__ __launch_bounds__(NT) void hadamard_pair_kernel(const double* __restrict__ W,
+                                                           double* __restrict__ A,
+                                                           double* __restrict__ B, int naux) {
+  __shared__ double t[PT][PT + 1];
+  const int64_t off = (int64_t)blockIdx.z * naux * naux;
+  const int q0 = blockIdx.y * PT, s0 = blockIdx.x * PT;
+  const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;   // 32 x 8
+#pragma unroll
+  for (int r = ty; r < PT; r += NT / PT) {
+    const int Q = q0 + r, S = s0 + tx;
+    const bool in = Q < naux && S < naux;
+    const int64_t at = off + (int64_t)Q * naux + S;
+    const double w = in ? W[at] : 0.0;
+    t[r][tx] = w;
+    if (in && A != nullptr) A[at] *= w;
+  }
+  if (B == nullptr) return;
+  __syncthreads();
+#pragma unroll
+  for (int r = ty; r < PT; r += NT / PT) {
+    const int S = s0 + r, Q = q0 + tx;   // element (S, Q) of the transposed tile
+    if (S < naux && Q < naux) B[off + (int64_t)S * naux + Q] *= t[tx][r];
+  }
+}
+
 }  // namespace
+
+hipError_t hadamard_pair(const double* W, double* A, double* B, int naux, int nb, hipStream_t s) {
+  if (naux <= 0 || nb <= 0 || (A == nullptr && B == nullptr)) return hipSuccess;
+  const unsigned nt = (unsigned)((naux + PT - 1) / PT);
+  hadamard_pair_kernel<<<dim3(nt, nt, nb), NT, 0, s>>>(W, A, B, naux);
+  return hipGetLastError();
+}
 
 hipError_t bubble_pi(const double* Gt, const double* Gbt, double* Pi, int naux, int nb,
                      hipStream_t s) {

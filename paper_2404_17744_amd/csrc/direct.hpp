@@ -13,4 +13,7 @@ hipError_t bubble_pi(const double* Gt, const double* Gbt, double* Pi, int naux, 
 // H[i] = W[i] * Gt[i], i < len (H may alias W).
 hipError_t hadamard64(const double* W, const double* Gt, double* H, int64_t len, hipStream_t s);
 
+// A[b] <- W[b] o A[b] and B[b] <- W[b]^T o B[b] for nb matrices [naux][naux] (A or B
+// may be null).
+hipError_t hadamard_pair(const double* W, double* A, double* B, int naux, int nb, hipStream_t s);
 }  // namespace thcsox

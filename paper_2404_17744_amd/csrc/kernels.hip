@@ -240,15 +240,46 @@ __global__ void energy_final_kernel(const double* tr, const double* w, int m, do
   }
 }
 
-__global__ __launch_bounds__(NT) void weighted_block_sum_kernel(const double* __restrict__ Pi,
-                                                                const double* __restrict__ w,
-                                                                int nb, int64_t len,
-                                                                double* __restrict__ Pi0,
-                                                                int accumulate) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < len; e += (int64_t)gridDim.x * NT) {
-    double acc = accumulate ? Pi0[e] : 0.0;
-    for (int b = 0; b < nb; ++b) acc = fma(w[b], Pi[(int64_t)b * len + e], acc);
-    Pi0[e] = acc;
+// Pi0 (+)= sum_l w[l] Pi_l + w[m-1-l] Pi_l^T over nb matrices: one 32 x 32 tile per
+// workgroup, the transposed sum taken from the mirrored tile (read along its rows)
+// through LDS.  Bound by reading each Pi twice.
+constexpr int WT = 32;
+__global__ __launch_bounds__(NT) void weighted_pair_sum_kernel(const double* __restrict__ Pi,
+                                                               const double* __restrict__ w, int m,
+                                                               int l0, int nb, int naux,
+                                                               double* __restrict__ Pi0,
+                                                               int accumulate) {
+  __shared__ double t[WT][WT + 1];
+  const int i0 = blockIdx.y * WT, j0 = blockIdx.x * WT;
+  const int tx = threadIdx.x % WT, ty = threadIdx.x / WT;   // 32 x 8
+  const int64_t aa = (int64_t)naux * naux;
+  constexpr int PER = WT * WT / NT;
+  double here[PER] = {}, there[PER] = {};
+#pragma unroll 4
+  for (int b = 0; b < nb; ++b) {
+    const int l = l0 + b;
+    const double wl = w[l], wu = m - 1 - l == l ? 0.0 : w[m - 1 - l];
+    const double* P = Pi + b * aa;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int r = ty + e * (NT / WT);
+      if (i0 + r < naux && j0 + tx < naux)
+        here[e] = fma(wl, P[(int64_t)(i0 + r) * naux + j0 + tx], here[e]);
+      if (j0 + r < naux && i0 + tx < naux)
+        there[e] = fma(wu, P[(int64_t)(j0 + r) * naux + i0 + tx], there[e]);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) t[ty + e * (NT / WT)][tx] = there[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int r = ty + e * (NT / WT);
+    if (i0 + r < naux && j0 + tx < naux) {
+      double* d = Pi0 + (int64_t)(i0 + r) * naux + j0 + tx;
+      const double v = here[e] + t[tx][r];
+      *d = accumulate ? *d + v : v;
+    }
   }
 }
 
@@ -261,12 +292,11 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 }  // namespace
 
-hipError_t weighted_block_sum(const double* Pi, const double* w, int nb, int64_t len,
-                              double* Pi0, int accumulate, hipStream_t s) {
-  if (len <= 0) return hipSuccess;
-  const int64_t b = (len + NT - 1) / NT;
-  weighted_block_sum_kernel<<<(unsigned)(b > 4096 ? 4096 : b), NT, 0, s>>>(Pi, w, nb, len, Pi0,
-                                                                          accumulate);
+hipError_t weighted_pair_sum(const double* Pi, const double* w, int m, int l0, int nb, int naux,
+                             double* Pi0, int accumulate, hipStream_t s) {
+  if (naux <= 0 || nb <= 0) return hipSuccess;
+  const unsigned nt = cdiv(naux, WT);
+  weighted_pair_sum_kernel<<<dim3(nt, nt), NT, 0, s>>>(Pi, w, m, l0, nb, naux, Pi0, accumulate);
   return hipGetLastError();
 }
 

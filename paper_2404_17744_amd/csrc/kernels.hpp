@@ -184,10 +184,10 @@ hipError_t khatri_rao(const double* X, int n, int naux, int q0, int q1, double* 
 hipError_t gj_inverse_real(const double* M, int n, double* Minv, double2* Am, int* piv, int* perm,
                            int* flag, hipStream_t s);
 
-// Pi0[e] (+)= sum_b w[b] Pi[b][e] over nb blocks of len elements, b in order
-// (accumulate = 0: Pi0 is overwritten).
-hipError_t weighted_block_sum(const double* Pi, const double* w, int nb, int64_t len,
-                              double* Pi0, int accumulate, hipStream_t s);
+// Pi0 (+)= sum_b w[l] Pi[b] + w[m-1-l] Pi[b]^T, l = l0 + b, over nb matrices [naux][naux],
+// b in order (accumulate = 0: Pi0 is overwritten); the middle point l = m-1-l once.
+hipError_t weighted_pair_sum(const double* Pi, const double* w, int m, int l0, int nb, int naux,
+                             double* Pi0, int accumulate, hipStream_t s);
 // A[i][i] += 1 for i < n (row-major n x n).
 hipError_t add_identity(double* A, int n, hipStream_t s);
 

@@ -43,6 +43,11 @@ int fail(int code, const std::string& msg) { return set_error(code, msg); }
 constexpr double SYM_RTOL_F64 = 1e-12;
 constexpr double SYM_RTOL_MIXED = 1e-10;
 
+// V counts as symmetric when max |V - V^T| <= V_RTOL max |V| (a few units in the last
+// place): the direct term then takes W(beta - tau) as the transpose of W(tau), which
+// differs from the product with V as given by no more than the product's own rounding.
+constexpr double V_RTOL = 0x1p-50;
+
 #define HIP_TRY(expr)                                                                  \
   do {                                                                                 \
     hipError_t e_ = (expr);                                                            \
@@ -118,11 +123,13 @@ struct thcsox_plan_s {
 
   double* X = nullptr;      // [n][naux]
   double* V = nullptr;      // [naux][naux] (the direct term)
-  double* dbuf = nullptr;   // direct term: 3 x [tbd][naux][naux], allocated on first use
+  double* dbuf = nullptr;   // direct term: dbufs x [tbd][naux][naux], allocated on first use
   double* ebuf = nullptr;   // basis energy: 2 x [ntau][n][n] coefficients, on first use
   double* ecoef = nullptr;  // basis energy: [2][ntau][ntau] (rows reversed, then as given)
   double* esign = nullptr;  // basis energy: [ntau]
-  int tbd = 0;              // tau points per direct-term batch
+  int tbd = 0;              // tau points (or mirrored pairs of them) per direct-term batch
+  int dbufs = 0;            // buffers per batch entry: 4 with mirrored pairs, else 3
+  bool vsym = false;        // V symmetric to rounding: W of mirrored points are transposes
   // screened exchange (allocated on first use): the second U (from the screened
   // core W, same layout and precision as U) and its max |.|, the static
   // polarization Pi0, 1 + V Pi0 and its inverse, and the Gauss-Jordan work
@@ -290,9 +297,9 @@ int build_u(thcsox_plan_s* p, const double* V, void* Uout, unsigned long long* a
 }
 
 // Sigma[b] = X Sig_thc[b] X^T for nb tau points at once (FP64 matrix cores);
-// Sig_thc[b] = St + b * st_stride, Sigma[b] = Sig + b * n * n (beta_out = 1: Sigma[b] +=).
+// Sig_thc[b] = St + b * st_stride, Sigma[b] = Sig + b * dir * n * n (beta_out = 1: Sigma[b] +=).
 int backproject_batch(thcsox_plan_s* p, const double* St, int64_t st_stride, double* Sig,
-                      int nb, double beta_out = 0.0, double alpha_out = 1.0) {
+                      int nb, double beta_out = 0.0, double alpha_out = 1.0, int dir = 1) {
   const int n = p->n, naux = p->naux;
   const hipStream_t s = p->stream;
   Gemm64Args b{};
@@ -304,7 +311,7 @@ int backproject_batch(thcsox_plan_s* p, const double* St, int64_t st_stride, dou
   b.N = n;
   b.A = p->T1; b.a_i = naux; b.a_k = 1; b.a_b = (int64_t)n * naux;
   b.B = p->X; b.b_k = 1; b.b_j = naux; b.b_b = 0;
-  b.C = Sig; b.c_i = n; b.c_j = 1; b.cj_in = n; b.cj_out = 0; b.c_b = (int64_t)n * n;
+  b.C = Sig; b.c_i = n; b.c_j = 1; b.cj_in = n; b.cj_out = 0; b.c_b = dir * (int64_t)n * n;
   b.alpha = alpha_out;
   b.beta = beta_out;   // 1: add to what Sig holds
   HIP_TRY(gemm64(b, s));
@@ -498,44 +505,100 @@ int bubble_batch(thcsox_plan_s* p, const double* G, int k0, int k1) {
   return 0;
 }
 
+// W = V Pi V for nb matrices (Pi in src, W in dst, V Pi in tmp).
+int screen_both_sides(thcsox_plan_s* p, const double* src, double* tmp, double* dst, int nb) {
+  const int naux = p->naux;
+  const int64_t aa = (int64_t)naux * naux;
+  Gemm64Args g{};
+  g.M = naux; g.N = naux; g.K = naux; g.batch = nb; g.alpha = 1.0; g.beta = 0.0;
+  g.A = p->V; g.a_i = naux; g.a_k = 1; g.a_b = 0;
+  g.B = src; g.b_k = naux; g.b_j = 1; g.b_b = aa;
+  g.C = tmp; g.c_i = naux; g.c_j = 1; g.cj_in = naux; g.cj_out = 0; g.c_b = aa;
+  HIP_TRY(gemm64(g, p->stream));
+  g.A = tmp; g.a_i = naux; g.a_k = 1; g.a_b = aa;
+  g.B = p->V; g.b_k = naux; g.b_j = 1; g.b_b = 0;
+  g.C = dst;
+  HIP_TRY(gemm64(g, p->stream));
+  return 0;
+}
+
 // GF2 direct (bubble) term for tau points k0 <= k < k1 (k1 - k0 <= tbd), FP64:
 //   Gt = X^T G[k] X, Gbt = X^T G[m-1-k] X, Pi = Gt o Gbt^T, W = V Pi V,
 //   Sigma[k] = X (W o Gt) X^T.
 int direct_batch(thcsox_plan_s* p, const double* G, double* Sigma, int k0, int k1,
                  bool accumulate) {
   const int n = p->n, naux = p->naux, nb = k1 - k0;
-  const hipStream_t s = p->stream;
   const int64_t nn = (int64_t)n * n, aa = (int64_t)naux * naux;
   double* bufA = p->dbuf;                          // Gt
   double* bufB = p->dbuf + (int64_t)p->tbd * aa;   // Gbt, then V Pi
   double* bufC = bufB + (int64_t)p->tbd * aa;      // Pi, then W, then W o Gt
   TRY(bubble_batch(p, G, k0, k1));
-  // W = (V Pi) V
-  Gemm64Args g{};
-  g.M = naux; g.N = naux; g.K = naux; g.batch = nb; g.alpha = 1.0; g.beta = 0.0;
-  g.A = p->V; g.a_i = naux; g.a_k = 1; g.a_b = 0;
-  g.B = bufC; g.b_k = naux; g.b_j = 1; g.b_b = aa;
-  g.C = bufB; g.c_i = naux; g.c_j = 1; g.cj_in = naux; g.cj_out = 0; g.c_b = aa;
-  HIP_TRY(gemm64(g, s));
-  g.A = bufB; g.a_i = naux; g.a_k = 1; g.a_b = aa;
-  g.B = p->V; g.b_k = naux; g.b_j = 1; g.b_b = 0;
-  g.C = bufC;
-  HIP_TRY(gemm64(g, s));
-  HIP_TRY(hadamard64(bufC, bufA, bufC, (int64_t)nb * aa, s));
+  TRY(screen_both_sides(p, bufC, bufB, bufC, nb));
+  HIP_TRY(hadamard64(bufC, bufA, bufC, (int64_t)nb * aa, p->stream));
   return backproject_batch(p, bufC, aa, Sigma + (int64_t)k0 * nn, nb, accumulate ? 1.0 : 0.0);
 }
 
-// The direct term's three batch buffers of naux^2 per tau point (also the
-// screened exchange's polarization batches), allocated on first use: about
-// 1 GB per batch at most, and no more than what the workspace limit leaves
-// (alloc refuses one point that does not fit with THCSOX_ENOMEM).
+// The same for the mirrored pairs (l, m-1-l), l0 <= l < l1 <= (m+1)/2: Pi[m-1-l] =
+// Pi[l]^T, and with a symmetric V also W[m-1-l] = W[l]^T, so one W serves both
+// points.  lo / hi: write Sigma[l] / Sigma[m-1-l] (hi is off for the middle point
+// of an odd grid).  W always comes from the lower point, so that a slice of the
+// grid gives the same bits as the whole.  The two products of W are most of the term's
+// flops: at n = 300, naux = 1800 the 100-point grid takes 33.6 ms by pairs, 61.0 by points.
+int direct_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int l0, int l1, bool lo, bool hi,
+                 bool accumulate) {
+  const int n = p->n, naux = p->naux, nb = l1 - l0;
+  const int64_t nn = (int64_t)n * n, aa = (int64_t)naux * naux, step = (int64_t)p->tbd * aa;
+  double* bufA = p->dbuf;          // Gt[l], then W o Gt[l]
+  double* bufB = bufA + step;      // Gt[m-1-l], then W^T o Gt[m-1-l]
+  double* bufC = bufB + step;      // Pi, then W
+  double* bufD = bufC + step;      // V Pi
+  const double beta = accumulate ? 1.0 : 0.0;
+  TRY(bubble_batch(p, G, l0, l1));
+  TRY(screen_both_sides(p, bufC, bufD, bufC, nb));
+  HIP_TRY(hadamard_pair(bufC, lo ? bufA : nullptr, hi ? bufB : nullptr, naux, nb, p->stream));
+  if (lo) TRY(backproject_batch(p, bufA, aa, Sigma + (int64_t)l0 * nn, nb, beta));
+  if (hi)
+    TRY(backproject_batch(p, bufB, aa, Sigma + (int64_t)(p->m - 1 - l0) * nn, nb, beta, 1.0, -1));
+  return 0;
+}
+
+// All tau points k_begin <= k < k_end by mirrored pairs: the lower points l of the
+// pairs the range touches form one run, cut where a pair is only half inside it.
+int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_begin, int k_end,
+                       bool accumulate) {
+  const int m = p->m, half = (m + 1) / 2;
+  auto lo_in = [&](int l) { return l >= k_begin && l < k_end; };
+  auto hi_in = [&](int l) { return m - 1 - l != l && m - 1 - l >= k_begin && m - 1 - l < k_end; };
+  for (int l = 0; l < half;) {
+    const bool lo = lo_in(l), hi = hi_in(l);
+    int e = l + 1;
+    while (e < half && e - l < p->tbd && lo_in(e) == lo && hi_in(e) == hi) ++e;
+    if (lo || hi) TRY(direct_pairs(p, G, Sigma, l, e, lo, hi, accumulate));
+    l = e;
+  }
+  return 0;
+}
+
+// The direct term's batch buffers of naux^2 per entry (also the screened exchange's
+// polarization batches), allocated on first use: about 1 GB per batch at most, and
+// no more than what the workspace limit leaves.  Three per tau point, or four per
+// mirrored pair of them where V is symmetric; under a limit the pairs take no more
+// memory than the points would (alloc refuses one point that does not fit with
+// THCSOX_ENOMEM).
 int ensure_direct_buffers(thcsox_plan_s* p) {
   if (p->dbuf != nullptr) return 0;
-  const double per_tau = 3.0 * 8.0 * (double)p->naux * p->naux;
+  const double one = 8.0 * (double)p->naux * p->naux;
   double cap = 1.0e9;
   if (p->limit) cap = std::min(cap, (double)p->limit - (double)p->bytes - 256.0);
-  p->tbd = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / per_tau)));
-  return p->alloc(&p->dbuf, (size_t)3 * p->tbd * p->naux * p->naux);
+  const int points = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / (3.0 * one))));
+  int pairs = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / (4.0 * one))));
+  if (p->limit) pairs = 3 * points / 4;
+  const bool use_pairs = p->vsym && p->m > 1 && pairs > 0;
+  p->tbd = use_pairs ? std::min(pairs, (p->m + 1) / 2) : points;
+  const int bufs = use_pairs ? 4 : 3;
+  TRY(p->alloc(&p->dbuf, (size_t)bufs * p->tbd * p->naux * p->naux));
+  p->dbufs = bufs;
+  return 0;
 }
 
 // Per-call preparation of G for the exchange contractions: max |G[k]| of every
@@ -756,7 +819,18 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
                           hipMemcpyDeviceToDevice, s)))
     return hip_bail(e, "copy V");
   if ((rc = build_u(p, V_dev, p->U, p->amax, p->norm2))) return bail(rc);
+  // is V symmetric to rounding?  (max |V - V^T| and max |V| in two per-tau slots
+  // that every later call clears before it uses them)
+  unsigned long long vs[2] = {0, 0};
+  if ((e = asym64(p->V, naux, 1, p->am_asym(), s)) || (e = fill_u64(p->am_g(), 1, 0ull, s)) ||
+      (e = absmax64(p->V, (int64_t)naux * naux, 0, 1, p->am_g(), s)) ||
+      (e = hipMemcpyAsync(&vs[0], p->am_asym(), sizeof(vs[0]), hipMemcpyDeviceToHost, s)) ||
+      (e = hipMemcpyAsync(&vs[1], p->am_g(), sizeof(vs[1]), hipMemcpyDeviceToHost, s)))
+    return hip_bail(e, "symmetry of V");
   if ((e = hipStreamSynchronize(s))) return hip_bail(e, "plan synchronise");
+  double vd[2];
+  std::memcpy(vd, vs, sizeof(vd));
+  p->vsym = vd[0] <= V_RTOL * vd[1];
   *out = p;
   return 0;
 }
@@ -809,6 +883,8 @@ int thcsox_sigma_direct(thcsox_plan_t p, const double* G_dev, double* Sigma_dev,
   const char* s0 = reinterpret_cast<const char*>(Sigma_dev);
   if (s0 < g0 + gbytes && g0 < s0 + gbytes) return fail(THCSOX_EINVAL, "Sigma aliases G");
   TRY(ensure_direct_buffers(p));
+  if (p->dbufs == 4)
+    return direct_range_pairs(p, G_dev, Sigma_dev, k_begin, k_end, accumulate != 0);
   for (int k = k_begin; k < k_end; k += p->tbd)
     TRY(direct_batch(p, G_dev, Sigma_dev, k, std::min(k_end, k + p->tbd), accumulate != 0));
   return 0;
@@ -831,12 +907,14 @@ int thcsox_static_screening(thcsox_plan_t p, const double* G_dev, double* W_dev)
     TRY(p->alloc(&p->Am, (size_t)aa));
     TRY(p->alloc(&p->gj, (size_t)2 * naux + 1));
   }
-  // Pi0 = sum_k w_k Pi(tau_k), batch by batch, in the order of k
+  // Pi0 = sum_k w_k Pi(tau_k) over the mirrored pairs, batch by batch: Pi(tau_{m-1-l})
+  // is the transpose of Pi(tau_l); the middle point of an odd grid has no partner
   const double* bufC = p->dbuf + 2 * (int64_t)p->tbd * aa;
-  for (int k0 = 0; k0 < m; k0 += p->tbd) {
-    const int k1 = std::min(m, k0 + p->tbd);
-    TRY(bubble_batch(p, G_dev, k0, k1));
-    HIP_TRY(weighted_block_sum(bufC, p->w + k0, k1 - k0, aa, p->Pi0, k0 > 0 ? 1 : 0, s));
+  const int half = (m + 1) / 2;
+  for (int l0 = 0; l0 < half; l0 += p->tbd) {
+    const int l1 = std::min(half, l0 + p->tbd);
+    TRY(bubble_batch(p, G_dev, l0, l1));
+    HIP_TRY(weighted_pair_sum(bufC, p->w, m, l0, l1 - l0, naux, p->Pi0, l0 > 0 ? 1 : 0, s));
   }
   // W = (1 + V Pi0)^-1 V
   Gemm64Args g{};
