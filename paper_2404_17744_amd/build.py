@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libthcsox.so")
 OBJ = os.path.join(os.path.dirname(HERE), "_build")
 SOURCES = ["kernels.hip", "gemm64.hip", "gemmk.hip", "astage_f16.hip", "astage_bf3.hip", "fused.hip", "fused_f16.hip", "fused_bf3.hip",
-           "thcsox.hip", "dyson.hip", "loopctl.hip", "direct.hip", "mlp.hip", "irgrid.cpp"]
+           "thcsox.hip", "dyson.hip", "gjinv.hip", "loopctl.hip", "direct.hip", "mlp.hip", "irgrid.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -230,8 +230,10 @@ const Tables& tables_for(int m, int nw, double beta) {
 // Am[w] = (i w_w + mu) 1 - F - Sigma(i w_w) as complex [n][n]; wfreq[w] = w_w.
 __global__ __launch_bounds__(NT) void build_a(const double* __restrict__ S, const double* __restrict__ F,
                                               double mu, const double* __restrict__ wfreq, int n,
-                                              int nw, double2* __restrict__ Am) {
+                                              int nw, double2* __restrict__ Am,
+                                              int* __restrict__ flag) {
   const int w = blockIdx.y;
+  if (w == 0 && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;   // before the elimination
   const double wn = wfreq[w];
   const int64_t nn = (int64_t)n * n;
   const double* Sre = S + (int64_t)w * nn;
@@ -248,202 +250,38 @@ __global__ __launch_bounds__(NT) void build_a(const double* __restrict__ S, cons
   }
 }
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// In-place Gauss-Jordan inversion with partial pivoting, blocked by panels of
-// GJ_B columns.  For the panel [k, k + bw):
-//   gje_panel: the n x bw panel sits in LDS; for each of its columns c the pivot
-//     is the largest |a_ic| over the rows i >= c not yet used as pivot rows, rows c
-//     and piv[c] are swapped in full (the panel in LDS, the other columns in
-//     memory), and the column is eliminated from the panel columns only: the
-//     pivot row is scaled by 1/p, every other row loses a_ic/p times it, and
-//     column c becomes the matching column of the inverse (1/p at the pivot,
-//     -a_ic/p elsewhere).  The panel ends as W, the panel's columns of the
-//     product of the panel's elimination matrices.
-//   gje_trail: every other column j gets the same eliminations at once,
-//     A[:, j] += (W - E) A[panel rows, j] with E the panel rows' unit columns.
-// After the last panel the matrix holds the inverse with its columns permuted by
-// the row interchanges; gje_perm and extract_inv undo them (last first).
-// One workgroup per frequency in gje_panel; flag[0] is set to 1 for a zero or
-// non-finite pivot.
-constexpr int GJ_B = 8;          // panel width
-constexpr int GJ_LDS = 9216;     // double2 panel elements in LDS (144 KiB): bw * n <= GJ_LDS
-constexpr int GJ_TCB = 64;       // columns per gje_trail workgroup
-constexpr int GJ_TRC = 32;       // rows per staged chunk of W
-
-__global__ __launch_bounds__(NT) void gje_panel(double2* __restrict__ Am, int n, int k, int bw,
-                                                int* __restrict__ piv, int* __restrict__ flag) {
-  __shared__ double2 P[GJ_LDS];  // column-major: P[t * n + i] = A[i][k + t]
-  __shared__ double bval[NT];
-  __shared__ int bidx[NT];
-  __shared__ double2 prow[GJ_B];
-  const int tid = threadIdx.x, w = blockIdx.x;
-  double2* A = Am + (int64_t)w * n * n;
-  for (int e = tid; e < n * bw; e += NT) {
-    const int i = e / bw, t = e % bw;
-    P[t * n + i] = A[(int64_t)i * n + k + t];
-  }
-  __syncthreads();
-  for (int t = 0; t < bw; ++t) {
-    const int c = k + t;
-    double best = -1.0;
-    int bi = c;
-    for (int i = c + tid; i < n; i += NT) {
-      const double2 a = P[t * n + i];
-      const double v = a.x * a.x + a.y * a.y;
-      if (v > best) { best = v; bi = i; }
-    }
-    bval[tid] = best;
-    bidx[tid] = bi;
-    __syncthreads();
-    for (int o = NT / 2; o > 0; o >>= 1) {
-      if (tid < o) {
-        const double v2 = bval[tid + o];
-        const int i2 = bidx[tid + o];
-        if (v2 > bval[tid] || (v2 == bval[tid] && i2 < bidx[tid])) {
-          bval[tid] = v2;
-          bidx[tid] = i2;
-        }
-      }
-      __syncthreads();
-    }
-    const int r = bidx[0];
-    if (tid == 0) {
-      piv[(int64_t)w * n + c] = r;
-      if (!(bval[0] > 0.0) || !isfinite(bval[0])) atomicExch(flag, 1);
-    }
-    if (r != c) {
-      for (int tt = tid; tt < bw; tt += NT) {
-        const double2 x = P[tt * n + c];
-        P[tt * n + c] = P[tt * n + r];
-        P[tt * n + r] = x;
-      }
-      for (int j = tid; j < n; j += NT) {
-        if (j >= k && j < k + bw) continue;
-        const double2 x = A[(int64_t)c * n + j];
-        A[(int64_t)c * n + j] = A[(int64_t)r * n + j];
-        A[(int64_t)r * n + j] = x;
-      }
-    }
-    __syncthreads();
-    if (tid < bw) {
-      const double2 p = P[t * n + c];
-      const double d = p.x * p.x + p.y * p.y;
-      const double2 pinv = d > 0.0 ? make_double2(p.x / d, -p.y / d) : make_double2(0.0, 0.0);
-      prow[tid] = tid == t ? pinv : cmul(P[tid * n + c], pinv);
-    }
-    __syncthreads();
-    const double2 pinv = prow[t];
-    for (int i = tid; i < n; i += NT) {
-      if (i == c) {
-        for (int tt = 0; tt < bw; ++tt) P[tt * n + c] = prow[tt];
-      } else {
-        const double2 f = P[t * n + i];
-        for (int tt = 0; tt < bw; ++tt) {
-          if (tt == t) continue;
-          const double2 q = cmul(f, prow[tt]);
-          P[tt * n + i].x -= q.x;
-          P[tt * n + i].y -= q.y;
-        }
-        const double2 q = cmul(f, pinv);
-        P[t * n + i] = make_double2(-q.x, -q.y);
-      }
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < n * bw; e += NT) {
-    const int i = e / bw, t = e % bw;
-    A[(int64_t)i * n + k + t] = P[t * n + i];
-  }
-}
-
-// A[:, j] += (W - E) A[k .. k+bw-1, j] for the columns j outside the panel; the
-// workgroup owns GJ_TCB columns (all rows) of one frequency, so the panel rows it
-// reads first are not yet overwritten.
-__global__ __launch_bounds__(NT) void gje_trail(double2* __restrict__ Am, int n, int k, int bw) {
-  __shared__ double2 X[GJ_B][GJ_TCB];
-  __shared__ double2 Wl[GJ_TRC][GJ_B];
-  const int tid = threadIdx.x, w = blockIdx.y;
-  double2* A = Am + (int64_t)w * n * n;
-  const int jj = tid % GJ_TCB, q = tid / GJ_TCB;
-  const int j0 = blockIdx.x * GJ_TCB, j = j0 + jj;
-  const bool active = j < n && (j < k || j >= k + bw);
-  for (int e = tid; e < bw * GJ_TCB; e += NT) {
-    const int t = e / GJ_TCB, c2 = e % GJ_TCB;
-    X[t][c2] = j0 + c2 < n ? A[(int64_t)(k + t) * n + j0 + c2] : make_double2(0.0, 0.0);
-  }
-  for (int i0 = 0; i0 < n; i0 += GJ_TRC) {
-    __syncthreads();
-    for (int e = tid; e < GJ_TRC * bw; e += NT) {
-      const int ii = e / bw, t = e % bw, i = i0 + ii;
-      double2 v = i < n ? A[(int64_t)i * n + k + t] : make_double2(0.0, 0.0);
-      if (i == k + t) v.x -= 1.0;
-      Wl[ii][t] = v;
-    }
-    __syncthreads();
-    if (active) {
-      for (int ii = q; ii < GJ_TRC && i0 + ii < n; ii += NT / GJ_TCB) {
-        double2 a = A[(int64_t)(i0 + ii) * n + j];
-        for (int t = 0; t < bw; ++t) {
-          const double2 wv = Wl[ii][t], x = X[t][jj];
-          a.x = fma(wv.x, x.x, fma(-wv.y, x.y, a.x));
-          a.y = fma(wv.x, x.y, fma(wv.y, x.x, a.y));
-        }
-        A[(int64_t)(i0 + ii) * n + j] = a;
-      }
-    }
-  }
-}
-
-// perm[w][j]: the column of the eliminated matrix that is column j of the
-// inverse (the row interchanges applied as column interchanges, last first).
-__global__ __launch_bounds__(NT) void gje_perm(const int* __restrict__ piv, int n, int nw,
-                                               int* __restrict__ perm) {
-  const int w = blockIdx.x * NT + threadIdx.x;
-  if (w >= nw) return;
-  int* pm = perm + (int64_t)w * n;
-  const int* pv = piv + (int64_t)w * n;
-  for (int j = 0; j < n; ++j) pm[j] = j;
-  for (int c = n - 1; c >= 0; --c) {
-    const int r = pv[c];
-    if (r != c) {
-      const int x = pm[c];
-      pm[c] = pm[r];
-      pm[r] = x;
-    }
-  }
-}
-
 // Gstack[w][ij] = Re G(i w)_ij, Gstack[nw + w][ij] = Im G(i w)_ij.
 __global__ __launch_bounds__(NT) void extract_inv(const double2* __restrict__ Am,
-                                                  const int* __restrict__ perm, int n, int nw,
+                                                  const int* __restrict__ piv,
+                                                  const int* __restrict__ col, int n, int nw,
                                                   double* __restrict__ Gs) {
   const int w = blockIdx.y;
   const int64_t nn = (int64_t)n * n;
   const double2* A = Am + (int64_t)w * nn;
-  const int* pm = perm + (int64_t)w * n;
+  const int* pv = piv + (int64_t)w * n;
+  const int* cl = col + (int64_t)w * n;
   for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < nn; e += (int64_t)gridDim.x * NT) {
-    const int64_t i = e / n, j = e % n;
-    const double2 v = A[i * n + pm[j]];
+    const int i = (int)(e / n), j = (int)(e % n);
+    const double2 v = A[(int64_t)pv[i] * n + cl[j]];
     Gs[(int64_t)w * nn + e] = v.x;
     Gs[(int64_t)(nw + w) * nn + e] = v.y;
   }
 }
 
 // tr[w] = Re Tr G(i w_w), tr[nw + w] = Im Tr G(i w_w): the diagonal of each
-// inverse, read through the column permutation (one workgroup per frequency).
+// inverse, read through the pivot permutations (one workgroup per frequency).
 __global__ __launch_bounds__(NT) void inv_traces(const double2* __restrict__ Am,
-                                                 const int* __restrict__ perm, int n, int nw,
+                                                 const int* __restrict__ piv,
+                                                 const int* __restrict__ col, int n, int nw,
                                                  double* __restrict__ tr) {
   __shared__ double r_re[NT], r_im[NT];
   const int w = blockIdx.x;
   const double2* A = Am + (int64_t)w * n * n;
-  const int* pm = perm + (int64_t)w * n;
+  const int* pv = piv + (int64_t)w * n;
+  const int* cl = col + (int64_t)w * n;
   double re = 0.0, im = 0.0;
   for (int i = threadIdx.x; i < n; i += NT) {
-    const double2 v = A[(int64_t)i * n + pm[i]];
+    const double2 v = A[(int64_t)pv[i] * n + cl[i]];
     re += v.x;
     im += v.y;
   }
@@ -483,53 +321,32 @@ __global__ __launch_bounds__(NT) void trace_ab(const double* A, const double* B,
 
 int dfail(int code, const std::string& m) { return set_error(code, m); }
 
-__global__ __launch_bounds__(NT) void real_to_complex(const double* __restrict__ M, int64_t nn,
-                                                      double2* __restrict__ Am) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < nn; e += (int64_t)gridDim.x * NT)
-    Am[e] = make_double2(M[e], 0.0);
-}
-
-// Minv[i][j] = Re of the eliminated matrix at column perm[j] (one matrix)
-__global__ __launch_bounds__(NT) void extract_real_inv(const double2* __restrict__ Am,
-                                                       const int* __restrict__ perm, int n,
-                                                       double* __restrict__ Minv) {
+// Minv[i][j] = S[piv[i]][col[j]]
+__global__ __launch_bounds__(NT) void unpack_real(const double* __restrict__ S,
+                                                  const int* __restrict__ piv,
+                                                  const int* __restrict__ col, int n,
+                                                  double* __restrict__ Minv) {
   const int64_t nn = (int64_t)n * n;
   for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < nn; e += (int64_t)gridDim.x * NT) {
-    const int64_t i = e / n, j = e % n;
-    Minv[e] = Am[i * n + perm[j]].x;
+    const int i = (int)(e / n), j = (int)(e % n);
+    Minv[e] = S[(int64_t)piv[i] * n + col[j]];
   }
 }
 
 }  // namespace
 
 namespace thcsox {
-hipError_t gj_inverse_real(const double* M, int n, double* Minv, double2* Am, int* piv, int* perm,
-                           int* flag, hipStream_t s) {
-  if (n <= 0 || n > GJ_LDS) return hipErrorInvalidValue;
-  const int64_t nn = (int64_t)n * n;
-  const unsigned bx = (unsigned)std::min<int64_t>(1024, (nn + NT - 1) / NT);
-  real_to_complex<<<bx, NT, 0, s>>>(M, nn, Am);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if ((e = hipMemsetAsync(flag, 0, sizeof(int), s)) != hipSuccess) return e;
-  int bw = GJ_B;
-  while (bw > 1 && (int64_t)bw * n > GJ_LDS) bw /= 2;
-  for (int k = 0; k < n; k += bw) {
-    const int w = std::min(bw, n - k);
-    gje_panel<<<1, NT, 0, s>>>(Am, n, k, w, piv, flag);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    gje_trail<<<dim3((unsigned)((n + GJ_TCB - 1) / GJ_TCB), 1), NT, 0, s>>>(Am, n, k, w);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  gje_perm<<<1, NT, 0, s>>>(piv, n, 1, perm);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  extract_real_inv<<<bx, NT, 0, s>>>(Am, perm, n, Minv);
+hipError_t gj_unpack(const double* S, const int* piv, const int* col, int n, double* Minv,
+                     hipStream_t s) {
+  if (n <= 0) return hipErrorInvalidValue;
+  const unsigned bx = (unsigned)std::min<int64_t>(1024, ((int64_t)n * n + NT - 1) / NT);
+  unpack_real<<<bx, NT, 0, s>>>(S, piv, col, n, Minv);
   return hipGetLastError();
 }
 }  // namespace thcsox
 
 struct thcsox_dyson_s {
-  int n = 0, m = 0, nw = 0, panel = GJ_B;
+  int n = 0, m = 0, nw = 0;
   double beta = 0, mu = 0;
   hipStream_t stream = nullptr;
   double* F = nullptr;     // [n][n]
@@ -539,7 +356,7 @@ struct thcsox_dyson_s {
   double* Siw = nullptr;   // [2nw][n n]
   double2* Am = nullptr;   // [nw][n][n]
   int* piv = nullptr;      // [nw][n]
-  int* perm = nullptr;     // [nw][n]
+  int* col = nullptr;      // [nw][n]
   double* Gs = nullptr;    // [2nw][n n]
   double* Gout = nullptr;  // [m+1][n n]
   int* flag = nullptr;
@@ -591,32 +408,22 @@ int dy_forward(thcsox_dyson_s* d, const double* Sigma_dev) {
 }
 
 // G(i w) = [(i w + mu) 1 - F - Sigma(i w)]^-1 for every frequency, left in Am
-// (columns permuted by perm); flag set for a singular matrix.
+// (permuted by piv and col); flag set for a singular matrix.
 int dy_invert(thcsox_dyson_s* d, double mu) {
   const int n = d->n, nw = d->nw;
   const int64_t nn = (int64_t)n * n;
   const hipStream_t s = d->stream;
   const unsigned bx = (unsigned)std::min<int64_t>(64, (nn + NT - 1) / NT);
-  build_a<<<dim3(bx, nw), NT, 0, s>>>(d->Siw, d->F, mu, d->wfreq, n, nw, d->Am);
+  build_a<<<dim3(bx, nw), NT, 0, s>>>(d->Siw, d->F, mu, d->wfreq, n, nw, d->Am, d->flag);
   DTRY(hipGetLastError());
-  DTRY(hipMemsetAsync(d->flag, 0, sizeof(int), s));
-  const int bw = d->panel;
-  for (int k = 0; k < n; k += bw) {
-    const int w = std::min(bw, n - k);
-    gje_panel<<<nw, NT, 0, s>>>(d->Am, n, k, w, d->piv, d->flag);
-    DTRY(hipGetLastError());
-    gje_trail<<<dim3((unsigned)((n + GJ_TCB - 1) / GJ_TCB), nw), NT, 0, s>>>(d->Am, n, k, w);
-    DTRY(hipGetLastError());
-  }
-  gje_perm<<<(unsigned)((nw + NT - 1) / NT), NT, 0, s>>>(d->piv, n, nw, d->perm);
-  DTRY(hipGetLastError());
+  DTRY(gj_inverse(d->Am, n, nw, d->piv, d->col, d->flag, s));
   return 0;
 }
 
 // Tr gamma of the inverses in Am: gamma = sum_j Wb[m][j] [Re G; Im G]_j, so only
 // the traces of the G(i w) are needed.  Synchronises the stream.
 int dy_electrons(thcsox_dyson_s* d, double* N) {
-  inv_traces<<<d->nw, NT, 0, d->stream>>>(d->Am, d->perm, d->n, d->nw, d->traces);
+  inv_traces<<<d->nw, NT, 0, d->stream>>>(d->Am, d->piv, d->col, d->n, d->nw, d->traces);
   DTRY(hipGetLastError());
   std::vector<double> tr((size_t)2 * d->nw);
   int flag = 0;
@@ -637,7 +444,7 @@ int dy_backward(thcsox_dyson_s* d, double* G_dev, double* gamma_dev) {
   const int64_t nn = (int64_t)n * n;
   const hipStream_t s = d->stream;
   const unsigned bx = (unsigned)std::min<int64_t>(64, (nn + NT - 1) / NT);
-  extract_inv<<<dim3(bx, nw), NT, 0, s>>>(d->Am, d->perm, n, nw, d->Gs);
+  extract_inv<<<dim3(bx, nw), NT, 0, s>>>(d->Am, d->piv, d->col, n, nw, d->Gs);
   DTRY(hipGetLastError());
   d->have_g = true;
   // [G(tau_0) .. G(tau_{m-1}); gamma] = Wb . [Re G(i w); Im G(i w)]
@@ -675,7 +482,6 @@ int dyson_create(thcsox_dyson_t* out, int n, int m, int nw, double beta, double 
   auto* d = new (std::nothrow) thcsox_dyson_s();
   if (d == nullptr) return dfail(THCSOX_ENOMEM, "host allocation failed");
   d->n = n; d->m = m; d->nw = nw; d->beta = beta; d->mu = mu;
-  while (d->panel > 1 && (int64_t)d->panel * n > GJ_LDS) d->panel /= 2;
   d->stream = static_cast<hipStream_t>(hip_stream);
   const int64_t nn = (int64_t)n * n;
   int rc;
@@ -685,7 +491,7 @@ int dyson_create(thcsox_dyson_t* out, int n, int m, int nw, double beta, double 
       (rc = dalloc(d, &d->Siw, (size_t)2 * d->nw * nn)) ||
       (rc = dalloc(d, &d->Am, (size_t)d->nw * nn)) ||
       (rc = dalloc(d, &d->piv, (size_t)d->nw * n)) ||
-      (rc = dalloc(d, &d->perm, (size_t)d->nw * n)) ||
+      (rc = dalloc(d, &d->col, (size_t)d->nw * n)) ||
       (rc = dalloc(d, &d->Gs, (size_t)2 * d->nw * nn)) ||
       (rc = dalloc(d, &d->Gout, (size_t)(d->m + 1) * nn)) || (rc = dalloc(d, &d->flag, 1)) ||
       (rc = dalloc(d, &d->scal, 1)) || (rc = dalloc(d, &d->traces, (size_t)2 * d->nw))) {
@@ -719,8 +525,8 @@ int thcsox_dyson_plan(thcsox_dyson_t* out, int n, int ntau, int n_matsubara, dou
   *out = nullptr;
   if (n <= 0 || ntau <= 1 || n_matsubara <= 0 || !(beta > 0.0))
     return dfail(THCSOX_EINVAL, "need n > 0, ntau > 1, n_matsubara > 0, beta > 0");
-  if ((int64_t)n > GJ_LDS)
-    return dfail(THCSOX_EINVAL, "n too large for the in-LDS panel of the Dyson inversion (n <= 9216)");
+  if (n > GJ_MAX_N)
+    return dfail(THCSOX_EINVAL, "n too large for the Dyson inversion (n <= 9216)");
   if (2 * n_matsubara < ntau)
     return dfail(THCSOX_EINVAL, "need 2 n_matsubara >= ntau for the least-squares fit");
   if (tau_host == nullptr || F_dev == nullptr) return dfail(THCSOX_EINVAL, "NULL argument");
@@ -747,8 +553,8 @@ int thcsox_dyson_plan_sampled(thcsox_dyson_t* out, int n, int ntau, int nfreq, d
   *out = nullptr;
   if (n <= 0 || ntau <= 1 || nfreq <= 0 || !(beta > 0.0))
     return dfail(THCSOX_EINVAL, "need n > 0, ntau > 1, nfreq > 0, beta > 0");
-  if ((int64_t)n > GJ_LDS)
-    return dfail(THCSOX_EINVAL, "n too large for the in-LDS panel of the Dyson inversion (n <= 9216)");
+  if (n > GJ_MAX_N)
+    return dfail(THCSOX_EINVAL, "n too large for the Dyson inversion (n <= 9216)");
   if (2 * nfreq < ntau) return dfail(THCSOX_EINVAL, "need 2 nfreq >= ntau for the fit");
   if (freq_n_host == nullptr || Wf_host == nullptr || Wb_host == nullptr || F_dev == nullptr)
     return dfail(THCSOX_EINVAL, "NULL argument");

@@ -283,8 +283,9 @@ __global__ __launch_bounds__(NT) void weighted_pair_sum_kernel(const double* __r
   }
 }
 
-__global__ __launch_bounds__(NT) void add_identity_kernel(double* A, int n) {
+__global__ __launch_bounds__(NT) void add_identity_kernel(double* A, int n, int* clear) {
   const int i = blockIdx.x * NT + threadIdx.x;
+  if (i == 0) *clear = 0;
   if (i < n) A[(int64_t)i * n + i] += 1.0;
 }
 
@@ -300,9 +301,9 @@ hipError_t weighted_pair_sum(const double* Pi, const double* w, int m, int l0, i
   return hipGetLastError();
 }
 
-hipError_t add_identity(double* A, int n, hipStream_t s) {
+hipError_t add_identity(double* A, int n, int* clear, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  add_identity_kernel<<<cdiv(n, NT), NT, 0, s>>>(A, n);
+  add_identity_kernel<<<cdiv(n, NT), NT, 0, s>>>(A, n, clear);
   return hipGetLastError();
 }
 

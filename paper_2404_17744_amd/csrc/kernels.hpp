@@ -177,19 +177,24 @@ hipError_t sym_flags(const unsigned long long* asym, const unsigned long long* a
 hipError_t khatri_rao(const double* X, int n, int naux, int q0, int q1, double* KR,
                       hipStream_t s);
 
-// Inverse of one real n x n matrix (row-major, n <= 9216) by the Dyson step's
-// blocked Gauss-Jordan elimination with partial pivoting on a complex copy.
-// Work: Am [n n] double2, piv and perm [n] ints, flag [1] int, set to 1 for a
-// zero or non-finite pivot (read it after synchronising).
-hipError_t gj_inverse_real(const double* M, int n, double* Minv, double2* Am, int* piv, int* perm,
-                           int* flag, hipStream_t s);
+// Gauss-Jordan elimination in place of nw complex matrices, or of one real matrix
+// (row-major n x n, n <= GJ_MAX_N), leaving in Am the array S with
+//   A^-1[i][j] = S[piv[i] n + col[j]].
+// piv, col [nw][n] ints; flag [1] int, cleared by the caller, set to 1 for a zero or
+// non-finite pivot; X (real form): work of 32 n doubles.
+constexpr int GJ_MAX_N = 9216;
+hipError_t gj_inverse(double2* Am, int n, int nw, int* piv, int* col, int* flag, hipStream_t s);
+hipError_t gj_inverse(double* Am, int n, int* piv, int* col, int* flag, double* X, hipStream_t s);
+// Minv[i][j] = S[piv[i] n + col[j]] of a real elimination.
+hipError_t gj_unpack(const double* S, const int* piv, const int* col, int n, double* Minv,
+                     hipStream_t s);
 
 // Pi0 (+)= sum_b w[l] Pi[b] + w[m-1-l] Pi[b]^T, l = l0 + b, over nb matrices [naux][naux],
 // b in order (accumulate = 0: Pi0 is overwritten); the middle point l = m-1-l once.
 hipError_t weighted_pair_sum(const double* Pi, const double* w, int m, int l0, int nb, int naux,
                              double* Pi0, int accumulate, hipStream_t s);
-// A[i][i] += 1 for i < n (row-major n x n).
-hipError_t add_identity(double* A, int n, hipStream_t s);
+// A[i][i] += 1 for i < n (row-major n x n); *clear = 0.
+hipError_t add_identity(double* A, int n, int* clear, hipStream_t s);
 
 // tr[k] = sum_pq G[m-1-k][q][p] Sigma[k][p][q]; then E = -1/2 sum_k w[k] tr[k].
 hipError_t energy_partials(const double* G, const double* S, int n, int m, double* tr,

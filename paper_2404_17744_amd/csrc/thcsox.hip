@@ -138,8 +138,8 @@ struct thcsox_plan_s {
   double* Pi0 = nullptr;
   double* Mscr = nullptr;
   double* Minv = nullptr;
-  double2* Am = nullptr;
-  int* gj = nullptr;        // [2 naux + 1]: pivots, permutation, flag
+  double* gjx = nullptr;    // [32][naux]
+  int* gj = nullptr;        // [2 naux + 1]: pivots, columns, flag
   double* w = nullptr;      // [m]
   void* U = nullptr;        // planes of [naux][n][ldk] (fp16x2: c32 rows [naux][n])
   int64_t u_plane = 0;
@@ -904,7 +904,7 @@ int thcsox_static_screening(thcsox_plan_t p, const double* G_dev, double* W_dev)
     TRY(p->alloc(&p->Pi0, (size_t)aa));
     TRY(p->alloc(&p->Mscr, (size_t)aa));
     TRY(p->alloc(&p->Minv, (size_t)aa));
-    TRY(p->alloc(&p->Am, (size_t)aa));
+    TRY(p->alloc(&p->gjx, (size_t)32 * naux));
     TRY(p->alloc(&p->gj, (size_t)2 * naux + 1));
   }
   // Pi0 = sum_k w_k Pi(tau_k) over the mirrored pairs, batch by batch: Pi(tau_{m-1-l})
@@ -923,11 +923,12 @@ int thcsox_static_screening(thcsox_plan_t p, const double* G_dev, double* W_dev)
   g.B = p->Pi0; g.b_k = naux; g.b_j = 1;
   g.C = p->Mscr; g.c_i = naux; g.c_j = 1; g.cj_in = naux; g.cj_out = 0;
   HIP_TRY(gemm64(g, s));
-  HIP_TRY(add_identity(p->Mscr, naux, s));
   int* piv = p->gj;
-  int* perm = p->gj + naux;
+  int* col = p->gj + naux;
   int* flag = p->gj + 2 * naux;
-  HIP_TRY(gj_inverse_real(p->Mscr, naux, p->Minv, p->Am, piv, perm, flag, s));
+  HIP_TRY(add_identity(p->Mscr, naux, flag, s));
+  HIP_TRY(gj_inverse(p->Mscr, naux, piv, col, flag, p->gjx, s));
+  HIP_TRY(gj_unpack(p->Mscr, piv, col, naux, p->Minv, s));
   g.A = p->Minv; g.B = p->V; g.C = W_dev;
   HIP_TRY(gemm64(g, s));
   int hflag = 0;
