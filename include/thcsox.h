@@ -211,7 +211,7 @@ int thcsox_sigma_direct(thcsox_plan_t p, const double* G_dev, double* Sigma_dev,
  *   W_dev  : [naux][naux] device array (output, caller-owned).
  * FP64 in every plan precision; 1 + V Pi0 is inverted by blocked Gauss-Jordan
  * elimination with partial pivoting (naux <= 9216, else THCSOX_EINVAL).  The
- * first call allocates 5 naux^2 doubles and the direct term's batch buffers
+ * first call allocates 3 naux^2 doubles and the direct term's batch buffers
  * (kept by the plan).  THCSOX_ENONFINITE for a singular 1 + V Pi0.
  * Synchronises the plan's stream. */
 int thcsox_static_screening(thcsox_plan_t p, const double* G_dev, double* W_dev);

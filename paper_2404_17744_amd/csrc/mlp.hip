@@ -26,141 +26,297 @@ namespace {
 
 constexpr int NT = 256;
 
-// C(i,j) = alpha * sum_k A(i,k) B(k,j) + beta * C(i,j), FP32 matrix cores.
-// A(i,k) = A[i*a_i + k*a_k], B(k,j) = B[k*b_k + j*b_j], C(i,j) = C[i*ldc + j].
-struct G32 {
-  int M, N, K;
-  float alpha, beta;
-  const float* A; int64_t a_i, a_k;
-  const float* B; int64_t b_k, b_j;
-  float* C; int64_t ldc;
-};
-
-__global__ __launch_bounds__(NT) void gemm32_kernel(G32 g) {
-  constexpr int BK = 16, LD = 17;
-  __shared__ float sA[64 * LD];
-  __shared__ float sB[64 * LD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  f4 acc[2][2];
-#pragma unroll
-  for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-    for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < g.K; k0 += BK) {
-#pragma unroll
-    for (int e = tid; e < 64 * BK; e += NT) {
-      int i, k;
-      if (g.a_k == 1) { i = e >> 4; k = e & 15; } else { i = e & 63; k = e >> 6; }
-      const int gi = i0 + i, gk = k0 + k;
-      sA[i * LD + k] = (gi < g.M && gk < g.K) ? g.A[(int64_t)gi * g.a_i + (int64_t)gk * g.a_k] : 0.f;
-    }
-#pragma unroll
-    for (int e = tid; e < 64 * BK; e += NT) {
-      int j, k;
-      if (g.b_j == 1) { j = e & 63; k = e >> 6; } else { j = e >> 4; k = e & 15; }
-      const int gj = j0 + j, gk = k0 + k;
-      sB[j * LD + k] = (gj < g.N && gk < g.K) ? g.B[(int64_t)gk * g.b_k + (int64_t)gj * g.b_j] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      float a[2], b[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        a[t] = sA[(32 * wr + 16 * t + (lane & 15)) * LD + kk + (lane >> 4)];
-        b[t] = sB[(32 * wc + 16 * t + (lane & 15)) * LD + kk + (lane >> 4)];
-      }
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = mfma1(a[ti], b[tj], acc[ti][tj]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 32 * wr + 16 * ti + out_row<MODE_F32>(lane, r);
-        const int j = j0 + 32 * wc + 16 * tj + (lane & 15);
-        if (i < g.M && j < g.N) {
-          float* c = g.C + (int64_t)i * g.ldc + j;
-          *c = g.alpha * acc[ti][tj][r] + (g.beta != 0.f ? g.beta * *c : 0.f);
-        }
-      }
-}
-
-hipError_t gemm32(const G32& g, hipStream_t s) {
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-  gemm32_kernel<<<grid, NT, 0, s>>>(g);
-  return hipGetLastError();
-}
-
 __device__ __forceinline__ float silu(float z) { return z / (1.f + __expf(-z)); }
 __device__ __forceinline__ float dsilu(float z) {
   const float s = 1.f / (1.f + __expf(-z));
   return s * (1.f + z * (1.f - s));
 }
 
-// z[b][j] += bias[j]; h = silu(z)
-__global__ void bias_silu(float* z, float* h, const float* bias, int64_t rows, int cols) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < rows * cols; e += (int64_t)gridDim.x * NT) {
-    const float v = z[e] + bias[e % cols];
-    z[e] = v;
-    h[e] = silu(v);
-  }
-}
+// ---------------------------------------------------------------------------
+// The layers' FP32 products, C(i,j) = sum_k A(i,k) B(k,j) on the FP32 matrix cores
+// (16x16x4), with what follows each product done on its accumulators:
+//   HIDDEN   z = C + bias, h = silu(z)
+//   OUTPUT   y = C + bias + x; with a target also d = 2 (y - t) / N and the
+//            workgroup's sum of (y - t)^2
+//   BACK     dz = C * silu'(z)
+//   GRADIENT a slice of k of a weight gradient, stored as a partial sum, and the
+//            slice's column sums of A (the bias gradient)
+// A is contiguous in k (AC) or i, B in k (BC) or j.  Tiles of T = 32 WT square, four
+// waves of T / 2 square, k steps of 32 double-buffered in LDS with one barrier each.
+// What bounds them: at batch 4096 and H = 512 a layer is 2.1 GFLOP, 14 us at the
+// matrix cores' rate, so what counts is filling the chip (the tile edge and the
+// number of slices are picked for about two workgroups per compute unit: a weight
+// gradient sums over the whole batch into few tiles) and not passing over the
+// activations again.  Training step at m = 64, H = 512, batch 4096: 4.4 ms with
+// 64 x 64 tiles over the whole batch and bias, activation and column-sum passes of
+// their own (0.75 ms for each column sum).
+enum Epilogue { HIDDEN, OUTPUT, BACK, GRADIENT };
 
-// y[b][c] += x[b][c] + bias[c]
-__global__ void residual_out(float* y, const float* x, const float* bias, int64_t rows, int cols) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < rows * cols; e += (int64_t)gridDim.x * NT)
-    y[e] += x[e] + bias[e % cols];
-}
+struct G32 {
+  int M, N, K;
+  const float* A; int64_t lda;   // AC: A[i lda + k], else A[k lda + i]
+  const float* B; int64_t ldb;   // BC: B[j ldb + k], else B[k ldb + j]
+  float* C;                      // h, y or dz [M][N]; GRADIENT: [slices][M N + M]
+  float* Z;                      // HIDDEN: z (null: not kept); BACK: z (read)
+  const float* bias;             // [N]
+  const float* x;                // OUTPUT: [M][N]
+  const float* t;                // OUTPUT: target [M][N] or null
+  float* D;                      // OUTPUT with a target: [M][N]
+  float scale;                   // OUTPUT with a target: 1 / count
+  double* part;                  // OUTPUT with a target: [workgroups]
+  int kslice;                    // GRADIENT: k per slice (a multiple of GBK)
+};
 
-// d = 2 (y - t) / N and per-block sums of (y - t)^2
-__global__ void mse_grad(const float* y, const float* t, float* d, int64_t count, float inv_n,
-                         double* partial) {
-  __shared__ double red[NT];
-  double s = 0.0;
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < count; e += (int64_t)gridDim.x * NT) {
-    const float r = y[e] - t[e];
-    d[e] = 2.f * r * inv_n;
-    s += (double)r * r;
-  }
-  red[threadIdx.x] = s;
+constexpr int GBK = 32;
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// LDS panel of T rows x 32 k.  KC: rows of 128 bytes, 16-byte piece c of row r at
+// c ^ (r / 2 mod 8); else [k][row] with 16 floats of padding.  A fragment takes k =
+// 4 s + g for lane group g: both put its 64 lanes on 64 banks.
+template <int T, bool KC> struct GPanel {
+  static constexpr int LD = KC ? GBK : T + 16;
+  static constexpr int SIZE = KC ? T * GBK : GBK * LD;
+};
+
+// ALIGNED: contiguous extents and strides are multiples of 4 and the bases 16-byte
+// aligned; else four single loads.
+template <int WT, bool AC, bool BC, int EPI, bool ALIGNED>
+__global__ __launch_bounds__(NT) void gemm32_kernel(G32 g, int ntj) {
+  constexpr int T = 32 * WT;
+  using LA = GPanel<T, AC>;
+  using LB = GPanel<T, BC>;
+  __shared__ __attribute__((aligned(16))) float sA[2][LA::SIZE];
+  __shared__ __attribute__((aligned(16))) float sB[2][LB::SIZE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = wave >> 1, wc = wave & 1;
+  const int i0 = (int)(blockIdx.x / ntj) * T, j0 = (int)(blockIdx.x % ntj) * T;
+  const int k_lo = EPI == GRADIENT ? blockIdx.y * g.kslice : 0;
+  const int k_hi = EPI == GRADIENT ? min(g.K, k_lo + g.kslice) : g.K;
+
+  // four consecutive elements from x on, addresses clamped into [0, lim)
+  auto quad = [&](const float* p, int x, int lim) -> f4 {
+    if (ALIGNED) return *reinterpret_cast<const f4*>(p + min(x, lim - 4));
+    return f4{p[min(x, lim - 1)], p[min(x + 1, lim - 1)], p[min(x + 2, lim - 1)],
+              p[min(x + 3, lim - 1)]};
+  };
+  f4 ra[WT], rb[WT];
+  auto fetch = [&](bool kc, const float* P, int64_t ld, int r0, int rows, int k0, int e) -> f4 {
+    if (kc) return quad(P + (int64_t)min(r0 + (e >> 3), rows - 1) * ld, k0 + 4 * (e & 7), g.K);
+    return quad(P + (int64_t)min(k0 + e / (T / 4), g.K - 1) * ld, r0 + 4 * (e % (T / 4)), rows);
+  };
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int t = 0; t < WT; ++t) {
+      ra[t] = fetch(AC, g.A, g.lda, i0, g.M, k0, tid + NT * t);
+      rb[t] = fetch(BC, g.B, g.ldb, j0, g.N, k0, tid + NT * t);
+    }
+  };
+  // store one quad, zero past k_hi (what lies past M or N only reaches outputs that
+  // are not stored)
+  auto put = [&](bool kc, float* s, int ld, int e, int k0, f4 v) {
+    if (kc) {
+      const int r = e >> 3, c = e & 7, k = k0 + 4 * c;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = k + q < k_hi ? v[q] : 0.f;
+      *reinterpret_cast<f4*>(s + r * GBK + ((c ^ ((r >> 1) & 7)) << 2)) = v;
+    } else {
+      const int kk = e / (T / 4);
+      if (k0 + kk >= k_hi) v = f4{0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f4*>(s + kk * ld + 4 * (e % (T / 4))) = v;
+    }
+  };
+  auto store = [&](int buf, int k0) {
+#pragma unroll
+    for (int t = 0; t < WT; ++t) {
+      put(AC, sA[buf], LA::LD, tid + NT * t, k0, ra[t]);
+      put(BC, sB[buf], LB::LD, tid + NT * t, k0, rb[t]);
+    }
+  };
+  const int fr = lane & 15, fg = lane >> 4;
+  auto frag = [&](bool kc, const float* s, int ld, int r, int st) -> float {
+    return kc ? s[r * GBK + ((st ^ ((r >> 1) & 7)) << 2) + fg] : s[(4 * st + fg) * ld + r];
+  };
+
+  // acc[ti][tj]: the tile's transpose, so that a lane holds four consecutive j of row
+  // i = 16 ti + lane % 16
+  f4 acc[WT][WT];
+#pragma unroll
+  for (int ti = 0; ti < WT; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < WT; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
+  float csum = 0.f;   // GRADIENT, first column of tiles: thread i < T sums row i of A
+
+  load(k_lo);
+  store(0, k_lo);
+  if (k_lo + GBK < k_hi) load(k_lo + GBK);
   __syncthreads();
-  for (int o = NT / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  int cur = 0;
+  for (int k0 = k_lo; k0 < k_hi; k0 += GBK, cur ^= 1) {
+    if (k0 + GBK < k_hi) store(cur ^ 1, k0 + GBK);
+    if (k0 + 2 * GBK < k_hi) load(k0 + 2 * GBK);
+#pragma unroll
+    for (int st = 0; st < GBK / 4; ++st) {
+      float a[WT], b[WT];
+#pragma unroll
+      for (int t = 0; t < WT; ++t) {
+        a[t] = frag(AC, sA[cur], LA::LD, 16 * (WT * wr + t) + fr, st);
+        b[t] = frag(BC, sB[cur], LB::LD, 16 * (WT * wc + t) + fr, st);
+      }
+#pragma unroll
+      for (int ti = 0; ti < WT; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < WT; ++tj) acc[ti][tj] = mfma1(b[tj], a[ti], acc[ti][tj]);
+    }
+    if (EPI == GRADIENT && j0 == 0 && tid < T) {
+#pragma unroll 8
+      for (int k = 0; k < GBK; ++k) csum += sA[cur][k * LA::LD + tid];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
 
-__global__ void sum_partials(const double* partial, int nb, double* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += partial[i];
-    *out = s;
+  double sse = 0.0;
+  const int64_t slice = EPI == GRADIENT ? (int64_t)blockIdx.y * ((int64_t)g.M * g.N + g.M) : 0;
+#pragma unroll
+  for (int ti = 0; ti < WT; ++ti) {
+    const int i = i0 + 16 * (WT * wr + ti) + fr;
+    if (i >= g.M) continue;
+#pragma unroll
+    for (int tj = 0; tj < WT; ++tj) {
+      const int j = j0 + 16 * (WT * wc + tj) + 4 * fg;
+      if (j >= g.N) continue;
+      const int64_t at = (int64_t)i * g.N + j;
+      const bool whole = j + 3 < g.N;
+      auto get = [&](const float* p) -> f4 {
+        if (whole) return *reinterpret_cast<const f4u*>(p);
+        return f4{p[0], j + 1 < g.N ? p[1] : 0.f, j + 2 < g.N ? p[2] : 0.f, 0.f};
+      };
+      auto set = [&](float* p, f4 v) {
+        if (whole) {
+          *reinterpret_cast<f4u*>(p) = v;
+        } else {
+          p[0] = v[0];
+          if (j + 1 < g.N) p[1] = v[1];
+          if (j + 2 < g.N) p[2] = v[2];
+        }
+      };
+      f4 v = acc[ti][tj];
+      if constexpr (EPI == HIDDEN) {
+        v += get(g.bias + j);
+        if (g.Z != nullptr) set(g.Z + at, v);
+        set(g.C + at, f4{silu(v[0]), silu(v[1]), silu(v[2]), silu(v[3])});
+      } else if constexpr (EPI == OUTPUT) {
+        v += get(g.x + at) + get(g.bias + j);
+        if (g.C != nullptr) set(g.C + at, v);
+        if (g.t != nullptr) {
+          const f4 r = v - get(g.t + at);
+          set(g.D + at, 2.f * r * g.scale);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (j + q < g.N) sse += (double)r[q] * r[q];
+        }
+      } else if constexpr (EPI == BACK) {
+        const f4 z = get(g.Z + at);
+        set(g.C + at, f4{v[0] * dsilu(z[0]), v[1] * dsilu(z[1]), v[2] * dsilu(z[2]),
+                         v[3] * dsilu(z[3])});
+      } else {
+        set(g.C + slice + at, v);
+      }
+    }
+  }
+  if (EPI == GRADIENT && j0 == 0 && tid < T && i0 + tid < g.M)
+    g.C[slice + (int64_t)g.M * g.N + i0 + tid] = csum;
+  if (EPI == OUTPUT && g.t != nullptr) {
+    __shared__ double red[NT];
+    red[tid] = sse;
+    __syncthreads();
+    for (int o = NT / 2; o > 0; o >>= 1) {
+      if (tid < o) red[tid] += red[tid + o];
+      __syncthreads();
+    }
+    if (tid == 0) g.part[blockIdx.x] = red[0];
   }
 }
 
-// dz = dh * silu'(z)
-__global__ void silu_back(const float* dh, const float* z, float* dz, int64_t count) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < count; e += (int64_t)gridDim.x * NT)
-    dz[e] = dh[e] * dsilu(z[e]);
+int tiles_of(int M, int N, int T) { return ((M + T - 1) / T) * ((N + T - 1) / T); }
+
+// Tile edge of a product that is not sliced: the least of rounds of tiles over 256
+// compute units x tile area x the cost per element of that tile relative to the
+// largest (smaller tiles load more per product).
+int tile_edge(int M, int N) {
+  auto cost = [&](int T, double rel) {
+    return std::ceil(tiles_of(M, N, T) / 256.0) * (double)T * T * rel;
+  };
+  const double c4 = cost(128, 1.0), c2 = cost(64, 1.2), c1 = cost(32, 1.8);
+  return c4 <= c2 && c4 <= c1 ? 128 : c2 <= c1 ? 64 : 32;
 }
 
-// g[c] = sum_b d[b][c] (one thread per column, fixed order)
-__global__ void colsum(const float* d, int64_t rows, int cols, float* g) {
-  const int c = blockIdx.x * NT + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int64_t b = 0; b < rows; ++b) s += d[b * cols + c];
-  g[c] = s;
+// Slices of k for a weight gradient of M x N tiles of 64: about 512 workgroups, at
+// most 64 slices, each of at least two k steps
+constexpr int MAX_SLICES = 64;
+int slices_of(int M, int N, int K) {
+  const int want = std::min(MAX_SLICES, std::max(1, 512 / tiles_of(M, N, 64)));
+  return std::max(1, std::min(want, K / (2 * GBK)));
+}
+
+template <bool AC, bool BC, int EPI>
+hipError_t gemm32(const G32& g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
+  auto four = [](int64_t v) { return (v & 3) == 0; };
+  const bool al = four(AC ? g.K : g.M) && four(BC ? g.K : g.N) && four(g.lda) && four(g.ldb) &&
+                  (reinterpret_cast<uintptr_t>(g.A) & 15) == 0 &&
+                  (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
+  const int T = EPI == GRADIENT ? 64 : tile_edge(g.M, g.N);
+  const dim3 grid(tiles_of(g.M, g.N, T), EPI == GRADIENT ? (g.K + g.kslice - 1) / g.kslice : 1);
+  const int ntj = (g.N + T - 1) / T;
+  if (T == 64) {
+    if (al) gemm32_kernel<2, AC, BC, EPI, true><<<grid, NT, 0, s>>>(g, ntj);
+    else gemm32_kernel<2, AC, BC, EPI, false><<<grid, NT, 0, s>>>(g, ntj);
+  } else if constexpr (EPI != GRADIENT) {
+    if (T == 128) {
+      if (al) gemm32_kernel<4, AC, BC, EPI, true><<<grid, NT, 0, s>>>(g, ntj);
+      else gemm32_kernel<4, AC, BC, EPI, false><<<grid, NT, 0, s>>>(g, ntj);
+    } else {
+      if (al) gemm32_kernel<1, AC, BC, EPI, true><<<grid, NT, 0, s>>>(g, ntj);
+      else gemm32_kernel<1, AC, BC, EPI, false><<<grid, NT, 0, s>>>(g, ntj);
+    }
+  }
+  return hipGetLastError();
+}
+
+// The three layers' weight and bias gradients summed over their slices, in order,
+// into the packed array (W, b of each layer follow each other in both), and the
+// loss over its workgroups' sums (by the last workgroup).
+struct SliceSums {
+  const float* src[3];
+  int64_t len[3];      // M N + M
+  int slices[3];
+  float* out;          // packed gradients
+  const double* part; int nparts; double* loss;
+};
+__global__ __launch_bounds__(NT) void sum_slices(SliceSums a, int64_t total) {
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ double red[NT];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < a.nparts; i += NT) s += a.part[i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = NT / 2; o > 0; o >>= 1) {
+      if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *a.loss = red[0];
+    return;
+  }
+  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total;
+       e += (int64_t)(gridDim.x - 1) * NT) {
+    int64_t at = e;
+    int l = 0;
+    while (at >= a.len[l]) at -= a.len[l++];
+    float s = 0.f;
+#pragma unroll 8
+    for (int q = 0; q < a.slices[l]; ++q) s += a.src[l][(int64_t)q * a.len[l] + at];
+    a.out[e] = s;
+  }
 }
 
 __global__ void adam(float* p, const float* g, float* m1, float* m2, int64_t count, float lr,
@@ -328,8 +484,9 @@ struct thcsox_mlp_s {
   int64_t oW1, ob1, oW2, ob2, oW3, ob3;
   hipStream_t stream = nullptr;
   float *P = nullptr, *Gr = nullptr, *M1 = nullptr, *M2 = nullptr;
-  float *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *Y = nullptr, *D = nullptr;
-  float *DH = nullptr, *DZ = nullptr;
+  float *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *D = nullptr;
+  float *DZ1 = nullptr, *DZ2 = nullptr;
+  float* slices[3] = {};     // partial weight and bias gradients of each layer
   double *part = nullptr, *loss = nullptr;
   __bf16* Pb = nullptr;      // bf16 copy of the parameters (inference), made on first use
   int pb_step = -1;          // the training step it was rounded at
@@ -362,63 +519,65 @@ int malloc_into(thcsox_mlp_s* q, T** p, size_t count) {
       return set_error(THCSOX_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-// forward for rows [0, B) of x; activations kept for the backward pass
-int forward(thcsox_mlp_s* q, const float* x, float* y, int B) {
+// The hidden layers for rows [0, B) of x (keep: z1, z2 for a backward pass), then
+// y = the output, or (t given) d and the loss sums of the batch.
+int forward(thcsox_mlp_s* q, const float* x, float* y, const float* t, int B, bool keep) {
   const hipStream_t s = q->stream;
   const int m = q->m, H = q->H;
   G32 g{};
-  g.alpha = 1.f; g.beta = 0.f;
-  g.M = B; g.N = H; g.K = m; g.A = x; g.a_i = m; g.a_k = 1;
-  g.B = q->P + q->oW1; g.b_k = 1; g.b_j = m; g.C = q->Z1; g.ldc = H;
-  MTRY(gemm32(g, s));
-  bias_silu<<<blocks_for((int64_t)B * H), NT, 0, s>>>(q->Z1, q->H1, q->P + q->ob1, B, H);
-  g.M = B; g.N = H; g.K = H; g.A = q->H1; g.a_i = H; g.a_k = 1;
-  g.B = q->P + q->oW2; g.b_k = 1; g.b_j = H; g.C = q->Z2; g.ldc = H;
-  MTRY(gemm32(g, s));
-  bias_silu<<<blocks_for((int64_t)B * H), NT, 0, s>>>(q->Z2, q->H2, q->P + q->ob2, B, H);
-  g.M = B; g.N = m; g.K = H; g.A = q->H2; g.a_i = H; g.a_k = 1;
-  g.B = q->P + q->oW3; g.b_k = 1; g.b_j = H; g.C = y; g.ldc = m;
-  MTRY(gemm32(g, s));
-  residual_out<<<blocks_for((int64_t)B * m), NT, 0, s>>>(y, x, q->P + q->ob3, B, m);
-  MTRY(hipGetLastError());
+  g.M = B; g.N = H; g.K = m; g.A = x; g.lda = m; g.B = q->P + q->oW1; g.ldb = m;
+  g.bias = q->P + q->ob1; g.C = q->H1; g.Z = keep ? q->Z1 : nullptr;
+  MTRY((gemm32<true, true, HIDDEN>(g, s)));
+  g.K = H; g.A = q->H1; g.lda = H; g.B = q->P + q->oW2; g.ldb = H;
+  g.bias = q->P + q->ob2; g.C = q->H2; g.Z = keep ? q->Z2 : nullptr;
+  MTRY((gemm32<true, true, HIDDEN>(g, s)));
+  g.N = m; g.A = q->H2; g.B = q->P + q->oW3; g.bias = q->P + q->ob3; g.x = x; g.C = y; g.Z = nullptr;
+  g.t = t; g.D = q->D; g.scale = 1.f / (float)((int64_t)B * m); g.part = q->part;
+  MTRY((gemm32<true, true, OUTPUT>(g, s)));
   return 0;
 }
 
-// gradients of the mean-squared loss into q->Gr, loss into q->loss
-int backward(thcsox_mlp_s* q, const float* x, const float* t, int B) {
+// the shape of layer l's weight gradient
+void layer_shape(const thcsox_mlp_s* q, int l, int* M, int* N) {
+  *M = l == 2 ? q->m : q->H;
+  *N = l == 0 ? q->m : q->H;
+}
+
+// gradients of the mean-squared loss into q->Gr, sum of squares into q->loss
+int backward(thcsox_mlp_s* q, const float* x, int B) {
   const hipStream_t s = q->stream;
   const int m = q->m, H = q->H;
-  const int64_t cnt = (int64_t)B * m;
-  const unsigned nb = blocks_for(cnt);
-  mse_grad<<<nb, NT, 0, s>>>(q->Y, t, q->D, cnt, 1.f / (float)cnt, q->part);
-  sum_partials<<<1, 64, 0, s>>>(q->part, (int)nb, q->loss);
-  G32 g{};
-  g.alpha = 1.f; g.beta = 0.f;
-  // gW3[c][j] = sum_b D[b][c] H2[b][j]
-  g.M = m; g.N = H; g.K = B; g.A = q->D; g.a_i = 1; g.a_k = m;
-  g.B = q->H2; g.b_k = H; g.b_j = 1; g.C = q->Gr + q->oW3; g.ldc = H;
-  MTRY(gemm32(g, s));
-  colsum<<<(m + NT - 1) / NT, NT, 0, s>>>(q->D, B, m, q->Gr + q->ob3);
-  // dH2 = D W3
-  g.M = B; g.N = H; g.K = m; g.A = q->D; g.a_i = m; g.a_k = 1;
-  g.B = q->P + q->oW3; g.b_k = H; g.b_j = 1; g.C = q->DH; g.ldc = H;
-  MTRY(gemm32(g, s));
-  silu_back<<<blocks_for((int64_t)B * H), NT, 0, s>>>(q->DH, q->Z2, q->DZ, (int64_t)B * H);
-  // gW2 = DZ2^T H1
-  g.M = H; g.N = H; g.K = B; g.A = q->DZ; g.a_i = 1; g.a_k = H;
-  g.B = q->H1; g.b_k = H; g.b_j = 1; g.C = q->Gr + q->oW2; g.ldc = H;
-  MTRY(gemm32(g, s));
-  colsum<<<(H + NT - 1) / NT, NT, 0, s>>>(q->DZ, B, H, q->Gr + q->ob2);
-  // dH1 = DZ2 W2
-  g.M = B; g.N = H; g.K = H; g.A = q->DZ; g.a_i = H; g.a_k = 1;
-  g.B = q->P + q->oW2; g.b_k = H; g.b_j = 1; g.C = q->DH; g.ldc = H;
-  MTRY(gemm32(g, s));
-  silu_back<<<blocks_for((int64_t)B * H), NT, 0, s>>>(q->DH, q->Z1, q->DZ, (int64_t)B * H);
-  // gW1 = DZ1^T X
-  g.M = H; g.N = m; g.K = B; g.A = q->DZ; g.a_i = 1; g.a_k = H;
-  g.B = x; g.b_k = m; g.b_j = 1; g.C = q->Gr + q->oW1; g.ldc = m;
-  MTRY(gemm32(g, s));
-  colsum<<<(H + NT - 1) / NT, NT, 0, s>>>(q->DZ, B, H, q->Gr + q->ob1);
+  SliceSums ss{};
+  // g[i][j] = sum_b dz[b][i] in[b][j] in slices of the batch
+  auto weights = [&](int l, const float* dz, const float* in) -> hipError_t {
+    G32 g{};
+    layer_shape(q, l, &g.M, &g.N);
+    g.K = B; g.A = dz; g.lda = g.M; g.B = in; g.ldb = g.N; g.C = q->slices[l];
+    const int n = slices_of(g.M, g.N, B);
+    g.kslice = ((B + n - 1) / n + GBK - 1) / GBK * GBK;
+    ss.src[l] = g.C;
+    ss.len[l] = (int64_t)g.M * g.N + g.M;
+    ss.slices[l] = (B + g.kslice - 1) / g.kslice;
+    return gemm32<false, false, GRADIENT>(g, s);
+  };
+  // dz_out[b][j] = silu'(z[b][j]) sum_i dz[b][i] W[i][j]
+  auto back = [&](int l, const float* dz, const float* W, float* z, float* out) -> hipError_t {
+    G32 g{};
+    g.M = B;
+    layer_shape(q, l, &g.K, &g.N);
+    g.A = dz; g.lda = g.K; g.B = W; g.ldb = g.N; g.Z = z; g.C = out;
+    return gemm32<true, false, BACK>(g, s);
+  };
+  MTRY(weights(2, q->D, q->H2));
+  MTRY(back(2, q->D, q->P + q->oW3, q->Z2, q->DZ2));
+  MTRY(weights(1, q->DZ2, q->H1));
+  MTRY(back(1, q->DZ2, q->P + q->oW2, q->Z1, q->DZ1));
+  MTRY(weights(0, q->DZ1, x));
+  ss.out = q->Gr;
+  ss.part = q->part;
+  ss.nparts = tiles_of(B, m, tile_edge(B, m));
+  ss.loss = q->loss;
+  sum_slices<<<blocks_for(q->np) + 1, NT, 0, s>>>(ss, q->np);
   MTRY(hipGetLastError());
   return 0;
 }
@@ -445,11 +604,21 @@ static int thcsox_mlp_create_impl(thcsox_mlp_t* out, int m, int hidden, int max_
       (rc = malloc_into(q, &q->M1, q->np)) || (rc = malloc_into(q, &q->M2, q->np)) ||
       (rc = malloc_into(q, &q->Z1, B * H)) || (rc = malloc_into(q, &q->H1, B * H)) ||
       (rc = malloc_into(q, &q->Z2, B * H)) || (rc = malloc_into(q, &q->H2, B * H)) ||
-      (rc = malloc_into(q, &q->Y, B * m)) || (rc = malloc_into(q, &q->D, B * m)) ||
-      (rc = malloc_into(q, &q->DH, B * H)) || (rc = malloc_into(q, &q->DZ, B * H)) ||
-      (rc = malloc_into(q, &q->part, 4096)) || (rc = malloc_into(q, &q->loss, 1))) {
+      (rc = malloc_into(q, &q->D, B * m)) ||
+      (rc = malloc_into(q, &q->DZ1, B * H)) || (rc = malloc_into(q, &q->DZ2, B * H)) ||
+      (rc = malloc_into(q, &q->part, tiles_of(max_batch, m, 32))) ||
+      (rc = malloc_into(q, &q->loss, 1))) {
     delete q;
     return rc;
+  }
+  for (int l = 0; l < 3; ++l) {
+    int M, N;
+    layer_shape(q, l, &M, &N);
+    const int n = slices_of(M, N, max_batch);   // no smaller batch takes more
+    if ((rc = malloc_into(q, &q->slices[l], (size_t)n * ((size_t)M * N + M)))) {
+      delete q;
+      return rc;
+    }
   }
   hipError_t e;
   if ((e = hipMemcpyAsync(q->P, params_host, sizeof(float) * q->np, hipMemcpyHostToDevice,
@@ -479,7 +648,8 @@ int thcsox_mlp_forward(thcsox_mlp_t q, const float* x_dev, float* y_dev, int bat
     return set_error(THCSOX_EINVAL, "bad argument");
   for (int b0 = 0; b0 < batch; b0 += q->maxb) {
     const int B = std::min(q->maxb, batch - b0);
-    const int rc = forward(q, x_dev + (int64_t)b0 * q->m, y_dev + (int64_t)b0 * q->m, B);
+    const int rc = forward(q, x_dev + (int64_t)b0 * q->m, y_dev + (int64_t)b0 * q->m, nullptr, B,
+                           false);
     if (rc) return rc;
   }
   return 0;
@@ -491,9 +661,9 @@ int thcsox_mlp_gradients(thcsox_mlp_t q, const float* x_dev, const float* target
   if (q == nullptr || x_dev == nullptr || target_dev == nullptr || batch <= 0 ||
       batch > q->maxb)
     return set_error(THCSOX_EINVAL, "bad argument (batch must be in 1..max_batch)");
-  int rc = forward(q, x_dev, q->Y, batch);
+  int rc = forward(q, x_dev, nullptr, target_dev, batch, true);
   if (rc) return rc;
-  if ((rc = backward(q, x_dev, target_dev, batch))) return rc;
+  if ((rc = backward(q, x_dev, batch))) return rc;
   double sse = 0.0;
   MTRY(hipMemcpyAsync(&sse, q->loss, sizeof(double), hipMemcpyDeviceToHost, q->stream));
   if (grads_host)
@@ -510,9 +680,9 @@ int thcsox_mlp_train_step(thcsox_mlp_t q, const float* x_dev, const float* targe
   if (q == nullptr || x_dev == nullptr || target_dev == nullptr || batch <= 0 ||
       batch > q->maxb)
     return set_error(THCSOX_EINVAL, "bad argument (batch must be in 1..max_batch)");
-  int rc = forward(q, x_dev, q->Y, batch);
+  int rc = forward(q, x_dev, nullptr, target_dev, batch, true);
   if (rc) return rc;
-  if ((rc = backward(q, x_dev, target_dev, batch))) return rc;
+  if ((rc = backward(q, x_dev, batch))) return rc;
   q->step += 1;
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, (float)q->step), c2 = 1.f - std::pow(b2, (float)q->step);
