@@ -473,7 +473,8 @@ int thcsox_pair_scatter(int m, int naux, const float* y_dev, const double* scale
  *   THCSOX_STAGE_BACK    : reduction of D, Sig_RP and the back-projection
  * thcsox_profile(p, 1) starts recording (and clears what was recorded);
  * thcsox_stage_times synchronises the stream and returns, per stage, the total
- * milliseconds and the number of timed launches since the last read, then clears. */
+ * milliseconds and the number of timed launches since the last read, then clears
+ * (a fused launch counts once per tau point that it covers). */
 enum {
   THCSOX_STAGE_PROJECT = 0,
   THCSOX_STAGE_A = 1,

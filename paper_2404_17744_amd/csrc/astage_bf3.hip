@@ -63,8 +63,8 @@ typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 // 16 tile0 on (wave w: tiles tile0 + NCT w .. + NCT - 1).
 template <int KST, int NCT>
 __device__ __forceinline__ void astage_b3_body(const AStageB3Args& g, B3Buf<KST>& b0,
-                                               B3Buf<KST>& b1, int tile0, int first, int last,
-                                               int stride) {
+                                               B3Buf<KST>& b1, int set, int tile0, int first,
+                                               int last, int stride) {
   constexpr int LDK = 32 * KST;
   using PR = Products<3>;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -80,7 +80,8 @@ __device__ __forceinline__ void astage_b3_body(const AStageB3Args& g, B3Buf<KST>
   __amdgpu_buffer_rsrc_t rG[3];
 #pragma unroll
   for (int p = 0; p < 3; ++p)
-    rG[p] = make_rsrc(static_cast<const __bf16*>(g.Gb) + p * g.gb_plane, (int64_t)g.n * LDK * 2);
+    rG[p] = make_rsrc(static_cast<const __bf16*>(g.Gb) + set * g.gb_set + p * g.gb_plane,
+                      (int64_t)g.n * LDK * 2);
   bf16x8 gr[NCT][KST][3];
   // the first fragments live in AGPRs (the matrix cores read them there), as many
   // as fit beside the accumulators; the rest in VGPRs
@@ -172,7 +173,7 @@ __device__ __forceinline__ void astage_b3_body(const AStageB3Args& g, B3Buf<KST>
   // stores: the lane's four q of column v at (v c_j + 16 a + 4 (lane / 16)) elements
   // from the step's piece of row (0, P) of a plane (offsets below 2^31: checked on
   // the host); columns v >= n lie past the end of the resource and are dropped
-  __bf16* const A = static_cast<__bf16*>(g.A);
+  __bf16* const A = static_cast<__bf16*>(g.A) + set * g.a_set;
   const int64_t c_j = (int64_t)g.naux * LDK;
   uint32_t cvoff[NCT];
 #pragma unroll
@@ -255,13 +256,16 @@ __global__ __launch_bounds__(BNT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void astage_bf3r_kernel(AStageB3Args g) {
   __shared__ __attribute__((aligned(16))) B3Buf<KST> b0;
   __shared__ __attribute__((aligned(16))) B3Buf<KST> b1;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  // the workers of all sets on an XCD walk its range, so its L2 serves U to them
+  const int xcd = blockIdx.x & 7, part = blockIdx.x >> 3;
+  const int set = __builtin_amdgcn_readfirstlane(part % g.nsets);
+  const int slot = __builtin_amdgcn_readfirstlane(part / g.nsets);
   const int nstep = g.naux * KST;
   const int lo = (int)((int64_t)nstep * xcd / 8), hi = (int)((int64_t)nstep * (xcd + 1) / 8);
   if (NCT1 == 0 || slot < g.wx0) {
-    astage_b3_body<KST, NCT0>(g, b0, b1, 0, lo + slot, hi, g.wx0);
+    astage_b3_body<KST, NCT0>(g, b0, b1, set, 0, lo + slot, hi, g.wx0);
   } else if constexpr (NCT1 > 0) {
-    astage_b3_body<KST, NCT1>(g, b0, b1, 4 * NCT0, lo + slot - g.wx0, hi, g.wx1);
+    astage_b3_body<KST, NCT1>(g, b0, b1, set, 4 * NCT0, lo + slot - g.wx0, hi, g.wx1);
   }
 }
 
@@ -272,14 +276,14 @@ hipError_t b3_launch(AStageB3Args g, hipStream_t s) {
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) == hipSuccess)
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const int wx = std::max(1, cus / 8);   // workers per XCD
+  const int wx = std::max(NCT1 == 0 ? 1 : 2, cus / (8 * g.nsets));   // workers per XCD and set
   if (NCT1 == 0) {
     g.wx0 = wx; g.wx1 = 0;
   } else {
     g.wx0 = std::min(wx - 1, std::max(1, (wx * NCT0 + (NCT0 + NCT1) / 2) / (NCT0 + NCT1)));
     g.wx1 = std::max(1, wx - g.wx0);
   }
-  astage_bf3r_kernel<KST, NCT0, NCT1><<<8 * (g.wx0 + g.wx1), BNT, 0, s>>>(g);
+  astage_bf3r_kernel<KST, NCT0, NCT1><<<8 * (g.wx0 + g.wx1) * g.nsets, BNT, 0, s>>>(g);
   return hipGetLastError();
 }
 
@@ -292,7 +296,7 @@ bool astage_bf3_fits(int n, int naux, int ldk) {
 }
 
 hipError_t astage_bf3(const AStageB3Args& g, hipStream_t s) {
-  if (g.naux <= 0 || g.n <= 0) return hipSuccess;
+  if (g.naux <= 0 || g.n <= 0 || g.nsets <= 0) return hipSuccess;
   if (!astage_bf3_fits(g.n, g.naux, g.ldk)) return hipErrorInvalidValue;
   // ldk = 32 ceil(n / 32): the tile counts follow from the chunk count
   const int tiles = (g.n + 15) / 16;

@@ -599,8 +599,8 @@ bool astage_f32_fits(int n, int naux, int ldk) {
 }
 
 hipError_t astage_f32(const AStageArgs& g, hipStream_t s) {
-  if (g.naux <= 0 || g.n <= 0) return hipSuccess;
-  if (g.nsets != 1 || !astage_f32_fits(g.n, g.naux, g.ldk)) return hipErrorInvalidValue;
+  if (g.naux <= 0 || g.n <= 0 || g.nsets <= 0) return hipSuccess;
+  if (!astage_f32_fits(g.n, g.naux, g.ldk)) return hipErrorInvalidValue;
   switch (g.ldk) {
     case 64: return r_launch(astage_f32r_kernel_2, g, s);
     case 128: return r_launch(astage_f32r_kernel_4, g, s);

@@ -71,7 +71,8 @@ __global__ __launch_bounds__(NT) void fused_kernel(FusedArgs f) {
   const int within = to - rb0 * npb;
   const int P0 = (within / bh) * TP, R0 = (rb0 + within % bh) * TR;
   // symmetric D: a tile wholly below the diagonal is the mirror of one above it
-  if (f.sym != nullptr && *f.sym != 0 && R0 >= P0 + TP) return;
+  const int set = blockIdx.y;
+  if (f.sym != nullptr && f.sym[set] != 0 && R0 >= P0 + TP) return;
   // v range: XCD x owns the consecutive ranges x q .. x q + q - 1 (q = vsplit / NXCD),
   // and the ranges split n as evenly as floor division allows, so every XCD gets
   // the same number of v to within one; range r is [r n / vsplit, (r + 1) n / vsplit)
@@ -85,8 +86,8 @@ __global__ __launch_bounds__(NT) void fused_kernel(FusedArgs f) {
   const int64_t a_v = (int64_t)f.naux * ldk;       // elements between v slabs of A
   const int rows_r = min(TR, f.naux - R0), rows_p = min(TP, f.naux - P0);
 
-  const T* Gt = static_cast<const T*>(f.Gt) + R0 * ldk;
-  const T* GX = static_cast<const T*>(f.GXt) + P0 * ldk;
+  const T* Gt = static_cast<const T*>(f.Gt) + set * f.g_set + R0 * ldk;
+  const T* GX = static_cast<const T*>(f.GXt) + set * f.g_set + P0 * ldk;
   const T* U = static_cast<const T*>(f.U) + R0 * u_row;
   __amdgpu_buffer_rsrc_t rG[NP], rX[NP];
 #pragma unroll
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(NT) void fused_kernel(FusedArgs f) {
     }
 #pragma unroll
     for (int p = 0; p < NP; ++p)
-      pA[p].load(make_rsrc(static_cast<const T*>(f.A) + p * f.a_plane + v * a_v + P0 * ldk,
+      pA[p].load(make_rsrc(static_cast<const T*>(f.A) + set * f.a_set + p * f.a_plane + v * a_v + P0 * ldk,
                            TP * ldk * ES),
                  k0);
   };
@@ -133,8 +134,8 @@ __global__ __launch_bounds__(NT) void fused_kernel(FusedArgs f) {
         accC[ti][tj][r] = 0;
         accD[ti][tj][r] = 0;
       }
-  double* D = f.Dpart + (int64_t)z * f.naux * f.naux;
-  float* D32 = reinterpret_cast<float*>(f.Dpart) + (int64_t)z * f.naux * f.naux;
+  double* D = f.Dpart + set * f.d_set + (int64_t)z * f.naux * f.naux;
+  float* D32 = reinterpret_cast<float*>(f.Dpart) + set * f.d_set + (int64_t)z * f.naux * f.naux;
   // add (or, the first time, store) the register partial sums into the FP64 tile
   auto flush = [&](bool first) {
 #pragma unroll
@@ -269,7 +270,7 @@ hipError_t sox_fused(int mode, const FusedArgs& f, hipStream_t s) {
   if (f.dpart_f32 && (mode == MODE_F64 || f.vchunk > FLUSH_V)) return hipErrorInvalidValue;
   // buffer offsets inside one tile's rows of U are 32-bit
   if ((int64_t)std::max(TR, TP) * f.n * f.ldk * 8 > 0x7fffffffLL) return hipErrorInvalidValue;
-  dim3 grid(cdiv(f.naux, TP) * cdiv(f.naux, TR) * f.vsplit);
+  dim3 grid(cdiv(f.naux, TP) * cdiv(f.naux, TR) * f.vsplit, f.nsets);
   switch (mode) {
     case MODE_F64: fused_kernel<MODE_F64><<<grid, NT, 0, s>>>(f); break;
     default: return hipErrorInvalidValue;

@@ -76,7 +76,8 @@ void fused_bf3_kernel(FusedArgs f) {
   // symmetric D only the tiles on or above the diagonal are walked.  The integer
   // divisions run on the vector unit; readfirstlane marks their results uniform.
   const int nb = (naux + TT - 1) / TT;
-  const bool symm = f.sym != nullptr && *f.sym != 0;
+  const int set = blockIdx.y;
+  const bool symm = f.sym != nullptr && f.sym[set] != 0;
   const int ntl = symm ? nb * (nb + 1) / 2 : nb * nb;
   const int b = blockIdx.x;
   const int xcd = b % NXCD, local = b / NXCD;
@@ -113,10 +114,10 @@ void fused_bf3_kernel(FusedArgs f) {
 
   // operand planes (rows past the valid range lie beyond the buffer resources
   // and read as zero)
-  const __bf16* Gt = static_cast<const __bf16*>(f.Gt);
-  const __bf16* GX = static_cast<const __bf16*>(f.GXt);
+  const __bf16* Gt = static_cast<const __bf16*>(f.Gt) + set * f.g_set;
+  const __bf16* GX = static_cast<const __bf16*>(f.GXt) + set * f.g_set;
   const __bf16* Ub = static_cast<const __bf16*>(f.U);
-  const __bf16* Ab = static_cast<const __bf16*>(f.A);
+  const __bf16* Ab = static_cast<const __bf16*>(f.A) + set * f.a_set;
   __amdgpu_buffer_rsrc_t rG[NPL], rX[NPL];
 #pragma unroll
   for (int p = 0; p < NPL; ++p) {
@@ -275,7 +276,7 @@ void fused_bf3_kernel(FusedArgs f) {
     const float* sDf = reinterpret_cast<const float*>(sD);
     const int Pt = tid & (TT - 1), P = P0 + Pt;
     const int pslot = (Pt >> 6) * 16 * 64 + ((Pt >> 4) & 3) * 64 + (Pt & 15);
-    const int64_t zo = (int64_t)z * naux * naux + P;
+    const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
     for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
       const int R = R0 + Rt;
       if (R < naux && P < naux) {
@@ -358,7 +359,7 @@ hipError_t sox_fused_bf3(const FusedArgs& f, hipStream_t s) {
   // buffer offsets inside one tile's rows of U (rows of 2 ldk bytes) are 32-bit
   if ((int64_t)TT * f.n * f.ldk * 2 > 0x7fffffffLL) return hipErrorInvalidValue;
   const unsigned nb = cdiv_bf3(f.naux, TT);
-  fused_bf3_kernel<<<dim3(nb * nb * f.vsplit), NTH, 0, s>>>(f);
+  fused_bf3_kernel<<<dim3(nb * nb * f.vsplit, f.nsets), NTH, 0, s>>>(f);
   return hipGetLastError();
 }
 

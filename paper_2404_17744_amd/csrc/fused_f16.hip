@@ -88,7 +88,8 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   // integer divisions run on the vector unit; readfirstlane marks their results
   // uniform so that buffer resources and offsets stay scalar.
   const int nb = (naux + TT - 1) / TT;
-  const bool symm = f.sym != nullptr && *f.sym != 0;
+  const int set = blockIdx.y;
+  const bool symm = f.sym != nullptr && f.sym[set] != 0;
   const int ntl = symm ? nb * (nb + 1) / 2 : nb * nb;
   const int b = blockIdx.x;
   const int xcd = b % NXCD16, local = b / NXCD16;
@@ -125,12 +126,12 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   const int ld2 = 2 * ldk;   // halves per c32 row
   const int rows_r = min(TT, naux - R0), rows_p = min(TT, naux - P0);
 
-  const _Float16* Gt = static_cast<const _Float16*>(f.Gt);
-  const _Float16* GX = static_cast<const _Float16*>(f.GXt);
+  const _Float16* Gt = static_cast<const _Float16*>(f.Gt) + set * f.g_set;
+  const _Float16* GX = static_cast<const _Float16*>(f.GXt) + set * f.g_set;
   const __amdgpu_buffer_rsrc_t rG = make_rsrc(Gt + (int64_t)R0 * ld2, (int64_t)rows_r * ld2 * 2);
   const __amdgpu_buffer_rsrc_t rX = make_rsrc(GX + (int64_t)P0 * ld2, (int64_t)rows_p * ld2 * 2);
   const _Float16* Ubase = static_cast<const _Float16*>(f.U) + (int64_t)R0 * n * ld2;
-  const _Float16* Abase = static_cast<const _Float16*>(f.A) + (int64_t)P0 * ld2;
+  const _Float16* Abase = static_cast<const _Float16*>(f.A) + set * f.a_set + (int64_t)P0 * ld2;
   const int64_t a_v = (int64_t)naux * ld2;   // halves between v slabs of A
 
   // memory -> LDS: one instruction moves 8 rows x 128 bytes; wave w moves the
@@ -317,7 +318,7 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
     const float* sDf = reinterpret_cast<const float*>(sD);
     const int Pt = tid & (TT - 1), P = P0 + Pt;
     const int pslot = (Pt >> 6) * 16 * 64 + ((Pt >> 4) & 3) * 64 + (Pt & 15);
-    const int64_t zo = (int64_t)z * naux * naux + P;
+    const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
     for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
       const int R = R0 + Rt;
       if (R < naux && P < naux) {
@@ -429,8 +430,8 @@ hipError_t sox_fused_pairs(int mode, const FusedArgs& f, hipStream_t s) {
   // buffer offsets inside one tile's rows of U (rows of 4 ldk bytes) are 32-bit
   if ((int64_t)TT * f.n * f.ldk * 4 > 0x7fffffffLL) return hipErrorInvalidValue;
   const unsigned nb = cdiv16(f.naux, TT);
-  if (mode == MODE_F16X2) fused_f16_kernel<<<dim3(nb * nb * f.vsplit), NTH, 0, s>>>(f);
-  else fused_f32_kernel<<<dim3(nb * nb * f.vsplit), NTH, 0, s>>>(f);
+  if (mode == MODE_F16X2) fused_f16_kernel<<<dim3(nb * nb * f.vsplit, f.nsets), NTH, 0, s>>>(f);
+  else fused_f32_kernel<<<dim3(nb * nb * f.vsplit, f.nsets), NTH, 0, s>>>(f);
   return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(NT) void gemmk_kernel(GemmKArgs g) {
   const int i0 = (blockIdx.x % nib) * TM, j0 = (blockIdx.x / nib) * TN;
 
   const T* A = static_cast<const T*>(g.A) + (int64_t)i0 * g.lda;
-  const T* B = static_cast<const T*>(g.B) + (int64_t)j0 * g.ldb;
+  const T* B = static_cast<const T*>(g.B) + blockIdx.y * g.b_set + (int64_t)j0 * g.ldb;
   __amdgpu_buffer_rsrc_t rA[NP], rB[NP];
   Panel<T, TM> pA[NP];
   Panel<T, TN> pB[NP];
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(NT) void gemmk_kernel(GemmKArgs g) {
   }
 
   double lmax = 0.0;
-  OutT* C = static_cast<OutT*>(g.C);
+  OutT* C = static_cast<OutT*>(g.C) + blockIdx.y * g.c_set;
   if constexpr (__is_same(OutT, __bf16)) {
     // three bf16 planes; a lane's four outputs are four consecutive rows i of one
     // column j: one 8-byte store per plane when they lie in one block of ci_in
@@ -151,7 +151,7 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 template <int M, int WTI, int WTJ>
 hipError_t launch(bool out_f64, const GemmKArgs& g, hipStream_t s) {
-  const unsigned grid = cdiv(g.M, 32 * WTI) * cdiv(g.N, 32 * WTJ);
+  const dim3 grid(cdiv(g.M, 32 * WTI) * cdiv(g.N, 32 * WTJ), g.nsets);
   if (out_f64) gemmk_kernel<M, WTI, WTJ, double><<<grid, NT, 0, s>>>(g);
   else gemmk_kernel<M, WTI, WTJ, float><<<grid, NT, 0, s>>>(g);
   return hipGetLastError();
@@ -169,7 +169,7 @@ hipError_t launch_mode(bool out_f64, const GemmKArgs& g, hipStream_t s) {
 hipError_t gemm_kmajor_bf3(const GemmKArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   const int wtj = g.N <= 320 ? 10 : 5;
-  const unsigned grid = cdiv(g.M, 128) * cdiv(g.N, 32 * wtj);
+  const dim3 grid(cdiv(g.M, 128) * cdiv(g.N, 32 * wtj), g.nsets);
   if (wtj == 10) gemmk_kernel<MODE_BF16X3, 4, 10, __bf16><<<grid, NT, 0, s>>>(g);
   else gemmk_kernel<MODE_BF16X3, 4, 5, __bf16><<<grid, NT, 0, s>>>(g);
   return hipGetLastError();

@@ -115,37 +115,45 @@ __global__ void fill_u64_kernel(unsigned long long* p, int64_t n, unsigned long 
 constexpr int DT = 32;          // reduction tile edge
 constexpr int DRP = NT / DT;    // rows per pass
 constexpr int DEL = DT / DRP;   // elements per thread
+// (vector types of element alignment: rows of any length are read in 16- or 32-byte pieces)
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d4u __attribute__((ext_vector_type(4), aligned(8)));
 __device__ __forceinline__ void add4(const float* p, double* acc) {
-  const float4 v = *reinterpret_cast<const float4*>(p);
-  acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
+  const f4u v = *reinterpret_cast<const f4u*>(p);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] += (double)v[e];
 }
 __device__ __forceinline__ void add4(const double* p, double* acc) {
-  const double2 v0 = *reinterpret_cast<const double2*>(p);
-  const double2 v1 = *reinterpret_cast<const double2*>(p + 2);
-  acc[0] += v0.x; acc[1] += v0.y; acc[2] += v1.x; acc[3] += v1.y;
+  const d4u v = *reinterpret_cast<const d4u*>(p);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] += v[e];
 }
 
 template <typename T>
 __global__ __launch_bounds__(NT) void dreduce_kernel(DReduceArgs a) {
   __shared__ double t[DT][DT + 1];
-  const double f = pow2_scale(a.amax_gt) * pow2_scale(a.amax_gx) * pow2_scale(a.amax_gb) *
-                   pow2_scale(a.amax_a) * pow2_scale(a.amax_u) *
+  const int set = blockIdx.y;
+  const double f = pow2_scale(a.amax_gt + set) * pow2_scale(a.amax_gx + set) *
+                   pow2_scale(a.amax_gb - set) *
+                   pow2_scale(a.amax_a != nullptr ? a.amax_a + set : nullptr) * pow2_scale(a.amax_u) *
                    pow2_scale(a.amax_u2 != nullptr ? a.amax_u2 : a.amax_u);
   const double inv = 1.0 / f;   // exact: a power of two
   const int64_t nn = (int64_t)a.naux * a.naux;
-  const bool sym = a.sym != nullptr && *a.sym != 0;
+  const bool sym = a.sym != nullptr && a.sym[set] != 0;
+  double* const Sthc = a.Sthc + set * a.s_set;
   const int nt = (a.naux + DT - 1) / DT;
   const int rb = blockIdx.x / nt, pb = blockIdx.x % nt;
   // symmetric D: the tiles below the diagonal are written by their transposes
   if (sym && rb > pb) return;
-  // sum over z: thread = (row ar, four consecutive columns ac..ac+3), 16-byte
-  // loads when the row length allows
+  // sum over z: thread = (row ar, four consecutive columns ac..ac+3), one load for the
+  // four except at the end of a row (single loads for every odd row length took 18
+  // instead of 8 us at naux = 485, 16 partial tiles)
   const int ar = threadIdx.x / (DT / 4), ac = 4 * (threadIdx.x % (DT / 4));
   const int gr = rb * DT + ar, gc = pb * DT + ac;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   if (gr < a.naux) {
-    const T* D0 = reinterpret_cast<const T*>(a.Dpart) + (int64_t)gr * a.naux + gc;
-    if (a.naux % 4 == 0 && gc + 3 < a.naux) {
+    const T* D0 = reinterpret_cast<const T*>(a.Dpart) + set * a.d_set + (int64_t)gr * a.naux + gc;
+    if (gc + 3 < a.naux) {
 #pragma unroll 4
       for (int z = 0; z < a.vsplit; ++z) add4(D0 + z * nn, acc);
     } else {
@@ -167,12 +175,12 @@ __global__ __launch_bounds__(NT) void dreduce_kernel(DReduceArgs a) {
     const int R = rb * DT + lr, P = pb * DT + lc;
     if (R < a.naux && P < a.naux) {
       const double v = (sym && rb == pb && R > P) ? t[lc][lr] : t[lr][lc];
-      a.Sthc[(int64_t)R * a.s_ld + P] = -inv * v;
+      Sthc[(int64_t)R * a.s_ld + P] = -inv * v;
     }
     // symmetric, off the diagonal: element (R2, P2) of the transposed tile (pb, rb)
     if (sym && rb < pb) {
       const int R2 = pb * DT + lr, P2 = rb * DT + lc;
-      if (R2 < a.naux && P2 < a.naux) a.Sthc[(int64_t)R2 * a.s_ld + P2] = -inv * t[lc][lr];
+      if (R2 < a.naux && P2 < a.naux) Sthc[(int64_t)R2 * a.s_ld + P2] = -inv * t[lc][lr];
     }
   }
 }
@@ -366,8 +374,8 @@ hipError_t fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipS
 hipError_t dreduce(const DReduceArgs& a, hipStream_t s) {
   if (a.naux <= 0) return hipSuccess;
   const unsigned nt = cdiv(a.naux, DT);
-  if (a.dpart_f32) dreduce_kernel<float><<<nt * nt, NT, 0, s>>>(a);
-  else dreduce_kernel<double><<<nt * nt, NT, 0, s>>>(a);
+  if (a.dpart_f32) dreduce_kernel<float><<<dim3(nt * nt, a.nsets), NT, 0, s>>>(a);
+  else dreduce_kernel<double><<<dim3(nt * nt, a.nsets), NT, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -375,7 +383,6 @@ hipError_t asym64(const double* G, int n, int m, unsigned long long* asym, hipSt
   if (n <= 0 || m <= 0) return hipSuccess;
   unsigned bx = cdiv((int64_t)n * n, NT);
   if (bx > 256) bx = 256;
-  fill_u64_kernel<<<cdiv(m, NT), NT, 0, s>>>(asym, m, 0ull);
   asym_kernel<<<dim3(bx, m), NT, 0, s>>>(G, n, asym);
   return hipGetLastError();
 }

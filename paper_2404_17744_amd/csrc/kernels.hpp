@@ -34,6 +34,8 @@ struct GemmKArgs {
   void* C; int64_t ci_in, ci_out, c_j;
   unsigned long long* amax;
   int64_t c_plane;   // gemm_kmajor_bf3: elements between the output planes
+  // nsets products of the same A: B and C of set x lie x b_set, x c_set elements further
+  int nsets; int64_t b_set, c_set;
 };
 hipError_t gemm_kmajor(int mode, bool out_f64, const GemmKArgs& g, hipStream_t s);
 // The same product in the bf16x3 mode with the output split into three bf16
@@ -55,14 +57,14 @@ struct AStageArgs {
   const unsigned long long* amax;
 };
 hipError_t astage_f16(const AStageArgs& a, hipStream_t s);
-// The same stage in the FP32 mode for one tau point (nsets = 1; amax, a_set
-// unused): U, Gb and A are FP32 K-major rows of ldk elements (A passed as the
-// address of its FP32 array), A written unscaled.  Only for ldk a multiple of 64
-// up to 320 with A's byte offsets in 31 bits (astage_f32_fits); otherwise
-// hipErrorInvalidValue (use gemm_kmajor).
+// The same stage in the FP32 mode (amax unused): U, Gb and A are FP32 K-major rows of
+// ldk elements (A passed as the address of its FP32 array; gb_set and a_set still
+// count halves), A written unscaled.  Only for ldk a multiple of 64 up to 320 with
+// A's byte offsets in 31 bits (astage_f32_fits); otherwise hipErrorInvalidValue
+// (use gemm_kmajor).
 bool astage_f32_fits(int n, int naux, int ldk);
 hipError_t astage_f32(const AStageArgs& a, hipStream_t s);
-// The A stage of the bf16x3 mode for one tau point:
+// The A stage of the bf16x3 mode for nsets tau points (gb_set, a_set elements apart):
 //   A[p][v][P][q] = plane p of the bf16x3 split of sum_s U[P][q][s] Gb[v][s]
 //   (q < n; rows n <= q < ldk get 0)
 // U rows (P, q) and Gb rows v (G(beta - tau)^T) are three bf16 planes of ldk
@@ -74,12 +76,13 @@ struct AStageB3Args {
   const void* U; int64_t u_plane;
   const void* Gb; int64_t gb_plane;
   void* A; int64_t a_plane;
+  int nsets; int64_t gb_set, a_set;
   int wx0, wx1;   // set by the launcher
 };
 bool astage_bf3_fits(int n, int naux, int ldk);
 hipError_t astage_bf3(const AStageB3Args& a, hipStream_t s);
 
-// The fused B/C/D stage for one tau point (v split over grid.z):
+// The fused B/C/D stage for nsets tau points (grid.y), each:
 //   Dpart[z][R][P] = sum_{v in split z} (sum_q Gt[R][q] A[v][P][q]) (sum_w U[R][v][w] GXt[P][w])
 // A holds the mode's planes (fp16x2: scaled by the power of two taken from
 // *amax_a, which the reduction divides out; otherwise unscaled).  In the fp16x2
@@ -101,6 +104,9 @@ struct FusedArgs {
   // symmetric): tiles lying wholly below the diagonal (every R > every P) are
   // skipped and their Dpart entries are left untouched.
   const int* sym;
+  // set x of the launch: Gt and GXt lie x g_set, A x a_set and Dpart x d_set elements
+  // (fp16x2 and FP32: halves; Dpart: of its own type) further, its flag at sym[x]
+  int nsets; int64_t g_set, a_set, d_set;
 };
 hipError_t sox_fused(int mode, const FusedArgs& f, hipStream_t s);
 void fused_tile(int mode, int* rows, int* cols);   // D tile one workgroup owns (R x P)
@@ -163,10 +169,13 @@ struct DReduceArgs {
   // the U of the C product when it differs from the A product's (two cores); null: amax_u
   const unsigned long long* amax_u2;
   const int* sym;
+  // set x of the launch (grid.y): Dpart lies x d_set elements of its type, Sthc x s_set
+  // further; amax_gt, amax_gx, amax_a and sym are taken at x, amax_gb at -x
+  int nsets; int64_t d_set, s_set;
 };
 hipError_t dreduce(const DReduceArgs& a, hipStream_t s);
 
-// asym[k] = max |G[k] - G[k]^T| (as the bits of a non-negative double), k < m.
+// asym[k] = max |G[k] - G[k]^T| (max-reduced, as the bits of a non-negative double), k < m.
 hipError_t asym64(const double* G, int n, int m, unsigned long long* asym, hipStream_t s);
 // flag[k] = 1 if both G[k] and G[m-1-k] are symmetric to within rtol of the
 // largest element of G on the whole grid (asym[k] <= rtol * max_j amax[j]), else 0.

@@ -143,9 +143,11 @@ struct thcsox_plan_s {
   double* w = nullptr;      // [m]
   void* U = nullptr;        // planes of [naux][n][ldk] (fp16x2: c32 rows [naux][n])
   int64_t u_plane = 0;
-  void* A = nullptr;        // planes of [n][naux][ldk] (fp16x2: [a_sets] c32 rows [n][naux])
-  int64_t a_plane = 0;
-  int a_sets = 1;           // tau points per A-stage launch (fp16x2: 2 while A is small)
+  void* A = nullptr;        // planes of [a_sets][n][naux][ldk] (fp16x2: c32 rows)
+  int64_t a_plane = 0, a_set = 0;   // elements between planes, between sets (of a row's type)
+  // tau points per launch of the A stage, and of the fused stage and its reduction (a
+  // divisor of it): enough to fill the chip several times, where the memory allows
+  int a_sets = 1, f_sets = 1;
   // fp16x2: the largest squared row norms of U ([0]) and of the screened core's
   // U ([1]), and of G(beta - tau)^T for each tau of a batch ([2 ..]): the A
   // stage's scale is taken from their product before A is formed
@@ -158,7 +160,7 @@ struct thcsox_plan_s {
   int64_t gb_plane = 0;
   double* Gt64 = nullptr;   // [tb][naux][n]
   double* GX64 = nullptr;   // [tb][naux][n]
-  double* Dpart = nullptr;  // [vsplit][naux][naux], FP64 or (dpart_f32) FP32
+  double* Dpart = nullptr;  // [f_sets][vsplit][naux][naux], FP64 or (dpart_f32) FP32
   bool dpart_f32 = false;
   int vsplit = 1, vchunk = 1;
   double* Sthc = nullptr;   // [tb][naux][naux]
@@ -178,6 +180,7 @@ struct thcsox_plan_s {
   struct Timer {
     std::vector<hipEvent_t> start, stop;
     size_t used = 0;
+    int count = 0;
   } timers[THCSOX_NSTAGES];
   double* tr = nullptr;     // [m]
   double* E = nullptr;      // [1]
@@ -210,7 +213,8 @@ struct thcsox_plan_s {
     }
     for (void* q : allocs) (void)hipFree(q);
   }
-  hipError_t mark(int stage, bool begin) {
+  // (count: what the stage's end adds to its launch count)
+  hipError_t mark(int stage, bool begin, int count = 1) {
     if (!profiling) return hipSuccess;
     Timer& t = timers[stage];
     if (begin && t.used == t.start.size()) {
@@ -222,6 +226,7 @@ struct thcsox_plan_s {
       t.stop.push_back(b);
     }
     if (begin) return hipEventRecord(t.start[t.used], stream);
+    t.count += count;
     return hipEventRecord(t.stop[t.used++], stream);
   }
 };
@@ -329,7 +334,8 @@ struct Cores {
 
 // Tau points k0 <= k < k1 (k1 - k0 <= tb): Sigma[k] (and Sig_thc[k]) from G,
 // Sigma[k] = alpha_out X Sig_thc X^T + beta_out Sigma[k].
-// Needs the per-tau max |G[k]| and the symmetry flags of every k (set by the caller).
+// Needs prepare_g's per-tau values (max |G[k]|, the symmetry flags, cleared maxima of
+// the projections).
 int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_out, int k0,
                 int k1, const Cores& cores, double alpha_out = 1.0, double beta_out = 0.0) {
   const bool same_core = cores.UA == cores.UC;
@@ -339,10 +345,6 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
   const int64_t nn = (int64_t)n * n, an = (int64_t)naux * n, aa = (int64_t)naux * naux;
   const size_t es = p->esize;
   HIP_TRY(p->mark(THCSOX_STAGE_PROJECT, true));
-  HIP_TRY(fill_u64(p->am_gt() + k0, nb, 0ull, s));
-  HIP_TRY(fill_u64(p->am_gx() + k0, nb, 0ull, s));
-  HIP_TRY(fill_u64(p->am_a() + k0, nb, 0ull, s));
-
   // projections of the batch: Gt[b][R][q] = sum_u X[u][R] G[k0+b][u][q],
   // GX[b][P][w] = sum_p G[k0+b][w][p] X[p][P]
   Gemm64Args g{};
@@ -387,48 +389,44 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
   // fp16x2 scales A by a power of two (bound taken before the A stage); the
   // bf16x3 A stage writes three unscaled bf16 planes (FP32's exponent range)
   const bool scaled_a = mode == MODE_F16X2;
-  for (int b = 0; b < nb; ++b) {
-    const int k = k0 + b, kb = m - 1 - k;
+  const int64_t g_set = (int64_t)naux * lrow, gb_set = (int64_t)n * lrow;
+  const int64_t d_set = (int64_t)p->vsplit * aa;
+  // the kernels that fp16x2 and FP32 share count the distances between sets in halves
+  const int halves = mode == MODE_F32 ? 2 : 1;
+  for (int b = 0; b < nb; b += p->f_sets) {
+    const int k = k0 + b, kb = m - 1 - k, ns = std::min(p->f_sets, nb - b);
     const int* sym = same_core && p->sym_mode == THCSOX_SYM_AUTO ? p->symflag + k : nullptr;
-    // A[v][P][q] = sum_s U[P][q][s] G(beta - tau)[s][v]: rows (P,q) of U against rows v of Gb
-    // (fp16x2: for up to a_sets tau points at once, into set b % a_sets of A)
-    const int aset = mode == MODE_F16X2 ? b % p->a_sets : 0;
-    const int64_t a_set = (int64_t)n * naux * lrow;   // fp16x2: halves per set of A
+    // A[v][P][q] = sum_s U[P][q][s] G(beta - tau)[s][v]: rows (P,q) of U against rows v of Gb,
+    // for up to a_sets tau points at once (U read once for all of them)
+    const int aset = b % p->a_sets;
     if (aset == 0) {
+      const int na = std::min(p->a_sets, nb - b);
+      const void* Gb = static_cast<const char*>(p->Gb) + (size_t)b * gb_set * es;
       HIP_TRY(p->mark(THCSOX_STAGE_A, true));
-      if (mode == MODE_F16X2) {
+      if (mode == MODE_F16X2 || (mode == MODE_F32 && astage_f32_fits(n, naux, ldk))) {
         AStageArgs ast{};
-        ast.naux = naux; ast.n = n; ast.ldk = ldk; ast.nsets = std::min(p->a_sets, nb - b);
-        ast.U = cores.UA;
-        ast.Gb = static_cast<const char*>(p->Gb) + (size_t)b * n * lrow * es;
-        ast.gb_set = (int64_t)n * lrow;
-        ast.A = static_cast<_Float16*>(p->A); ast.a_set = a_set;
+        ast.naux = naux; ast.n = n; ast.ldk = ldk; ast.nsets = na;
+        ast.U = cores.UA; ast.Gb = Gb;
+        ast.gb_set = halves * gb_set;
+        ast.A = static_cast<_Float16*>(p->A); ast.a_set = halves * p->a_set;
         ast.amax = p->am_a() + k;
-        HIP_TRY(astage_f16(ast, s));
-      } else if (mode == MODE_F32 && astage_f32_fits(n, naux, ldk)) {
-        AStageArgs ast{};
-        ast.naux = naux; ast.n = n; ast.ldk = ldk; ast.nsets = 1;
-        ast.U = cores.UA;
-        ast.Gb = static_cast<const char*>(p->Gb) + (size_t)b * n * ldk * es;
-        ast.A = static_cast<_Float16*>(p->A);
-        HIP_TRY(astage_f32(ast, s));
+        if (mode == MODE_F16X2) HIP_TRY(astage_f16(ast, s));
+        else HIP_TRY(astage_f32(ast, s));
       } else if (mode == MODE_BF16X3 && astage_bf3_fits(n, naux, ldk)) {
         AStageB3Args ab{};
-        ab.naux = naux; ab.n = n; ab.ldk = ldk;
+        ab.naux = naux; ab.n = n; ab.ldk = ldk; ab.nsets = na;
         ab.U = cores.UA; ab.u_plane = p->u_plane;
-        ab.Gb = static_cast<const char*>(p->Gb) + (size_t)b * n * ldk * es;
-        ab.gb_plane = p->gb_plane;
-        ab.A = p->A; ab.a_plane = p->a_plane;
+        ab.Gb = Gb; ab.gb_plane = p->gb_plane; ab.gb_set = gb_set;
+        ab.A = p->A; ab.a_plane = p->a_plane; ab.a_set = p->a_set;
         HIP_TRY(astage_bf3(ab, s));
       } else {
         GemmKArgs ga{};
         ga.M = naux * n; ga.N = n; ga.kpad = ldk; ga.alpha = 1.0;
         ga.A = cores.UA; ga.lda = ldk; ga.a_plane = p->u_plane;
-        ga.B = static_cast<const char*>(p->Gb) + (size_t)b * n * ldk * es;
-        ga.ldb = ldk; ga.b_plane = p->gb_plane;
+        ga.B = Gb; ga.ldb = ldk; ga.b_plane = p->gb_plane;
         ga.ci_in = n; ga.ci_out = ldk; ga.c_j = (int64_t)naux * ldk;
         ga.C = p->A;
-        ga.amax = nullptr;
+        ga.nsets = na; ga.b_set = gb_set; ga.c_set = p->a_set;
         if (mode == MODE_BF16X3) {
           ga.c_plane = p->a_plane;
           HIP_TRY(gemm_kmajor_bf3(ga, s));
@@ -441,19 +439,20 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
 
     FusedArgs f{};
     f.n = n; f.naux = naux; f.ldk = ldk; f.vsplit = p->vsplit; f.vchunk = p->vchunk;
-    f.Gt = static_cast<const char*>(p->Gt) + (size_t)b * naux * lrow * es;
-    f.GXt = static_cast<const char*>(p->GX) + (size_t)b * naux * lrow * es;
+    f.Gt = static_cast<const char*>(p->Gt) + (size_t)b * g_set * es;
+    f.GXt = static_cast<const char*>(p->GX) + (size_t)b * g_set * es;
     f.g_plane = p->g_plane;
     f.U = cores.UC; f.u_plane = p->u_plane;
     // A already in the mode's planes (fp16x2: split and scaled by the A stage)
-    f.A = c32 ? static_cast<const void*>(static_cast<const _Float16*>(p->A) + aset * a_set) : p->A;
+    f.A = static_cast<const char*>(p->A) + (size_t)aset * p->a_set * es;
     f.a_plane = p->a_plane;
     f.amax_a = scaled_a ? p->am_a() + k : nullptr;
     f.Dpart = p->Dpart; f.dpart_f32 = p->dpart_f32;
     f.sym = sym;
+    f.nsets = ns; f.g_set = halves * g_set; f.a_set = halves * p->a_set; f.d_set = d_set;
     HIP_TRY(p->mark(THCSOX_STAGE_FUSED, true));
     HIP_TRY(sox_fused(mode, f, s));
-    HIP_TRY(p->mark(THCSOX_STAGE_FUSED, false));
+    HIP_TRY(p->mark(THCSOX_STAGE_FUSED, false, ns));
 
     HIP_TRY(p->mark(THCSOX_STAGE_BACK, true));
     DReduceArgs d{};
@@ -465,6 +464,7 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
     d.amax_u = (mode == MODE_F64) ? nullptr : cores.amaxA;
     d.amax_u2 = (mode == MODE_F64) ? nullptr : cores.amaxC;
     d.sym = sym;
+    d.nsets = ns; d.d_set = d_set; d.s_set = aa;
     HIP_TRY(dreduce(d, s));
     HIP_TRY(p->mark(THCSOX_STAGE_BACK, false));
   }
@@ -601,13 +601,13 @@ int ensure_direct_buffers(thcsox_plan_s* p) {
   return 0;
 }
 
-// Per-call preparation of G for the exchange contractions: max |G[k]| of every
-// tau point (the power-of-two scales) and, under THCSOX_SYM_AUTO, the flags of
-// the symmetric-D path.
+// Per-call preparation of G for the exchange contractions: the per-tau maxima
+// cleared, max |G[k]| of every tau point (the power-of-two scales) and, under
+// THCSOX_SYM_AUTO, the flags of the symmetric-D path.
 int prepare_g(thcsox_plan_s* p, const double* G_dev) {
   const hipStream_t s = p->stream;
   const int64_t nn = (int64_t)p->n * p->n;
-  HIP_TRY(fill_u64(p->am_g(), p->m, 0ull, s));
+  HIP_TRY(fill_u64(p->am_gt(), 5 * (int64_t)p->m, 0ull, s));   // every per-tau maximum
   HIP_TRY(absmax64(G_dev, nn, nn, p->m, p->am_g(), s));
   if (p->sym_mode == THCSOX_SYM_AUTO) {
     HIP_TRY(asym64(G_dev, p->n, p->m, p->am_asym(), s));
@@ -742,32 +742,54 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   int rc = 0;
   const size_t es = p->esize, np = p->np;
   p->u_plane = (int64_t)naux * n * ldk;
-  p->a_plane = (int64_t)n * naux * ldk;
+  const double row_bytes = (double)np * es;               // per element of an operand row
+  const double a_bytes = row_bytes * n * naux * ldk;      // one set of A
+  const double d_bytes = (p->dpart_f32 ? 4.0 : 8.0) * p->vsplit * (double)naux * naux;
   // the fp16x2 A stage forms two tau points per launch (U read once for both)
-  // while their FP32 A arrays take at most 2 GB together
-  if (precision == THCSOX_FP16X2 && ntau > 1 && 8.0 * p->a_plane <= 2.0e9) p->a_sets = 2;
+  // while their A arrays take at most 2 GB together
+  if (precision == THCSOX_FP16X2 && ntau > 1 && 2.0 * a_bytes <= 2.0e9) p->a_sets = 2;
+  // tau batch of the projections and back-projection: up to 16 points within ~2 GB
+  const double per_tau = 8.0 * (2.0 * naux * n + (double)naux * naux + (double)n * naux) +
+                         row_bytes * ((2.0 * naux + n) * ldk);
+  // what the plan keeps besides (X, V and the per-tau scalars in FP64, U, A, the
+  // partial tiles), plus 1 MiB of slack; the U build's temporaries (Khatri-Rao
+  // chunk, and its FP64 result in the split modes) are allocated last and freed
+  // after the build, so they count too
+  const double per_q = 8.0 * n * naux;
+  const double qb = std::max(1.0, std::min((double)n, std::floor((double)(size_t(256) << 20) / per_q)));
+  const double temps = qb * per_q * (precision == THCSOX_FP64 ? 1.0 : 2.0);
+  const double fixed = 8.0 * ((double)n * naux + (double)naux * naux + 7.0 * ntau + 2.0) +
+                       row_bytes * naux * n * ldk + p->a_sets * a_bytes + d_bytes + temps + (1 << 20);
   {
-    // tau batch of the projections and back-projection: up to 16 points within ~2 GB
-    const double per_tau = 8.0 * (2.0 * naux * n + (double)naux * naux + (double)n * naux) +
-                           (double)p->np * p->esize * ((2.0 * naux + n) * ldk);
     double cap = 2.0e9;
-    if (workspace_limit > 0) {
-      // what the plan keeps besides the batch buffers, plus 1 MiB of slack
-      // the U build's temporaries (Khatri-Rao chunk, and its FP64 result in the split
-      // modes) are allocated last and freed after the build, so they count too
-      const double per_q = 8.0 * n * naux;
-      const double qb = std::max(1.0, std::min((double)n, std::floor((double)(size_t(256) << 20) / per_q)));
-      const double temps = qb * per_q * (precision == THCSOX_FP64 ? 1.0 : 2.0);
-      // (X, V and the per-tau scalars in FP64, U, A, the partial tiles)
-      const double fixed = 8.0 * ((double)n * naux + (double)naux * naux + 7.0 * ntau + 2.0) +
-                           (double)p->np * p->esize * naux * n * ldk +
-                           (double)p->np * p->esize * p->a_sets * n * naux * ldk +
-                           (p->dpart_f32 ? 4.0 : 8.0) * p->vsplit * (double)naux * naux +
-                           temps + (1 << 20);
-      cap = std::min(cap, (double)workspace_limit - fixed);
-    }
+    if (workspace_limit > 0) cap = std::min(cap, (double)workspace_limit - fixed);
     p->tb = (int)std::max(1.0, std::min({16.0, (double)ntau, std::floor(cap / per_tau)}));
   }
+  {
+    // Tau points per launch of the A, fused and reduction stages.  A launch of few
+    // workgroups leaves compute units idle and a launch of a few microseconds is
+    // mostly its own latency, so small systems take several points: about eight
+    // workgroups per compute unit, and at least the A stage's sets.  Their A and
+    // partial tiles may add as much memory as the plan takes anyway (or 2 MB); under a
+    // workspace limit only what the buffers allocated on first use cannot need.
+    int TR = 0, TP = 0;
+    fused_tile(precision, &TR, &TP);
+    const double wgs = std::ceil((double)naux / TR) * std::ceil((double)naux / TP) * p->vsplit;
+    const double base = fixed + p->tb * per_tau;
+    double room = std::max(1.2 * base, 2.0e6);
+    if (workspace_limit > 0) {
+      const double aa8 = 8.0 * naux * naux;
+      const double later = aa8 * (3.0 * p->tb + 5.0) + row_bytes * naux * n * ldk +
+                           16.0 * ntau * ((double)n * n + ntau + 1.0) + (1 << 20);
+      room = std::min(room, (double)workspace_limit - base - later);
+    }
+    const double want = std::max((double)p->a_sets, std::ceil(8.0 * 256.0 / wgs));
+    const double fit = 1.0 + std::floor((room + (p->a_sets - 1) * a_bytes) / (a_bytes + d_bytes));
+    const int sets = (int)std::min({want, fit, (double)p->tb});
+    if (sets > 1 && sets >= p->a_sets) p->a_sets = p->f_sets = sets;
+  }
+  p->a_set = (int64_t)n * naux * ldk * (precision == THCSOX_FP16X2 ? 2 : 1);
+  p->a_plane = (int64_t)p->a_sets * n * naux * ldk;
   p->g_plane = (int64_t)p->tb * naux * ldk;
   p->gb_plane = (int64_t)p->tb * n * ldk;
   char* tmp = nullptr;
@@ -779,7 +801,7 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   if ((rc = p->alloc(&p->E, 1))) return bail(rc);
   if ((rc = p->alloc(&tmp, np * es * (size_t)p->u_plane))) return bail(rc);
   p->U = tmp;
-  if ((rc = p->alloc(&tmp, np * es * (size_t)p->a_sets * p->a_plane))) return bail(rc);
+  if ((rc = p->alloc(&tmp, np * es * (size_t)p->a_plane))) return bail(rc);
   p->A = tmp;
   if (precision == THCSOX_FP16X2 && (rc = p->alloc(&p->norm2, (size_t)2 + p->tb)))
     return bail(rc);
@@ -792,7 +814,7 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   if ((rc = p->alloc(&p->Gt64, (size_t)p->tb * naux * n))) return bail(rc);
   if ((rc = p->alloc(&p->GX64, (size_t)p->tb * naux * n))) return bail(rc);
   {
-    const size_t dn = (size_t)p->vsplit * naux * naux;
+    const size_t dn = (size_t)p->f_sets * p->vsplit * naux * naux;
     if ((rc = p->alloc(&p->Dpart, p->dpart_f32 ? (dn + 1) / 2 : dn))) return bail(rc);
   }
   if ((rc = p->alloc(&p->Sthc, (size_t)p->tb * naux * naux))) return bail(rc);
@@ -810,7 +832,7 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
     return hip_bail(e, "copy weights");
   // zero the operand pads once (stages only ever write the first n of ldk columns)
   if ((e = hipMemsetAsync(p->U, 0, np * es * (size_t)p->u_plane, s))) return hip_bail(e, "zero U");
-  if (p->A && (e = hipMemsetAsync(p->A, 0, np * es * (size_t)p->a_sets * p->a_plane, s)))
+  if (p->A && (e = hipMemsetAsync(p->A, 0, np * es * (size_t)p->a_plane, s)))
     return hip_bail(e, "zero A");
   if ((e = hipMemsetAsync(p->symflag, 0, sizeof(int) * (size_t)ntau, s)))
     return hip_bail(e, "zero flags");
@@ -822,7 +844,8 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   // is V symmetric to rounding?  (max |V - V^T| and max |V| in two per-tau slots
   // that every later call clears before it uses them)
   unsigned long long vs[2] = {0, 0};
-  if ((e = asym64(p->V, naux, 1, p->am_asym(), s)) || (e = fill_u64(p->am_g(), 1, 0ull, s)) ||
+  if ((e = fill_u64(p->am_asym(), 1, 0ull, s)) || (e = asym64(p->V, naux, 1, p->am_asym(), s)) ||
+      (e = fill_u64(p->am_g(), 1, 0ull, s)) ||
       (e = absmax64(p->V, (int64_t)naux * naux, 0, 1, p->am_g(), s)) ||
       (e = hipMemcpyAsync(&vs[0], p->am_asym(), sizeof(vs[0]), hipMemcpyDeviceToHost, s)) ||
       (e = hipMemcpyAsync(&vs[1], p->am_g(), sizeof(vs[1]), hipMemcpyDeviceToHost, s)))
@@ -1125,7 +1148,7 @@ int thcsox_profile(thcsox_plan_t p, int enable) {
   if (p == nullptr) return fail(THCSOX_EINVAL, "plan is NULL");
   HIP_TRY(hipStreamSynchronize(p->stream));
   p->profiling = enable != 0;
-  for (auto& t : p->timers) t.used = 0;
+  for (auto& t : p->timers) t.used = t.count = 0;
   return 0;
 }
 
@@ -1143,8 +1166,8 @@ int thcsox_stage_times(thcsox_plan_t p, double* ms, int* launches) {
       tot += e;
     }
     ms[st] = tot;
-    launches[st] = (int)t.used;
-    t.used = 0;
+    launches[st] = t.count;
+    t.used = t.count = 0;
   }
   return 0;
 }
