@@ -677,8 +677,7 @@ int thcsox_dyson_commutator(thcsox_dyson_t d, const double* Sigma_in_dev,
   g.A = d->Wf; g.a_i = m; g.a_k = 1;
   g.B = Sigma_out_dev; g.b_k = nn; g.b_j = 1;
   g.C = d->Dw; g.c_i = nn; g.c_j = 1; g.cj_in = nn; g.cj_out = 0;
-  DTRY(gemm64(g, s));
-  g.B = Sigma_in_dev; g.alpha = -1.0; g.beta = 1.0;
+  g.more = 1; g.A_t[0] = d->Wf; g.B_t[0] = Sigma_in_dev; g.sign[0] = -1.0;
   DTRY(gemm64(g, s));
   // e = G D - D G per frequency, G = Gr + i Gi from the last step (d->Gs), D = Dr + i Di:
   //   Re e = Gr Dr - Gi Di - Dr Gr + Di Gi,  Im e = Gr Di + Gi Dr - Dr Gi - Di Gr
@@ -688,18 +687,26 @@ int thcsox_dyson_commutator(thcsox_dyson_t d, const double* Sigma_in_dev,
   const double* Di = d->Dw + (int64_t)nw * nn;
   double* er = e_dev;
   double* ei = e_dev + (int64_t)nw * nn;
-  struct Term { const double* A; const double* B; double alpha; double* C; };
-  const Term terms[8] = {{Gr, Dr, 1.0, er}, {Gi, Di, -1.0, er}, {Dr, Gr, -1.0, er}, {Di, Gi, 1.0, er},
-                         {Gr, Di, 1.0, ei}, {Gi, Dr, 1.0, ei}, {Dr, Gi, -1.0, ei}, {Di, Gr, -1.0, ei}};
-  for (int t = 0; t < 8; ++t) {
-    Gemm64Args b{};
-    b.M = n; b.N = n; b.K = n; b.batch = nw; b.alpha = terms[t].alpha;
-    b.beta = (t == 0 || t == 4) ? 0.0 : 1.0;
-    b.A = terms[t].A; b.a_i = n; b.a_k = 1; b.a_b = nn;
-    b.B = terms[t].B; b.b_k = n; b.b_j = 1; b.b_b = nn;
-    b.C = terms[t].C; b.c_i = n; b.c_j = 1; b.cj_in = n; b.cj_out = 0; b.c_b = nn;
-    DTRY(gemm64(b, s));
-  }
+  // four products each, summed in one pass (eight products into e one after the other
+  // read and wrote e eight times: 2.6 ms against 1.8 at n = 300, 256 frequencies)
+  Gemm64Args p{};
+  p.M = n; p.N = n; p.K = n; p.batch = nw; p.alpha = 1.0; p.beta = 0.0;
+  p.a_i = n; p.a_k = 1; p.a_b = nn;
+  p.b_k = n; p.b_j = 1; p.b_b = nn;
+  p.c_i = n; p.c_j = 1; p.cj_in = n; p.cj_out = 0; p.c_b = nn;
+  p.more = 3;
+  auto sum4 = [&](double* C, const double* A0, const double* B0, const double* A1, const double* B1,
+                  double s1, const double* A2, const double* B2, const double* A3,
+                  const double* B3, double s3) -> hipError_t {
+    p.C = C;
+    p.A = A0; p.B = B0;
+    p.A_t[0] = A1; p.B_t[0] = B1; p.sign[0] = s1;
+    p.A_t[1] = A2; p.B_t[1] = B2; p.sign[1] = -1.0;
+    p.A_t[2] = A3; p.B_t[2] = B3; p.sign[2] = s3;
+    return gemm64(p, s);
+  };
+  DTRY(sum4(er, Gr, Dr, Gi, Di, -1.0, Dr, Gr, Di, Gi, 1.0));
+  DTRY(sum4(ei, Gr, Di, Gi, Dr, 1.0, Dr, Gi, Di, Gr, -1.0));
   return 0;
 }
 

@@ -6,9 +6,11 @@
 // size decides.  A T x T tile needs 16 T bytes per k for 2 T^2 flops: at T = 64
 // the full rate takes 9 TB/s out of the L2s, at 128 half of that.  So:
 //   - square tiles of 128, 64 or 32 (four waves of 64, 32 or 16 square; the
-//     dispatch below picks one), k steps of 16, two LDS buffers and one barrier a
-//     step: step t + 1 goes from registers to LDS and step t + 2's loads are
-//     issued before the products of step t, which give them thousands of cycles;
+//     dispatch below picks one), two LDS buffers and one barrier a k step: step t + 1
+//     goes from registers to LDS and step t + 2's loads are issued before the
+//     products of step t, which give them thousands of cycles.  k steps of 16, and
+//     of 32 or 64 where small tiles alone on a compute unit would otherwise wait
+//     for the latency of each short step's loads;
 //   - at 128 two workgroups share a compute unit (64-68 KiB of LDS, 256
 //     registers), so one's barrier is covered by the other's products;
 //   - tiles are dealt to the XCDs in contiguous runs and walked in bands of eight
@@ -20,6 +22,7 @@
 // LDS buffer and branches, the kernel before this one: 35); the f64 matrix peak
 // is 78.6 and a library product of 8192 reaches 72.
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "mfma.hpp"
@@ -28,22 +31,26 @@ namespace thcsox {
 namespace {
 
 constexpr int NT = 256;      // threads per workgroup (4 wavefronts)
-constexpr int BK = 16;       // k per step
 constexpr int NXCD = 8;
 constexpr int BAND = 8;      // row tiles per band of the tile walk
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-// An operand's panel in LDS.  The four lane groups g of an MFMA step s take k = 4 g + s.
-// KC (k contiguous in memory): rows of 16 k (128 bytes), 16-byte pair c of row r
-//   at piece c ^ (r / 2 mod 8): a lane reads its four k in two 16-byte pieces, and
-//   16 rows at one pair touch 16 distinct pieces of two 128-byte rows.
+// An operand's panel in LDS.  Within 16 k the four lane groups g of an MFMA step s
+// take k = 4 g + s.
+// KC (k contiguous in memory): rows of BK k, 16-byte pair c of row r at the piece
+//   swz(r, c): a lane reads its four k in two 16-byte pieces, and 16 rows at one
+//   pair touch 16 distinct 16-byte columns of the banks.
 // otherwise (row index contiguous): [k][row], 32 bytes of padding per k, so that
 //   lane groups four k apart fall on different halves of the banks.
-template <int T, bool KC>
+template <int T, int BK, bool KC>
 struct PanelLayout {
   static constexpr int LD = KC ? BK : T + 4;
   static constexpr int SIZE = KC ? T * BK : BK * LD;
 };
+template <int BK>
+__device__ __forceinline__ int swz(int r, int c) {
+  return BK == 16 ? c ^ ((r >> 1) & 7) : c ^ (r & 15);   // two rows of 128 bytes, or one of 256 or 512
+}
 
 // How pairs along an operand's contiguous dimension are read: 16-byte aligned, at
 // any 8-byte address, or as two 8-byte loads (contiguous extent of 1).
@@ -63,12 +70,13 @@ __device__ __forceinline__ d2 pair_at(const double* p, int x, int lim) {
 }
 
 // AC / BC: A / B contiguous in k (otherwise in i / j).
-template <int WT, bool AC, bool BC, Access ACC>
-__global__ __launch_bounds__(NT, WT == 4 ? 2 : 4) void gemm64_kernel(Gemm64Args g, int nti, int ntj) {
+template <int WT, int BK, bool AC, bool BC, Access ACC>
+__global__ __launch_bounds__(NT, WT == 2 && BK == 16 ? 4 : 2) void gemm64_kernel(Gemm64Args g, int nti, int ntj) {
   constexpr int T = 32 * WT;           // tile edge
-  constexpr int NP = T * BK / 2 / NT;  // pairs per thread and operand panel
-  using LA = PanelLayout<T, AC>;
-  using LB = PanelLayout<T, BC>;
+  constexpr int RP = BK / 2;           // pairs per row of a panel contiguous in k
+  constexpr int NP = T * RP / NT;      // pairs per thread and operand panel
+  using LA = PanelLayout<T, BK, AC>;
+  using LB = PanelLayout<T, BK, BC>;
   __shared__ __attribute__((aligned(16))) double sA[2][LA::SIZE];
   __shared__ __attribute__((aligned(16))) double sB[2][LB::SIZE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -84,47 +92,67 @@ __global__ __launch_bounds__(NT, WT == 4 ? 2 : 4) void gemm64_kernel(Gemm64Args 
   const int i_lo = w / (BAND * ntj) * BAND, bh = min(BAND, nti - i_lo);
   const int in = w - i_lo * ntj;
   const int i0 = (i_lo + in % bh) * T, j0 = in / bh * T;
+  // the step being loaded (term lt, from k = lk) and the one held in registers
+  int lt = 0, lk = 0, sk = 0;
+  double sign = 1.0;
   const double* A = g.A + b * g.a_b;
   const double* B = g.B + b * g.b_b;
 
   d2 ra[NP], rb[NP];
-  auto load = [&](int k0) {
+  auto load = [&]() {
+    const int k0 = lk;
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
       const int e = tid + NT * t;
       if (AC) {   // row i, k pair
-        const int i = min(i0 + (e >> 3), g.M - 1);
-        ra[t] = pair_at<ACC>(A + (int64_t)i * g.a_i, k0 + 2 * (e & 7), g.K);
+        const int i = min(i0 + e / RP, g.M - 1);
+        ra[t] = pair_at<ACC>(A + (int64_t)i * g.a_i, k0 + 2 * (e % RP), g.K);
       } else {    // one k, i pair
         const int k = min(k0 + e / (T / 2), g.K - 1);
         ra[t] = pair_at<ACC>(A + (int64_t)k * g.a_k, i0 + 2 * (e % (T / 2)), g.M);
       }
       if (BC) {
-        const int j = min(j0 + (e >> 3), g.N - 1);
-        rb[t] = pair_at<ACC>(B + (int64_t)j * g.b_j, k0 + 2 * (e & 7), g.K);
+        const int j = min(j0 + e / RP, g.N - 1);
+        rb[t] = pair_at<ACC>(B + (int64_t)j * g.b_j, k0 + 2 * (e % RP), g.K);
       } else {
         const int k = min(k0 + e / (T / 2), g.K - 1);
         rb[t] = pair_at<ACC>(B + (int64_t)k * g.b_k, j0 + 2 * (e % (T / 2)), g.N);
       }
     }
   };
+  auto load_next = [&]() {
+    load();
+    sk = lk;
+    sign = lt == 0 ? 1.0 : g.sign[lt - 1];
+    lk += BK;
+    if (lk >= g.K && lt < g.more) {
+      lk = 0;
+      A = g.A_t[lt] + b * g.a_b;
+      B = g.B_t[lt] + b * g.b_b;
+      ++lt;
+    }
+  };
   // what lies past K in the pair e of a panel whose step starts at k0
   auto cut = [&](bool kc, int e, int k0, d2 v) {
-    const int k = k0 + (kc ? 2 * (e & 7) : e / (T / 2));
+    const int k = k0 + (kc ? 2 * (e % RP) : e / (T / 2));
     return d2{k < g.K ? v[0] : 0.0, k + (kc ? 1 : 0) < g.K ? v[1] : 0.0};
   };
   auto put = [&](bool kc, double* s, int ld, int e, d2 v) {
-    const int at = kc ? (e >> 3) * BK + (((e & 7) ^ ((e >> 4) & 7)) << 1)
+    const int at = kc ? e / RP * BK + (swz<BK>(e / RP, e % RP) << 1)
                       : e / (T / 2) * ld + 2 * (e % (T / 2));
     *reinterpret_cast<d2*>(s + at) = v;
   };
-  auto store = [&](int buf, int k0) {
-    if (k0 + BK > g.K) {
+  auto store = [&](int buf) {
+    if (sk + BK > g.K) {
 #pragma unroll
       for (int t = 0; t < NP; ++t) {
-        ra[t] = cut(AC, tid + NT * t, k0, ra[t]);
-        rb[t] = cut(BC, tid + NT * t, k0, rb[t]);
+        ra[t] = cut(AC, tid + NT * t, sk, ra[t]);
+        rb[t] = cut(BC, tid + NT * t, sk, rb[t]);
       }
+    }
+    if (g.more > 0) {
+#pragma unroll
+      for (int t = 0; t < NP; ++t) ra[t] *= sign;
     }
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
@@ -133,11 +161,11 @@ __global__ __launch_bounds__(NT, WT == 4 ? 2 : 4) void gemm64_kernel(Gemm64Args 
     }
   };
   const int fr = lane & 15, fg = lane >> 4;
-  // elements k = 4 g + 2 h, 4 g + 2 h + 1 of the rows 16 t + fr of the wave's part
-  auto frag = [&](bool kc, const double* s, int ld, int r0, int t, int h) -> d2 {
+  // elements k = 16 kb + 4 fg + 2 h and the next of row 16 t + fr of the wave's part
+  auto frag = [&](bool kc, const double* s, int ld, int r0, int t, int kb, int h) -> d2 {
     const int r = r0 + 16 * t + fr;
-    if (kc) return *reinterpret_cast<const d2*>(s + r * BK + (((2 * fg + h) ^ ((r >> 1) & 7)) << 1));
-    const int k = 4 * fg + 2 * h;
+    if (kc) return *reinterpret_cast<const d2*>(s + r * BK + (swz<BK>(r, 8 * kb + 2 * fg + h) << 1));
+    const int k = 16 * kb + 4 * fg + 2 * h;
     return d2{s[k * ld + r], s[(k + 1) * ld + r]};
   };
 
@@ -147,21 +175,22 @@ __global__ __launch_bounds__(NT, WT == 4 ? 2 : 4) void gemm64_kernel(Gemm64Args 
 #pragma unroll
     for (int tj = 0; tj < WT; ++tj) acc[ti][tj] = d4{0.0, 0.0, 0.0, 0.0};
 
-  load(0);
-  store(0, 0);
-  if (g.K > BK) load(BK);
+  const int steps = (g.K + BK - 1) / BK * (g.more + 1);
+  load_next();
+  store(0);
+  if (steps > 1) load_next();
   __syncthreads();
   int cur = 0;
-  for (int k0 = 0; k0 < g.K; k0 += BK, cur ^= 1) {
-    if (k0 + BK < g.K) store(cur ^ 1, k0 + BK);
-    if (k0 + 2 * BK < g.K) load(k0 + 2 * BK);
+  for (int st = 0; st < steps; ++st, cur ^= 1) {
+    if (st + 1 < steps) store(cur ^ 1);
+    if (st + 2 < steps) load_next();
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int kh = 0; kh < BK / 8; ++kh) {
       d2 a[WT], bb[WT];
 #pragma unroll
       for (int t = 0; t < WT; ++t) {
-        a[t] = frag(AC, sA[cur], LA::LD, 16 * WT * wr, t, h);
-        bb[t] = frag(BC, sB[cur], LB::LD, 16 * WT * wc, t, h);
+        a[t] = frag(AC, sA[cur], LA::LD, 16 * WT * wr, t, kh >> 1, kh & 1);
+        bb[t] = frag(BC, sB[cur], LB::LD, 16 * WT * wc, t, kh >> 1, kh & 1);
       }
 #pragma unroll
       for (int s = 0; s < 2; ++s)
@@ -200,17 +229,17 @@ __global__ __launch_bounds__(NT, WT == 4 ? 2 : 4) void gemm64_kernel(Gemm64Args 
   }
 }
 
-template <int WT, Access ACC>
+template <int WT, int BK, Access ACC>
 hipError_t launch(const Gemm64Args& g, bool ac, bool bc, hipStream_t s) {
   const int64_t nti = (g.M + 32 * WT - 1) / (32 * WT), ntj = ((int64_t)g.N + 32 * WT - 1) / (32 * WT);
   const int64_t total = nti * ntj * g.batch;
   if (total > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)total);
   const int ni = (int)nti, nj = (int)ntj;
-  if (ac && bc) gemm64_kernel<WT, true, true, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
-  else if (ac) gemm64_kernel<WT, true, false, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
-  else if (bc) gemm64_kernel<WT, false, true, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
-  else gemm64_kernel<WT, false, false, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
+  if (ac && bc) gemm64_kernel<WT, BK, true, true, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
+  else if (ac) gemm64_kernel<WT, BK, true, false, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
+  else if (bc) gemm64_kernel<WT, BK, false, true, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
+  else gemm64_kernel<WT, BK, false, false, ACC><<<grid, NT, 0, s>>>(g, ni, nj);
   return hipGetLastError();
 }
 
@@ -218,19 +247,21 @@ hipError_t launch(const Gemm64Args& g, bool ac, bool bc, hipStream_t s) {
 
 hipError_t gemm64(const Gemm64Args& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-  if (g.K <= 0) return hipErrorInvalidValue;
+  if (g.K <= 0 || g.more < 0 || g.more > 3) return hipErrorInvalidValue;
   // the contiguous dimension of each operand
   if ((g.a_k != 1 && g.a_i != 1) || (g.b_j != 1 && g.b_k != 1)) return hipErrorInvalidValue;
   const bool ac = g.a_k == 1, bc = g.b_j != 1;
   const int ext_a = ac ? g.K : g.M, ext_b = bc ? g.K : g.N;   // contiguous extents
-  if (ext_a < 2 || ext_b < 2) return launch<1, SINGLE>(g, ac, bc, s);
+  if (ext_a < 2 || ext_b < 2) return launch<1, 64, SINGLE>(g, ac, bc, s);
   // 16-byte loads need even strides, even extents and 16-byte aligned bases (tile
   // starts are even)
   auto even = [](int64_t x) { return (x & 1) == 0; };
+  uintptr_t low = reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B);
+  for (int t = 0; t < g.more; ++t)
+    low |= reinterpret_cast<uintptr_t>(g.A_t[t]) | reinterpret_cast<uintptr_t>(g.B_t[t]);
   const bool aligned = even(ext_a) && even(ext_b) && even(ac ? g.a_i : g.a_k) && even(g.a_b) &&
                        even(bc ? g.b_j : g.b_k) && even(g.b_b) &&
-                       (reinterpret_cast<uintptr_t>(g.A) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
+                       (low & 15) == 0;
   // tile edge: the least of rounds of tiles over 256 compute units x tile area x
   // the cost per element of that tile on a full unit relative to the largest
   auto cost = [&](int t, double rel) {
@@ -238,11 +269,20 @@ hipError_t gemm64(const Gemm64Args& g, hipStream_t s) {
     return std::ceil(tiles / 256.0) * (double)t * t * rel;
   };
   const double c4 = cost(128, 1.0), c2 = cost(64, 1.3), c1 = cost(32, 2.0);
-  if (c4 <= c2 && c4 <= c1)
-    return aligned ? launch<4, ALIGNED>(g, ac, bc, s) : launch<4, UNALIGNED>(g, ac, bc, s);
-  if (c2 <= c1)
-    return aligned ? launch<2, ALIGNED>(g, ac, bc, s) : launch<2, UNALIGNED>(g, ac, bc, s);
-  return aligned ? launch<1, ALIGNED>(g, ac, bc, s) : launch<1, UNALIGNED>(g, ac, bc, s);
+  auto go = [&](auto wt, auto bk) {
+    constexpr int W = decltype(wt)::value, K = decltype(bk)::value;
+    return aligned ? launch<W, K, ALIGNED>(g, ac, bc, s) : launch<W, K, UNALIGNED>(g, ac, bc, s);
+  };
+  using std::integral_constant;
+  if (c4 <= c2 && c4 <= c1) return go(integral_constant<int, 4>(), integral_constant<int, 16>());
+  if (c2 <= c1) {
+    // 64: short steps where three or more workgroups share a compute unit, else long
+    // ones (1740 tiles, K = 1800: 390 us at 16, 423 at 32; 256 tiles, K = 485: 58, 48)
+    const double tiles = std::ceil(g.M / 64.0) * std::ceil(g.N / 64.0) * g.batch;
+    if (tiles >= 768) return go(integral_constant<int, 2>(), integral_constant<int, 16>());
+    return go(integral_constant<int, 2>(), integral_constant<int, 32>());
+  }
+  return go(integral_constant<int, 1>(), integral_constant<int, 64>());
 }
 
 }  // namespace thcsox

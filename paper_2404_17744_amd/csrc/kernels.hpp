@@ -9,13 +9,17 @@ namespace thcsox {
 //   C(i,j) = alpha * sum_k A(i,k) B(k,j) + beta * C(i,j)
 //   A(i,k) = A[b*a_b + i*a_i + k*a_k],  B(k,j) = B[b*b_b + k*b_k + j*b_j],
 //   C(i,j) = C[b*c_b + i*c_i + (j / cj_in) * cj_out + (j % cj_in) * c_j].
-// beta == 0 never reads C.
+// beta == 0 never reads C.  more > 0: the sum also runs over up to three further
+// terms sign[t] A_t(i,k) B_t(k,j) with operands of the same strides (and the same
+// alignment), in one pass over C.
 struct Gemm64Args {
   int M, N, K, batch;
   double alpha, beta;
   const double* A; int64_t a_i, a_k, a_b;
   const double* B; int64_t b_k, b_j, b_b;
   double* C; int64_t c_i, c_j, c_b; int64_t cj_in, cj_out;
+  int more;
+  const double* A_t[3]; const double* B_t[3]; double sign[3];
 };
 hipError_t gemm64(const Gemm64Args& g, hipStream_t s);
 
