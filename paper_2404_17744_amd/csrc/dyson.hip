@@ -27,6 +27,7 @@
 #include "../../include/thcsox.h"
 #include "error.hpp"
 #include "kernels.hpp"
+#include "reduce.hpp"
 
 using namespace thcsox;
 
@@ -301,22 +302,13 @@ __global__ __launch_bounds__(NT) void inv_traces(const double2* __restrict__ Am,
   }
 }
 
-// out = sum_pq A[p][q] B[q][p] (one workgroup, fixed order).
-__global__ __launch_bounds__(NT) void trace_ab(const double* A, const double* B, int n, double* out) {
-  __shared__ double red[NT];
-  double s = 0.0;
-  const int64_t nn = (int64_t)n * n;
-  for (int64_t e = threadIdx.x; e < nn; e += NT) {
-    const int64_t p = e / n, q = e % n;
-    s = fma(A[e], B[q * n + p], s);
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = NT / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = red[0];
+// out[b] = workgroup b's part of sum_pq A[p][q] B[q][p] (fixed order); the host adds them.
+constexpr int TW = 4;              // its waves
+constexpr int TRACE_PARTS = 64;    // workgroups at most
+__global__ __launch_bounds__(64 * TW) void trace_ab(const double* A, const double* B, int n,
+                                                    double* out) {
+  const double t = block_trace<TW>(A, B, n, blockIdx.x, gridDim.x);
+  if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
 
 int dfail(int code, const std::string& m) { return set_error(code, m); }
@@ -360,7 +352,7 @@ struct thcsox_dyson_s {
   double* Gs = nullptr;    // [2nw][n n]
   double* Gout = nullptr;  // [m+1][n n]
   int* flag = nullptr;
-  double* scal = nullptr;
+  double* scal = nullptr;  // [TRACE_PARTS]
   double* traces = nullptr;   // [2 nw]
   double* Dw = nullptr;       // [2nw][n n], commutator DIIS: Sigma_out - Sigma_in in frequency
   bool have_g = false;        // Gs holds the G(i w) of a completed step
@@ -494,7 +486,7 @@ int dyson_create(thcsox_dyson_t* out, int n, int m, int nw, double beta, double 
       (rc = dalloc(d, &d->col, (size_t)d->nw * n)) ||
       (rc = dalloc(d, &d->Gs, (size_t)2 * d->nw * nn)) ||
       (rc = dalloc(d, &d->Gout, (size_t)(d->m + 1) * nn)) || (rc = dalloc(d, &d->flag, 1)) ||
-      (rc = dalloc(d, &d->scal, 1)) || (rc = dalloc(d, &d->traces, (size_t)2 * d->nw))) {
+      (rc = dalloc(d, &d->scal, TRACE_PARTS)) || (rc = dalloc(d, &d->traces, (size_t)2 * d->nw))) {
     delete d;
     return rc;
   }
@@ -714,10 +706,17 @@ int thcsox_dyson_onebody(thcsox_dyson_t d, const double* gamma_dev, double* E1_h
   clear_error();
   if (d == nullptr || gamma_dev == nullptr || E1_host == nullptr)
     return dfail(THCSOX_EINVAL, "NULL argument");
-  trace_ab<<<1, NT, 0, d->stream>>>(d->F, gamma_dev, d->n, d->scal);
+  // a wave for each block of 64 x 32 elements, up to TRACE_PARTS workgroups
+  const int64_t items = (int64_t)((d->n + 63) / 64) * ((d->n + 31) / 32);
+  const int parts = (int)std::min<int64_t>(TRACE_PARTS, (items + TW - 1) / TW);
+  trace_ab<<<parts, 64 * TW, 0, d->stream>>>(d->F, gamma_dev, d->n, d->scal);
   DTRY(hipGetLastError());
-  DTRY(hipMemcpyAsync(E1_host, d->scal, sizeof(double), hipMemcpyDeviceToHost, d->stream));
+  double sums[TRACE_PARTS];
+  DTRY(hipMemcpyAsync(sums, d->scal, sizeof(double) * parts, hipMemcpyDeviceToHost, d->stream));
   DTRY(hipStreamSynchronize(d->stream));
+  double e1 = 0.0;
+  for (int b = 0; b < parts; ++b) e1 += sums[b];
+  *E1_host = e1;
   return 0;
 }
 

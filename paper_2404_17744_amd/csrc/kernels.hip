@@ -219,25 +219,13 @@ __global__ __launch_bounds__(NT) void khatri_rao_kernel(const double* X, int n, 
     KR[row * naux + Q] = X[(int64_t)q * naux + Q] * X[(int64_t)s * naux + Q];
 }
 
-__global__ __launch_bounds__(NT) void energy_partials_kernel(const double* G, const double* S,
-                                                             int n, int m, double* tr) {
-  __shared__ double red[NT];
+constexpr int EW = 8;   // waves per workgroup (one per tau point)
+__global__ __launch_bounds__(64 * EW) void energy_partials_kernel(const double* G, const double* S,
+                                                                  int n, int m, double* tr) {
   const int k = blockIdx.x;
-  const double* Gb = G + (int64_t)(m - 1 - k) * n * n;
-  const double* Sk = S + (int64_t)k * n * n;
-  double acc = 0.0;
   const int64_t nn = (int64_t)n * n;
-  for (int64_t e = threadIdx.x; e < nn; e += NT) {
-    const int64_t p = e / n, q = e % n;
-    acc = fma(Gb[q * n + p], Sk[e], acc);
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = NT / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) tr[k] = red[0];
+  const double t = block_trace<EW>(G + (int64_t)(m - 1 - k) * nn, S + (int64_t)k * nn, n);
+  if (threadIdx.x == 0) tr[k] = t;
 }
 
 __global__ void energy_final_kernel(const double* tr, const double* w, int m, double* E) {
@@ -404,7 +392,7 @@ hipError_t khatri_rao(const double* X, int n, int naux, int q0, int q1, double* 
 
 hipError_t energy_partials(const double* G, const double* S, int n, int m, double* tr,
                            hipStream_t s) {
-  energy_partials_kernel<<<m, NT, 0, s>>>(G, S, n, m, tr);
+  energy_partials_kernel<<<m, 64 * EW, 0, s>>>(G, S, n, m, tr);
   return hipGetLastError();
 }
 
