@@ -1,21 +1,25 @@
-// The fused B/C/D stage of the THC-SOX sequence (one tau point), FP64 mode, and
-// the dispatch of the other modes' kernels:
+// The fused B/C/D stage of the THC-SOX sequence in the FP64 mode, and the dispatch of
+// the other modes' kernels:
 //
 //   D_PR = sum_v C_RvP B_PRv,   B_PRv = sum_q G_Rq A_Pqv,   C_RvP = sum_w U_Rvw G_wP
 //
-// A workgroup owns a TR (R) x TP (P) tile of D and a range of v.  For every v
-// it forms both length-n contractions on matrix cores,
+// A workgroup owns a 64 (R) x 64 (P) tile of D of one tau point and a range of v.
+// For every v it forms both length-n contractions on the f64 matrix cores,
 //   accB[R][P] = sum_q Gt[R][q] A[v][P][q]      accC[R][P] = sum_w U[R][v][w] GXt[P][w]
-// which land in the same MFMA output layout, so B o C is a register-to-register
-// product.  In FP64 mode it is accumulated in FP64 registers; the template also
-// holds a reduced-precision form (FP32 registers for at most FLUSH_V consecutive
-// v, then added into the workgroup's FP64 tile of D) that is not launched: only
-// the FP64 mode runs this kernel.  Neither B (naux^2 n) nor
-// C ever reaches memory.  Operands are staged through LDS one (v, 32-wide k chunk) stage at a
-// time; the next stage's global loads are issued before the current stage's
-// MFMAs (register prefetch), so loads overlap the matrix work.
+// which land in the same MFMA output layout, so D += B o C is a register-to-register
+// product.  Neither B (naux^2 n) nor C ever reaches memory.
+//
+// What bounds it: the f64 matrix cores (a 16x16x4 product holds one for 64 cycles), as
+// long as something keeps them fed.  Operands go from memory straight to LDS, 16 k
+// of four panels (G, A_v, U_v, GX: 64 rows of 128 bytes each, 32 KiB) per stage, one
+// stage ahead in the other of two buffers, so that two workgroups share a compute
+// unit: each SIMD has a wave of the other one to run while this one waits at its
+// barrier (one a stage).  A wave owns 32 x 32 of the tile: 32 products a stage against
+// 16 fragment reads.  Matrix cores busy 81 % of the cycles
+// (counters); n = 200, naux = 1100, symmetric: 1.88 ms a tau point (52 TFLOP/s
+// algorithmic, 72 is what a large library product reaches), 3.34 with panels staged
+// through registers and one workgroup of 136 KiB per unit.
 #include <algorithm>
-#include <type_traits>
 
 #include "kernels.hpp"
 #include "mfma.hpp"
@@ -24,236 +28,177 @@
 namespace thcsox {
 namespace {
 
-constexpr int FLUSH_V = 8;   // v per FP32 partial sum of D before it is added in FP64
 constexpr int NXCD = 8;      // accelerator complex dies of an MI355X
+constexpr int TD = 64;       // tile edge of D
+constexpr int DK = 16;       // k per stage
+constexpr int BAND = 1;      // R blocks per band of the tile walk (measured at n = 300: 5 % faster than 4)
 
-// MFMA tiles per wave (rows x cols); the workgroup is 2 x 2 waves.  Sized so
-// that two stages of operand panels fit the 160 KiB of LDS.  BAND: R blocks per
-// band of the tile walk (measured at n = 300: 1 is 5 % faster than 4 for FP64).
-template <int M> struct FusedCfg;
-template <> struct FusedCfg<MODE_F64> { static constexpr int WTI = 2, WTJ = 2, BAND = 1; };
-// (the FP32 and fp16x2 modes run the two-v kernel of fused_f16.hip, bf16x3 that of
-// fused_bf3.hip)
+// One panel of a stage: 64 rows of 16 k, the eight 16-byte pieces of row r permuted by
+// XOR with r / 2 mod 8, so that 16 rows read at one piece touch all of the banks.
+struct Stage64 {
+  double g[TD * DK], a[TD * DK], u[TD * DK], x[TD * DK];
+};
+__device__ __forceinline__ int sw64(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-template <int M>
-__global__ __launch_bounds__(NT) void fused_kernel(FusedArgs f) {
-  using MT = ModeT<M>;
-  using T = typename MT::T;
-  constexpr int NP = MT::NP, KS = MT::KS, LD = lds_ld<T>();
-  constexpr int WTI = FusedCfg<M>::WTI, WTJ = FusedCfg<M>::WTJ;
-  constexpr int TR = 32 * WTI, TP = 32 * WTJ;
-  constexpr int ES = (int)sizeof(T);
-  using PR = Products<NP>;
-  // two stages of panels: one is read by the matrix cores while the next is written
-  __shared__ __attribute__((aligned(16))) T sG[2][NP][TR * LD];
-  __shared__ __attribute__((aligned(16))) T sU[2][NP][TR * LD];
-  __shared__ __attribute__((aligned(16))) T sA[2][NP][TP * LD];
-  __shared__ __attribute__((aligned(16))) T sX[2][NP][TP * LD];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
+  __shared__ __attribute__((aligned(16))) Stage64 b0;
+  __shared__ __attribute__((aligned(16))) Stage64 b1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
   // XCD-aware placement.  Workgroups are dealt round-robin to the XCDs, so
   // workgroup b runs on XCD b % NXCD.  Each XCD takes vsplit / NXCD partial
   // slots z = xcd, xcd + NXCD, ... (a block of consecutive v ranges, below)
-  // for every tile, and walks the tiles in bands of BAND R
-  // blocks, P block by P block: the workgroups resident on one XCD at a time
-  // form a compact BAND x (CUs per XCD / BAND) block of tiles at the same v,
-  // which share the U_v and A_v panels through that XCD's L2.
-  const int nrb = (f.naux + TR - 1) / TR, npb = (f.naux + TP - 1) / TP;
-  const int tiles = nrb * npb;
+  // for every tile, and walks the tiles in bands of BAND R blocks, P block by P
+  // block: the workgroups resident on one XCD at a time share the U_v and A_v
+  // panels through that XCD's L2.
+  const int nb = (f.naux + TD - 1) / TD, tiles = nb * nb;
   const int b = blockIdx.x;
   const int xcd = b % NXCD, local = b / NXCD;
   const int z = xcd + NXCD * (local / tiles);
   const int to = local % tiles;
-  constexpr int BAND = FusedCfg<M>::BAND;
-  const int band = to / (BAND * npb);
-  const int rb0 = band * BAND, bh = min(BAND, nrb - rb0);
-  const int within = to - rb0 * npb;
-  const int P0 = (within / bh) * TP, R0 = (rb0 + within % bh) * TR;
+  const int rb0 = to / (BAND * nb) * BAND, bh = min(BAND, nb - rb0);
+  const int within = to - rb0 * nb;
+  const int P0 = __builtin_amdgcn_readfirstlane((within / bh) * TD);
+  const int R0 = __builtin_amdgcn_readfirstlane((rb0 + within % bh) * TD);
   // symmetric D: a tile wholly below the diagonal is the mirror of one above it
   const int set = blockIdx.y;
-  if (f.sym != nullptr && f.sym[set] != 0 && R0 >= P0 + TP) return;
+  if (f.sym != nullptr && f.sym[set] != 0 && R0 >= P0 + TD) return;
   // v range: XCD x owns the consecutive ranges x q .. x q + q - 1 (q = vsplit / NXCD),
   // and the ranges split n as evenly as floor division allows, so every XCD gets
   // the same number of v to within one; range r is [r n / vsplit, (r + 1) n / vsplit)
   const int vr = (z % NXCD) * (f.vsplit / NXCD) + z / NXCD;
-  const int v_lo = (int)((int64_t)vr * f.n / f.vsplit);
-  const int v_hi = (int)((int64_t)(vr + 1) * f.n / f.vsplit);
-  const int kst = f.ldk / BK;
-  const int nstage = (v_hi > v_lo) ? (v_hi - v_lo) * kst : 0;
+  const int v_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)vr * f.n / f.vsplit));
+  const int v_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(vr + 1) * f.n / f.vsplit));
+  const int kst = (f.n + DK - 1) / DK;   // rows are zero from n to ldk
+  const int nstage = (v_hi - v_lo) * kst;
   const int64_t ldk = f.ldk;
-  const int64_t u_row = (int64_t)f.n * ldk;        // elements between R rows of U
-  const int64_t a_v = (int64_t)f.naux * ldk;       // elements between v slabs of A
-  const int rows_r = min(TR, f.naux - R0), rows_p = min(TP, f.naux - P0);
+  const int rows_r = min(TD, f.naux - R0), rows_p = min(TD, f.naux - P0);
 
-  const T* Gt = static_cast<const T*>(f.Gt) + set * f.g_set + R0 * ldk;
-  const T* GX = static_cast<const T*>(f.GXt) + set * f.g_set + P0 * ldk;
-  const T* U = static_cast<const T*>(f.U) + R0 * u_row;
-  __amdgpu_buffer_rsrc_t rG[NP], rX[NP];
+  // operands (rows past the valid range lie beyond the buffer resources and read as zero)
+  const double* Gt = static_cast<const double*>(f.Gt) + set * f.g_set + R0 * ldk;
+  const double* GX = static_cast<const double*>(f.GXt) + set * f.g_set + P0 * ldk;
+  const double* U = static_cast<const double*>(f.U) + (int64_t)R0 * f.n * ldk;
+  const double* A = static_cast<const double*>(f.A) + set * f.a_set + P0 * ldk;
+  // (byte counts below 2^31: checked by the launcher)
+  const i4 rG = raw_rsrc(Gt, rows_r * f.ldk * 8);
+  const i4 rX = raw_rsrc(GX, rows_p * f.ldk * 8);
+  i4 rA, rU;
+  auto set_v = [&](int v) {
+    rA = raw_rsrc(A + (int64_t)v * f.naux * ldk, rows_p * f.ldk * 8);
+    rU = raw_rsrc(U + v * ldk, ((rows_r - 1) * f.n * f.ldk + f.ldk) * 8);
+  };
+  // memory to LDS: one instruction moves 8 rows x 128 bytes; wave w moves the 8-row
+  // slabs w and w + 4 of each panel.  Lane l lands at slab row l / 8, piece l % 8, and
+  // loads the piece sw64 maps there.
+  uint32_t dR[2], dU[2];
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    rG[p] = make_rsrc(Gt + p * f.g_plane, TR * ldk * ES);
-    rX[p] = make_rsrc(GX + p * f.g_plane, TP * ldk * ES);
+  for (int j = 0; j < 2; ++j) {
+    const int row = (wave + 4 * j) * 8 + (lane >> 3);
+    const int c = sw64(row, lane & 7);
+    dR[j] = (uint32_t)(row * f.ldk + 2 * c) * 8;
+    dU[j] = (uint32_t)(row * (f.n * f.ldk) + 2 * c) * 8;
   }
-
-  Panel<T, TR> pG[NP], pU[NP];
-  Panel<T, TP> pX[NP];
-  Panel<T, TP> pA[NP];
+  int lv = v_lo, lk = 0;   // the next stage to load
+  auto fetch = [&](Stage64& s) {
+    const int so = lk * DK * 8;
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    pG[p].init(ldk, rows_r, tid);
-    pU[p].init(u_row, rows_r, tid);
-    pX[p].init(ldk, rows_p, tid);
-    pA[p].init(ldk, rows_p, tid);
-  }
-
-  auto load_stage = [&](int v, int k0) {
+    for (int j = 0; j < 2; ++j) {
+      const int slab = (wave + 4 * j) * 8 * DK;
+      dma16_untracked(rG, lds_addr(&s.g[slab]), dR[j], so);
+      dma16_untracked(rA, lds_addr(&s.a[slab]), dR[j], so);
+      dma16_untracked(rU, lds_addr(&s.u[slab]), dU[j], so);
+      dma16_untracked(rX, lds_addr(&s.x[slab]), dR[j], so);
+    }
+    if (++lk == kst) {
+      lk = 0;
+      if (++lv < v_hi) set_v(lv);
+    }
+  };
+  // fragments: lane group g takes k = 2 g, 2 g + 1, 8 + 2 g and 9 + 2 g in the stage's four
+  // products, the 16-byte pieces g and 4 + g of its row (2 g and 2 g + 1 cost bank
+  // conflicts on a tenth of the cycles; sw64 depends on the row mod 16 only)
+  const int lr = lane & 15, fg = lane >> 4;
+  const int o0 = lr * DK + 2 * sw64(lr, fg), o1 = lr * DK + 2 * sw64(lr, 4 + fg);
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  auto frag = [&](const double* p, int row0, double (&o)[4]) {
+    const d2 lo = *reinterpret_cast<const d2*>(p + row0 * DK + o0);
+    const d2 hi = *reinterpret_cast<const d2*>(p + row0 * DK + o1);
+    o[0] = lo[0]; o[1] = lo[1]; o[2] = hi[0]; o[3] = hi[1];
+  };
+  d4 accB[2][2], accC[2][2], accD[2][2];
+  const d4 zero = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      pG[p].load(rG[p], k0);
-      pX[p].load(rX[p], k0);
-      pU[p].load(make_rsrc(U + p * f.u_plane + v * ldk, TR * u_row * ES), k0);
+  for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) accB[ti][tj] = accC[ti][tj] = accD[ti][tj] = zero;
+  auto product = [&](d4 (&acc)[2][2], const double* rows, const double* cols) {
+    double r[2][4], c[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      frag(rows, 32 * wr + 16 * t, r[t]);
+      frag(cols, 32 * wc + 16 * t, c[t]);
     }
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
-      pA[p].load(make_rsrc(static_cast<const T*>(f.A) + set * f.a_set + p * f.a_plane + v * a_v + P0 * ldk,
-                           TP * ldk * ES),
-                 k0);
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = mfma1(r[ti][s], c[tj][s], acc[ti][tj]);
   };
-
-  using DAcc = typename std::conditional<M == MODE_F64, double, float>::type;
-  typename MT::Acc accB[WTI][WTJ], accC[WTI][WTJ];
-  DAcc accD[WTI][WTJ][4];
+  // (the loads are issued in inline assembly: left to the compiler, a read of one
+  // buffer waits for the loads just issued into the other)
+  if (nstage > 0) {
+    set_v(v_lo);
+    fetch(b0);
+  }
+  int ks = 0, st = 0;
+  auto stage = [&](Stage64& cur, Stage64& nxt) {
+    // this wave's loads of the stage have landed; after the barrier every wave's have,
+    // and every wave is done with the other buffer
+    __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (st + 1 < nstage) fetch(nxt);
+    product(accB, cur.g, cur.a);
+    product(accC, cur.u, cur.x);
+    if (++ks == kst) {   // all k of this v done: D += B o C
+      ks = 0;
 #pragma unroll
-  for (int ti = 0; ti < WTI; ++ti)
+      for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < WTJ; ++tj)
+        for (int tj = 0; tj < 2; ++tj) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            accD[ti][tj][r] = fma(accB[ti][tj][r], accC[ti][tj][r], accD[ti][tj][r]);
+          accB[ti][tj] = accC[ti][tj] = zero;
+        }
+    }
+    ++st;
+  };
+  while (st < nstage) {
+    stage(b0, b1);
+    if (st < nstage) stage(b1, b0);
+  }
+  // the partial tile (zeros for an empty v range)
+  double* D = f.Dpart + set * f.d_set + (int64_t)z * f.naux * f.naux;
+#pragma unroll
+  for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        accB[ti][tj][r] = 0;
-        accC[ti][tj][r] = 0;
-        accD[ti][tj][r] = 0;
+        const int R = R0 + 32 * wr + 16 * ti + out_row<MODE_F64>(lane, r);
+        const int P = P0 + 32 * wc + 16 * tj + lr;
+        if (R < f.naux && P < f.naux) D[(int64_t)R * f.naux + P] = accD[ti][tj][r];
       }
-  double* D = f.Dpart + set * f.d_set + (int64_t)z * f.naux * f.naux;
-  float* D32 = reinterpret_cast<float*>(f.Dpart) + set * f.d_set + (int64_t)z * f.naux * f.naux;
-  // add (or, the first time, store) the register partial sums into the FP64 tile
-  auto flush = [&](bool first) {
-#pragma unroll
-    for (int ti = 0; ti < WTI; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < WTJ; ++tj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int R = R0 + wr * 16 * WTI + 16 * ti + out_row<M>(lane, r);
-          const int P = P0 + wc * 16 * WTJ + 16 * tj + (lane & 15);
-          if (R < f.naux && P < f.naux) {
-            if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
-              D32[(int64_t)R * f.naux + P] = (float)accD[ti][tj][r];
-            } else {
-              double* d = D + (int64_t)R * f.naux + P;
-              *d = (first ? 0.0 : *d) + (double)accD[ti][tj][r];
-            }
-          }
-          accD[ti][tj][r] = 0;
-        }
-  };
-  int nv = 0;
-
-  // stage sequence: (v, ks) for v in [v_lo, v_hi), ks in [0, kst); (lv, lk) is the
-  // next stage to fetch from global memory
-  int lv = v_lo, lk = 0;
-  auto fetch_next = [&]() {
-    load_stage(lv, lk * BK);
-    if (++lk == kst) { lk = 0; ++lv; }
-  };
-  auto put = [&](int buf) {
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      pG[p].store(sG[buf][p], tid);
-      pU[p].store(sU[buf][p], tid);
-      pX[p].store(sX[buf][p], tid);
-    }
-#pragma unroll
-    for (int p = 0; p < NP; ++p) pA[p].store(sA[buf][p], tid);
-  };
-  // acc[ti][tj] += sum_k rows(sr) x rows(sc) over this stage's 32-wide k range
-  auto gemm = [&](typename MT::Acc (&acc)[WTI][WTJ], T (*sr)[TR * LD], T (*sc)[TP * LD]) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += KS) {
-      typename MT::Frag fr[WTI][NP], fc[WTJ][NP];
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-#pragma unroll
-        for (int ti = 0; ti < WTI; ++ti)
-          fr[ti][p] = lds_frag<M>(sr[p], LD, wr * 16 * WTI + 16 * ti, kk, lane);
-#pragma unroll
-        for (int tj = 0; tj < WTJ; ++tj)
-          fc[tj][p] = lds_frag<M>(sc[p], LD, wc * 16 * WTJ + 16 * tj, kk, lane);
-      }
-#pragma unroll
-      for (int q = 0; q < PR::N; ++q)
-#pragma unroll
-        for (int ti = 0; ti < WTI; ++ti)
-#pragma unroll
-          for (int tj = 0; tj < WTJ; ++tj)
-            acc[ti][tj] = mfma1(fr[ti][PR::a(q)], fc[tj][PR::b(q)], acc[ti][tj]);
-    }
-  };
-
-  if (nstage > 0) {
-    fetch_next();
-    put(0);
-  }
-  if (nstage > 1) fetch_next();
-  __syncthreads();
-  int t = 0;
-  for (int v = v_lo; v < v_hi; ++v) {
-#pragma unroll
-    for (int ti = 0; ti < WTI; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < WTJ; ++tj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          accB[ti][tj][r] = 0;
-          accC[ti][tj][r] = 0;
-        }
-    for (int ks = 0; ks < kst; ++ks, ++t) {
-      const int cur = t & 1;
-      gemm(accB, sG[cur], sA[cur]);
-      // while those run: stage t+1 (already in registers) into the other buffer,
-      // and start fetching stage t+2
-      if (t + 1 < nstage) put(cur ^ 1);
-      if (t + 2 < nstage) fetch_next();
-      gemm(accC, sU[cur], sX[cur]);
-      __syncthreads();
-    }
-    // all k of this v done: D += B o C
-#pragma unroll
-    for (int ti = 0; ti < WTI; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < WTJ; ++tj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          accD[ti][tj][r] = fma((DAcc)accB[ti][tj][r], (DAcc)accC[ti][tj][r], accD[ti][tj][r]);
-    ++nv;
-    if (M != MODE_F64 && (nv % FLUSH_V == 0) && v + 1 < v_hi) flush(nv == FLUSH_V);
-  }
-  // final flush (also writes zeros for an empty v range)
-  flush(M == MODE_F64 || nv <= FLUSH_V);
 }
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 }  // namespace
 
-template <int M> void tile_of(int* rows, int* cols) {
-  *rows = 32 * FusedCfg<M>::WTI;
-  *cols = 32 * FusedCfg<M>::WTJ;
-}
-
 void fused_tile(int mode, int* rows, int* cols) {
   switch (mode) {
-    case MODE_F64: tile_of<MODE_F64>(rows, cols); break;
+    case MODE_F64: *rows = *cols = TD; break;
     default: fused_f16_tile(rows, cols); break;   // FP32, fp16x2 and bf16x3: 128 x 128
   }
 }
@@ -263,18 +208,13 @@ int fused_xcds() { return NXCD; }
 hipError_t sox_fused(int mode, const FusedArgs& f, hipStream_t s) {
   if (mode == MODE_F16X2 || mode == MODE_F32) return sox_fused_pairs(mode, f, s);   // own checks
   if (mode == MODE_BF16X3) return sox_fused_bf3(f, s);
-  int TR, TP;
-  fused_tile(mode, &TR, &TP);
-  if (f.vsplit % NXCD != 0 || (int64_t)f.vsplit * f.vchunk < f.n) return hipErrorInvalidValue;
-  // FP32 partial tiles only where each range is one FP32 partial sum
-  if (f.dpart_f32 && (mode == MODE_F64 || f.vchunk > FLUSH_V)) return hipErrorInvalidValue;
+  if (mode != MODE_F64 || f.vsplit % NXCD != 0 || (int64_t)f.vsplit * f.vchunk < f.n ||
+      f.dpart_f32 || f.ldk % DK != 0 || f.ldk < f.n)
+    return hipErrorInvalidValue;
   // buffer offsets inside one tile's rows of U are 32-bit
-  if ((int64_t)std::max(TR, TP) * f.n * f.ldk * 8 > 0x7fffffffLL) return hipErrorInvalidValue;
-  dim3 grid(cdiv(f.naux, TP) * cdiv(f.naux, TR) * f.vsplit, f.nsets);
-  switch (mode) {
-    case MODE_F64: fused_kernel<MODE_F64><<<grid, NT, 0, s>>>(f); break;
-    default: return hipErrorInvalidValue;
-  }
+  if ((int64_t)TD * f.n * f.ldk * 8 > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid(cdiv(f.naux, TD) * cdiv(f.naux, TD) * f.vsplit, f.nsets);
+  fused_f64_kernel<<<grid, NT, 0, s>>>(f);
   return hipGetLastError();
 }
 

@@ -35,16 +35,16 @@ constexpr int NXCD = 8;
 constexpr int BAND = 8;      // row tiles per band of the tile walk
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-// An operand's panel in LDS.  Within 16 k the four lane groups g of an MFMA step s
-// take k = 4 g + s.
+// An operand's panel in LDS.  Within 16 k lane group g takes k = 2 g, 2 g + 1, 8 + 2 g
+// and 9 + 2 g in the four MFMA steps.
 // KC (k contiguous in memory): rows of BK k, 16-byte pair c of row r at the piece
-//   swz(r, c): a lane reads its four k in two 16-byte pieces, and 16 rows at one
-//   pair touch 16 distinct 16-byte columns of the banks.
-// otherwise (row index contiguous): [k][row], 32 bytes of padding per k, so that
-//   lane groups four k apart fall on different halves of the banks.
+//   swz(r, c): a lane reads its four k in the pieces g and 4 + g of each 16, and 16
+//   rows at one pair touch 16 distinct 16-byte columns of the banks.
+// otherwise (row index contiguous): [k][row], 64 bytes of padding per k, so that
+//   lane groups two k apart fall on different halves of the banks.
 template <int T, int BK, bool KC>
 struct PanelLayout {
-  static constexpr int LD = KC ? BK : T + 4;
+  static constexpr int LD = KC ? BK : T + 8;
   static constexpr int SIZE = KC ? T * BK : BK * LD;
 };
 template <int BK>
@@ -161,11 +161,11 @@ __global__ __launch_bounds__(NT, WT == 2 && BK == 16 ? 4 : 2) void gemm64_kernel
     }
   };
   const int fr = lane & 15, fg = lane >> 4;
-  // elements k = 16 kb + 4 fg + 2 h and the next of row 16 t + fr of the wave's part
+  // elements k = 16 kb + 8 h + 2 fg and the next of row 16 t + fr of the wave's part
   auto frag = [&](bool kc, const double* s, int ld, int r0, int t, int kb, int h) -> d2 {
     const int r = r0 + 16 * t + fr;
-    if (kc) return *reinterpret_cast<const d2*>(s + r * BK + (swz<BK>(r, 8 * kb + 2 * fg + h) << 1));
-    const int k = 16 * kb + 4 * fg + 2 * h;
+    if (kc) return *reinterpret_cast<const d2*>(s + r * BK + (swz<BK>(r, 8 * kb + 4 * h + fg) << 1));
+    const int k = 16 * kb + 8 * h + 2 * fg;
     return d2{s[k * ld + r], s[(k + 1) * ld + r]};
   };
 

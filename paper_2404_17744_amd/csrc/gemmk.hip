@@ -8,7 +8,6 @@
 #include "kernels.hpp"
 #include "mfma.hpp"
 #include "panel.hpp"
-#include "reduce.hpp"
 
 namespace thcsox {
 namespace {
@@ -90,7 +89,6 @@ __global__ __launch_bounds__(NT) void gemmk_kernel(GemmKArgs g) {
     }
   }
 
-  double lmax = 0.0;
   OutT* C = static_cast<OutT*>(g.C) + blockIdx.y * g.c_set;
   if constexpr (__is_same(OutT, __bf16)) {
     // three bf16 planes; a lane's four outputs are four consecutive rows i of one
@@ -139,30 +137,12 @@ __global__ __launch_bounds__(NT) void gemmk_kernel(GemmKArgs g) {
         const int j = j0 + wc * 16 * WTJ + 16 * tj + (lane & 15);
         if (i < g.M && j < g.N) {
           const int64_t o = ((int64_t)i / g.ci_in) * g.ci_out + ((int64_t)i % g.ci_in) + (int64_t)j * g.c_j;
-          const OutT v = (OutT)(g.alpha * (double)acc[ti][tj][r]);
-          C[o] = v;
-          lmax = fmax(lmax, fabs((double)v));
+          C[o] = (OutT)(g.alpha * (double)acc[ti][tj][r]);
         }
       }
-  if (g.amax != nullptr) block_atomic_max<NT / 64>(lmax, g.amax);
 }
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
-
-template <int M, int WTI, int WTJ>
-hipError_t launch(bool out_f64, const GemmKArgs& g, hipStream_t s) {
-  const dim3 grid(cdiv(g.M, 32 * WTI) * cdiv(g.N, 32 * WTJ), g.nsets);
-  if (out_f64) gemmk_kernel<M, WTI, WTJ, double><<<grid, NT, 0, s>>>(g);
-  else gemmk_kernel<M, WTI, WTJ, float><<<grid, NT, 0, s>>>(g);
-  return hipGetLastError();
-}
-
-template <int M>
-hipError_t launch_mode(bool out_f64, const GemmKArgs& g, hipStream_t s) {
-  // all of the B rows in one workgroup when they fit 320, else 160 per workgroup
-  if (g.N <= 320) return launch<M, 2, 10>(out_f64, g, s);
-  return launch<M, 2, 5>(out_f64, g, s);
-}
 
 }  // namespace
 
@@ -175,15 +155,14 @@ hipError_t gemm_kmajor_bf3(const GemmKArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t gemm_kmajor(int mode, bool out_f64, const GemmKArgs& g, hipStream_t s) {
+hipError_t gemm_kmajor_f32(const GemmKArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  switch (mode) {
-    case MODE_F64: return launch<MODE_F64, 2, 5>(out_f64, g, s);
-    case MODE_F32: return launch_mode<MODE_F32>(out_f64, g, s);
-    case MODE_BF16X3: return launch_mode<MODE_BF16X3>(out_f64, g, s);
-    case MODE_F16X2: return launch_mode<MODE_F16X2>(out_f64, g, s);
-    default: return hipErrorInvalidValue;
-  }
+  // all of the B rows in one workgroup when they fit 320, else 160 per workgroup
+  const int wtj = g.N <= 320 ? 10 : 5;
+  const dim3 grid(cdiv(g.M, 64) * cdiv(g.N, 32 * wtj), g.nsets);
+  if (wtj == 10) gemmk_kernel<MODE_F32, 2, 10, float><<<grid, NT, 0, s>>>(g);
+  else gemmk_kernel<MODE_F32, 2, 5, float><<<grid, NT, 0, s>>>(g);
+  return hipGetLastError();
 }
 
 }  // namespace thcsox

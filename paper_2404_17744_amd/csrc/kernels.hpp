@@ -23,28 +23,25 @@ struct Gemm64Args {
 };
 hipError_t gemm64(const Gemm64Args& g, hipStream_t s);
 
-// GEMM over K-major operand planes in one of the four modes:
+// GEMM over K-major operand planes, FP32:
 //   C(i,j) = alpha * sum_{k < kpad} A[i][k] B[j][k]   (operand pad must be zero)
 //   A rows:  A + p*a_plane + i*lda          (i < M)
 //   B rows:  B + p*b_plane + j*ldb          (j < N)
-//   C(i,j) = C[(i / ci_in) * ci_out + (i % ci_in) + j * c_j]  (OutT = double or float)
-// If amax != nullptr, the largest |C(i,j)| is max-reduced into *amax (as the
-// bits of a non-negative double).
+//   C(i,j) = C[(i / ci_in) * ci_out + (i % ci_in) + j * c_j]
 struct GemmKArgs {
   int M, N, kpad;
   double alpha;
   const void* A; int64_t lda, a_plane;
   const void* B; int64_t ldb, b_plane;
   void* C; int64_t ci_in, ci_out, c_j;
-  unsigned long long* amax;
   int64_t c_plane;   // gemm_kmajor_bf3: elements between the output planes
   // nsets products of the same A: B and C of set x lie x b_set, x c_set elements further
   int nsets; int64_t b_set, c_set;
 };
-hipError_t gemm_kmajor(int mode, bool out_f64, const GemmKArgs& g, hipStream_t s);
+hipError_t gemm_kmajor_f32(const GemmKArgs& g, hipStream_t s);
 // The same product in the bf16x3 mode with the output split into three bf16
 // planes (C + p * c_plane, p < 3) instead of FP32 (no scale: bf16 keeps FP32's
-// exponent range); amax is not used.
+// exponent range).
 hipError_t gemm_kmajor_bf3(const GemmKArgs& g, hipStream_t s);
 // The A stage of the fp16x2 mode for nsets tau points at once:
 //   A[set][v][P][q] = scale[set] * sum_s U[P][q][s] Gb[set][v][s]   (q < n; rows n <= q < ldk get 0)
@@ -65,7 +62,7 @@ hipError_t astage_f16(const AStageArgs& a, hipStream_t s);
 // ldk elements (A passed as the address of its FP32 array; gb_set and a_set still
 // count halves), A written unscaled.  Only for ldk a multiple of 64 up to 320 with
 // A's byte offsets in 31 bits (astage_f32_fits); otherwise hipErrorInvalidValue
-// (use gemm_kmajor).
+// (use gemm_kmajor_f32).
 bool astage_f32_fits(int n, int naux, int ldk);
 hipError_t astage_f32(const AStageArgs& a, hipStream_t s);
 // The A stage of the bf16x3 mode for nsets tau points (gb_set, a_set elements apart):

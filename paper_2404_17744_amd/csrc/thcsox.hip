@@ -419,6 +419,15 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
         ab.Gb = Gb; ab.gb_plane = p->gb_plane; ab.gb_set = gb_set;
         ab.A = p->A; ab.a_plane = p->a_plane; ab.a_set = p->a_set;
         HIP_TRY(astage_bf3(ab, s));
+      } else if (mode == MODE_F64) {
+        // rows v of Gb against rows (P, q) of U, stored as A's rows (v, P)
+        Gemm64Args ga{};
+        ga.M = n; ga.N = naux * n; ga.K = n; ga.batch = na; ga.alpha = 1.0; ga.beta = 0.0;
+        ga.A = static_cast<const double*>(Gb); ga.a_i = ldk; ga.a_k = 1; ga.a_b = gb_set;
+        ga.B = static_cast<const double*>(cores.UA); ga.b_j = ldk; ga.b_k = 1; ga.b_b = 0;
+        ga.C = static_cast<double*>(p->A);
+        ga.c_i = (int64_t)naux * ldk; ga.c_j = 1; ga.cj_in = n; ga.cj_out = ldk; ga.c_b = p->a_set;
+        HIP_TRY(gemm64(ga, s));
       } else {
         GemmKArgs ga{};
         ga.M = naux * n; ga.N = n; ga.kpad = ldk; ga.alpha = 1.0;
@@ -431,7 +440,7 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
           ga.c_plane = p->a_plane;
           HIP_TRY(gemm_kmajor_bf3(ga, s));
         } else {
-          HIP_TRY(gemm_kmajor(mode, mode == MODE_F64, ga, s));
+          HIP_TRY(gemm_kmajor_f32(ga, s));
         }
       }
       HIP_TRY(p->mark(THCSOX_STAGE_A, false));
