@@ -92,38 +92,36 @@ __global__ __launch_bounds__(NT, WT == 2 && BK == 16 ? 4 : 2) void gemm64_kernel
   const int i_lo = w / (BAND * ntj) * BAND, bh = min(BAND, nti - i_lo);
   const int in = w - i_lo * ntj;
   const int i0 = (i_lo + in % bh) * T, j0 = in / bh * T;
-  // the step being loaded (term lt, from k = lk) and the one held in registers
-  int lt = 0, lk = 0, sk = 0;
-  double sign = 1.0;
+  int lt = 0, lk = 0;   // the step to load next: term lt, from k = lk
   const double* A = g.A + b * g.a_b;
   const double* B = g.B + b * g.b_b;
 
-  d2 ra[NP], rb[NP];
-  auto load = [&]() {
-    const int k0 = lk;
+  struct Held {   // a step in registers
+    d2 a[NP], b[NP];
+    int k0;
+    double sign;
+  };
+  auto load = [&](Held& h) {
+    const int k0 = h.k0 = lk;
+    h.sign = lt == 0 ? 1.0 : g.sign[lt - 1];
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
       const int e = tid + NT * t;
       if (AC) {   // row i, k pair
         const int i = min(i0 + e / RP, g.M - 1);
-        ra[t] = pair_at<ACC>(A + (int64_t)i * g.a_i, k0 + 2 * (e % RP), g.K);
+        h.a[t] = pair_at<ACC>(A + (int64_t)i * g.a_i, k0 + 2 * (e % RP), g.K);
       } else {    // one k, i pair
         const int k = min(k0 + e / (T / 2), g.K - 1);
-        ra[t] = pair_at<ACC>(A + (int64_t)k * g.a_k, i0 + 2 * (e % (T / 2)), g.M);
+        h.a[t] = pair_at<ACC>(A + (int64_t)k * g.a_k, i0 + 2 * (e % (T / 2)), g.M);
       }
       if (BC) {
         const int j = min(j0 + e / RP, g.N - 1);
-        rb[t] = pair_at<ACC>(B + (int64_t)j * g.b_j, k0 + 2 * (e % RP), g.K);
+        h.b[t] = pair_at<ACC>(B + (int64_t)j * g.b_j, k0 + 2 * (e % RP), g.K);
       } else {
         const int k = min(k0 + e / (T / 2), g.K - 1);
-        rb[t] = pair_at<ACC>(B + (int64_t)k * g.b_k, j0 + 2 * (e % (T / 2)), g.N);
+        h.b[t] = pair_at<ACC>(B + (int64_t)k * g.b_k, j0 + 2 * (e % (T / 2)), g.N);
       }
     }
-  };
-  auto load_next = [&]() {
-    load();
-    sk = lk;
-    sign = lt == 0 ? 1.0 : g.sign[lt - 1];
     lk += BK;
     if (lk >= g.K && lt < g.more) {
       lk = 0;
@@ -142,22 +140,22 @@ __global__ __launch_bounds__(NT, WT == 2 && BK == 16 ? 4 : 2) void gemm64_kernel
                       : e / (T / 2) * ld + 2 * (e % (T / 2));
     *reinterpret_cast<d2*>(s + at) = v;
   };
-  auto store = [&](int buf) {
-    if (sk + BK > g.K) {
+  auto store = [&](int buf, Held& h) {
+    if (h.k0 + BK > g.K) {
 #pragma unroll
       for (int t = 0; t < NP; ++t) {
-        ra[t] = cut(AC, tid + NT * t, sk, ra[t]);
-        rb[t] = cut(BC, tid + NT * t, sk, rb[t]);
+        h.a[t] = cut(AC, tid + NT * t, h.k0, h.a[t]);
+        h.b[t] = cut(BC, tid + NT * t, h.k0, h.b[t]);
       }
     }
     if (g.more > 0) {
 #pragma unroll
-      for (int t = 0; t < NP; ++t) ra[t] *= sign;
+      for (int t = 0; t < NP; ++t) h.a[t] *= h.sign;
     }
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
-      put(AC, sA[buf], LA::LD, tid + NT * t, ra[t]);
-      put(BC, sB[buf], LB::LD, tid + NT * t, rb[t]);
+      put(AC, sA[buf], LA::LD, tid + NT * t, h.a[t]);
+      put(BC, sB[buf], LB::LD, tid + NT * t, h.b[t]);
     }
   };
   const int fr = lane & 15, fg = lane >> 4;
@@ -175,22 +173,14 @@ __global__ __launch_bounds__(NT, WT == 2 && BK == 16 ? 4 : 2) void gemm64_kernel
 #pragma unroll
     for (int tj = 0; tj < WT; ++tj) acc[ti][tj] = d4{0.0, 0.0, 0.0, 0.0};
 
-  const int steps = (g.K + BK - 1) / BK * (g.more + 1);
-  load_next();
-  store(0);
-  if (steps > 1) load_next();
-  __syncthreads();
-  int cur = 0;
-  for (int st = 0; st < steps; ++st, cur ^= 1) {
-    if (st + 1 < steps) store(cur ^ 1);
-    if (st + 2 < steps) load_next();
+  auto multiply = [&](int buf) {
 #pragma unroll
     for (int kh = 0; kh < BK / 8; ++kh) {
       d2 a[WT], bb[WT];
 #pragma unroll
       for (int t = 0; t < WT; ++t) {
-        a[t] = frag(AC, sA[cur], LA::LD, 16 * WT * wr, t, kh >> 1, kh & 1);
-        bb[t] = frag(BC, sB[cur], LB::LD, 16 * WT * wc, t, kh >> 1, kh & 1);
+        a[t] = frag(AC, sA[buf], LA::LD, 16 * WT * wr, t, kh >> 1, kh & 1);
+        bb[t] = frag(BC, sB[buf], LB::LD, 16 * WT * wc, t, kh >> 1, kh & 1);
       }
 #pragma unroll
       for (int s = 0; s < 2; ++s)
@@ -199,7 +189,27 @@ __global__ __launch_bounds__(NT, WT == 2 && BK == 16 ? 4 : 2) void gemm64_kernel
 #pragma unroll
           for (int tj = 0; tj < WT; ++tj) acc[ti][tj] = mfma1(a[ti][s], bb[tj][s], acc[ti][tj]);
     }
+  };
+  // In step st the buffer st mod 2 is multiplied while step st + 1 goes from registers to
+  // the other one and later steps load: st + 2, and st + 3 where registers allow.
+  constexpr bool DEEP = WT < 4;
+  const int steps = (g.K + BK - 1) / BK * (g.more + 1);
+  Held h0, h1;
+  Held& later = DEEP ? h1 : h0;
+  load(h0);
+  if (DEEP && steps > 1) load(h1);
+  store(0, h0);
+  if (steps > (DEEP ? 2 : 1)) load(h0);
+  __syncthreads();
+  auto step = [&](int st, int cur, Held& h) {
+    if (st + 1 < steps) store(cur ^ 1, h);
+    if (st + (DEEP ? 3 : 2) < steps) load(h);
+    multiply(cur);
     __syncthreads();
+  };
+  for (int st = 0; st < steps; st += 2) {
+    step(st, 0, later);
+    if (st + 1 < steps) step(st + 1, 1, h0);
   }
 #pragma unroll
   for (int tj = 0; tj < WT; ++tj) {
