@@ -336,30 +336,80 @@ __global__ void adam(float* p, const float* g, float* m1, float* m2, int64_t cou
 __global__ void pair_scale_kernel(const double* S, int m, int64_t aa, double* scale) {
   for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < aa; e += (int64_t)gridDim.x * NT) {
     double mx = 0.0;
+#pragma unroll 8
     for (int k = 0; k < m; ++k) mx = fmax(mx, fabs(S[(int64_t)k * aa + e]));
     scale[e] = mx > 0.0 ? mx : 1.0;
   }
 }
 
+// The network's rows x[b][k] and the THC self-energy's slices S[k][pair] are each other's
+// transposes: blocks of 64 pairs x 64 tau points go through LDS, so that both sides
+// are touched in whole lines (S in runs of 64 pairs, x in runs of up to 64 tau points).
+// naux = 505, 64 tau points: 41 us each, 4.9 TB/s (105 and 307 us with one side strided).
+constexpr int PT = 64;             // pairs and tau points per block
+constexpr int PTS = NT / PT;       // rows of a block per pass
+
 // x[b][k] = S[k][pair_b] / scale[pair_b]; pair_b = pairs[b] (or b if pairs is null)
-__global__ void pair_gather_kernel(const double* S, int m, int64_t aa, const double* scale,
-                                   const int64_t* pairs, int64_t npairs, float* x) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < npairs * m;
-       e += (int64_t)gridDim.x * NT) {
-    const int64_t b = e / m;
-    const int k = (int)(e % m);
-    const int64_t pr = pairs ? pairs[b] : b;
-    x[e] = (pr >= 0 && pr < aa) ? (float)(S[(int64_t)k * aa + pr] / scale[pr]) : 0.f;
+__global__ __launch_bounds__(NT) void pair_gather_kernel(const double* __restrict__ S, int m,
+                                                         int64_t aa,
+                                                         const double* __restrict__ scale,
+                                                         const int64_t* __restrict__ pairs,
+                                                         int64_t npairs, float* __restrict__ x) {
+  __shared__ float t[PT][PT + 1];   // [tau][pair]
+  const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;
+  const int64_t b0 = (int64_t)blockIdx.x * PT;
+  const int64_t b = b0 + tx;
+  const int64_t pr = b < npairs ? (pairs ? pairs[b] : b) : -1;
+  const bool in = pr >= 0 && pr < aa;   // a pair outside the array reads as zero
+  const double sc = in ? scale[pr] : 1.0;
+  for (int k0 = 0; k0 < m; k0 += PT) {
+    const int nk = min(PT, m - k0);
+    double v[PT / PTS];
+#pragma unroll
+    for (int e = 0; e < PT / PTS; ++e)
+      v[e] = S[(int64_t)(k0 + min(ty + e * PTS, nk - 1)) * aa + (in ? pr : 0)];
+#pragma unroll
+    for (int e = 0; e < PT / PTS; ++e)
+      if (ty + e * PTS < nk) t[ty + e * PTS][tx] = in ? (float)(v[e] / sc) : 0.f;
+    __syncthreads();
+    // consecutive threads along tau, then along pairs
+    const int rows = (int)(npairs - b0 < PT ? npairs - b0 : PT);
+    for (int e = threadIdx.x; e < rows * nk; e += NT) {
+      const int r = e / nk, k = e - r * nk;
+      x[(b0 + r) * m + k0 + k] = t[k][r];
+    }
+    __syncthreads();
   }
 }
 
 // S[k][pair] = y[pair][k] * scale[pair] for every pair
-__global__ void pair_scatter_kernel(const float* y, int m, int64_t aa, const double* scale,
-                                    double* S) {
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < aa * m; e += (int64_t)gridDim.x * NT) {
-    const int k = (int)(e / aa);
-    const int64_t pr = e % aa;
-    S[e] = (double)y[pr * m + k] * scale[pr];
+__global__ __launch_bounds__(NT) void pair_scatter_kernel(const float* __restrict__ y, int m,
+                                                          int64_t aa,
+                                                          const double* __restrict__ scale,
+                                                          double* __restrict__ S) {
+  __shared__ float t[PT][PT + 1];   // [tau][pair]
+  const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;
+  const int64_t p0 = (int64_t)blockIdx.x * PT;
+  const int rows = (int)(aa - p0 < PT ? aa - p0 : PT);
+  const double sc = tx < rows ? scale[p0 + tx] : 0.0;
+  for (int k0 = 0; k0 < m; k0 += PT) {
+    const int nk = min(PT, m - k0);
+    float v[PT * PT / NT];   // all in flight together (addresses clamped into the block)
+#pragma unroll
+    for (int i = 0; i < PT * PT / NT; ++i) {
+      const int e = min((int)threadIdx.x + i * NT, rows * nk - 1), r = e / nk;
+      v[i] = y[(p0 + r) * m + k0 + e - r * nk];
+    }
+#pragma unroll
+    for (int i = 0; i < PT * PT / NT; ++i) {
+      const int e = (int)threadIdx.x + i * NT, r = e / nk;
+      if (e < rows * nk) t[e - r * nk][r] = v[i];
+    }
+    __syncthreads();
+    if (tx < rows)
+      for (int k = ty; k < nk; k += PTS)
+        S[(int64_t)(k0 + k) * aa + p0 + tx] = (double)t[k][tx] * sc;
+    __syncthreads();
   }
 }
 
@@ -369,19 +419,22 @@ unsigned blocks_for(int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// Inference with bf16 weights: one fused kernel per 64 rows on the bf16 matrix
+// Inference with bf16 weights: one fused kernel per 64 or 128 rows on the bf16 matrix
 // cores (16x16x32, FP32 accumulation); the hidden activations never leave LDS.
 // Each layer's input (x, h1, h2) is rounded to bf16 (nearest, ties to even);
 // bias, silu and the residual add on the exact FP32 x stay in FP32.
 //
 // Eight waves: in layers 1 and 2 wave w owns the hidden units [16 HT w,
-// 16 HT (w + 1)) of all 64 rows, taking the weight rows as the MFMA's first
+// 16 HT (w + 1)) of all rows, taking the weight rows as the MFMA's first
 // operand and the activation rows (from LDS) as its second, so a lane's four
 // results are four consecutive hidden units of one row: one 8-byte LDS write of
-// the next layer's bf16 input.  Layer 3's m x 64 output tiles are dealt to the
-// waves in turn; a lane's results are four consecutive outputs of one row, one
-// 16-byte store.
-constexpr int IRB = 64;               // rows per workgroup
+// the next layer's bf16 input.  Layer 3's output tiles are dealt to the waves; a
+// lane's results are four consecutive outputs of one row, one 16-byte store.
+// What bounds it: the weights come from L2 for every block of rows, one flop per row
+// and byte, so 128 rows (all of the LDS at H = 512) halve the 17 TB/s that 64 rows
+// need at the matrix cores' rate; the next k step's weights are loaded while one is
+// multiplied.  m = 64, H = 512, 255025 rows: 373 us (563 with 64 rows and no prefetch),
+// about half of it the silu of two hidden layers, which no wave's products overlap.
 constexpr int INW = 8, INTH = 64 * INW;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -389,21 +442,21 @@ __device__ __forceinline__ bf16x4 to_bf16x4(float a, float b, float c, float d) 
   return bf16x4{(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
 }
 
-template <int HT, int MT>   // hidden width H = 128 HT, m = 16 MT
+template <int HT, int MT, int RB>   // hidden width H = 128 HT, m = 16 MT, RB rows per workgroup
 __global__ __launch_bounds__(INTH) void mlp_infer_bf16_kernel(
     const float* __restrict__ x, float* __restrict__ y, int64_t batch,
     const __bf16* __restrict__ W1, const float* __restrict__ b1,
     const __bf16* __restrict__ W2, const float* __restrict__ b2,
     const __bf16* __restrict__ W3, const float* __restrict__ b3) {
-  constexpr int H = 128 * HT, m = 16 * MT;
+  constexpr int H = 128 * HT, m = 16 * MT, RT = RB / 16;   // row tiles
   constexpr int XLD = m + 8, HLD = H + 8;   // padded rows (in bf16): 16-lane reads hit distinct banks
-  __shared__ __attribute__((aligned(16))) __bf16 xs[IRB * XLD];
-  __shared__ __attribute__((aligned(16))) __bf16 hs[IRB * HLD];
+  __shared__ __attribute__((aligned(16))) __bf16 xs[RB * XLD];
+  __shared__ __attribute__((aligned(16))) __bf16 hs[RB * HLD];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t r0 = (int64_t)blockIdx.x * IRB;
-  const int rows = (int)(batch - r0 < IRB ? batch - r0 : IRB);
-  for (int e = tid; e < IRB * m / 4; e += INTH) {
+  const int64_t r0 = (int64_t)blockIdx.x * RB;
+  const int rows = (int)(batch - r0 < RB ? batch - r0 : RB);
+  for (int e = tid; e < RB * m / 4; e += INTH) {
     const int r = e / (m / 4), c = 4 * (e % (m / 4));
     const f4 v = r < rows ? *reinterpret_cast<const f4*>(x + (r0 + r) * m + c) : f4{0.f, 0.f, 0.f, 0.f};
     *reinterpret_cast<bf16x4*>(&xs[r * XLD + c]) = to_bf16x4(v[0], v[1], v[2], v[3]);
@@ -411,25 +464,32 @@ __global__ __launch_bounds__(INTH) void mlp_infer_bf16_kernel(
   __syncthreads();
   const int fr = lane & 15, fk = 8 * (lane >> 4);   // fragment row, k offset
   const int hid0 = 16 * HT * wave;
-  f4 acc[HT][4];
+  f4 acc[HT][RT];
   // one hidden layer: acc = W rows [hid0, hid0 + 16 HT) . act^T over K, act in LDS
   auto layer = [&](const __bf16* __restrict__ W, const __bf16* act, int ld, int K) {
 #pragma unroll
     for (int t = 0; t < HT; ++t)
 #pragma unroll
-      for (int p = 0; p < 4; ++p) acc[t][p] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int p = 0; p < RT; ++p) acc[t][p] = f4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 next[HT];
+#pragma unroll
+    for (int t = 0; t < HT; ++t)
+      next[t] = *reinterpret_cast<const bf16x8*>(W + (int64_t)(hid0 + 16 * t + fr) * K + fk);
     for (int k0 = 0; k0 < K; k0 += 32) {
-      bf16x8 a[HT], b[4];
+      bf16x8 a[HT], b[RT];
+#pragma unroll
+      for (int t = 0; t < HT; ++t) a[t] = next[t];
+      const int kn = min(k0 + 32, K - 32);   // (the last step loads its own again)
 #pragma unroll
       for (int t = 0; t < HT; ++t)
-        a[t] = *reinterpret_cast<const bf16x8*>(W + (int64_t)(hid0 + 16 * t + fr) * K + k0 + fk);
+        next[t] = *reinterpret_cast<const bf16x8*>(W + (int64_t)(hid0 + 16 * t + fr) * K + kn + fk);
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
+      for (int p = 0; p < RT; ++p)
         b[p] = *reinterpret_cast<const bf16x8*>(&act[(16 * p + fr) * ld + k0 + fk]);
 #pragma unroll
       for (int t = 0; t < HT; ++t)
 #pragma unroll
-        for (int p = 0; p < 4; ++p) acc[t][p] = mfma1(a[t], b[p], acc[t][p]);
+        for (int p = 0; p < RT; ++p) acc[t][p] = mfma1(a[t], b[p], acc[t][p]);
     }
   };
   // h = bf16(silu(acc + bias)) into hs[row][hid]
@@ -439,7 +499,7 @@ __global__ __launch_bounds__(INTH) void mlp_infer_bf16_kernel(
       const int h = hid0 + 16 * t + 4 * (lane >> 4);
       const f4 bv = *reinterpret_cast<const f4*>(bias + h);
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
+      for (int p = 0; p < RT; ++p)
         *reinterpret_cast<bf16x4*>(&hs[(16 * p + fr) * HLD + h]) =
             to_bf16x4(silu(acc[t][p][0] + bv[0]), silu(acc[t][p][1] + bv[1]),
                       silu(acc[t][p][2] + bv[2]), silu(acc[t][p][3] + bv[3]));
@@ -452,20 +512,28 @@ __global__ __launch_bounds__(INTH) void mlp_infer_bf16_kernel(
   __syncthreads();   // every wave has read all of h1
   to_hidden(b2);
   __syncthreads();
-  // layer 3: tile q = (o, p) of the m x 64 output, o < MT, p < 4
-  for (int q = wave; q < MT * 4; q += INW) {
-    const int o = q / 4, p = q % 4;
-    f4 c = f4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < H; k0 += 32) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(W3 + (int64_t)(16 * o + fr) * H + k0 + fk);
-      const bf16x8 b = *reinterpret_cast<const bf16x8*>(&hs[(16 * p + fr) * HLD + k0 + fk]);
-      c = mfma1(a, b, c);
-    }
-    const int row = 16 * p + fr, out0 = 16 * o + 4 * (lane >> 4);
+  // layer 3: of the MT x RT output tiles a wave takes one block of 16 outputs and
+  // RT MT / 8 of its row tiles, so its weights serve them all
+  constexpr int PT3 = RT * MT / INW;   // row tiles per wave
+  static_assert(PT3 >= 1 && RT % PT3 == 0, "the output tiles are dealt out evenly");
+  const int o = wave / (RT / PT3), p3 = wave % (RT / PT3) * PT3;
+  f4 c[PT3];
+#pragma unroll
+  for (int p = 0; p < PT3; ++p) c[p] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int k0 = 0; k0 < H; k0 += 32) {
+    const bf16x8 a = *reinterpret_cast<const bf16x8*>(W3 + (int64_t)(16 * o + fr) * H + k0 + fk);
+#pragma unroll
+    for (int p = 0; p < PT3; ++p)
+      c[p] = mfma1(a, *reinterpret_cast<const bf16x8*>(&hs[(16 * (p3 + p) + fr) * HLD + k0 + fk]), c[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < PT3; ++p) {
+    const int row = 16 * (p3 + p) + fr, out0 = 16 * o + 4 * (lane >> 4);
     if (row < rows) {
       const f4 xv = *reinterpret_cast<const f4*>(x + (r0 + row) * m + out0);
       const f4 bv = *reinterpret_cast<const f4*>(b3 + out0);
-      *reinterpret_cast<f4*>(y + (r0 + row) * m + out0) = xv + (c + bv);
+      *reinterpret_cast<f4*>(y + (r0 + row) * m + out0) = xv + (c[p] + bv);
     }
   }
 }
@@ -722,7 +790,10 @@ int thcsox_mlp_forward_bf16(thcsox_mlp_t q, const float* x_dev, float* y_dev, in
     MTRY(hipGetLastError());
     q->pb_step = q->step;
   }
-  const int64_t nblk = (batch + IRB - 1) / IRB;
+  // 128 rows per workgroup where that still fills the chip twice (it then reads the
+  // weights half as often), else 64
+  const bool big = HT >= 2 && batch >= 2 * 256 * 128;
+  const int64_t nblk = (batch + (big ? 127 : 63)) / (big ? 128 : 64);
   if (nblk > 0x7fffffffLL) return set_error(THCSOX_EINVAL, "batch too large");
   const __bf16 *W1 = q->Pb + q->oW1, *W2 = q->Pb + q->oW2, *W3 = q->Pb + q->oW3;
   const float *b1 = q->P + q->ob1, *b2 = q->P + q->ob2, *b3 = q->P + q->ob3;
@@ -730,13 +801,13 @@ int thcsox_mlp_forward_bf16(thcsox_mlp_t q, const float* x_dev, float* y_dev, in
     kernel<<<(unsigned)nblk, INTH, 0, q->stream>>>(x_dev, y_dev, batch, W1, b1, W2, b2, W3, b3);
   };
   if (MT == 4) {
-    if (HT == 4) go(mlp_infer_bf16_kernel<4, 4>);
-    else if (HT == 2) go(mlp_infer_bf16_kernel<2, 4>);
-    else go(mlp_infer_bf16_kernel<1, 4>);
+    if (HT == 4) big ? go(mlp_infer_bf16_kernel<4, 4, 128>) : go(mlp_infer_bf16_kernel<4, 4, 64>);
+    else if (HT == 2) big ? go(mlp_infer_bf16_kernel<2, 4, 128>) : go(mlp_infer_bf16_kernel<2, 4, 64>);
+    else go(mlp_infer_bf16_kernel<1, 4, 64>);
   } else {
-    if (HT == 4) go(mlp_infer_bf16_kernel<4, 2>);
-    else if (HT == 2) go(mlp_infer_bf16_kernel<2, 2>);
-    else go(mlp_infer_bf16_kernel<1, 2>);
+    if (HT == 4) big ? go(mlp_infer_bf16_kernel<4, 2, 128>) : go(mlp_infer_bf16_kernel<4, 2, 64>);
+    else if (HT == 2) big ? go(mlp_infer_bf16_kernel<2, 2, 128>) : go(mlp_infer_bf16_kernel<2, 2, 64>);
+    else go(mlp_infer_bf16_kernel<1, 2, 64>);
   }
   MTRY(hipGetLastError());
   return 0;
@@ -768,7 +839,10 @@ int thcsox_pair_gather(int m, int naux, const double* S_dev, const double* scale
   if (m <= 0 || naux <= 0 || S_dev == nullptr || scale_dev == nullptr || x_dev == nullptr ||
       npairs < 0 || (pairs_dev == nullptr && npairs > aa))
     return set_error(THCSOX_EINVAL, "bad argument");
-  pair_gather_kernel<<<blocks_for(npairs * m), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
+  if (npairs == 0) return 0;
+  const long long blocks = (npairs + PT - 1) / PT;
+  if (blocks > 0x7fffffffLL) return set_error(THCSOX_EINVAL, "too many pairs");
+  pair_gather_kernel<<<(unsigned)blocks, NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
       S_dev, m, aa, scale_dev, reinterpret_cast<const int64_t*>(pairs_dev), npairs, x_dev);
   MTRY(hipGetLastError());
   return 0;
@@ -780,7 +854,7 @@ int thcsox_pair_scatter(int m, int naux, const float* y_dev, const double* scale
   if (m <= 0 || naux <= 0 || S_dev == nullptr || scale_dev == nullptr || y_dev == nullptr)
     return set_error(THCSOX_EINVAL, "bad argument");
   const int64_t aa = (int64_t)naux * naux;
-  pair_scatter_kernel<<<blocks_for(aa * m), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
+  pair_scatter_kernel<<<(unsigned)((aa + PT - 1) / PT), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
       y_dev, m, aa, scale_dev, S_dev);
   MTRY(hipGetLastError());
   return 0;
