@@ -319,17 +319,21 @@ template <int KST> struct RBuf {
   _Float16 u[KST][RM * 64];     // [chunk][row][plane][32], 16-byte chunks permuted by sw8a
   // the lines of A computed from u: [wave][line v][plane][32 rows], the eight
   // 16-byte pieces of line v permuted by XOR with v % 8
-  _Float16 stg[RNW][16 * (KST / 2)][64];
+  _Float16 stg[RNW][16 * ((KST + 1) / 2)][64];
 };
 
 // M = MODE_F16X2, or MODE_F32: FP32 K-major rows, whose 32-wide k chunks are
 // 128 bytes as in c32, so the loads, the LDS layout and the stores are the same;
 // a chunk is eight 16x16x4 FP32 MFMAs per tile (lane group g takes k = 8 g + j,
-// 32 contiguous bytes, in both operands), and A is written unscaled as FP32.
+// 32 contiguous bytes, in both operands), and A is written unscaled as FP32.  With
+// an odd number of chunks product j takes k = 4 j + g instead, the order of the
+// general kernel (gemm_kmajor_f32) that larger n take (n = 149, naux = 797: 140 us per 2 points, 330 us through the
+// general kernel).
 template <int M, int KST>
 __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0, RBuf<KST>& b1) {
   constexpr bool F32 = M == MODE_F32;
-  constexpr int NCT = KST / 2;              // 16-column tiles per wave: 4 waves cover ldk columns
+  constexpr bool SEQ = F32 && KST % 2 == 1;
+  constexpr int NCT = (KST + 1) / 2;        // 16-column tiles per wave: 4 waves cover ldk columns
   constexpr int LDK = 32 * KST;
   constexpr int LD2 = 2 * LDK;              // halves per c32 row
   const int tid = threadIdx.x, lane = tid & 63;
@@ -362,6 +366,15 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
   auto gload = [&](int f) {
     const int t = f / (2 * KST), c = (f / 2) % KST, p = f % 2;
     const int v = 16 * (NCT * wave + t) + (lane & 15);
+    if constexpr (SEQ) {   // k = 32 c + 4 (4 p + e) + lane / 16, e < 4
+      const uint32_t gv = (uint32_t)(v * LD2 * 2 + (lane >> 4) * 4);
+      u4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[e] = __builtin_amdgcn_raw_buffer_load_b32(rG, gv, c * 128 + 64 * p + 16 * e, 0);
+      gr[t][c][p] = __builtin_bit_cast(f16x8, x);
+      return;
+    }
     const uint32_t gv = (uint32_t)((v * LD2 + (F32 ? 16 : 8) * (lane >> 4)) * 2);
     gr[t][c][p] = __builtin_bit_cast(
         f16x8, __builtin_amdgcn_raw_buffer_load_b128(rG, gv, (c * 64 + (F32 ? 8 : 32) * p) * 2, 0));
@@ -399,6 +412,16 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
   int uoff[2];
 #pragma unroll
   for (int p = 0; p < 2; ++p) uoff[p] = lr * 64 + sw8a(lr, F32 ? 2 * kc + p : 4 * p + kc) * 8;
+  auto uread = [&](const RBuf<KST>& bf, int c, int a, int p) -> f16x8 {
+    if constexpr (SEQ) {   // float lane / 16 of the 16-byte pieces 4 p .. 4 p + 3
+      f4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[e] = reinterpret_cast<const float*>(&bf.u[c][(16 * a + lr) * 64 + sw8a(lr, 4 * p + e) * 8])[kc];
+      return __builtin_bit_cast(f16x8, x);
+    }
+    return *reinterpret_cast<const f16x8*>(&bf.u[c][uoff[p] + a * 16 * 64]);
+  };
   // the two 16-row halves of a step run one after the other on the same
   // accumulators (16 x 16 NCT of A per wave)
   f4 acc[NCT];
@@ -406,15 +429,14 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
     // the fragments of chunk c + 1 are read while chunk c's MFMAs run
     f16x8 u[2], un[2];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) un[p] = *reinterpret_cast<const f16x8*>(&bf.u[0][uoff[p] + a * 16 * 64]);
+    for (int p = 0; p < 2; ++p) un[p] = uread(bf, 0, a, p);
 #pragma unroll
     for (int c = 0; c < KST; ++c) {
 #pragma unroll
       for (int p = 0; p < 2; ++p) u[p] = un[p];
       if (c + 1 < KST) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
-          un[p] = *reinterpret_cast<const f16x8*>(&bf.u[c + 1][uoff[p] + a * 16 * 64]);
+        for (int p = 0; p < 2; ++p) un[p] = uread(bf, c + 1, a, p);
       }
       if constexpr (F32) {
         auto el = [](const f16x8& lo, const f16x8& hi, int e) {
@@ -543,15 +565,25 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
     __shared__ __attribute__((aligned(16))) RBuf<K> b1;                                 \
     astage_r_body<M, K>(g, b0, b1);                                                     \
   }
+THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_1, MODE_F16X2, 1)
 THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_2, MODE_F16X2, 2)
+THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_3, MODE_F16X2, 3)
 THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_4, MODE_F16X2, 4)
+THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_5, MODE_F16X2, 5)
 THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_6, MODE_F16X2, 6)
+THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_7, MODE_F16X2, 7)
 THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_8, MODE_F16X2, 8)
+THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_9, MODE_F16X2, 9)
 THCSOX_ASTAGE_R_KERNEL(astage_f16r_kernel_10, MODE_F16X2, 10)
+THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_1, MODE_F32, 1)
 THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_2, MODE_F32, 2)
+THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_3, MODE_F32, 3)
 THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_4, MODE_F32, 4)
+THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_5, MODE_F32, 5)
 THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_6, MODE_F32, 6)
+THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_7, MODE_F32, 7)
 THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_8, MODE_F32, 8)
+THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_9, MODE_F32, 9)
 THCSOX_ASTAGE_R_KERNEL(astage_f32r_kernel_10, MODE_F32, 10)
 #undef THCSOX_ASTAGE_R_KERNEL
 
@@ -570,23 +602,30 @@ hipError_t r_launch(void (*kernel)(AStageArgs), const AStageArgs& g, hipStream_t
 
 }  // namespace
 
+// the register-resident kernels serve both modes at the same sizes
 hipError_t astage_f16(const AStageArgs& g, hipStream_t s) {
   if (g.naux <= 0 || g.n <= 0 || g.nsets <= 0) return hipSuccess;
-  if (g.ldk % (2 * AKC) != 0 || g.ldk < g.n) return hipErrorInvalidValue;
+  if (g.ldk % AKC != 0 || g.ldk < g.n) return hipErrorInvalidValue;
   // 32-bit row indices and buffer offsets inside one tile (c32 rows of 4 ldk bytes)
   if ((int64_t)g.naux * g.ldk + AM > 0x7fffffffLL ||
       (int64_t)(AM + 2 * g.n) * g.ldk * 4 > 0x7fffffffLL || (int64_t)320 * g.ldk * 4 > 0x7fffffffLL)
     return hipErrorInvalidValue;
   // G in registers while ldk <= 320 and the byte offsets of A's rows (v, P) fit in
   // 31 bits (the stores address a set from the step's row piece)
-  if ((int64_t)g.n * g.naux * g.ldk * 4 < 0x7fffffffLL) switch (g.ldk) {
-    case 64: return r_launch(astage_f16r_kernel_2, g, s);
-    case 128: return r_launch(astage_f16r_kernel_4, g, s);
-    case 192: return r_launch(astage_f16r_kernel_6, g, s);
-    case 256: return r_launch(astage_f16r_kernel_8, g, s);
-    case 320: return r_launch(astage_f16r_kernel_10, g, s);
-    default: break;
+  if (astage_f32_fits(g.n, g.naux, g.ldk)) switch (g.ldk / AKC) {
+    case 1: return r_launch(astage_f16r_kernel_1, g, s);
+    case 2: return r_launch(astage_f16r_kernel_2, g, s);
+    case 3: return r_launch(astage_f16r_kernel_3, g, s);
+    case 4: return r_launch(astage_f16r_kernel_4, g, s);
+    case 5: return r_launch(astage_f16r_kernel_5, g, s);
+    case 6: return r_launch(astage_f16r_kernel_6, g, s);
+    case 7: return r_launch(astage_f16r_kernel_7, g, s);
+    case 8: return r_launch(astage_f16r_kernel_8, g, s);
+    case 9: return r_launch(astage_f16r_kernel_9, g, s);
+    default: return r_launch(astage_f16r_kernel_10, g, s);
   }
+  // the streaming kernel takes an even number of k chunks
+  if (g.ldk % (2 * AKC) != 0) return hipErrorInvalidValue;
   if (g.n <= 128) return a_launch<2>(astage_f16_kernel_2, g, s);
   if (g.n <= 192) return a_launch<3>(astage_f16_kernel_3, g, s);
   if (g.n <= 256) return a_launch<4>(astage_f16_kernel_4, g, s);
@@ -594,18 +633,23 @@ hipError_t astage_f16(const AStageArgs& g, hipStream_t s) {
 }
 
 bool astage_f32_fits(int n, int naux, int ldk) {
-  return n > 0 && naux > 0 && ldk >= n && ldk % 64 == 0 && ldk <= 320 &&
+  return n > 0 && naux > 0 && ldk >= n && ldk % 32 == 0 && ldk <= 320 &&
          (int64_t)n * naux * ldk * 4 < 0x7fffffffLL;
 }
 
 hipError_t astage_f32(const AStageArgs& g, hipStream_t s) {
   if (g.naux <= 0 || g.n <= 0 || g.nsets <= 0) return hipSuccess;
   if (!astage_f32_fits(g.n, g.naux, g.ldk)) return hipErrorInvalidValue;
-  switch (g.ldk) {
-    case 64: return r_launch(astage_f32r_kernel_2, g, s);
-    case 128: return r_launch(astage_f32r_kernel_4, g, s);
-    case 192: return r_launch(astage_f32r_kernel_6, g, s);
-    case 256: return r_launch(astage_f32r_kernel_8, g, s);
+  switch (g.ldk / AKC) {
+    case 1: return r_launch(astage_f32r_kernel_1, g, s);
+    case 2: return r_launch(astage_f32r_kernel_2, g, s);
+    case 3: return r_launch(astage_f32r_kernel_3, g, s);
+    case 4: return r_launch(astage_f32r_kernel_4, g, s);
+    case 5: return r_launch(astage_f32r_kernel_5, g, s);
+    case 6: return r_launch(astage_f32r_kernel_6, g, s);
+    case 7: return r_launch(astage_f32r_kernel_7, g, s);
+    case 8: return r_launch(astage_f32r_kernel_8, g, s);
+    case 9: return r_launch(astage_f32r_kernel_9, g, s);
     default: return r_launch(astage_f32r_kernel_10, g, s);
   }
 }

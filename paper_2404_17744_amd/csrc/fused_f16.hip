@@ -122,7 +122,7 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   const int p_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)vr * npair / f.vsplit));
   const int p_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(vr + 1) * npair / f.vsplit));
   const int npr = p_hi - p_lo;
-  const int kst = ldk / KC;
+  const int kst = (n + KC - 1) / KC;   // chunks with any k < n (rows are zero from n to ldk)
   const int ld2 = 2 * ldk;   // halves per c32 row
   const int rows_r = min(TT, naux - R0), rows_p = min(TT, naux - P0);
 

@@ -49,7 +49,8 @@ hipError_t gemm_kmajor_bf3(const GemmKArgs& g, hipStream_t s);
 // r * 2 ldk + (k / 32) * 64 + 32 p + k % 32): U rows (P, q), Gb rows (set, v)
 // (G(beta - tau)^T, gb_set = n * 2 ldk halves apart), A rows (set, v, P) with
 // k = q (a_set halves apart).  scale[set] = 2^-ilogb(amax[set]); amax[set] must
-// bound max |A| / 2^14 (see ascale_bound).  ldk must be a multiple of 64.
+// bound max |A| / 2^14 (see ascale_bound).  ldk must be a multiple of 32, beyond the
+// sizes of astage_f32_fits of 64.
 struct AStageArgs {
   int naux, n, ldk, nsets;
   const void* U;
@@ -60,7 +61,7 @@ struct AStageArgs {
 hipError_t astage_f16(const AStageArgs& a, hipStream_t s);
 // The same stage in the FP32 mode (amax unused): U, Gb and A are FP32 K-major rows of
 // ldk elements (A passed as the address of its FP32 array; gb_set and a_set still
-// count halves), A written unscaled.  Only for ldk a multiple of 64 up to 320 with
+// count halves), A written unscaled.  Only for ldk a multiple of 32 up to 320 with
 // A's byte offsets in 31 bits (astage_f32_fits); otherwise hipErrorInvalidValue
 // (use gemm_kmajor_f32).
 bool astage_f32_fits(int n, int naux, int ldk);
