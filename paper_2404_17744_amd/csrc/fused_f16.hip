@@ -17,7 +17,8 @@
 // two v at a time: the k loop of a pair forms B and C for both v at once, so
 // the v-independent panels (G rows R, GX rows P) are loaded once per pair and
 // feed four products.  Four waves (one per SIMD) in a 2 x 2 arrangement each
-// own 64 x 64 of the tile: the four accumulator sets B1, B2, C1, C2 (256
+// own 64 x 64 of the tile (16 x 16 tiles alternating between the waves of a row and
+// of a column): the four accumulator sets B1, B2, C1, C2 (256
 // registers) live in the matrix-core registers (AGPRs), fragments in the
 // ordinary ones.  The partial sum of D (FP32, at most 8 v) lives in LDS, one
 // private 16-byte slot per lane and MFMA tile, and is updated once per pair:
@@ -37,6 +38,8 @@
 // fragment is read one phase ahead of its products.  The first chunk of a pair
 // starts the accumulators from zero inside the MFMA (no register clearing).
 // Past the last chunk the loads repeat it (never used).
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "mfma.hpp"
 #include "panel.hpp"
@@ -69,51 +72,22 @@ __device__ __forceinline__ void vm_lds_barrier() {
   __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// M = MODE_F16X2 or MODE_F32.  sB: G, A_v1, A_v2; sC: GX, U_v1, U_v2; sD: the
-// partial sum of D.
-template <int M>
-__device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Half& sC, f4* sD) {
+// One tile's range of pairs.  M = MODE_F16X2 or MODE_F32.  sB: G, A_v1, A_v2; sC: GX,
+// U_v1, U_v2; sD: the partial sum of D.  Each wave forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the
+// rows R of the workgroup's tile beyond 32 TI and the columns P beyond 32 TJ lie past
+// naux and are neither loaded nor multiplied (a D element's products and their order
+// do not depend on TI and TJ).
+template <int M, int TI, int TJ>
+__device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& sC, f4* sD, int set,
+                                           int z, int R0, int P0) {
   constexpr bool F32 = M == MODE_F32;
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  // (the compiler must not merge the seven forms' address arithmetic above their branch)
+  __asm__ volatile("" : "+v"(tid), "+s"(set), "+s"(z), "+s"(R0), "+s"(P0));
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
   const int naux = f.naux, n = f.n, ldk = f.ldk;
-
-  // tile and pair range: XCD-aware order (workgroup b runs on XCD b mod 8; each
-  // XCD owns the partial slots z = xcd, xcd + 8, ..., a block of consecutive
-  // pair ranges, and walks the tiles of one slot in bands of two R blocks, P by
-  // P with R fastest, so its resident workgroups share panels in its L2).  With
-  // symmetric D only the tiles on or above the diagonal are walked (nb (nb + 1)
-  // / 2 of them; the grid has nb^2 per slot, the rest exit at once).  The
-  // integer divisions run on the vector unit; readfirstlane marks their results
-  // uniform so that buffer resources and offsets stay scalar.
-  const int nb = (naux + TT - 1) / TT;
-  const int set = blockIdx.y;
-  const bool symm = f.sym != nullptr && f.sym[set] != 0;
-  const int ntl = symm ? nb * (nb + 1) / 2 : nb * nb;
-  const int b = blockIdx.x;
-  const int xcd = b % NXCD16, local = b / NXCD16;
-  if (local >= ntl * (f.vsplit / NXCD16)) return;
-  const int z = __builtin_amdgcn_readfirstlane(xcd + NXCD16 * (local / ntl));
-  int t = local % ntl, r0 = 0;
-  for (;;) {   // the band of rows r0, r0 + 1 (one row at the end when nb is odd)
-    const int rows = min(2, nb - r0);
-    const int cnt = symm ? (rows == 2 ? 2 * (nb - r0) - 1 : nb - r0) : rows * nb;
-    if (t < cnt) break;
-    t -= cnt;
-    r0 += 2;
-  }
-  int rb, pb;
-  if (symm) {   // (r0, r0), then (r0, p), (r0 + 1, p) for p > r0
-    rb = t == 0 ? r0 : r0 + (t - 1) % 2;
-    pb = t == 0 ? r0 : r0 + 1 + (t - 1) / 2;
-  } else {
-    const int rows = min(2, nb - r0);
-    rb = r0 + t % rows;
-    pb = t / rows;
-  }
-  const int P0 = __builtin_amdgcn_readfirstlane(pb * TT);
-  const int R0 = __builtin_amdgcn_readfirstlane(rb * TT);
 
   // pair range: XCD x owns the consecutive ranges x q .. x q + q - 1
   // (q = vsplit / 8); range r is pairs [r np / vsplit, (r + 1) np / vsplit)
@@ -164,9 +138,9 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int slab = (wave + NW * j) * 8 * 64;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rG, &sB.s[0][slab], 16, dR[j], so, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rA1, &sB.s[1][slab], 16, dR[j], so, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rA2, &sB.s[2][slab], 16, dR[j], so, 0, 0);
+      if (j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rG, &sB.s[0][slab], 16, dR[j], so, 0, 0);
+      if (j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA1, &sB.s[1][slab], 16, dR[j], so, 0, 0);
+      if (j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA2, &sB.s[2][slab], 16, dR[j], so, 0, 0);
     }
   };
   auto dmaC = [&](int k0) {
@@ -174,9 +148,9 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int slab = (wave + NW * j) * 8 * 64;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, &sC.s[0][slab], 16, dR[j], so, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rU1, &sC.s[1][slab], 16, dU[j], so, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rU2, &sC.s[2][slab], 16, dU[j], so, 0, 0);
+      if (j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, &sC.s[0][slab], 16, dR[j], so, 0, 0);
+      if (j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rU1, &sC.s[1][slab], 16, dU[j], so, 0, 0);
+      if (j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rU2, &sC.s[2][slab], 16, dU[j], so, 0, 0);
     }
   };
 
@@ -185,55 +159,56 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   // assignment of the chunk's 32 k to its eight MFMAs j and four lane groups serves
   // when both operands use it: lane group g takes k = 8 g + j, two 16-byte reads
   // at logical chunks 2 g and 2 g + 1 (in "planes" 0 and 1 below).  sw8 depends on
-  // r mod 16 only, so the rows of tile t are 16 t * 64 halves further.
+  // r mod 16 only, so the rows of tile t are 32 t * 64 halves further (the tiles of
+  // the two waves of a row or column alternate, so both waves work in a short tile).
   const int lr = lane & 15, kc = lane >> 4;
-  const int rr = wr * 64 + lr, rc = wc * 64 + lr;
+  const int rr = wr * 16 + lr, rc = wc * 16 + lr;
   const int c0 = F32 ? 2 * kc : kc, c1 = F32 ? 2 * kc + 1 : 4 + kc;
   const int fr0 = rr * 64 + sw8(rr, c0) * 8, fr1 = rr * 64 + sw8(rr, c1) * 8;
   const int fc0 = rc * 64 + sw8(rc, c0) * 8, fc1 = rc * 64 + sw8(rc, c1) * 8;
   // fragments of one half stage: the shared operand s (G or GX) and the per-v
   // operands m1, m2 (A_v or U_v), [plane][tile]
-  struct Frags { f16x8 s[2][4], m1[2][4], m2[2][4]; };
-  Frags fb, fc;
+  struct FragsB { f16x8 s[2][TI], m1[2][TJ], m2[2][TJ]; } fb;
+  struct FragsC { f16x8 s[2][TJ], m1[2][TI], m2[2][TI]; } fc;
   auto rd = [&](const _Float16* base, int off, int t) {
-    return *reinterpret_cast<const f16x8*>(base + off + t * 16 * 64);
+    return *reinterpret_cast<const f16x8*>(base + off + t * 32 * 64);
   };
-  auto readB = [&](Frags& fr) {   // G (R side), A_v1, A_v2 (P side)
+  auto readB = [&](FragsB& fr) {   // G (R side), A_v1, A_v2 (P side)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      fr.s[0][t] = rd(sB.s[0], fr0, t);  fr.s[1][t] = rd(sB.s[0], fr1, t);
-      fr.m1[0][t] = rd(sB.s[1], fc0, t); fr.m1[1][t] = rd(sB.s[1], fc1, t);
-      fr.m2[0][t] = rd(sB.s[2], fc0, t); fr.m2[1][t] = rd(sB.s[2], fc1, t);
+      if (t < TI) { fr.s[0][t] = rd(sB.s[0], fr0, t);  fr.s[1][t] = rd(sB.s[0], fr1, t); }
+      if (t < TJ) { fr.m1[0][t] = rd(sB.s[1], fc0, t); fr.m1[1][t] = rd(sB.s[1], fc1, t); }
+      if (t < TJ) { fr.m2[0][t] = rd(sB.s[2], fc0, t); fr.m2[1][t] = rd(sB.s[2], fc1, t); }
     }
   };
-  auto readC = [&](Frags& fr) {   // GX (P side), U_v1, U_v2 (R side)
+  auto readC = [&](FragsC& fr) {   // GX (P side), U_v1, U_v2 (R side)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      fr.s[0][t] = rd(sC.s[0], fc0, t);  fr.s[1][t] = rd(sC.s[0], fc1, t);
-      fr.m1[0][t] = rd(sC.s[1], fr0, t); fr.m1[1][t] = rd(sC.s[1], fr1, t);
-      fr.m2[0][t] = rd(sC.s[2], fr0, t); fr.m2[1][t] = rd(sC.s[2], fr1, t);
+      if (t < TJ) { fr.s[0][t] = rd(sC.s[0], fc0, t);  fr.s[1][t] = rd(sC.s[0], fc1, t); }
+      if (t < TI) { fr.m1[0][t] = rd(sC.s[1], fr0, t); fr.m1[1][t] = rd(sC.s[1], fr1, t); }
+      if (t < TI) { fr.m2[0][t] = rd(sC.s[2], fr0, t); fr.m2[1][t] = rd(sC.s[2], fr1, t); }
     }
   };
 
   // accumulators [ti][tj]: rows R of tile ti, columns P of tile tj (cleared once
   // here; each pair then starts them from zero inside its first MFMAs)
-  f4 B1[4][4], B2[4][4], C1[4][4], C2[4][4];
+  f4 B1[TI][TJ], B2[TI][TJ], C1[TI][TJ], C2[TI][TJ];
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti)
+  for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) B1[ti][tj] = B2[ti][tj] = C1[ti][tj] = C2[ti][tj] = zero;
+    for (int tj = 0; tj < TJ; ++tj) B1[ti][tj] = B2[ti][tj] = C1[ti][tj] = C2[ti][tj] = zero;
   // FP32: operand j (k = 8 g + j) of a fragment pair
   auto el = [](const f16x8& lo, const f16x8& hi, int j) {
     return j < 4 ? __builtin_bit_cast(f4, lo)[j] : __builtin_bit_cast(f4, hi)[j - 4];
   };
   // B products: acc[ti][tj] += G[ti] . A_m[tj] (fp16x2: planes x1 y0 + x0 y1 + x0 y0;
   // FP32: eight 16x16x4 products, the two v interleaved)
-  auto mfmaB = [&](const Frags& fr, bool first) {
+  auto mfmaB = [&](const FragsB& fr, bool first) {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj) {
+      for (int tj = 0; tj < TJ; ++tj) {
         if constexpr (F32) {
           f4 a1 = first ? zero : B1[ti][tj];
           f4 a2 = first ? zero : B2[ti][tj];
@@ -258,11 +233,11 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
       }
   };
   // C products: acc[ti][tj] += U_m[ti] . GX[tj]
-  auto mfmaC = [&](const Frags& fr, bool first) {
+  auto mfmaC = [&](const FragsC& fr, bool first) {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj) {
+      for (int tj = 0; tj < TJ; ++tj) {
         if constexpr (F32) {
           f4 a1 = first ? zero : C1[ti][tj];
           f4 a2 = first ? zero : C2[ti][tj];
@@ -291,38 +266,38 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   f4* const Dw = sD + wave * 16 * 64 + lane;
   auto dzero = [&]() {
 #pragma unroll
-    for (int t = 0; t < 16; ++t) Dw[t * 64] = zero;
+    for (int t = 0; t < TI * TJ; ++t) Dw[t * 64] = zero;
   };
   auto dupdate = [&]() {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj) {
-        f4 d = Dw[(ti * 4 + tj) * 64];
+      for (int tj = 0; tj < TJ; ++tj) {
+        f4 d = Dw[(ti * TJ + tj) * 64];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           d[r] = fmaf(B1[ti][tj][r], C1[ti][tj][r], d[r]);
           d[r] = fmaf(B2[ti][tj][r], C2[ti][tj][r], d[r]);
         }
-        Dw[(ti * 4 + tj) * 64] = d;
+        Dw[(ti * TJ + tj) * 64] = d;
       }
   };
   // D tile -> partial tile z (FP32 store, or FP64 add unless first): thread t
   // takes column P0 + t % 128 and rows R0 + t / 128 + 2 i, reading each element
   // from the LDS slot of the lane that formed it (lane 16 (R % 16 / 4) + P % 16
-  // of wave 2 (R / 64) + P / 64, tile (R % 64 / 16, P % 64 / 16), element R % 4),
+  // of wave 2 (R / 16 % 2) + P / 16 % 2, tile (R / 32, P / 32), element R % 4),
   // so the global writes are coalesced rows.  Barriers before (other waves'
   // slots) and after (the slots may be cleared next).
   auto flush = [&](bool first) {
     __syncthreads();
     const float* sDf = reinterpret_cast<const float*>(sD);
     const int Pt = tid & (TT - 1), P = P0 + Pt;
-    const int pslot = (Pt >> 6) * 16 * 64 + ((Pt >> 4) & 3) * 64 + (Pt & 15);
+    const int pslot = ((Pt >> 4) & 1) * 16 * 64 + (Pt >> 5) * 64 + (Pt & 15);
     const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
     for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
       const int R = R0 + Rt;
       if (R < naux && P < naux) {
-        const int slot = pslot + (Rt >> 6) * 2 * 16 * 64 + ((Rt >> 4) & 3) * 4 * 64 + ((Rt >> 2) & 3) * 16;
+        const int slot = pslot + ((Rt >> 4) & 1) * 2 * 16 * 64 + (Rt >> 5) * TJ * 64 + ((Rt >> 2) & 3) * 16;
         const float v = sDf[slot * 4 + (Rt & 3)];
         const int64_t o = zo + (int64_t)R * naux;
         if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
@@ -358,10 +333,12 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   // meanwhile, while loads issued late have less time to land (measured at n =
   // 300: fp16x2, 96 MFMAs per phase, fastest at 3 of 1, 2, 3, 4, 8; FP32, 256
   // MFMAs per phase, at 16 of 10, 12, 16, 21)
-  constexpr int MPL = F32 ? 16 : 3;
-  auto spread = [&]() {
+  constexpr int NM = (F32 ? 16 : 6) * TI * TJ;   // MFMAs per phase
+  auto spread = [&](auto loads) {
+    constexpr int L = decltype(loads)::value;
+    constexpr int MPL = F32 ? (NM / L < 16 ? NM / L : 16) : (NM / L < 3 ? NM / L : 3);
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
+    for (int i = 0; i < L; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);     // one memory instruction
       __builtin_amdgcn_sched_group_barrier(0x008, MPL, 0);   // MPL MFMAs
     }
@@ -371,13 +348,13 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
     dmaB(ck * KC);
     readC(fc);
     mfmaB(fb, first);
-    spread();
+    spread(std::integral_constant<int, TI + 2 * TJ>{});
     vm_lds_barrier();
     dmaC(ck * KC);
     advance();
     readB(fb);
     mfmaC(fc, first);
-    spread();
+    spread(std::integral_constant<int, 2 * TI + TJ>{});
   };
   int done = 0;
   for (int pr = 0; pr < npr; ++pr) {
@@ -393,6 +370,65 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   // the last (repeated) memory-to-LDS loads land before the workgroup may end
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   flush(done <= FLUSH_PAIRS);   // also writes zeros for an empty range
+}
+
+template <int M>
+__device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Half& sC, f4* sD) {
+  const int naux = f.naux;
+
+  // tile and pair range: XCD-aware order (workgroup b runs on XCD b mod 8; each
+  // XCD owns the partial slots z = xcd, xcd + 8, ..., a block of consecutive
+  // pair ranges, and walks the tiles of one slot in bands of two R blocks, P by
+  // P with R fastest, so its resident workgroups share panels in its L2).  With
+  // symmetric D only the tiles on or above the diagonal are walked (nb (nb + 1)
+  // / 2 of them; the grid has nb^2 per slot, the rest exit at once).  The
+  // integer divisions run on the vector unit; readfirstlane marks their results
+  // uniform so that buffer resources and offsets stay scalar.
+  const int nb = (naux + TT - 1) / TT;
+  const int set = blockIdx.y;
+  const bool symm = f.sym != nullptr && f.sym[set] != 0;
+  const int ntl = symm ? nb * (nb + 1) / 2 : nb * nb;
+  const int b = blockIdx.x;
+  const int xcd = b % NXCD16, local = b / NXCD16;
+  if (local >= ntl * (f.vsplit / NXCD16)) return;
+  const int z = __builtin_amdgcn_readfirstlane(xcd + NXCD16 * (local / ntl));
+  int t = local % ntl, r0 = 0;
+  for (;;) {   // the band of rows r0, r0 + 1 (one row at the end when nb is odd)
+    const int rows = min(2, nb - r0);
+    const int cnt = symm ? (rows == 2 ? 2 * (nb - r0) - 1 : nb - r0) : rows * nb;
+    if (t < cnt) break;
+    t -= cnt;
+    r0 += 2;
+  }
+  int rb, pb;
+  if (symm) {   // (r0, r0), then (r0, p), (r0 + 1, p) for p > r0
+    rb = t == 0 ? r0 : r0 + (t - 1) % 2;
+    pb = t == 0 ? r0 : r0 + 1 + (t - 1) / 2;
+  } else {
+    const int rows = min(2, nb - r0);
+    rb = r0 + t % rows;
+    pb = t / rows;
+  }
+  const int P0 = __builtin_amdgcn_readfirstlane(pb * TT);
+  const int R0 = __builtin_amdgcn_readfirstlane(rb * TT);
+
+  // the last block of naux % 128 columns or rows forms only the 32-wide strips that hold
+  // a THC point (the corner tile is treated as a column).  Against full 128 x 128 products
+  // everywhere: n = 149, naux = 797 (29 of the last 128), general, FP32: 696 -> 590 us a
+  // tau point; n = 300, naux = 1800 (8 of 128), symmetric, fp16x2: 1927 -> 1867 us, where
+  // the short tiles wait for memory (a short tile takes 0.75 of a full one's time)
+  const int tj = (naux - P0 + 31) / 32, ti = (naux - R0 + 31) / 32;
+  if (tj < 4) {
+    if (tj == 1) fused_tile<M, 4, 1>(f, sB, sC, sD, set, z, R0, P0);
+    else if (tj == 2) fused_tile<M, 4, 2>(f, sB, sC, sD, set, z, R0, P0);
+    else fused_tile<M, 4, 3>(f, sB, sC, sD, set, z, R0, P0);
+  } else if (ti < 4) {
+    if (ti == 1) fused_tile<M, 1, 4>(f, sB, sC, sD, set, z, R0, P0);
+    else if (ti == 2) fused_tile<M, 2, 4>(f, sB, sC, sD, set, z, R0, P0);
+    else fused_tile<M, 3, 4>(f, sB, sC, sD, set, z, R0, P0);
+  } else {
+    fused_tile<M, 4, 4>(f, sB, sC, sD, set, z, R0, P0);
+  }
 }
 
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
