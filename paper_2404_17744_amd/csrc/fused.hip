@@ -14,9 +14,10 @@
 // of four panels (G, A_v, U_v, GX: 64 rows of 128 bytes each, 32 KiB) per stage, one
 // stage ahead in the other of two buffers, so that two workgroups share a compute
 // unit: each SIMD has a wave of the other one to run while this one waits at its
-// barrier (one a stage).  A wave owns 32 x 32 of the tile: 32 products a stage against
+// barrier (one a stage).  A wave owns 32 x 32 of the tile (16 x 16 tiles alternating
+// between the waves): 32 products a stage against
 // 16 fragment reads.  Matrix cores busy 81 % of the cycles
-// (counters); n = 200, naux = 1100, symmetric: 1.88 ms a tau point (52 TFLOP/s
+// (counters); n = 200, naux = 1100, symmetric: 1.78 ms a tau point (55 TFLOP/s
 // algorithmic, 72 is what a large library product reaches), 3.34 with panels staged
 // through registers and one workgroup of 136 KiB per unit.
 #include <algorithm>
@@ -40,30 +41,14 @@ struct Stage64 {
 };
 __device__ __forceinline__ int sw64(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-__global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
-  __shared__ __attribute__((aligned(16))) Stage64 b0;
-  __shared__ __attribute__((aligned(16))) Stage64 b1;
+// One tile's range of v.  Each wave forms TI x TJ tiles of 16 x 16 out of its 2 x 2: rows
+// beyond 32 TI and columns beyond 32 TJ lie past naux.
+template <int TI, int TJ>
+__device__ __forceinline__ void fused_f64_tile(const FusedArgs& f, Stage64& b0, Stage64& b1, int set,
+                                               int z, int R0, int P0) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
-  // XCD-aware placement.  Workgroups are dealt round-robin to the XCDs, so
-  // workgroup b runs on XCD b % NXCD.  Each XCD takes vsplit / NXCD partial
-  // slots z = xcd, xcd + NXCD, ... (a block of consecutive v ranges, below)
-  // for every tile, and walks the tiles in bands of BAND R blocks, P block by P
-  // block: the workgroups resident on one XCD at a time share the U_v and A_v
-  // panels through that XCD's L2.
-  const int nb = (f.naux + TD - 1) / TD, tiles = nb * nb;
-  const int b = blockIdx.x;
-  const int xcd = b % NXCD, local = b / NXCD;
-  const int z = xcd + NXCD * (local / tiles);
-  const int to = local % tiles;
-  const int rb0 = to / (BAND * nb) * BAND, bh = min(BAND, nb - rb0);
-  const int within = to - rb0 * nb;
-  const int P0 = __builtin_amdgcn_readfirstlane((within / bh) * TD);
-  const int R0 = __builtin_amdgcn_readfirstlane((rb0 + within % bh) * TD);
-  // symmetric D: a tile wholly below the diagonal is the mirror of one above it
-  const int set = blockIdx.y;
-  if (f.sym != nullptr && f.sym[set] != 0 && R0 >= P0 + TD) return;
   // v range: XCD x owns the consecutive ranges x q .. x q + q - 1 (q = vsplit / NXCD),
   // and the ranges split n as evenly as floor division allows, so every XCD gets
   // the same number of v to within one; range r is [r n / vsplit, (r + 1) n / vsplit)
@@ -105,10 +90,10 @@ __global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int slab = (wave + 4 * j) * 8 * DK;
-      dma16_untracked(rG, lds_addr(&s.g[slab]), dR[j], so);
-      dma16_untracked(rA, lds_addr(&s.a[slab]), dR[j], so);
-      dma16_untracked(rU, lds_addr(&s.u[slab]), dU[j], so);
-      dma16_untracked(rX, lds_addr(&s.x[slab]), dR[j], so);
+      if (j < TI) dma16_untracked(rG, lds_addr(&s.g[slab]), dR[j], so);
+      if (j < TJ) dma16_untracked(rA, lds_addr(&s.a[slab]), dR[j], so);
+      if (j < TI) dma16_untracked(rU, lds_addr(&s.u[slab]), dU[j], so);
+      if (j < TJ) dma16_untracked(rX, lds_addr(&s.x[slab]), dR[j], so);
     }
     if (++lk == kst) {
       lk = 0;
@@ -126,25 +111,24 @@ __global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
     const d2 hi = *reinterpret_cast<const d2*>(p + row0 * DK + o1);
     o[0] = lo[0]; o[1] = lo[1]; o[2] = hi[0]; o[3] = hi[1];
   };
-  d4 accB[2][2], accC[2][2], accD[2][2];
+  d4 accB[TI][TJ], accC[TI][TJ], accD[TI][TJ];
   const d4 zero = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int ti = 0; ti < 2; ++ti)
+  for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj) accB[ti][tj] = accC[ti][tj] = accD[ti][tj] = zero;
-  auto product = [&](d4 (&acc)[2][2], const double* rows, const double* cols) {
-    double r[2][4], c[2][4];
+    for (int tj = 0; tj < TJ; ++tj) accB[ti][tj] = accC[ti][tj] = accD[ti][tj] = zero;
+  auto product = [&](d4 (&acc)[TI][TJ], const double* rows, const double* cols) {
+    double r[TI][4], c[TJ][4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      frag(rows, 32 * wr + 16 * t, r[t]);
-      frag(cols, 32 * wc + 16 * t, c[t]);
-    }
+    for (int t = 0; t < TI; ++t) frag(rows, 16 * wr + 32 * t, r[t]);
+#pragma unroll
+    for (int t = 0; t < TJ; ++t) frag(cols, 16 * wc + 32 * t, c[t]);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
+      for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = mfma1(r[ti][s], c[tj][s], acc[ti][tj]);
+        for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma1(r[ti][s], c[tj][s], acc[ti][tj]);
   };
   // (the loads are issued in inline assembly: left to the compiler, a read of one
   // buffer waits for the loads just issued into the other)
@@ -163,9 +147,9 @@ __global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
     if (++ks == kst) {   // all k of this v done: D += B o C
       ks = 0;
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
+      for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < 2; ++tj) {
+        for (int tj = 0; tj < TJ; ++tj) {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             accD[ti][tj][r] = fma(accB[ti][tj][r], accC[ti][tj][r], accD[ti][tj][r]);
@@ -181,15 +165,44 @@ __global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
   // the partial tile (zeros for an empty v range)
   double* D = f.Dpart + set * f.d_set + (int64_t)z * f.naux * f.naux;
 #pragma unroll
-  for (int ti = 0; ti < 2; ++ti)
+  for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
+    for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int R = R0 + 32 * wr + 16 * ti + out_row<MODE_F64>(lane, r);
-        const int P = P0 + 32 * wc + 16 * tj + lr;
+        const int R = R0 + 16 * wr + 32 * ti + out_row<MODE_F64>(lane, r);
+        const int P = P0 + 16 * wc + 32 * tj + lr;
         if (R < f.naux && P < f.naux) D[(int64_t)R * f.naux + P] = accD[ti][tj][r];
       }
+}
+
+__global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
+  __shared__ __attribute__((aligned(16))) Stage64 b0;
+  __shared__ __attribute__((aligned(16))) Stage64 b1;
+  // XCD-aware placement.  Workgroups are dealt round-robin to the XCDs, so
+  // workgroup b runs on XCD b % NXCD.  Each XCD takes vsplit / NXCD partial
+  // slots z = xcd, xcd + NXCD, ... (a block of consecutive v ranges, below)
+  // for every tile, and walks the tiles in bands of BAND R blocks, P block by P
+  // block: the workgroups resident on one XCD at a time share the U_v and A_v
+  // panels through that XCD's L2.
+  const int nb = (f.naux + TD - 1) / TD, tiles = nb * nb;
+  const int b = blockIdx.x;
+  const int xcd = b % NXCD, local = b / NXCD;
+  const int z = xcd + NXCD * (local / tiles);
+  const int to = local % tiles;
+  const int rb0 = to / (BAND * nb) * BAND, bh = min(BAND, nb - rb0);
+  const int within = to - rb0 * nb;
+  const int P0 = __builtin_amdgcn_readfirstlane((within / bh) * TD);
+  const int R0 = __builtin_amdgcn_readfirstlane((rb0 + within % bh) * TD);
+  // symmetric D: a tile wholly below the diagonal is the mirror of one above it
+  const int set = blockIdx.y;
+  if (f.sym != nullptr && f.sym[set] != 0 && R0 >= P0 + TD) return;
+  // the last block of columns or rows forms only the 32-wide strips that hold a THC point
+  // (the corner tile is treated as a column): 1.88 -> 1.78 ms at n = 200, naux = 1100 (12 of
+  // the last 64)
+  if (f.naux - P0 <= 32) fused_f64_tile<2, 1>(f, b0, b1, set, z, R0, P0);
+  else if (f.naux - R0 <= 32) fused_f64_tile<1, 2>(f, b0, b1, set, z, R0, P0);
+  else fused_f64_tile<2, 2>(f, b0, b1, set, z, R0, P0);
 }
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
