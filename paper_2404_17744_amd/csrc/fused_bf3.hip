@@ -59,49 +59,20 @@ __device__ __forceinline__ void bf3_vm_lds_barrier() {
   __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void fused_bf3_kernel(FusedArgs f) {
-  __shared__ __attribute__((aligned(16))) Half3 sB;   // G, A_v
-  __shared__ __attribute__((aligned(16))) Half3 sC;   // GX, U_v
-  __shared__ __attribute__((aligned(16))) f4 sD[NW * 16 * 64];
-  const int tid = threadIdx.x, lane = tid & 63;
+// One tile's range of v.  sB: G, A_v; sC: GX, U_v; sD: the partial sum of D.  Each wave
+// forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the rows R of the workgroup's tile
+// beyond 32 TI and the columns P beyond 32 TJ lie past naux and are neither loaded nor
+// multiplied (a D element's products and their order do not depend on TI and TJ).
+template <int TI, int TJ>
+__device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Half3& sC, f4* sD, int set,
+                                               int z, int R0, int P0) {
+  int tid = threadIdx.x;
+  // (the compiler must not merge the seven forms' address arithmetic above their branch)
+  __asm__ volatile("" : "+v"(tid), "+s"(set), "+s"(z), "+s"(R0), "+s"(P0));
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
   const int naux = f.naux, n = f.n, ldk = f.ldk;
-
-  // tile and v range: XCD-aware order (workgroup b runs on XCD b mod 8; each XCD
-  // owns the partial slots z = xcd, xcd + 8, ..., a block of consecutive v
-  // ranges, and walks the tiles of one slot in bands of two R blocks, P by P
-  // with R fastest, so its resident workgroups share panels in its L2).  With
-  // symmetric D only the tiles on or above the diagonal are walked.  The integer
-  // divisions run on the vector unit; readfirstlane marks their results uniform.
-  const int nb = (naux + TT - 1) / TT;
-  const int set = blockIdx.y;
-  const bool symm = f.sym != nullptr && f.sym[set] != 0;
-  const int ntl = symm ? nb * (nb + 1) / 2 : nb * nb;
-  const int b = blockIdx.x;
-  const int xcd = b % NXCD, local = b / NXCD;
-  if (local >= ntl * (f.vsplit / NXCD)) return;
-  const int z = __builtin_amdgcn_readfirstlane(xcd + NXCD * (local / ntl));
-  int t = local % ntl, r0 = 0;
-  for (;;) {   // the band of rows r0, r0 + 1 (one row at the end when nb is odd)
-    const int rows = min(2, nb - r0);
-    const int cnt = symm ? (rows == 2 ? 2 * (nb - r0) - 1 : nb - r0) : rows * nb;
-    if (t < cnt) break;
-    t -= cnt;
-    r0 += 2;
-  }
-  int rb, pb;
-  if (symm) {   // (r0, r0), then (r0, p), (r0 + 1, p) for p > r0
-    rb = t == 0 ? r0 : r0 + (t - 1) % 2;
-    pb = t == 0 ? r0 : r0 + 1 + (t - 1) / 2;
-  } else {
-    const int rows = min(2, nb - r0);
-    rb = r0 + t % rows;
-    pb = t / rows;
-  }
-  const int P0 = __builtin_amdgcn_readfirstlane(pb * TT);
-  const int R0 = __builtin_amdgcn_readfirstlane(rb * TT);
 
   // v range: XCD x owns the consecutive ranges x q .. x q + q - 1 (q = vsplit /
   // 8); range r is v in [r n / vsplit, (r + 1) n / vsplit)
@@ -156,8 +127,8 @@ void fused_bf3_kernel(FusedArgs f) {
       const int slab = (wave + NW * j) * 16 * 32;
 #pragma unroll
       for (int p = 0; p < NPL; ++p) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rG[p], &sB.s[0][p][slab], 16, dR[j], so, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rA[p], &sB.s[1][p][slab], 16, dR[j], so, 0, 0);
+        if (2 * j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rG[p], &sB.s[0][p][slab], 16, dR[j], so, 0, 0);
+        if (2 * j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA[p], &sB.s[1][p][slab], 16, dR[j], so, 0, 0);
       }
     }
   };
@@ -168,63 +139,59 @@ void fused_bf3_kernel(FusedArgs f) {
       const int slab = (wave + NW * j) * 16 * 32;
 #pragma unroll
       for (int p = 0; p < NPL; ++p) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rX[p], &sC.s[0][p][slab], 16, dR[j], so, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rU[p], &sC.s[1][p][slab], 16, dU[j], so, 0, 0);
+        if (2 * j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rX[p], &sC.s[0][p][slab], 16, dR[j], so, 0, 0);
+        if (2 * j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rU[p], &sC.s[1][p][slab], 16, dU[j], so, 0, 0);
       }
     }
   };
 
   // fragment (row r, k chunk lane / 16) of a plane at r * 32 + lds_chunk(r, lane / 16) * 8.
-  // For r = 64 h + 16 t + lane % 16 the map depends on t only through t mod 2
-  // (it flips bit 1 of the chunk), so even and odd tiles take two offsets.
+  // The 16 x 16 tiles alternate between the two waves of a row or column, so both work in
+  // a short tile; the map repeats every 32 rows, so tile t is 32 t rows further.
   const int lr = lane & 15, kc = lane >> 4;
-  auto frag_off = [&](int base, int tpar) {
-    const int r = base + 16 * tpar + lr;
-    return (r - 16 * tpar) * 32 + lds_chunk(r, kc) * 8;
-  };
-  const int fR[2] = {frag_off(wr * 64, 0), frag_off(wr * 64, 1)};   // R side rows
-  const int fP[2] = {frag_off(wc * 64, 0), frag_off(wc * 64, 1)};   // P side rows
+  const int fR = (wr * 16 + lr) * 32 + lds_chunk(wr * 16 + lr, kc) * 8;   // R side rows
+  const int fP = (wc * 16 + lr) * 32 + lds_chunk(wc * 16 + lr, kc) * 8;   // P side rows
   // fragments of one half stage: the shared operand s (G or GX) and the per-v
   // operand m (A_v or U_v), [plane][tile]
-  struct Frags { bf16x8 s[NPL][4], m[NPL][4]; };
-  Frags fb, fc;
-  auto rd = [&](const __bf16* base, const int* off, int t) {
-    return *reinterpret_cast<const bf16x8*>(base + off[t & 1] + t * 16 * 32);
+  struct FragsB { bf16x8 s[NPL][TI], m[NPL][TJ]; } fb;
+  struct FragsC { bf16x8 s[NPL][TJ], m[NPL][TI]; } fc;
+  auto rd = [&](const __bf16* base, int off, int t) {
+    return *reinterpret_cast<const bf16x8*>(base + off + t * 32 * 32);
   };
-  auto readB = [&](Frags& fr) {   // G (R side), A_v (P side)
+  auto readB = [&](FragsB& fr) {   // G (R side), A_v (P side)
 #pragma unroll
     for (int p = 0; p < NPL; ++p)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        fr.s[p][t] = rd(sB.s[0][p], fR, t);
-        fr.m[p][t] = rd(sB.s[1][p], fP, t);
+        if (t < TI) fr.s[p][t] = rd(sB.s[0][p], fR, t);
+        if (t < TJ) fr.m[p][t] = rd(sB.s[1][p], fP, t);
       }
   };
-  auto readC = [&](Frags& fr) {   // GX (P side), U_v (R side)
+  auto readC = [&](FragsC& fr) {   // GX (P side), U_v (R side)
 #pragma unroll
     for (int p = 0; p < NPL; ++p)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        fr.s[p][t] = rd(sC.s[0][p], fP, t);
-        fr.m[p][t] = rd(sC.s[1][p], fR, t);
+        if (t < TJ) fr.s[p][t] = rd(sC.s[0][p], fP, t);
+        if (t < TI) fr.m[p][t] = rd(sC.s[1][p], fR, t);
       }
   };
 
   // accumulators [ti][tj]: rows R of tile ti, columns P of tile tj (cleared once
   // here; each v then starts them from zero inside its first MFMAs)
-  f4 B[4][4], C[4][4];
+  f4 B[TI][TJ], C[TI][TJ];
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti)
+  for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) B[ti][tj] = C[ti][tj] = zero;
+    for (int tj = 0; tj < TJ; ++tj) B[ti][tj] = C[ti][tj] = zero;
   using PR = Products<NPL>;   // plane pairs, smallest terms first
   // B products: B[ti][tj] += G[ti] . A_v[tj]
-  auto mfmaB = [&](const Frags& fr, bool first) {
+  auto mfmaB = [&](const FragsB& fr, bool first) {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj) {
+      for (int tj = 0; tj < TJ; ++tj) {
         f4 a = first ? zero : B[ti][tj];
 #pragma unroll
         for (int q = 0; q < PR::N; ++q)
@@ -234,11 +201,11 @@ void fused_bf3_kernel(FusedArgs f) {
       }
   };
   // C products: C[ti][tj] += U_v[ti] . GX[tj]
-  auto mfmaC = [&](const Frags& fr, bool first) {
+  auto mfmaC = [&](const FragsC& fr, bool first) {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj) {
+      for (int tj = 0; tj < TJ; ++tj) {
         f4 a = first ? zero : C[ti][tj];
 #pragma unroll
         for (int q = 0; q < PR::N; ++q)
@@ -252,35 +219,35 @@ void fused_bf3_kernel(FusedArgs f) {
   f4* const Dw = sD + wave * 16 * 64 + lane;
   auto dzero = [&]() {
 #pragma unroll
-    for (int tt = 0; tt < 16; ++tt) Dw[tt * 64] = zero;
+    for (int tt = 0; tt < TI * TJ; ++tt) Dw[tt * 64] = zero;
   };
   auto dupdate = [&]() {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj) {
-        f4 d = Dw[(ti * 4 + tj) * 64];
+      for (int tj = 0; tj < TJ; ++tj) {
+        f4 d = Dw[(ti * TJ + tj) * 64];
 #pragma unroll
         for (int r = 0; r < 4; ++r) d[r] = fmaf(B[ti][tj][r], C[ti][tj][r], d[r]);
-        Dw[(ti * 4 + tj) * 64] = d;
+        Dw[(ti * TJ + tj) * 64] = d;
       }
   };
   // D tile -> partial tile z (FP32 store, or FP64 add unless first): thread t
   // takes column P0 + t % 128 and rows R0 + t / 128 + 2 i, reading each element
   // from the LDS slot of the lane that formed it (lane 16 (R % 16 / 4) + P % 16
-  // of wave 2 (R / 64) + P / 64, tile (R % 64 / 16, P % 64 / 16), element R % 4),
+  // of wave 2 (R / 16 % 2) + P / 16 % 2, tile (R / 32, P / 32), element R % 4),
   // so the global writes are coalesced rows.  Barriers before (other waves'
   // slots) and after (the slots may be cleared next).
   auto flush = [&](bool first) {
     __syncthreads();
     const float* sDf = reinterpret_cast<const float*>(sD);
     const int Pt = tid & (TT - 1), P = P0 + Pt;
-    const int pslot = (Pt >> 6) * 16 * 64 + ((Pt >> 4) & 3) * 64 + (Pt & 15);
+    const int pslot = ((Pt >> 4) & 1) * 16 * 64 + (Pt >> 5) * 64 + (Pt & 15);
     const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
     for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
       const int R = R0 + Rt;
       if (R < naux && P < naux) {
-        const int slot = pslot + (Rt >> 6) * 2 * 16 * 64 + ((Rt >> 4) & 3) * 4 * 64 + ((Rt >> 2) & 3) * 16;
+        const int slot = pslot + ((Rt >> 4) & 1) * 2 * 16 * 64 + (Rt >> 5) * TJ * 64 + ((Rt >> 2) & 3) * 16;
         const float v = sDf[slot * 4 + (Rt & 3)];
         const int64_t o = zo + (int64_t)R * naux;
         if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
@@ -310,12 +277,14 @@ void fused_bf3_kernel(FusedArgs f) {
     bf3_vm_lds_barrier();
     readB(fb);
   }
-  // spread a phase's 12 memory-to-LDS loads over its 96 MFMAs (one per 8)
+  // spread a phase's memory-to-LDS loads over its MFMAs: 12 over 96 in a full tile
+  constexpr int NR = TI > 2 ? 6 : 3, NP = TJ > 2 ? 6 : 3;   // loads of a panel of rows, of columns
   auto spread = [&]() {
+    constexpr int MPL = PR::N * TI * TJ / (NR + NP) < 8 ? PR::N * TI * TJ / (NR + NP) : 8;
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);   // one memory instruction
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);   // eight MFMAs
+    for (int i = 0; i < NR + NP; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);     // one memory instruction
+      __builtin_amdgcn_sched_group_barrier(0x008, MPL, 0);   // MPL MFMAs
     }
   };
   auto chunk = [&](bool first) {
@@ -345,6 +314,64 @@ void fused_bf3_kernel(FusedArgs f) {
   // the last (repeated) memory-to-LDS loads land before the workgroup may end
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   flush(done <= FLUSH_V);   // also writes zeros for an empty range
+}
+
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void fused_bf3_kernel(FusedArgs f) {
+  __shared__ __attribute__((aligned(16))) Half3 sB;
+  __shared__ __attribute__((aligned(16))) Half3 sC;
+  __shared__ __attribute__((aligned(16))) f4 sD[NW * 16 * 64];
+  const int naux = f.naux;
+
+  // tile and v range: XCD-aware order (workgroup b runs on XCD b mod 8; each XCD
+  // owns the partial slots z = xcd, xcd + 8, ..., a block of consecutive v
+  // ranges, and walks the tiles of one slot in bands of two R blocks, P by P
+  // with R fastest, so its resident workgroups share panels in its L2).  With
+  // symmetric D only the tiles on or above the diagonal are walked.  The integer
+  // divisions run on the vector unit; readfirstlane marks their results uniform.
+  const int nb = (naux + TT - 1) / TT;
+  const int set = blockIdx.y;
+  const bool symm = f.sym != nullptr && f.sym[set] != 0;
+  const int ntl = symm ? nb * (nb + 1) / 2 : nb * nb;
+  const int b = blockIdx.x;
+  const int xcd = b % NXCD, local = b / NXCD;
+  if (local >= ntl * (f.vsplit / NXCD)) return;
+  const int z = __builtin_amdgcn_readfirstlane(xcd + NXCD * (local / ntl));
+  int t = local % ntl, r0 = 0;
+  for (;;) {   // the band of rows r0, r0 + 1 (one row at the end when nb is odd)
+    const int rows = min(2, nb - r0);
+    const int cnt = symm ? (rows == 2 ? 2 * (nb - r0) - 1 : nb - r0) : rows * nb;
+    if (t < cnt) break;
+    t -= cnt;
+    r0 += 2;
+  }
+  int rb, pb;
+  if (symm) {   // (r0, r0), then (r0, p), (r0 + 1, p) for p > r0
+    rb = t == 0 ? r0 : r0 + (t - 1) % 2;
+    pb = t == 0 ? r0 : r0 + 1 + (t - 1) / 2;
+  } else {
+    const int rows = min(2, nb - r0);
+    rb = r0 + t % rows;
+    pb = t / rows;
+  }
+  const int P0 = __builtin_amdgcn_readfirstlane(pb * TT);
+  const int R0 = __builtin_amdgcn_readfirstlane(rb * TT);
+
+  // the last block of naux % 128 columns or rows forms only the 32-wide strips that hold a
+  // THC point (the corner tile is treated as a column): 190 -> 181 us a tau point at n =
+  // 120, naux = 600 (88 of the last 128)
+  const int tj = (naux - P0 + 31) / 32, ti = (naux - R0 + 31) / 32;
+  if (tj < 4) {
+    if (tj == 1) fused_bf3_tile<4, 1>(f, sB, sC, sD, set, z, R0, P0);
+    else if (tj == 2) fused_bf3_tile<4, 2>(f, sB, sC, sD, set, z, R0, P0);
+    else fused_bf3_tile<4, 3>(f, sB, sC, sD, set, z, R0, P0);
+  } else if (ti < 4) {
+    if (ti == 1) fused_bf3_tile<1, 4>(f, sB, sC, sD, set, z, R0, P0);
+    else if (ti == 2) fused_bf3_tile<2, 4>(f, sB, sC, sD, set, z, R0, P0);
+    else fused_bf3_tile<3, 4>(f, sB, sC, sD, set, z, R0, P0);
+  } else {
+    fused_bf3_tile<4, 4>(f, sB, sC, sD, set, z, R0, P0);
+  }
 }
 
 inline unsigned cdiv_bf3(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
