@@ -547,44 +547,48 @@ int direct_batch(thcsox_plan_s* p, const double* G, double* Sigma, int k0, int k
   return backproject_batch(p, bufC, aa, Sigma + (int64_t)k0 * nn, nb, accumulate ? 1.0 : 0.0);
 }
 
-// The same for the mirrored pairs (l, m-1-l), l0 <= l < l1 <= (m+1)/2: Pi[m-1-l] =
-// Pi[l]^T, and with a symmetric V also W[m-1-l] = W[l]^T, so one W serves both
-// points.  lo / hi: write Sigma[l] / Sigma[m-1-l] (hi is off for the middle point
-// of an odd grid).  W always comes from the lower point, so that a slice of the
-// grid gives the same bits as the whole.  The two products of W are most of the term's
-// flops: at n = 300, naux = 1800 the 100-point grid takes 33.6 ms by pairs, 61.0 by points.
-int direct_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int l0, int l1, bool lo, bool hi,
-                 bool accumulate) {
-  const int n = p->n, naux = p->naux, nb = l1 - l0;
+// The same for the tau points k_begin <= k < k_end of the mirrored pairs (l, m-1-l), l0 <= l
+// < l1 <= (m+1)/2: Pi[m-1-l] = Pi[l]^T, and with a symmetric V also W[m-1-l] = W[l]^T, so
+// one W serves both points.  W always comes from the lower point, so that a slice of the
+// grid gives the same bits as the whole; a pair that is only half inside the range goes
+// with the others (a batch of few points takes as long as its launches: n = 79, naux =
+// 439, 7 of 9 points: 227 us, 358 with the half pairs apart, 293 by points).  The two
+// products of W are most of the term's flops: at n = 300, naux = 1800 the 100-point grid takes 33.6 ms by pairs, 61.0 by
+// points.
+int direct_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int l0, int l1, int k_begin,
+                 int k_end, bool accumulate) {
+  const int n = p->n, naux = p->naux, m = p->m, nb = l1 - l0;
   const int64_t nn = (int64_t)n * n, aa = (int64_t)naux * naux, step = (int64_t)p->tbd * aa;
   double* bufA = p->dbuf;          // Gt[l], then W o Gt[l]
   double* bufB = bufA + step;      // Gt[m-1-l], then W^T o Gt[m-1-l]
   double* bufC = bufB + step;      // Pi, then W
   double* bufD = bufC + step;      // V Pi
   const double beta = accumulate ? 1.0 : 0.0;
+  // the lower and the upper points in the range (the middle point of an odd grid is a
+  // lower one)
+  const int a0 = std::max(l0, k_begin), a1 = std::min(l1, k_end);
+  const int b0 = std::max(l0, m - k_end), b1 = std::min({l1, m - k_begin, m / 2});
   TRY(bubble_batch(p, G, l0, l1));
   TRY(screen_both_sides(p, bufC, bufD, bufC, nb));
-  HIP_TRY(hadamard_pair(bufC, lo ? bufA : nullptr, hi ? bufB : nullptr, naux, nb, p->stream));
-  if (lo) TRY(backproject_batch(p, bufA, aa, Sigma + (int64_t)l0 * nn, nb, beta));
-  if (hi)
-    TRY(backproject_batch(p, bufB, aa, Sigma + (int64_t)(p->m - 1 - l0) * nn, nb, beta, 1.0, -1));
+  HIP_TRY(hadamard_pair(bufC, a0 < a1 ? bufA : nullptr, b0 < b1 ? bufB : nullptr, naux, nb,
+                        p->stream));
+  if (a0 < a1)
+    TRY(backproject_batch(p, bufA + (a0 - l0) * aa, aa, Sigma + a0 * nn, a1 - a0, beta));
+  if (b0 < b1)
+    TRY(backproject_batch(p, bufB + (b0 - l0) * aa, aa, Sigma + (m - 1 - b0) * nn, b1 - b0, beta,
+                          1.0, -1));
   return 0;
 }
 
-// All tau points k_begin <= k < k_end by mirrored pairs: the lower points l of the
-// pairs the range touches form one run, cut where a pair is only half inside it.
+// All tau points k_begin <= k < k_end by mirrored pairs: the lower points of the pairs that
+// the range touches are consecutive.
 int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_begin, int k_end,
                        bool accumulate) {
   const int m = p->m, half = (m + 1) / 2;
-  auto lo_in = [&](int l) { return l >= k_begin && l < k_end; };
-  auto hi_in = [&](int l) { return m - 1 - l != l && m - 1 - l >= k_begin && m - 1 - l < k_end; };
-  for (int l = 0; l < half;) {
-    const bool lo = lo_in(l), hi = hi_in(l);
-    int e = l + 1;
-    while (e < half && e - l < p->tbd && lo_in(e) == lo && hi_in(e) == hi) ++e;
-    if (lo || hi) TRY(direct_pairs(p, G, Sigma, l, e, lo, hi, accumulate));
-    l = e;
-  }
+  const int first = k_end <= half ? k_begin : k_begin >= half ? m - k_end : std::min(k_begin, m - k_end);
+  const int end = k_end <= half ? k_end : k_begin >= half ? m - k_begin : half;
+  for (int l = first; l < end; l += p->tbd)
+    TRY(direct_pairs(p, G, Sigma, l, std::min(end, l + p->tbd), k_begin, k_end, accumulate));
   return 0;
 }
 
@@ -851,15 +855,14 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   if ((e = hipMemcpyAsync(p->V, V_dev, sizeof(double) * (size_t)naux * naux,
                           hipMemcpyDeviceToDevice, s)))
     return hip_bail(e, "copy V");
-  if ((rc = build_u(p, V_dev, p->U, p->amax, p->norm2))) return bail(rc);
   // is V symmetric to rounding?  (max |V - V^T| and max |V| in two per-tau slots
   // that every later call clears before it uses them)
   unsigned long long vs[2] = {0, 0};
-  if ((e = fill_u64(p->am_asym(), 1, 0ull, s)) || (e = asym64(p->V, naux, 1, p->am_asym(), s)) ||
-      (e = fill_u64(p->am_g(), 1, 0ull, s)) ||
-      (e = absmax64(p->V, (int64_t)naux * naux, 0, 1, p->am_g(), s)) ||
-      (e = hipMemcpyAsync(&vs[0], p->am_asym(), sizeof(vs[0]), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(&vs[1], p->am_g(), sizeof(vs[1]), hipMemcpyDeviceToHost, s)))
+  if ((e = fill_u64(p->am_gt(), 2, 0ull, s)) || (e = asym64(p->V, naux, 1, p->am_gt(), s)) ||
+      (e = absmax64(p->V, (int64_t)naux * naux, 0, 1, p->am_gt() + 1, s)))
+    return hip_bail(e, "symmetry of V");
+  if ((rc = build_u(p, V_dev, p->U, p->amax, p->norm2))) return bail(rc);
+  if ((e = hipMemcpyAsync(vs, p->am_gt(), sizeof(vs), hipMemcpyDeviceToHost, s)))
     return hip_bail(e, "symmetry of V");
   if ((e = hipStreamSynchronize(s))) return hip_bail(e, "plan synchronise");
   double vd[2];
