@@ -17,7 +17,7 @@
 // barrier (one a stage).  A wave owns 32 x 32 of the tile (16 x 16 tiles alternating
 // between the waves): 32 products a stage against
 // 16 fragment reads.  Matrix cores busy 81 % of the cycles
-// (counters); n = 200, naux = 1100, symmetric: 1.78 ms a tau point (55 TFLOP/s
+// (counters); n = 200, naux = 1100, symmetric: 1.70 ms a tau point (57 TFLOP/s
 // algorithmic, 72 is what a large library product reaches), 3.34 with panels staged
 // through registers and one workgroup of 136 KiB per unit.
 #include <algorithm>
@@ -42,8 +42,10 @@ struct Stage64 {
 __device__ __forceinline__ int sw64(int r, int c) { return c ^ ((r >> 1) & 7); }
 
 // One tile's range of v.  Each wave forms TI x TJ tiles of 16 x 16 out of its 2 x 2: rows
-// beyond 32 TI and columns beyond 32 TJ lie past naux.
-template <int TI, int TJ>
+// beyond 32 TI and columns beyond 32 TJ lie past naux.  TRI: a diagonal tile of a symmetric
+// D, of which only the 16 x 16 tiles ti <= tj of each wave are formed: they hold every
+// element on and above the diagonal.
+template <int TI, int TJ, bool TRI>
 __device__ __forceinline__ void fused_f64_tile(const FusedArgs& f, Stage64& b0, Stage64& b1, int set,
                                                int z, int R0, int P0) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -116,7 +118,7 @@ __device__ __forceinline__ void fused_f64_tile(const FusedArgs& f, Stage64& b0, 
 #pragma unroll
   for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < TJ; ++tj) accB[ti][tj] = accC[ti][tj] = accD[ti][tj] = zero;
+    for (int tj = TRI ? ti : 0; tj < TJ; ++tj) accB[ti][tj] = accC[ti][tj] = accD[ti][tj] = zero;
   auto product = [&](d4 (&acc)[TI][TJ], const double* rows, const double* cols) {
     double r[TI][4], c[TJ][4];
 #pragma unroll
@@ -128,7 +130,7 @@ __device__ __forceinline__ void fused_f64_tile(const FusedArgs& f, Stage64& b0, 
 #pragma unroll
       for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma1(r[ti][s], c[tj][s], acc[ti][tj]);
+        for (int tj = TRI ? ti : 0; tj < TJ; ++tj) acc[ti][tj] = mfma1(r[ti][s], c[tj][s], acc[ti][tj]);
   };
   // (the loads are issued in inline assembly: left to the compiler, a read of one
   // buffer waits for the loads just issued into the other)
@@ -149,7 +151,7 @@ __device__ __forceinline__ void fused_f64_tile(const FusedArgs& f, Stage64& b0, 
 #pragma unroll
       for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) {
+        for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             accD[ti][tj][r] = fma(accB[ti][tj][r], accC[ti][tj][r], accD[ti][tj][r]);
@@ -167,7 +169,7 @@ __device__ __forceinline__ void fused_f64_tile(const FusedArgs& f, Stage64& b0, 
 #pragma unroll
   for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < TJ; ++tj)
+    for (int tj = TRI ? ti : 0; tj < TJ; ++tj)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int R = R0 + 16 * wr + 32 * ti + out_row<MODE_F64>(lane, r);
@@ -197,12 +199,16 @@ __global__ __launch_bounds__(NT, 2) void fused_f64_kernel(FusedArgs f) {
   // symmetric D: a tile wholly below the diagonal is the mirror of one above it
   const int set = blockIdx.y;
   if (f.sym != nullptr && f.sym[set] != 0 && R0 >= P0 + TD) return;
-  // the last block of columns or rows forms only the 32-wide strips that hold a THC point
-  // (the corner tile is treated as a column): 1.88 -> 1.78 ms at n = 200, naux = 1100 (12 of
-  // the last 64)
-  if (f.naux - P0 <= 32) fused_f64_tile<2, 1>(f, b0, b1, set, z, R0, P0);
-  else if (f.naux - R0 <= 32) fused_f64_tile<1, 2>(f, b0, b1, set, z, R0, P0);
-  else fused_f64_tile<2, 2>(f, b0, b1, set, z, R0, P0);
+  // The last block of columns or rows forms only the 32-wide strips that hold a THC point,
+  // and a diagonal tile of a symmetric D only its upper triangle: 1.88 -> 1.70 ms at n = 200,
+  // naux = 1100 (12 of the last 64)
+  const bool one_p = f.naux - P0 <= 32, one_r = f.naux - R0 <= 32;
+  const bool diag = f.sym != nullptr && f.sym[set] != 0 && R0 == P0;
+  if (one_r && one_p) fused_f64_tile<1, 1, false>(f, b0, b1, set, z, R0, P0);
+  else if (one_p) fused_f64_tile<2, 1, false>(f, b0, b1, set, z, R0, P0);
+  else if (one_r) fused_f64_tile<1, 2, false>(f, b0, b1, set, z, R0, P0);
+  else if (diag) fused_f64_tile<2, 2, true>(f, b0, b1, set, z, R0, P0);
+  else fused_f64_tile<2, 2, false>(f, b0, b1, set, z, R0, P0);
 }
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }

@@ -62,12 +62,14 @@ __device__ __forceinline__ void bf3_vm_lds_barrier() {
 // One tile's range of v.  sB: G, A_v; sC: GX, U_v; sD: the partial sum of D.  Each wave
 // forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the rows R of the workgroup's tile
 // beyond 32 TI and the columns P beyond 32 TJ lie past naux and are neither loaded nor
-// multiplied (a D element's products and their order do not depend on TI and TJ).
-template <int TI, int TJ>
+// multiplied.  TRI: a diagonal tile of a symmetric D, of which only the 16 x 16 tiles ti
+// <= tj of each wave are formed: they hold every element on and above the diagonal.  (A
+// D element's products and their order do not depend on TI, TJ and TRI.)
+template <int TI, int TJ, bool TRI>
 __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Half3& sC, f4* sD, int set,
                                                int z, int R0, int P0) {
   int tid = threadIdx.x;
-  // (the compiler must not merge the seven forms' address arithmetic above their branch)
+  // (the compiler must not merge the forms' address arithmetic above their branch)
   __asm__ volatile("" : "+v"(tid), "+s"(set), "+s"(z), "+s"(R0), "+s"(P0));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -184,14 +186,14 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
 #pragma unroll
   for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < TJ; ++tj) B[ti][tj] = C[ti][tj] = zero;
+    for (int tj = TRI ? ti : 0; tj < TJ; ++tj) B[ti][tj] = C[ti][tj] = zero;
   using PR = Products<NPL>;   // plane pairs, smallest terms first
   // B products: B[ti][tj] += G[ti] . A_v[tj]
   auto mfmaB = [&](const FragsB& fr, bool first) {
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
         f4 a = first ? zero : B[ti][tj];
 #pragma unroll
         for (int q = 0; q < PR::N; ++q)
@@ -205,7 +207,7 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
         f4 a = first ? zero : C[ti][tj];
 #pragma unroll
         for (int q = 0; q < PR::N; ++q)
@@ -225,7 +227,7 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
         f4 d = Dw[(ti * TJ + tj) * 64];
 #pragma unroll
         for (int r = 0; r < 4; ++r) d[r] = fmaf(B[ti][tj][r], C[ti][tj][r], d[r]);
@@ -246,7 +248,7 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
     const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
     for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
       const int R = R0 + Rt;
-      if (R < naux && P < naux) {
+      if (R < naux && P < naux && (!TRI || (Rt >> 5) <= (Pt >> 5))) {
         const int slot = pslot + ((Rt >> 4) & 1) * 2 * 16 * 64 + (Rt >> 5) * TJ * 64 + ((Rt >> 2) & 3) * 16;
         const float v = sDf[slot * 4 + (Rt & 3)];
         const int64_t o = zo + (int64_t)R * naux;
@@ -280,7 +282,8 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
   // spread a phase's memory-to-LDS loads over its MFMAs: 12 over 96 in a full tile
   constexpr int NR = TI > 2 ? 6 : 3, NP = TJ > 2 ? 6 : 3;   // loads of a panel of rows, of columns
   auto spread = [&]() {
-    constexpr int MPL = PR::N * TI * TJ / (NR + NP) < 8 ? PR::N * TI * TJ / (NR + NP) : 8;
+    constexpr int NM = PR::N * (TRI ? TI * (TI + 1) / 2 : TI * TJ);
+    constexpr int MPL = NM / (NR + NP) < 8 ? NM / (NR + NP) : 8;
 #pragma unroll
     for (int i = 0; i < NR + NP; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);     // one memory instruction
@@ -357,21 +360,32 @@ void fused_bf3_kernel(FusedArgs f) {
   const int P0 = __builtin_amdgcn_readfirstlane(pb * TT);
   const int R0 = __builtin_amdgcn_readfirstlane(rb * TT);
 
-  // the last block of naux % 128 columns or rows forms only the 32-wide strips that hold a
-  // THC point (the corner tile is treated as a column): 190 -> 181 us a tau point at n =
-  // 120, naux = 600 (88 of the last 128)
-  const int tj = (naux - P0 + 31) / 32, ti = (naux - R0 + 31) / 32;
-  if (tj < 4) {
-    if (tj == 1) fused_bf3_tile<4, 1>(f, sB, sC, sD, set, z, R0, P0);
-    else if (tj == 2) fused_bf3_tile<4, 2>(f, sB, sC, sD, set, z, R0, P0);
-    else fused_bf3_tile<4, 3>(f, sB, sC, sD, set, z, R0, P0);
-  } else if (ti < 4) {
-    if (ti == 1) fused_bf3_tile<1, 4>(f, sB, sC, sD, set, z, R0, P0);
-    else if (ti == 2) fused_bf3_tile<2, 4>(f, sB, sC, sD, set, z, R0, P0);
-    else fused_bf3_tile<3, 4>(f, sB, sC, sD, set, z, R0, P0);
-  } else {
-    fused_bf3_tile<4, 4>(f, sB, sC, sD, set, z, R0, P0);
+  // The last block of naux % 128 columns or rows forms only the 32-wide strips that hold a
+  // THC point, and a diagonal tile of a symmetric D only its upper triangle: 190 -> 181 us a
+  // tau point at n = 120, naux = 600 (88 of the last 128), general
+  const int tj = min((naux - P0 + 31) / 32, 4), ti = min((naux - R0 + 31) / 32, 4);
+  const bool diag = symm && R0 == P0;
+#define THCSOX_TILE(TI, TJ, TRI) fused_bf3_tile<TI, TJ, TRI>(f, sB, sC, sD, set, z, R0, P0)
+  if (diag) {
+    if (tj == 4) THCSOX_TILE(4, 4, true);
+    else if (tj == 3) THCSOX_TILE(3, 3, true);
+    else if (tj == 2) THCSOX_TILE(2, 2, true);
+    else THCSOX_TILE(1, 1, true);
+  } else if (ti == 4) {
+    if (tj == 4) THCSOX_TILE(4, 4, false);
+    else if (tj == 3) THCSOX_TILE(4, 3, false);
+    else if (tj == 2) THCSOX_TILE(4, 2, false);
+    else THCSOX_TILE(4, 1, false);
+  } else if (tj == 4) {
+    if (ti == 3) THCSOX_TILE(3, 4, false);
+    else if (ti == 2) THCSOX_TILE(2, 4, false);
+    else THCSOX_TILE(1, 4, false);
+  } else {   // the corner of a general D
+    if (ti == 3) THCSOX_TILE(3, 3, false);
+    else if (ti == 2) THCSOX_TILE(2, 2, false);
+    else THCSOX_TILE(1, 1, false);
   }
+#undef THCSOX_TILE
 }
 
 inline unsigned cdiv_bf3(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }

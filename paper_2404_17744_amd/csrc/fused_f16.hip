@@ -75,14 +75,16 @@ __device__ __forceinline__ void vm_lds_barrier() {
 // One tile's range of pairs.  M = MODE_F16X2 or MODE_F32.  sB: G, A_v1, A_v2; sC: GX,
 // U_v1, U_v2; sD: the partial sum of D.  Each wave forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the
 // rows R of the workgroup's tile beyond 32 TI and the columns P beyond 32 TJ lie past
-// naux and are neither loaded nor multiplied (a D element's products and their order
-// do not depend on TI and TJ).
-template <int M, int TI, int TJ>
+// naux and are neither loaded nor multiplied.  TRI: a diagonal tile of a symmetric D, of
+// which only the 16 x 16 tiles ti <= tj of each wave are formed: they hold every element
+// on and above the diagonal.  (A D element's products and their order do not depend on
+// TI, TJ and TRI.)
+template <int M, int TI, int TJ, bool TRI>
 __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& sC, f4* sD, int set,
                                            int z, int R0, int P0) {
   constexpr bool F32 = M == MODE_F32;
   int tid = threadIdx.x;
-  // (the compiler must not merge the seven forms' address arithmetic above their branch)
+  // (the compiler must not merge the forms' address arithmetic above their branch)
   __asm__ volatile("" : "+v"(tid), "+s"(set), "+s"(z), "+s"(R0), "+s"(P0));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -197,7 +199,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
 #pragma unroll
   for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < TJ; ++tj) B1[ti][tj] = B2[ti][tj] = C1[ti][tj] = C2[ti][tj] = zero;
+    for (int tj = TRI ? ti : 0; tj < TJ; ++tj) B1[ti][tj] = B2[ti][tj] = C1[ti][tj] = C2[ti][tj] = zero;
   // FP32: operand j (k = 8 g + j) of a fragment pair
   auto el = [](const f16x8& lo, const f16x8& hi, int j) {
     return j < 4 ? __builtin_bit_cast(f4, lo)[j] : __builtin_bit_cast(f4, hi)[j - 4];
@@ -208,7 +210,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
         if constexpr (F32) {
           f4 a1 = first ? zero : B1[ti][tj];
           f4 a2 = first ? zero : B2[ti][tj];
@@ -237,7 +239,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
         if constexpr (F32) {
           f4 a1 = first ? zero : C1[ti][tj];
           f4 a2 = first ? zero : C2[ti][tj];
@@ -272,7 +274,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
         f4 d = Dw[(ti * TJ + tj) * 64];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -296,7 +298,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
     const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
     for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
       const int R = R0 + Rt;
-      if (R < naux && P < naux) {
+      if (R < naux && P < naux && (!TRI || (Rt >> 5) <= (Pt >> 5))) {
         const int slot = pslot + ((Rt >> 4) & 1) * 2 * 16 * 64 + (Rt >> 5) * TJ * 64 + ((Rt >> 2) & 3) * 16;
         const float v = sDf[slot * 4 + (Rt & 3)];
         const int64_t o = zo + (int64_t)R * naux;
@@ -333,7 +335,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
   // meanwhile, while loads issued late have less time to land (measured at n =
   // 300: fp16x2, 96 MFMAs per phase, fastest at 3 of 1, 2, 3, 4, 8; FP32, 256
   // MFMAs per phase, at 16 of 10, 12, 16, 21)
-  constexpr int NM = (F32 ? 16 : 6) * TI * TJ;   // MFMAs per phase
+  constexpr int NM = (F32 ? 16 : 6) * (TRI ? TI * (TI + 1) / 2 : TI * TJ);   // MFMAs per phase
   auto spread = [&](auto loads) {
     constexpr int L = decltype(loads)::value;
     constexpr int MPL = F32 ? (NM / L < 16 ? NM / L : 16) : (NM / L < 3 ? NM / L : 3);
@@ -412,23 +414,35 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   const int P0 = __builtin_amdgcn_readfirstlane(pb * TT);
   const int R0 = __builtin_amdgcn_readfirstlane(rb * TT);
 
-  // the last block of naux % 128 columns or rows forms only the 32-wide strips that hold
-  // a THC point (the corner tile is treated as a column).  Against full 128 x 128 products
-  // everywhere: n = 149, naux = 797 (29 of the last 128), general, FP32: 696 -> 590 us a
-  // tau point; n = 300, naux = 1800 (8 of 128), symmetric, fp16x2: 1927 -> 1867 us, where
-  // the short tiles wait for memory (a short tile takes 0.75 of a full one's time)
-  const int tj = (naux - P0 + 31) / 32, ti = (naux - R0 + 31) / 32;
-  if (tj < 4) {
-    if (tj == 1) fused_tile<M, 4, 1>(f, sB, sC, sD, set, z, R0, P0);
-    else if (tj == 2) fused_tile<M, 4, 2>(f, sB, sC, sD, set, z, R0, P0);
-    else fused_tile<M, 4, 3>(f, sB, sC, sD, set, z, R0, P0);
-  } else if (ti < 4) {
-    if (ti == 1) fused_tile<M, 1, 4>(f, sB, sC, sD, set, z, R0, P0);
-    else if (ti == 2) fused_tile<M, 2, 4>(f, sB, sC, sD, set, z, R0, P0);
-    else fused_tile<M, 3, 4>(f, sB, sC, sD, set, z, R0, P0);
-  } else {
-    fused_tile<M, 4, 4>(f, sB, sC, sD, set, z, R0, P0);
+  // The last block of naux % 128 columns or rows forms only the 32-wide strips that hold
+  // a THC point, and a diagonal tile of a symmetric D only its upper triangle.  Against
+  // full 128 x 128 products everywhere: n = 149, naux = 797 (29 of the last 128), general,
+  // FP32: 696 -> 590 us a tau point; n = 300, naux = 1800 (8 of 128), symmetric, fp16x2:
+  // 1927 -> 1833 us (the short tiles wait for memory: they take 0.75 of a full one's time
+  // for a quarter of its products)
+  const int tj = min((naux - P0 + 31) / 32, 4), ti = min((naux - R0 + 31) / 32, 4);
+  const bool diag = symm && R0 == P0;
+#define THCSOX_TILE(TI, TJ, TRI) fused_tile<M, TI, TJ, TRI>(f, sB, sC, sD, set, z, R0, P0)
+  if (diag) {
+    if (tj == 4) THCSOX_TILE(4, 4, true);
+    else if (tj == 3) THCSOX_TILE(3, 3, true);
+    else if (tj == 2) THCSOX_TILE(2, 2, true);
+    else THCSOX_TILE(1, 1, true);
+  } else if (ti == 4) {
+    if (tj == 4) THCSOX_TILE(4, 4, false);
+    else if (tj == 3) THCSOX_TILE(4, 3, false);
+    else if (tj == 2) THCSOX_TILE(4, 2, false);
+    else THCSOX_TILE(4, 1, false);
+  } else if (tj == 4) {
+    if (ti == 3) THCSOX_TILE(3, 4, false);
+    else if (ti == 2) THCSOX_TILE(2, 4, false);
+    else THCSOX_TILE(1, 4, false);
+  } else {   // the corner of a general D
+    if (ti == 3) THCSOX_TILE(3, 3, false);
+    else if (ti == 2) THCSOX_TILE(2, 2, false);
+    else THCSOX_TILE(1, 1, false);
   }
+#undef THCSOX_TILE
 }
 
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
