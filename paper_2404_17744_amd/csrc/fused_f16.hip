@@ -19,25 +19,31 @@
 // feed four products.  Four waves (one per SIMD) in a 2 x 2 arrangement each
 // own 64 x 64 of the tile (16 x 16 tiles alternating between the waves of a row and
 // of a column): the four accumulator sets B1, B2, C1, C2 (256
-// registers) live in the matrix-core registers (AGPRs), fragments in the
-// ordinary ones.  The partial sum of D (FP32, at most 8 v) lives in LDS, one
-// private 16-byte slot per lane and MFMA tile, and is updated once per pair:
-// D += B1 o C1 + B2 o C2.
+// registers) live in the matrix-core registers (AGPRs); the partial sum of D (FP32, at
+// most 8 v) and the fragments in the ordinary ones.  D is updated once per pair, row
+// by row among the last products: D += B1 o C1 + B2 o C2.
 //
-// Pipeline.  A k chunk is two half stages, each three panels of 128 rows x 32 k
-// x 2 planes (FP32: one plane of 4-byte elements; 48 KiB either way): the B half (G, A_v1, A_v2) in LDS buffer sB and the C
-// half (GX, U_v1, U_v2) in sC.  With 64 KiB for D the workgroup uses the full
-// 160 KiB of LDS.  Chunk t runs as
-//   phase B(t): barrier (C(t) is in sC, every wave has read B(t) from sB);
-//               loads of B(t+1) -> sB; fragments of C(t) <- sC;
-//               matrix cores: B1, B2 += products of B(t) (fragments read before)
-//   phase C(t): barrier (B(t+1) is in sB, every wave has read C(t) from sC);
-//               loads of C(t+1) -> sC; fragments of B(t+1) <- sB;
-//               matrix cores: C1, C2 += products of C(t)
-// so each half stage is loaded one phase ahead of its fragment reads, and each
-// fragment is read one phase ahead of its products.  The first chunk of a pair
-// starts the accumulators from zero inside the MFMA (no register clearing).
-// Past the last chunk the loads repeat it (never used).
+// Pipeline.  A k chunk is two phases, B and C, each of which reads a half stage of three
+// panels of 128 rows x 32 k x 2 planes (FP32: one plane of 4-byte elements; 48 KiB either
+// way): G, A_v1, A_v2, then GX, U_v1, U_v2.  LDS holds three of them (144 KiB; the other 16
+// take D to memory).  A phase forms its 4 x 4 tiles in four steps, a column (B) or a row
+// (C) of them each: the fragments of G or GX are read for the whole phase, those of A or U
+// one step ahead.  Before the last step of a phase every wave waits for the next half
+// stage and at the workgroup barrier, then reads that step's fragments of the next phase
+// and begins to load the half stage after the next two into the buffer that the barrier
+// set free.  So a load has two phases to land.
+//
+// What bounds it: the matrix cores run 0.65 of the time; the rest is the LDS writes of the
+// loads and the fragment reads that one wave per SIMD hides only in part (n = 300, naux =
+// 1800, a pair of v of a full tile: 21.3 us; 16.8 without the loads, 13.8 without the
+// reads either).  Two buffers with D in LDS, loads one phase ahead and fragments read a
+// phase ahead (which spilled) took 25.8, and its 64 single-word stores a thread 8.6
+// instead of 3.4 us a tile.  Whole launches: n = 300, symmetric, fp16x2 1.83 -> 1.62 ms a tau
+// point; n = 97, naux = 485 30.2 -> 24.0 us; n = 149, naux = 797, general, FP32 590 -> 555
+// us.  The loads are issued in inline assembly: tracked ones would make the compiler wait
+// before it reads another part of LDS.  The first chunk of a pair starts the accumulators
+// from zero inside the MFMA (no register clearing).  Past the last chunk the loads
+// repeat it (never used).
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -56,8 +62,10 @@ constexpr int NXCD16 = 8;
 
 // One half stage: three panels, each [row][plane][32] (128-byte rows) with the
 // eight 16-byte chunks of a row permuted by sw8.
-struct Half {
-  _Float16 s[3][PANEL];
+constexpr int HALF = 3 * PANEL;   // halves
+struct Smem {
+  _Float16 st[3 * HALF];   // the half stages of three phases
+  float d[32 * TT];        // 32 rows of D on their way to memory
 };
 
 // Physical 16-byte chunk of logical chunk c (= 4 plane + k / 8) in LDS row r.
@@ -66,26 +74,34 @@ struct Half {
 // two consecutive 128-byte rows (rocprofv3 counts no LDS bank conflicts).
 __device__ __forceinline__ int sw8(int r, int c) { return c ^ ((r >> 1) & 7); }
 
+// All but the newest LEFT of this wave's memory loads (including those that write LDS)
+// and all of its LDS accesses complete, then the workgroup barrier.
+template <int LEFT>
 __device__ __forceinline__ void vm_lds_barrier() {
-  // this wave's memory loads (including those that write LDS) and LDS accesses
-  // complete, then the workgroup barrier
-  __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+}
+// The same for the LDS accesses alone.
+__device__ __forceinline__ void lds_barrier() {
+  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// One tile's range of pairs.  M = MODE_F16X2 or MODE_F32.  sB: G, A_v1, A_v2; sC: GX,
-// U_v1, U_v2; sD: the partial sum of D.  Each wave forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the
+// One tile's range of pairs.  M = MODE_F16X2 or MODE_F32.  Each wave forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the
 // rows R of the workgroup's tile beyond 32 TI and the columns P beyond 32 TJ lie past
 // naux and are neither loaded nor multiplied.  TRI: a diagonal tile of a symmetric D, of
 // which only the 16 x 16 tiles ti <= tj of each wave are formed: they hold every element
 // on and above the diagonal.  (A D element's products and their order do not depend on
 // TI, TJ and TRI.)
 template <int M, int TI, int TJ, bool TRI>
-__device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& sC, f4* sD, int set,
-                                           int z, int R0, int P0) {
+__device__ __forceinline__ void fused_tile(const FusedArgs& f, Smem& sm, int set, int z, int R0,
+                                           int P0) {
   constexpr bool F32 = M == MODE_F32;
   int tid = threadIdx.x;
   // (the compiler must not merge the forms' address arithmetic above their branch)
-  __asm__ volatile("" : "+v"(tid), "+s"(set), "+s"(z), "+s"(R0), "+s"(P0));
+  __asm__ volatile("" : "+v"(tid));
+  __asm__ volatile("" : "+s"(set));
+  __asm__ volatile("" : "+s"(z));
+  __asm__ volatile("" : "+s"(R0));
+  __asm__ volatile("" : "+s"(P0));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
@@ -104,8 +120,9 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
 
   const _Float16* Gt = static_cast<const _Float16*>(f.Gt) + set * f.g_set;
   const _Float16* GX = static_cast<const _Float16*>(f.GXt) + set * f.g_set;
-  const __amdgpu_buffer_rsrc_t rG = make_rsrc(Gt + (int64_t)R0 * ld2, (int64_t)rows_r * ld2 * 2);
-  const __amdgpu_buffer_rsrc_t rX = make_rsrc(GX + (int64_t)P0 * ld2, (int64_t)rows_p * ld2 * 2);
+  // (byte counts below 2^31: checked by the launcher)
+  const i4 rG = raw_rsrc(Gt + (int64_t)R0 * ld2, rows_r * ld2 * 2);
+  const i4 rX = raw_rsrc(GX + (int64_t)P0 * ld2, rows_p * ld2 * 2);
   const _Float16* Ubase = static_cast<const _Float16*>(f.U) + (int64_t)R0 * n * ld2;
   const _Float16* Abase = static_cast<const _Float16*>(f.A) + set * f.a_set + (int64_t)P0 * ld2;
   const int64_t a_v = (int64_t)naux * ld2;   // halves between v slabs of A
@@ -114,46 +131,49 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
   // 8-row slabs w, w + 4, w + 8, w + 12 of each panel.  Lane l lands at slab row
   // l / 8, physical chunk l % 8, and loads the logical chunk sw8 maps there.
   // Rows past the valid range lie beyond the buffer resource and read as zero.
-  uint32_t dR[4], dU[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = (wave + NW * j) * 8 + (lane >> 3);
-    const int c = sw8(row, lane & 7);
-    dR[j] = (uint32_t)((row * ld2 + 8 * c) * 2);
-    dU[j] = (uint32_t)((row * (n * ld2) + 8 * c) * 2);
-  }
-  // per pair: A slabs v1, v2 (rows P) and U rows (R, v1), (R, v2); a missing
-  // second v (odd n) gets empty resources, so its panels read as zero and B2 = 0
-  __amdgpu_buffer_rsrc_t rA1, rA2, rU1, rU2;
-  const int64_t a_bytes = (int64_t)rows_p * ld2 * 2;
-  const int64_t u_bytes = ((int64_t)(rows_r - 1) * n * ld2 + ld2) * 2;
-  auto set_pair = [&](int pr) {
-    const int v1 = 2 * (p_lo + pr);
-    const bool two = v1 + 1 < n;
-    rA1 = make_rsrc(Abase + (int64_t)v1 * a_v, a_bytes);
-    rA2 = make_rsrc(Abase + (int64_t)(v1 + 1) * a_v, two ? a_bytes : 0);
-    rU1 = make_rsrc(Ubase + (int64_t)v1 * ld2, u_bytes);
-    rU2 = make_rsrc(Ubase + (int64_t)(v1 + 1) * ld2, two ? u_bytes : 0);
+  const int drow = wave * 8 + (lane >> 3), dch = 8 * sw8(drow, lane & 7);
+  uint32_t dR = (uint32_t)((drow * ld2 + dch) * 2), dU = (uint32_t)((drow * (n * ld2) + dch) * 2);
+  const uint32_t sR = 32 * ld2 * 2, sU = sR * n;   // 32 rows further (the same chunks)
+  // fetch cursors (pair, k chunk) of the two kinds of half stages, clamped to the last
+  // chunk, and the resources of their pairs: A slabs v1, v2 (rows P) and U rows (R, v1),
+  // (R, v2); a missing second v (odd n) gets empty resources, so its panels read as zero
+  // and B2 = 0
+  i4 rA1, rA2, rU1, rU2;
+  const int a_bytes = rows_p * ld2 * 2;
+  const int u_bytes = ((rows_r - 1) * n * ld2 + ld2) * 2;
+  int pB = 0, kB = 0, pC = 0, kC = 0;
+  auto set_b = [&]() {
+    const int v1 = 2 * (p_lo + pB);
+    rA1 = raw_rsrc(Abase + (int64_t)v1 * a_v, a_bytes);
+    rA2 = raw_rsrc(Abase + (int64_t)(v1 + 1) * a_v, v1 + 1 < n ? a_bytes : 0);
   };
-  auto dmaB = [&](int k0) {
-    const int so = k0 * 4;   // bytes to the k chunk (both planes)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int slab = (wave + NW * j) * 8 * 64;
-      if (j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rG, &sB.s[0][slab], 16, dR[j], so, 0, 0);
-      if (j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA1, &sB.s[1][slab], 16, dR[j], so, 0, 0);
-      if (j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA2, &sB.s[2][slab], 16, dR[j], so, 0, 0);
-    }
+  auto set_c = [&]() {
+    const int v1 = 2 * (p_lo + pC);
+    rU1 = raw_rsrc(Ubase + (int64_t)v1 * ld2, u_bytes);
+    rU2 = raw_rsrc(Ubase + (int64_t)(v1 + 1) * ld2, v1 + 1 < n ? u_bytes : 0);
   };
-  auto dmaC = [&](int k0) {
-    const int so = k0 * 4;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int slab = (wave + NW * j) * 8 * 64;
-      if (j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, &sC.s[0][slab], 16, dR[j], so, 0, 0);
-      if (j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rU1, &sC.s[1][slab], 16, dU[j], so, 0, 0);
-      if (j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rU2, &sC.s[2][slab], 16, dU[j], so, 0, 0);
-    }
+  // (no branch: one would keep a phase's loads and MFMAs apart)
+  auto next = [&](int& pr, int& k) {
+    const bool wrap = k == kst - 1, last = wrap && pr == npr - 1;
+    k = last ? k : (wrap ? 0 : k + 1);
+    pr += wrap && !last ? 1 : 0;
+  };
+  // loads q of a half stage into the buffer at sm.st + buf
+  constexpr int NB = TI + 2 * TJ, NC = TJ + 2 * TI;   // loads of a B and a C half per wave
+  auto dst = [&](int buf, int panel, int j) {
+    return lds_addr(sm.st) + (uint32_t)(buf + panel * PANEL + (wave + NW * j) * 8 * 64) * 2;
+  };
+  auto dmaB = [&](int q, int buf) {
+    const int so = kB * KC * 4;   // bytes to the k chunk (both planes)
+    if (q < TI) dma16_untracked(rG, dst(buf, 0, q), dR + q * sR, so);
+    else if ((q - TI) % 2 == 0) dma16_untracked(rA1, dst(buf, 1, (q - TI) / 2), dR + (q - TI) / 2 * sR, so);
+    else dma16_untracked(rA2, dst(buf, 2, (q - TI) / 2), dR + (q - TI) / 2 * sR, so);
+  };
+  auto dmaC = [&](int q, int buf) {
+    const int so = kC * KC * 4;
+    if (q < TJ) dma16_untracked(rX, dst(buf, 0, q), dR + q * sR, so);
+    else if ((q - TJ) % 2 == 0) dma16_untracked(rU1, dst(buf, 1, (q - TJ) / 2), dU + (q - TJ) / 2 * sU, so);
+    else dma16_untracked(rU2, dst(buf, 2, (q - TJ) / 2), dU + (q - TJ) / 2 * sU, so);
   };
 
   // fp16x2: fragment (row r, plane p, k chunk lane / 16) at halves r * 64 + sw8(r, 4 p +
@@ -166,216 +186,265 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Half& sB, Half& s
   const int lr = lane & 15, kc = lane >> 4;
   const int rr = wr * 16 + lr, rc = wc * 16 + lr;
   const int c0 = F32 ? 2 * kc : kc, c1 = F32 ? 2 * kc + 1 : 4 + kc;
-  const int fr0 = rr * 64 + sw8(rr, c0) * 8, fr1 = rr * 64 + sw8(rr, c1) * 8;
-  const int fc0 = rc * 64 + sw8(rc, c0) * 8, fc1 = rc * 64 + sw8(rc, c1) * 8;
-  // fragments of one half stage: the shared operand s (G or GX) and the per-v
-  // operands m1, m2 (A_v or U_v), [plane][tile]
-  struct FragsB { f16x8 s[2][TI], m1[2][TJ], m2[2][TJ]; } fb;
-  struct FragsC { f16x8 s[2][TJ], m1[2][TI], m2[2][TI]; } fc;
-  auto rd = [&](const _Float16* base, int off, int t) {
-    return *reinterpret_cast<const f16x8*>(base + off + t * 32 * 64);
+  const int oR[2] = {rr * 64 + sw8(rr, c0) * 8, rr * 64 + sw8(rr, c1) * 8};
+  const int oP[2] = {rc * 64 + sw8(rc, c0) * 8, rc * 64 + sw8(rc, c1) * 8};
+  // fragments: G and GX of a whole phase [plane][tile]; of A and U the two v of one tile
+  // column or row at a time, [step parity][2 v + plane]
+  f16x8 gs[2][TI], xs[2][TJ], ma[2][4], mu[2][4];
+  auto rd = [&](int buf, int panel, int off, int t) {
+    return *reinterpret_cast<const f16x8*>(sm.st + buf + panel * PANEL + off + t * 32 * 64);
   };
-  auto readB = [&](FragsB& fr) {   // G (R side), A_v1, A_v2 (P side)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t < TI) { fr.s[0][t] = rd(sB.s[0], fr0, t);  fr.s[1][t] = rd(sB.s[0], fr1, t); }
-      if (t < TJ) { fr.m1[0][t] = rd(sB.s[1], fc0, t); fr.m1[1][t] = rd(sB.s[1], fc1, t); }
-      if (t < TJ) { fr.m2[0][t] = rd(sB.s[2], fc0, t); fr.m2[1][t] = rd(sB.s[2], fc1, t); }
-    }
+  // reads q of what a step takes (m) and, from q = 4 on, of what a phase takes (s)
+  auto readB = [&](int q, int buf, int par, int t) {
+    if (q < 4) ma[par][q] = rd(buf, 1 + q / 2, oP[q % 2], t);
+    else gs[q % 2][(q - 4) / 2] = rd(buf, 0, oR[q % 2], (q - 4) / 2);
   };
-  auto readC = [&](FragsC& fr) {   // GX (P side), U_v1, U_v2 (R side)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t < TJ) { fr.s[0][t] = rd(sC.s[0], fc0, t);  fr.s[1][t] = rd(sC.s[0], fc1, t); }
-      if (t < TI) { fr.m1[0][t] = rd(sC.s[1], fr0, t); fr.m1[1][t] = rd(sC.s[1], fr1, t); }
-      if (t < TI) { fr.m2[0][t] = rd(sC.s[2], fr0, t); fr.m2[1][t] = rd(sC.s[2], fr1, t); }
-    }
+  auto readC = [&](int q, int buf, int par, int t) {
+    if (q < 4) mu[par][q] = rd(buf, 1 + q / 2, oR[q % 2], t);
+    else xs[q % 2][(q - 4) / 2] = rd(buf, 0, oP[q % 2], (q - 4) / 2);
   };
 
-  // accumulators [ti][tj]: rows R of tile ti, columns P of tile tj (cleared once
-  // here; each pair then starts them from zero inside its first MFMAs)
-  f4 B1[TI][TJ], B2[TI][TJ], C1[TI][TJ], C2[TI][TJ];
+  // accumulators [ti][tj]: rows R of tile ti, columns P of tile tj (each pair starts them
+  // from zero inside its first MFMAs), and the partial sum of D
+  f4 B1[TI][TJ], B2[TI][TJ], C1[TI][TJ], C2[TI][TJ], D[TI][TJ];
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = TRI ? ti : 0; tj < TJ; ++tj) B1[ti][tj] = B2[ti][tj] = C1[ti][tj] = C2[ti][tj] = zero;
+    for (int tj = TRI ? ti : 0; tj < TJ; ++tj)
+      B1[ti][tj] = B2[ti][tj] = C1[ti][tj] = C2[ti][tj] = D[ti][tj] = zero;
   // FP32: operand j (k = 8 g + j) of a fragment pair
   auto el = [](const f16x8& lo, const f16x8& hi, int j) {
     return j < 4 ? __builtin_bit_cast(f4, lo)[j] : __builtin_bit_cast(f4, hi)[j - 4];
   };
   // B products: acc[ti][tj] += G[ti] . A_m[tj] (fp16x2: planes x1 y0 + x0 y1 + x0 y0;
   // FP32: eight 16x16x4 products, the two v interleaved)
-  auto mfmaB = [&](const FragsB& fr, bool first) {
+  auto mfmaB = [&](int ti, int tj, int par, bool first) {
+    f4 a1 = first ? zero : B1[ti][tj], a2 = first ? zero : B2[ti][tj];
+    if constexpr (F32) {
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
-        if constexpr (F32) {
-          f4 a1 = first ? zero : B1[ti][tj];
-          f4 a2 = first ? zero : B2[ti][tj];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float g = el(fr.s[0][ti], fr.s[1][ti], j);
-            a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g, el(fr.m1[0][tj], fr.m1[1][tj], j), a1, 0, 0, 0);
-            a2 = __builtin_amdgcn_mfma_f32_16x16x4f32(g, el(fr.m2[0][tj], fr.m2[1][tj], j), a2, 0, 0, 0);
-          }
-          B1[ti][tj] = a1;
-          B2[ti][tj] = a2;
-        } else {
-          f4 a1 = first ? zero : B1[ti][tj];
-          a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.s[1][ti], fr.m1[0][tj], a1, 0, 0, 0);
-          a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.s[0][ti], fr.m1[1][tj], a1, 0, 0, 0);
-          B1[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.s[0][ti], fr.m1[0][tj], a1, 0, 0, 0);
-          f4 a2 = first ? zero : B2[ti][tj];
-          a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.s[1][ti], fr.m2[0][tj], a2, 0, 0, 0);
-          a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.s[0][ti], fr.m2[1][tj], a2, 0, 0, 0);
-          B2[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.s[0][ti], fr.m2[0][tj], a2, 0, 0, 0);
-        }
+      for (int j = 0; j < 8; ++j) {
+        const float g = el(gs[0][ti], gs[1][ti], j);
+        a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g, el(ma[par][0], ma[par][1], j), a1, 0, 0, 0);
+        a2 = __builtin_amdgcn_mfma_f32_16x16x4f32(g, el(ma[par][2], ma[par][3], j), a2, 0, 0, 0);
       }
+    } else {
+      a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(gs[1][ti], ma[par][0], a1, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(gs[0][ti], ma[par][1], a1, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(gs[0][ti], ma[par][0], a1, 0, 0, 0);
+      a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(gs[1][ti], ma[par][2], a2, 0, 0, 0);
+      a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(gs[0][ti], ma[par][3], a2, 0, 0, 0);
+      a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(gs[0][ti], ma[par][2], a2, 0, 0, 0);
+    }
+    B1[ti][tj] = a1;
+    B2[ti][tj] = a2;
   };
   // C products: acc[ti][tj] += U_m[ti] . GX[tj]
-  auto mfmaC = [&](const FragsC& fr, bool first) {
+  auto mfmaC = [&](int ti, int tj, int par, bool first) {
+    f4 a1 = first ? zero : C1[ti][tj], a2 = first ? zero : C2[ti][tj];
+    if constexpr (F32) {
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
-        if constexpr (F32) {
-          f4 a1 = first ? zero : C1[ti][tj];
-          f4 a2 = first ? zero : C2[ti][tj];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float x = el(fr.s[0][tj], fr.s[1][tj], j);
-            a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(el(fr.m1[0][ti], fr.m1[1][ti], j), x, a1, 0, 0, 0);
-            a2 = __builtin_amdgcn_mfma_f32_16x16x4f32(el(fr.m2[0][ti], fr.m2[1][ti], j), x, a2, 0, 0, 0);
-          }
-          C1[ti][tj] = a1;
-          C2[ti][tj] = a2;
-        } else {
-          f4 a1 = first ? zero : C1[ti][tj];
-          a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.m1[1][ti], fr.s[0][tj], a1, 0, 0, 0);
-          a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.m1[0][ti], fr.s[1][tj], a1, 0, 0, 0);
-          C1[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.m1[0][ti], fr.s[0][tj], a1, 0, 0, 0);
-          f4 a2 = first ? zero : C2[ti][tj];
-          a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.m2[1][ti], fr.s[0][tj], a2, 0, 0, 0);
-          a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.m2[0][ti], fr.s[1][tj], a2, 0, 0, 0);
-          C2[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fr.m2[0][ti], fr.s[0][tj], a2, 0, 0, 0);
-        }
+      for (int j = 0; j < 8; ++j) {
+        const float x = el(xs[0][tj], xs[1][tj], j);
+        a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(el(mu[par][0], mu[par][1], j), x, a1, 0, 0, 0);
+        a2 = __builtin_amdgcn_mfma_f32_16x16x4f32(el(mu[par][2], mu[par][3], j), x, a2, 0, 0, 0);
       }
+    } else {
+      a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(mu[par][1], xs[0][tj], a1, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(mu[par][0], xs[1][tj], a1, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(mu[par][0], xs[0][tj], a1, 0, 0, 0);
+      a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(mu[par][3], xs[0][tj], a2, 0, 0, 0);
+      a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(mu[par][2], xs[1][tj], a2, 0, 0, 0);
+      a2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(mu[par][2], xs[0][tj], a2, 0, 0, 0);
+    }
+    C1[ti][tj] = a1;
+    C2[ti][tj] = a2;
+  };
+  auto dupdate = [&](int ti, int tj) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      D[ti][tj][r] = fmaf(B1[ti][tj][r], C1[ti][tj][r], D[ti][tj][r]);
+      D[ti][tj][r] = fmaf(B2[ti][tj][r], C2[ti][tj][r], D[ti][tj][r]);
+    }
   };
 
-  // the partial sum of D: slot (wave, tile) of each lane, 64 lanes x 16 bytes
-  f4* const Dw = sD + wave * 16 * 64 + lane;
-  auto dzero = [&]() {
+  // A phase's steps: B takes the columns tj one by one, C the rows ti (a triangle from its
+  // short end, so that the last step, which has the most reads, is the longest).  share:
+  // the part of n items that slot s of S does.
+  auto row_of = [](int i) { return TRI ? TI - 1 - i : i; };
+  auto share = [](int n_items, int s, int S) { return s * n_items / S; };
+  int b0 = 0, b1 = HALF, b2 = 2 * HALF;   // buffers of B(t), C(t), B(t+1)
+  auto chunk = [&](auto first_c, auto last_c) {
+    constexpr bool first = decltype(first_c)::value, last = decltype(last_c)::value;
+    // (the offsets of the other rows are formed here, not kept in registers over the loops)
+    __asm__ volatile("" : "+v"(dR));
+    __asm__ volatile("" : "+v"(dU));
 #pragma unroll
-    for (int t = 0; t < TI * TJ; ++t) Dw[t * 64] = zero;
+    for (int i = 0; i < TJ; ++i) {
+      const bool end = i == TJ - 1;
+      if (end) {   // C(t) has landed, every wave has read B(t)
+        vm_lds_barrier<NB>();
+        next(pC, kC);
+        set_c();
+      }
+      const int tiles = TRI ? i + 1 : TI;
+      const int reads = end ? 4 + 2 * TJ : 4, pace = (reads + max(tiles - 1, 1) - 1) / max(tiles - 1, 1);
+      const int q0 = end ? 0 : share(NB, i + 1, TJ), q1 = end ? share(NC, 1, TI) : share(NB, i + 2, TJ);
+#pragma unroll
+      for (int u = 0; u < tiles; ++u) {
+#pragma unroll
+        for (int q = u * pace; q < min((u + 1) * pace, reads); ++q) {
+          if (end) readC(q, b1, 0, row_of(0));
+          else readB(q, b0, (i + 1) % 2, i + 1);
+        }
+#pragma unroll
+        for (int q = q0 + share(q1 - q0, u, tiles); q < q0 + share(q1 - q0, u + 1, tiles); ++q) {
+          if (end) dmaC(q, b0);
+          else dmaB(q, b2);
+        }
+        mfmaB(u, i, i % 2, first);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const bool end = i == TI - 1;
+      if (end) {   // B(t+1) has landed, every wave has read C(t)
+        vm_lds_barrier<NC>();
+        next(pB, kB);
+        set_b();
+      }
+      const int ti = row_of(i), tj0 = TRI ? ti : 0, tiles = TJ - tj0;
+      const int reads = end ? 4 + 2 * TI : 4, pace = (reads + max(tiles - 1, 1) - 1) / max(tiles - 1, 1);
+      const int q0 = end ? 0 : share(NC, i + 1, TI), q1 = end ? share(NB, 1, TJ) : share(NC, i + 2, TI);
+#pragma unroll
+      for (int u = 0; u < tiles; ++u) {
+#pragma unroll
+        for (int q = u * pace; q < min((u + 1) * pace, reads); ++q) {
+          if (end) readB(q, b2, 0, 0);
+          else readC(q, b1, (i + 1) % 2, row_of(i + 1));
+        }
+#pragma unroll
+        for (int q = q0 + share(q1 - q0, u, tiles); q < q0 + share(q1 - q0, u + 1, tiles); ++q) {
+          if (end) dmaB(q, b1);
+          else dmaC(q, b0);
+        }
+        mfmaC(ti, tj0 + u, i % 2, first);
+        if (last && i > 0) {   // D of the row before
+          const int tb = row_of(i - 1);
+#pragma unroll
+          for (int tj = 0; tj < TJ; ++tj)
+            if (tj >= (TRI ? tb : 0) && (tj - (TRI ? tb : 0)) * tiles / (TJ - (TRI ? tb : 0)) == u) dupdate(tb, tj);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (last) {
+      const int tb = row_of(TI - 1);
+#pragma unroll
+      for (int tj = TRI ? tb : 0; tj < TJ; ++tj) dupdate(tb, tj);
+    }
+    const int b = b2;
+    b2 = b1;
+    b1 = b0;
+    b0 = b;
   };
-  auto dupdate = [&]() {
+
+  // D tile -> partial tile z (FP32 store, or FP64 add unless first), 32 rows at a time
+  // through LDS so that rows are written in 16-byte pieces (of element alignment); the 16
+  // columns of a tile are permuted by the row, else its four row groups share banks
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef double d4u __attribute__((ext_vector_type(4), aligned(8)));
+  auto flush = [&](bool first) {
+    // (its addresses are computed here, not kept in registers over the k loops)
+    uint32_t all = ~0u;
+    __asm__ volatile("" : "+s"(all));
+    const int ft = 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+    const int fr = (ft & 15), fk = (ft >> 4) & 3, frow = ft >> 5, col = (ft & 31) * 4;
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
+    for (int ti = 0; ti < TI; ++ti) {
 #pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
-        f4 d = Dw[(ti * TJ + tj) * 64];
+      for (int tj = TRI ? ti : 0; tj < TJ; ++tj)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          d[r] = fmaf(B1[ti][tj][r], C1[ti][tj][r], d[r]);
-          d[r] = fmaf(B2[ti][tj][r], C2[ti][tj][r], d[r]);
+          sm.d[(wr * 16 + 4 * fk + r) * TT + ((((2 * tj + wc) ^ fk) << 4) | fr)] = D[ti][tj][r];
+          D[ti][tj][r] = 0.f;
         }
-        Dw[(ti * TJ + tj) * 64] = d;
-      }
-  };
-  // D tile -> partial tile z (FP32 store, or FP64 add unless first): thread t
-  // takes column P0 + t % 128 and rows R0 + t / 128 + 2 i, reading each element
-  // from the LDS slot of the lane that formed it (lane 16 (R % 16 / 4) + P % 16
-  // of wave 2 (R / 16 % 2) + P / 16 % 2, tile (R / 32, P / 32), element R % 4),
-  // so the global writes are coalesced rows.  Barriers before (other waves'
-  // slots) and after (the slots may be cleared next).
-  auto flush = [&](bool first) {
-    __syncthreads();
-    const float* sDf = reinterpret_cast<const float*>(sD);
-    const int Pt = tid & (TT - 1), P = P0 + Pt;
-    const int pslot = ((Pt >> 4) & 1) * 16 * 64 + (Pt >> 5) * 64 + (Pt & 15);
-    const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
-    for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
-      const int R = R0 + Rt;
-      if (R < naux && P < naux && (!TRI || (Rt >> 5) <= (Pt >> 5))) {
-        const int slot = pslot + ((Rt >> 4) & 1) * 2 * 16 * 64 + (Rt >> 5) * TJ * 64 + ((Rt >> 2) & 3) * 16;
-        const float v = sDf[slot * 4 + (Rt & 3)];
-        const int64_t o = zo + (int64_t)R * naux;
-        if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
-          reinterpret_cast<float*>(f.Dpart)[o] = v;
-        } else {
-          f.Dpart[o] = (first ? 0.0 : f.Dpart[o]) + (double)v;
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = frow + 8 * i;
+        const int R = R0 + 32 * ti + row, P = P0 + col;
+        if (R < naux && P < naux && (!TRI || ti <= (col >> 5))) {
+          const f4 v = *reinterpret_cast<const f4*>(&sm.d[row * TT + (col ^ (((row >> 2) & 3) << 4))]);
+          const int64_t o = set * f.d_set + (int64_t)z * naux * naux + (int64_t)R * naux + P;
+          const int left = naux - P;
+          if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
+            float* dst = reinterpret_cast<float*>(f.Dpart) + o;
+            if (left >= 4) {
+              *reinterpret_cast<f4u*>(dst) = v;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                if (e < left) dst[e] = v[e];
+            }
+          } else {
+            double* dst = f.Dpart + o;
+            if (left >= 4) {
+              d4u w = {v[0], v[1], v[2], v[3]};
+              if (!first) w += *reinterpret_cast<const d4u*>(dst);
+              *reinterpret_cast<d4u*>(dst) = w;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                if (e < left) dst[e] = (first ? 0.0 : dst[e]) + (double)v[e];
+            }
+          }
         }
       }
+      lds_barrier();
     }
-    __syncthreads();
   };
 
-  dzero();
-  // fetch cursor over (pair, chunk), clamped to the last chunk
-  int cp = 0, ck = 0;
-  auto advance = [&]() {
-    const bool last = (cp == npr - 1) && (ck == kst - 1);
-    const bool wrap = (ck == kst - 1);
-    ck = last ? ck : (wrap ? 0 : ck + 1);
-    if (wrap && !last) set_pair(++cp);
-  };
   if (npr > 0) {
-    set_pair(0);
-    dmaB(0);
-    dmaC(0);
-    advance();
-    vm_lds_barrier();
-    readB(fb);
-  }
-  // interleave a phase's 12 memory-to-LDS loads with its first MFMAs, one load
-  // per MPL of them: a load the texture unit cannot take yet stalls its wave,
-  // and with one wave per SIMD nothing else would keep the matrix core busy
-  // meanwhile, while loads issued late have less time to land (measured at n =
-  // 300: fp16x2, 96 MFMAs per phase, fastest at 3 of 1, 2, 3, 4, 8; FP32, 256
-  // MFMAs per phase, at 16 of 10, 12, 16, 21)
-  constexpr int NM = (F32 ? 16 : 6) * (TRI ? TI * (TI + 1) / 2 : TI * TJ);   // MFMAs per phase
-  auto spread = [&](auto loads) {
-    constexpr int L = decltype(loads)::value;
-    constexpr int MPL = F32 ? (NM / L < 16 ? NM / L : 16) : (NM / L < 3 ? NM / L : 3);
+    set_b();
+    set_c();
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);     // one memory instruction
-      __builtin_amdgcn_sched_group_barrier(0x008, MPL, 0);   // MPL MFMAs
-    }
-  };
-  auto chunk = [&](bool first) {
-    vm_lds_barrier();
-    dmaB(ck * KC);
-    readC(fc);
-    mfmaB(fb, first);
-    spread(std::integral_constant<int, TI + 2 * TJ>{});
-    vm_lds_barrier();
-    dmaC(ck * KC);
-    advance();
-    readB(fb);
-    mfmaC(fc, first);
-    spread(std::integral_constant<int, 2 * TI + TJ>{});
-  };
-  int done = 0;
-  for (int pr = 0; pr < npr; ++pr) {
-    chunk(true);
-    for (int k = 1; k < kst; ++k) chunk(false);
-    dupdate();
-    ++done;
-    if (done % FLUSH_PAIRS == 0 && pr + 1 < npr) {
-      flush(done == FLUSH_PAIRS);
-      dzero();
-    }
+    for (int q = 0; q < NB; ++q) dmaB(q, b0);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) dmaC(q, b1);
+    next(pB, kB);
+    set_b();
+    constexpr int SLOT = NB / TJ;   // share(NB, 1, TJ)
+#pragma unroll
+    for (int q = 0; q < SLOT; ++q) dmaB(q, b2);
+    vm_lds_barrier<NC + SLOT>();
+#pragma unroll
+    for (int q = 0; q < 4 + 2 * TI; ++q) readB(q, b0, 0, 0);
   }
+  const std::true_type yes;
+  const std::false_type no;
+  int pr = 0;
+  do {
+    if (npr > 0) {
+      if (kst == 1) {
+        chunk(yes, yes);
+      } else {
+        chunk(yes, no);
+        for (int k = 2; k < kst; ++k) chunk(no, no);
+        chunk(no, yes);
+      }
+      ++pr;
+    }
+    // (an empty range writes zeros)
+    if (pr == npr || pr % FLUSH_PAIRS == 0) flush(pr <= FLUSH_PAIRS);
+  } while (pr < npr);
   // the last (repeated) memory-to-LDS loads land before the workgroup may end
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  flush(done <= FLUSH_PAIRS);   // also writes zeros for an empty range
 }
 
 template <int M>
-__device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Half& sC, f4* sD) {
+__device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Smem& sm) {
   const int naux = f.naux;
 
   // tile and pair range: XCD-aware order (workgroup b runs on XCD b mod 8; each
@@ -418,11 +487,10 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
   // a THC point, and a diagonal tile of a symmetric D only its upper triangle.  Against
   // full 128 x 128 products everywhere: n = 149, naux = 797 (29 of the last 128), general,
   // FP32: 696 -> 590 us a tau point; n = 300, naux = 1800 (8 of 128), symmetric, fp16x2:
-  // 1927 -> 1833 us (the short tiles wait for memory: they take 0.75 of a full one's time
-  // for a quarter of its products)
+  // 1927 -> 1833 us
   const int tj = min((naux - P0 + 31) / 32, 4), ti = min((naux - R0 + 31) / 32, 4);
   const bool diag = symm && R0 == P0;
-#define THCSOX_TILE(TI, TJ, TRI) fused_tile<M, TI, TJ, TRI>(f, sB, sC, sD, set, z, R0, P0)
+#define THCSOX_TILE(TI, TJ, TRI) fused_tile<M, TI, TJ, TRI>(f, sm, set, z, R0, P0)
   if (diag) {
     if (tj == 4) THCSOX_TILE(4, 4, true);
     else if (tj == 3) THCSOX_TILE(3, 3, true);
@@ -447,18 +515,14 @@ __device__ __forceinline__ void fused_pair_body(const FusedArgs& f, Half& sB, Ha
 
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void fused_f16_kernel(FusedArgs f) {
-  __shared__ __attribute__((aligned(16))) Half sB;
-  __shared__ __attribute__((aligned(16))) Half sC;
-  __shared__ __attribute__((aligned(16))) f4 sD[NW * 16 * 64];
-  fused_pair_body<MODE_F16X2>(f, sB, sC, sD);
+  __shared__ __attribute__((aligned(16))) Smem sm;
+  fused_pair_body<MODE_F16X2>(f, sm);
 }
 
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void fused_f32_kernel(FusedArgs f) {
-  __shared__ __attribute__((aligned(16))) Half sB;
-  __shared__ __attribute__((aligned(16))) Half sC;
-  __shared__ __attribute__((aligned(16))) f4 sD[NW * 16 * 64];
-  fused_pair_body<MODE_F32>(f, sB, sC, sD);
+  __shared__ __attribute__((aligned(16))) Smem sm;
+  fused_pair_body<MODE_F32>(f, sm);
 }
 
 inline unsigned cdiv16(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }

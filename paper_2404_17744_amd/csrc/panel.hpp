@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // in inline assembly: the compiler does not track it, so it inserts no waits for
 // it before other LDS accesses (it cannot tell other LDS data apart from the
 // buffer being loaded).  The kernel waits for these loads itself (s_waitcnt
-// vmcnt(0) before each barrier) and touches the loaded buffer only after that
+// vmcnt before each barrier) and touches the loaded buffer only after that
 // barrier.  Nothing else in the kernel uses m0.
 __device__ __forceinline__ void dma16_untracked(const i4& rsrc, uint32_t lds, uint32_t voff,
                                                 uint32_t soff) {
