@@ -68,7 +68,7 @@ def fused_source_hash():
     import re
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2404_17744_amd", "csrc")
-    for f in ("fused_f16.hip", "panel.hpp", "mfma.hpp"):
+    for f in ("fused_f16.hip", "dtile.hpp", "panel.hpp", "mfma.hpp"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     with open(os.path.join(csrc, "kernels.hpp")) as fh:

@@ -10,28 +10,28 @@
 //
 // Work split.  A workgroup owns a 128 x 128 tile of D and a range of v, one v at
 // a time.  Four waves (one per SIMD) in a 2 x 2 arrangement each own 64 x 64 of
-// the tile: the accumulators of B and C (128 registers) live in the matrix-core
-// registers (AGPRs), the fragments of the three planes in the ordinary ones.  The
-// partial sum of D (FP32, at most 8 v) lives in LDS, one private 16-byte slot per
-// lane and MFMA tile, updated once per v: D += B o C.  (The fp16x2 kernel takes
-// two v per pass in the same registers and LDS: two planes of two v there, three
-// planes of one v here.)
+// the tile (16 x 16 tiles alternating between the waves of a row and of a column): the
+// accumulators of B and C (128 registers) live in the matrix-core
+// registers (AGPRs), the partial sum of D (FP32, at most 8 v) and the fragments of the
+// three planes in the ordinary ones.  D is updated once per v: D += B o C.  (The fp16x2
+// kernel takes two v per pass: two planes of two v there, three planes of one v here.)
 //
-// Pipeline.  A k chunk is two half stages, each two panels of 128 rows x 32 k x
-// 3 planes (48 KiB): the B half (G, A_v) in LDS buffer sB and the C half (GX,
-// U_v) in sC; with 64 KiB for D the workgroup uses the full 160 KiB of LDS.  A
-// plane of a panel is 128 rows of 64 bytes, each row's four 16-byte chunks
-// placed by lds_chunk.  Chunk t runs as
-//   phase B(t): barrier (C(t) is in sC, every wave has read B(t) from sB);
-//               loads of B(t+1) -> sB; fragments of C(t) <- sC;
-//               matrix cores: B += products of B(t) (fragments read before)
-//   phase C(t): barrier (B(t+1) is in sB, every wave has read C(t) from sC);
-//               loads of C(t+1) -> sC; fragments of B(t+1) <- sB;
-//               matrix cores: C += products of C(t)
-// so each half stage is loaded one phase ahead of its fragment reads, and each
-// fragment is read one phase ahead of its products.  The first chunk of a v
-// starts the accumulators from zero inside the MFMA.  Past the last chunk the
-// loads repeat it (never used).
+// Pipeline: that of the fp16x2 kernel.  A k chunk is two phases, B (G, A_v) and C (GX,
+// U_v), each of which reads a half stage of two panels of 128 rows x 32 k x 3 planes (48
+// KiB; a plane of a panel is 128 rows of 64 bytes, each row's four 16-byte chunks placed
+// by lds_chunk).  LDS holds three half stages and 16 KiB through which D goes to memory.
+// A phase forms its 4 x 4 tiles in four steps, a column (B) or a row (C) of them each; the
+// fragments of G or GX are read for the whole phase, those of A or U one step ahead.
+// Before the last step of a phase every wave waits for the next half stage and at the
+// workgroup barrier, then reads that step's fragments of the next phase and begins to
+// load the half stage after the next two into the buffer that the barrier set free: a
+// load has two phases to land.  n = 120, naux = 600: 181 -> 146 us a tau point against
+// two buffers with D in LDS and loads one phase ahead.  The first chunk of a v starts the
+// accumulators from zero inside the MFMA.  Past the last chunk the loads repeat it
+// (never used).
+#include <type_traits>
+
+#include "dtile.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
 #include "panel.hpp"
@@ -39,7 +39,6 @@
 namespace thcsox {
 namespace {
 
-constexpr int TT = 128;          // tile edge of D (R and P)
 constexpr int NW = 4, NTH = 64 * NW;
 constexpr int KC = 32;           // k per chunk (one bf16 MFMA)
 constexpr int NPL = 3;           // bf16 planes
@@ -49,28 +48,27 @@ constexpr int NXCD = 8;
 
 // One half stage: panel 0 is the v-independent operand (G or GX), panel 1 the
 // per-v one (A_v or U_v); [panel][plane][row * 32 + k].
-struct Half3 {
-  __bf16 s[2][NPL][PP];
+constexpr int HALF3 = 2 * NPL * PP;   // elements
+struct Smem3 {
+  __bf16 st[3 * HALF3];   // the half stages of three phases
+  float d[32 * TT];       // 32 rows of D on their way to memory
 };
 
-__device__ __forceinline__ void bf3_vm_lds_barrier() {
-  // this wave's memory loads (including those that write LDS) and LDS accesses
-  // complete, then the workgroup barrier
-  __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// One tile's range of v.  sB: G, A_v; sC: GX, U_v; sD: the partial sum of D.  Each wave
-// forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the rows R of the workgroup's tile
+// One tile's range of v.  Each wave forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the rows R of the workgroup's tile
 // beyond 32 TI and the columns P beyond 32 TJ lie past naux and are neither loaded nor
 // multiplied.  TRI: a diagonal tile of a symmetric D, of which only the 16 x 16 tiles ti
 // <= tj of each wave are formed: they hold every element on and above the diagonal.  (A
 // D element's products and their order do not depend on TI, TJ and TRI.)
 template <int TI, int TJ, bool TRI>
-__device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Half3& sC, f4* sD, int set,
-                                               int z, int R0, int P0) {
+__device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Smem3& sm, int set, int z, int R0,
+                                               int P0) {
   int tid = threadIdx.x;
   // (the compiler must not merge the forms' address arithmetic above their branch)
-  __asm__ volatile("" : "+v"(tid), "+s"(set), "+s"(z), "+s"(R0), "+s"(P0));
+  __asm__ volatile("" : "+v"(tid));
+  __asm__ volatile("" : "+s"(set));
+  __asm__ volatile("" : "+s"(z));
+  __asm__ volatile("" : "+s"(R0));
+  __asm__ volatile("" : "+s"(P0));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 1, wc = wave & 1;
@@ -85,65 +83,56 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
   const int kst = ldk / KC;
   const int rows_r = min(TT, naux - R0), rows_p = min(TT, naux - P0);
 
-  // operand planes (rows past the valid range lie beyond the buffer resources
-  // and read as zero)
-  const __bf16* Gt = static_cast<const __bf16*>(f.Gt) + set * f.g_set;
-  const __bf16* GX = static_cast<const __bf16*>(f.GXt) + set * f.g_set;
-  const __bf16* Ub = static_cast<const __bf16*>(f.U);
-  const __bf16* Ab = static_cast<const __bf16*>(f.A) + set * f.a_set;
-  __amdgpu_buffer_rsrc_t rG[NPL], rX[NPL];
-#pragma unroll
-  for (int p = 0; p < NPL; ++p) {
-    rG[p] = make_rsrc(Gt + p * f.g_plane + (int64_t)R0 * ldk, (int64_t)rows_r * ldk * 2);
-    rX[p] = make_rsrc(GX + p * f.g_plane + (int64_t)P0 * ldk, (int64_t)rows_p * ldk * 2);
-  }
-  const int64_t a_bytes = (int64_t)rows_p * ldk * 2;
-  const int64_t u_bytes = ((int64_t)(rows_r - 1) * n * ldk + ldk) * 2;
-  // per v: A rows (v, P) and U rows (R, v)
-  __amdgpu_buffer_rsrc_t rA[NPL], rU[NPL];
-  auto set_v = [&](int iv) {
-    const int v = v_lo + iv;
-#pragma unroll
-    for (int p = 0; p < NPL; ++p) {
-      rA[p] = make_rsrc(Ab + p * f.a_plane + ((int64_t)v * naux + P0) * ldk, a_bytes);
-      rU[p] = make_rsrc(Ub + p * f.u_plane + ((int64_t)R0 * n + v) * ldk, u_bytes);
-    }
-  };
+  // operands, plane 0 (rows past the valid range lie beyond the buffer resources and read
+  // as zero; byte counts below 2^31: checked by the launcher)
+  const __bf16* Gt = static_cast<const __bf16*>(f.Gt) + set * f.g_set + (int64_t)R0 * ldk;
+  const __bf16* GX = static_cast<const __bf16*>(f.GXt) + set * f.g_set + (int64_t)P0 * ldk;
+  const __bf16* Ub = static_cast<const __bf16*>(f.U) + (int64_t)R0 * n * ldk;
+  const __bf16* Ab = static_cast<const __bf16*>(f.A) + set * f.a_set + (int64_t)P0 * ldk;
+  const int r_bytes = rows_r * ldk * 2, p_bytes = rows_p * ldk * 2;
+  const int u_bytes = ((rows_r - 1) * n * ldk + ldk) * 2;
 
   // memory -> LDS: one instruction moves 16 rows x 64 bytes of one plane; wave w
   // moves the 16-row slabs w and w + 4 of each plane of each panel.  Lane l
   // lands at slab row l / 4, physical chunk l % 4, and loads the logical chunk
   // lds_chunk maps there (the map is its own inverse for a given row).
-  uint32_t dR[2], dU[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = (wave + NW * j) * 16 + (lane >> 2);
-    const int c = lds_chunk(row, lane & 3);
-    dR[j] = (uint32_t)((row * ldk + 8 * c) * 2);
-    dU[j] = (uint32_t)((row * (n * ldk) + 8 * c) * 2);
-  }
-  auto dmaB = [&](int k0) {
-    const int so = k0 * 2;   // bytes to the k chunk
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int slab = (wave + NW * j) * 16 * 32;
-#pragma unroll
-      for (int p = 0; p < NPL; ++p) {
-        if (2 * j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rG[p], &sB.s[0][p][slab], 16, dR[j], so, 0, 0);
-        if (2 * j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA[p], &sB.s[1][p][slab], 16, dR[j], so, 0, 0);
-      }
+  const int drow = wave * 16 + (lane >> 2), dch = 8 * lds_chunk(drow, lane & 3);
+  uint32_t dR = (uint32_t)((drow * ldk + dch) * 2), dU = (uint32_t)((drow * (n * ldk) + dch) * 2);
+  const uint32_t sR = 64 * ldk * 2, sU = sR * n;   // 64 rows further (the same chunks)
+  // fetch cursors (v, k chunk) of the two kinds of half stages, clamped to the last chunk
+  // (no branch: one would keep a phase's loads and MFMAs apart)
+  int vB = 0, kB = 0, vC = 0, kC = 0;
+  auto next = [&](int& v, int& k) {
+    const bool wrap = k == kst - 1, last = wrap && v == nv - 1;
+    k = last ? k : (wrap ? 0 : k + 1);
+    v += wrap && !last ? 1 : 0;
+  };
+  // loads q of a half stage into the buffer at sm.st + buf: the slabs of the panel of rows
+  // and of the panel of columns, three planes each
+  constexpr int LR = NPL * (TI > 2 ? 2 : 1), LP = NPL * (TJ > 2 ? 2 : 1), NL = LR + LP;
+  auto dst = [&](int buf, int panel, int p, int j) {
+    return lds_addr(sm.st) + (uint32_t)(buf + (panel * NPL + p) * PP + (wave + NW * j) * 16 * 32) * 2;
+  };
+  auto dmaB = [&](int q, int buf) {
+    const int so = kB * KC * 2, p = q % NPL;   // bytes to the k chunk; plane
+    if (q < LR) {
+      const int j = q / NPL;
+      dma16_untracked(raw_rsrc(Gt + p * f.g_plane, r_bytes), dst(buf, 0, p, j), dR + j * sR, so);
+    } else {
+      const int j = (q - LR) / NPL;
+      dma16_untracked(raw_rsrc(Ab + p * f.a_plane + (int64_t)(v_lo + vB) * naux * ldk, p_bytes),
+                      dst(buf, 1, p, j), dR + j * sR, so);
     }
   };
-  auto dmaC = [&](int k0) {
-    const int so = k0 * 2;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int slab = (wave + NW * j) * 16 * 32;
-#pragma unroll
-      for (int p = 0; p < NPL; ++p) {
-        if (2 * j < TJ) __builtin_amdgcn_raw_ptr_buffer_load_lds(rX[p], &sC.s[0][p][slab], 16, dR[j], so, 0, 0);
-        if (2 * j < TI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rU[p], &sC.s[1][p][slab], 16, dU[j], so, 0, 0);
-      }
+  auto dmaC = [&](int q, int buf) {
+    const int so = kC * KC * 2, p = q % NPL;
+    if (q < LP) {
+      const int j = q / NPL;
+      dma16_untracked(raw_rsrc(GX + p * f.g_plane, p_bytes), dst(buf, 0, p, j), dR + j * sR, so);
+    } else {
+      const int j = (q - LP) / NPL;
+      dma16_untracked(raw_rsrc(Ub + p * f.u_plane + (int64_t)(v_lo + vC) * ldk, u_bytes),
+                      dst(buf, 1, p, j), dU + j * sU, so);
     }
   };
 
@@ -151,179 +140,172 @@ __device__ __forceinline__ void fused_bf3_tile(const FusedArgs& f, Half3& sB, Ha
   // The 16 x 16 tiles alternate between the two waves of a row or column, so both work in
   // a short tile; the map repeats every 32 rows, so tile t is 32 t rows further.
   const int lr = lane & 15, kc = lane >> 4;
-  const int fR = (wr * 16 + lr) * 32 + lds_chunk(wr * 16 + lr, kc) * 8;   // R side rows
-  const int fP = (wc * 16 + lr) * 32 + lds_chunk(wc * 16 + lr, kc) * 8;   // P side rows
-  // fragments of one half stage: the shared operand s (G or GX) and the per-v
-  // operand m (A_v or U_v), [plane][tile]
-  struct FragsB { bf16x8 s[NPL][TI], m[NPL][TJ]; } fb;
-  struct FragsC { bf16x8 s[NPL][TJ], m[NPL][TI]; } fc;
-  auto rd = [&](const __bf16* base, int off, int t) {
-    return *reinterpret_cast<const bf16x8*>(base + off + t * 32 * 32);
+  const int oR = (wr * 16 + lr) * 32 + lds_chunk(wr * 16 + lr, kc) * 8;   // R side rows
+  const int oP = (wc * 16 + lr) * 32 + lds_chunk(wc * 16 + lr, kc) * 8;   // P side rows
+  // fragments: G and GX of a whole phase [plane][tile]; A and U of one tile column or row at
+  // a time, [step parity][plane]
+  bf16x8 gs[NPL][TI], xs[NPL][TJ], ma[2][NPL], mu[2][NPL];
+  auto rd = [&](int buf, int panel, int p, int off, int t) {
+    return *reinterpret_cast<const bf16x8*>(sm.st + buf + (panel * NPL + p) * PP + off + t * 32 * 32);
   };
-  auto readB = [&](FragsB& fr) {   // G (R side), A_v (P side)
-#pragma unroll
-    for (int p = 0; p < NPL; ++p)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        if (t < TI) fr.s[p][t] = rd(sB.s[0][p], fR, t);
-        if (t < TJ) fr.m[p][t] = rd(sB.s[1][p], fP, t);
-      }
+  // reads q of what a step takes and, from q = 3 on, of what a phase takes
+  auto readB = [&](int q, int buf, int par, int t) {
+    if (q < NPL) ma[par][q] = rd(buf, 1, q, oP, t);
+    else gs[q % NPL][q / NPL - 1] = rd(buf, 0, q % NPL, oR, q / NPL - 1);
   };
-  auto readC = [&](FragsC& fr) {   // GX (P side), U_v (R side)
-#pragma unroll
-    for (int p = 0; p < NPL; ++p)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        if (t < TJ) fr.s[p][t] = rd(sC.s[0][p], fP, t);
-        if (t < TI) fr.m[p][t] = rd(sC.s[1][p], fR, t);
-      }
+  auto readC = [&](int q, int buf, int par, int t) {
+    if (q < NPL) mu[par][q] = rd(buf, 1, q, oR, t);
+    else xs[q % NPL][q / NPL - 1] = rd(buf, 0, q % NPL, oP, q / NPL - 1);
   };
 
-  // accumulators [ti][tj]: rows R of tile ti, columns P of tile tj (cleared once
-  // here; each v then starts them from zero inside its first MFMAs)
-  f4 B[TI][TJ], C[TI][TJ];
+  // accumulators [ti][tj]: rows R of tile ti, columns P of tile tj (each v starts them
+  // from zero inside its first MFMAs), and the partial sum of D
+  f4 B[TI][TJ], C[TI][TJ], D[TI][TJ];
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-    for (int tj = TRI ? ti : 0; tj < TJ; ++tj) B[ti][tj] = C[ti][tj] = zero;
+    for (int tj = TRI ? ti : 0; tj < TJ; ++tj) B[ti][tj] = C[ti][tj] = D[ti][tj] = zero;
   using PR = Products<NPL>;   // plane pairs, smallest terms first
   // B products: B[ti][tj] += G[ti] . A_v[tj]
-  auto mfmaB = [&](const FragsB& fr, bool first) {
+  auto mfmaB = [&](int ti, int tj, int par, bool first) {
+    f4 a = first ? zero : B[ti][tj];
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
-        f4 a = first ? zero : B[ti][tj];
-#pragma unroll
-        for (int q = 0; q < PR::N; ++q)
-          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.s[PR::a(q)][ti], fr.m[PR::b(q)][tj], a,
-                                                      0, 0, 0);
-        B[ti][tj] = a;
-      }
+    for (int q = 0; q < PR::N; ++q)
+      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gs[PR::a(q)][ti], ma[par][PR::b(q)], a, 0, 0, 0);
+    B[ti][tj] = a;
   };
   // C products: C[ti][tj] += U_v[ti] . GX[tj]
-  auto mfmaC = [&](const FragsC& fr, bool first) {
+  auto mfmaC = [&](int ti, int tj, int par, bool first) {
+    f4 a = first ? zero : C[ti][tj];
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
+    for (int q = 0; q < PR::N; ++q)
+      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mu[par][PR::a(q)], xs[PR::b(q)][tj], a, 0, 0, 0);
+    C[ti][tj] = a;
+  };
+  auto dupdate = [&](int ti, int tj) {
 #pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
-        f4 a = first ? zero : C[ti][tj];
-#pragma unroll
-        for (int q = 0; q < PR::N; ++q)
-          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.m[PR::a(q)][ti], fr.s[PR::b(q)][tj], a,
-                                                      0, 0, 0);
-        C[ti][tj] = a;
-      }
+    for (int r = 0; r < 4; ++r) D[ti][tj][r] = fmaf(B[ti][tj][r], C[ti][tj][r], D[ti][tj][r]);
   };
 
-  // the partial sum of D: slot (wave, tile) of each lane, 64 lanes x 16 bytes
-  f4* const Dw = sD + wave * 16 * 64 + lane;
-  auto dzero = [&]() {
+  // A phase's steps: B takes the columns tj one by one, C the rows ti (a triangle from its
+  // short end, so that the last step, which has the most reads, is the longest).  share:
+  // what slots 0 .. s - 1 of S do of n items.
+  auto row_of = [](int i) { return TRI ? TI - 1 - i : i; };
+  auto share = [](int n_items, int s, int S) { return s * n_items / S; };
+  int b0 = 0, b1 = HALF3, b2 = 2 * HALF3;   // buffers of B(t), C(t), B(t+1)
+  auto chunk = [&](auto first_c, auto last_c) {
+    constexpr bool first = decltype(first_c)::value, last = decltype(last_c)::value;
+    // (the offsets of the other rows are formed here, not kept in registers over the loops)
+    __asm__ volatile("" : "+v"(dR));
+    __asm__ volatile("" : "+v"(dU));
 #pragma unroll
-    for (int tt = 0; tt < TI * TJ; ++tt) Dw[tt * 64] = zero;
-  };
-  auto dupdate = [&]() {
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj) {
-        f4 d = Dw[(ti * TJ + tj) * 64];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) d[r] = fmaf(B[ti][tj][r], C[ti][tj][r], d[r]);
-        Dw[(ti * TJ + tj) * 64] = d;
+    for (int i = 0; i < TJ; ++i) {
+      const bool end = i == TJ - 1;
+      if (end) {   // C(t) has landed, every wave has read B(t)
+        vm_lds_barrier<NL>();
+        next(vC, kC);
       }
-  };
-  // D tile -> partial tile z (FP32 store, or FP64 add unless first): thread t
-  // takes column P0 + t % 128 and rows R0 + t / 128 + 2 i, reading each element
-  // from the LDS slot of the lane that formed it (lane 16 (R % 16 / 4) + P % 16
-  // of wave 2 (R / 16 % 2) + P / 16 % 2, tile (R / 32, P / 32), element R % 4),
-  // so the global writes are coalesced rows.  Barriers before (other waves'
-  // slots) and after (the slots may be cleared next).
-  auto flush = [&](bool first) {
-    __syncthreads();
-    const float* sDf = reinterpret_cast<const float*>(sD);
-    const int Pt = tid & (TT - 1), P = P0 + Pt;
-    const int pslot = ((Pt >> 4) & 1) * 16 * 64 + (Pt >> 5) * 64 + (Pt & 15);
-    const int64_t zo = set * f.d_set + (int64_t)z * naux * naux + P;
-    for (int Rt = tid >> 7; Rt < TT; Rt += NTH / TT) {
-      const int R = R0 + Rt;
-      if (R < naux && P < naux && (!TRI || (Rt >> 5) <= (Pt >> 5))) {
-        const int slot = pslot + ((Rt >> 4) & 1) * 2 * 16 * 64 + (Rt >> 5) * TJ * 64 + ((Rt >> 2) & 3) * 16;
-        const float v = sDf[slot * 4 + (Rt & 3)];
-        const int64_t o = zo + (int64_t)R * naux;
-        if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
-          reinterpret_cast<float*>(f.Dpart)[o] = v;
-        } else {
-          f.Dpart[o] = (first ? 0.0 : f.Dpart[o]) + (double)v;
+      const int tiles = TRI ? i + 1 : TI;
+      const int reads = end ? NPL + NPL * TJ : NPL, pace = (reads + max(tiles - 1, 1) - 1) / max(tiles - 1, 1);
+      const int q0 = end ? 0 : share(NL, i + 1, TJ), q1 = end ? share(NL, 1, TI) : share(NL, i + 2, TJ);
+#pragma unroll
+      for (int u = 0; u < tiles; ++u) {
+#pragma unroll
+        for (int q = u * pace; q < min((u + 1) * pace, reads); ++q) {
+          if (end) readC(q, b1, 0, row_of(0));
+          else readB(q, b0, (i + 1) % 2, i + 1);
         }
+#pragma unroll
+        for (int q = q0 + share(q1 - q0, u, tiles); q < q0 + share(q1 - q0, u + 1, tiles); ++q) {
+          if (end) dmaC(q, b0);
+          else dmaB(q, b2);
+        }
+        mfmaB(u, i, i % 2, first);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const bool end = i == TI - 1;
+      if (end) {   // B(t+1) has landed, every wave has read C(t)
+        vm_lds_barrier<NL>();
+        next(vB, kB);
+      }
+      const int ti = row_of(i), tj0 = TRI ? ti : 0, tiles = TJ - tj0;
+      const int reads = end ? NPL + NPL * TI : NPL, pace = (reads + max(tiles - 1, 1) - 1) / max(tiles - 1, 1);
+      const int q0 = end ? 0 : share(NL, i + 1, TI), q1 = end ? share(NL, 1, TJ) : share(NL, i + 2, TI);
+#pragma unroll
+      for (int u = 0; u < tiles; ++u) {
+#pragma unroll
+        for (int q = u * pace; q < min((u + 1) * pace, reads); ++q) {
+          if (end) readB(q, b2, 0, 0);
+          else readC(q, b1, (i + 1) % 2, row_of(i + 1));
+        }
+#pragma unroll
+        for (int q = q0 + share(q1 - q0, u, tiles); q < q0 + share(q1 - q0, u + 1, tiles); ++q) {
+          if (end) dmaB(q, b1);
+          else dmaC(q, b0);
+        }
+        mfmaC(ti, tj0 + u, i % 2, first);
+        if (last && i > 0) {   // D of the row before
+          const int tb = row_of(i - 1), t0 = TRI ? tb : 0;
+#pragma unroll
+          for (int tj = 0; tj < TJ; ++tj)
+            if (tj >= t0 && (tj - t0) * tiles / (TJ - t0) == u) dupdate(tb, tj);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (last) {
+      const int tb = row_of(TI - 1);
+#pragma unroll
+      for (int tj = TRI ? tb : 0; tj < TJ; ++tj) dupdate(tb, tj);
+    }
+    const int b = b2;
+    b2 = b1;
+    b1 = b0;
+    b0 = b;
   };
 
-  dzero();
-  // fetch cursor over (v, chunk), clamped to the last chunk
-  int cv = 0, ck = 0;
-  auto advance = [&]() {
-    const bool last = (cv == nv - 1) && (ck == kst - 1);
-    const bool wrap = (ck == kst - 1);
-    ck = last ? ck : (wrap ? 0 : ck + 1);
-    if (wrap && !last) set_v(++cv);
-  };
   if (nv > 0) {
-    set_v(0);
-    dmaB(0);
-    dmaC(0);
-    advance();
-    bf3_vm_lds_barrier();
-    readB(fb);
-  }
-  // spread a phase's memory-to-LDS loads over its MFMAs: 12 over 96 in a full tile
-  constexpr int NR = TI > 2 ? 6 : 3, NP = TJ > 2 ? 6 : 3;   // loads of a panel of rows, of columns
-  auto spread = [&]() {
-    constexpr int NM = PR::N * (TRI ? TI * (TI + 1) / 2 : TI * TJ);
-    constexpr int MPL = NM / (NR + NP) < 8 ? NM / (NR + NP) : 8;
 #pragma unroll
-    for (int i = 0; i < NR + NP; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);     // one memory instruction
-      __builtin_amdgcn_sched_group_barrier(0x008, MPL, 0);   // MPL MFMAs
-    }
-  };
-  auto chunk = [&](bool first) {
-    bf3_vm_lds_barrier();
-    dmaB(ck * KC);
-    readC(fc);
-    mfmaB(fb, first);
-    spread();
-    bf3_vm_lds_barrier();
-    dmaC(ck * KC);
-    advance();
-    readB(fb);
-    mfmaC(fc, first);
-    spread();
-  };
-  int done = 0;
-  for (int iv = 0; iv < nv; ++iv) {
-    chunk(true);
-    for (int k = 1; k < kst; ++k) chunk(false);
-    dupdate();
-    ++done;
-    if (done % FLUSH_V == 0 && iv + 1 < nv) {
-      flush(done == FLUSH_V);
-      dzero();
-    }
+    for (int q = 0; q < NL; ++q) dmaB(q, b0);
+#pragma unroll
+    for (int q = 0; q < NL; ++q) dmaC(q, b1);
+    next(vB, kB);
+    constexpr int SLOT = NL / TJ;   // share(NL, 1, TJ)
+#pragma unroll
+    for (int q = 0; q < SLOT; ++q) dmaB(q, b2);
+    vm_lds_barrier<NL + SLOT>();
+#pragma unroll
+    for (int q = 0; q < NPL + NPL * TI; ++q) readB(q, b0, 0, 0);
   }
+  const std::true_type yes;
+  const std::false_type no;
+  int iv = 0;
+  do {
+    if (nv > 0) {
+      if (kst == 1) {
+        chunk(yes, yes);
+      } else {
+        chunk(yes, no);
+        for (int k = 2; k < kst; ++k) chunk(no, no);
+        chunk(no, yes);
+      }
+      ++iv;
+    }
+    // (an empty range writes zeros)
+    if (iv == nv || iv % FLUSH_V == 0)
+      store_d<TI, TJ, TRI>(D, sm.d, f, set, z, R0, P0, wave, iv <= FLUSH_V);
+  } while (iv < nv);
   // the last (repeated) memory-to-LDS loads land before the workgroup may end
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  flush(done <= FLUSH_V);   // also writes zeros for an empty range
 }
 
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void fused_bf3_kernel(FusedArgs f) {
-  __shared__ __attribute__((aligned(16))) Half3 sB;
-  __shared__ __attribute__((aligned(16))) Half3 sC;
-  __shared__ __attribute__((aligned(16))) f4 sD[NW * 16 * 64];
+  __shared__ __attribute__((aligned(16))) Smem3 sm;
   const int naux = f.naux;
 
   // tile and v range: XCD-aware order (workgroup b runs on XCD b mod 8; each XCD
@@ -365,7 +347,7 @@ void fused_bf3_kernel(FusedArgs f) {
   // tau point at n = 120, naux = 600 (88 of the last 128), general
   const int tj = min((naux - P0 + 31) / 32, 4), ti = min((naux - R0 + 31) / 32, 4);
   const bool diag = symm && R0 == P0;
-#define THCSOX_TILE(TI, TJ, TRI) fused_bf3_tile<TI, TJ, TRI>(f, sB, sC, sD, set, z, R0, P0)
+#define THCSOX_TILE(TI, TJ, TRI) fused_bf3_tile<TI, TJ, TRI>(f, sm, set, z, R0, P0)
   if (diag) {
     if (tj == 4) THCSOX_TILE(4, 4, true);
     else if (tj == 3) THCSOX_TILE(3, 3, true);

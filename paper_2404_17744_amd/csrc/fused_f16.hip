@@ -46,6 +46,7 @@
 // repeat it (never used).
 #include <type_traits>
 
+#include "dtile.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
 #include "panel.hpp"
@@ -53,7 +54,6 @@
 namespace thcsox {
 namespace {
 
-constexpr int TT = 128;          // tile edge of D (R and P)
 constexpr int NW = 4, NTH = 64 * NW;
 constexpr int KC = 32;           // k per chunk (one f16 MFMA)
 constexpr int PANEL = TT * KC * 2;   // halves per panel (both planes)
@@ -73,17 +73,6 @@ struct Smem {
 // chunk with (r / 2) mod 8 places the 16 rows' chunks at all eight positions of
 // two consecutive 128-byte rows (rocprofv3 counts no LDS bank conflicts).
 __device__ __forceinline__ int sw8(int r, int c) { return c ^ ((r >> 1) & 7); }
-
-// All but the newest LEFT of this wave's memory loads (including those that write LDS)
-// and all of its LDS accesses complete, then the workgroup barrier.
-template <int LEFT>
-__device__ __forceinline__ void vm_lds_barrier() {
-  __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
-}
-// The same for the LDS accesses alone.
-__device__ __forceinline__ void lds_barrier() {
-  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 // One tile's range of pairs.  M = MODE_F16X2 or MODE_F32.  Each wave forms TI x TJ tiles of 16 x 16 out of its 4 x 4: the
 // rows R of the workgroup's tile beyond 32 TI and the columns P beyond 32 TJ lie past
@@ -270,7 +259,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Smem& sm, int set
 
   // A phase's steps: B takes the columns tj one by one, C the rows ti (a triangle from its
   // short end, so that the last step, which has the most reads, is the longest).  share:
-  // the part of n items that slot s of S does.
+  // what slots 0 .. s - 1 of S do of n items.
   auto row_of = [](int i) { return TRI ? TI - 1 - i : i; };
   auto share = [](int n_items, int s, int S) { return s * n_items / S; };
   int b0 = 0, b1 = HALF, b2 = 2 * HALF;   // buffers of B(t), C(t), B(t+1)
@@ -350,62 +339,6 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Smem& sm, int set
     b0 = b;
   };
 
-  // D tile -> partial tile z (FP32 store, or FP64 add unless first), 32 rows at a time
-  // through LDS so that rows are written in 16-byte pieces (of element alignment); the 16
-  // columns of a tile are permuted by the row, else its four row groups share banks
-  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-  typedef double d4u __attribute__((ext_vector_type(4), aligned(8)));
-  auto flush = [&](bool first) {
-    // (its addresses are computed here, not kept in registers over the k loops)
-    uint32_t all = ~0u;
-    __asm__ volatile("" : "+s"(all));
-    const int ft = 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
-    const int fr = (ft & 15), fk = (ft >> 4) & 3, frow = ft >> 5, col = (ft & 31) * 4;
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti) {
-#pragma unroll
-      for (int tj = TRI ? ti : 0; tj < TJ; ++tj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          sm.d[(wr * 16 + 4 * fk + r) * TT + ((((2 * tj + wc) ^ fk) << 4) | fr)] = D[ti][tj][r];
-          D[ti][tj][r] = 0.f;
-        }
-      lds_barrier();
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = frow + 8 * i;
-        const int R = R0 + 32 * ti + row, P = P0 + col;
-        if (R < naux && P < naux && (!TRI || ti <= (col >> 5))) {
-          const f4 v = *reinterpret_cast<const f4*>(&sm.d[row * TT + (col ^ (((row >> 2) & 3) << 4))]);
-          const int64_t o = set * f.d_set + (int64_t)z * naux * naux + (int64_t)R * naux + P;
-          const int left = naux - P;
-          if (f.dpart_f32) {   // one range = one FP32 partial sum (first is true)
-            float* dst = reinterpret_cast<float*>(f.Dpart) + o;
-            if (left >= 4) {
-              *reinterpret_cast<f4u*>(dst) = v;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 3; ++e)
-                if (e < left) dst[e] = v[e];
-            }
-          } else {
-            double* dst = f.Dpart + o;
-            if (left >= 4) {
-              d4u w = {v[0], v[1], v[2], v[3]};
-              if (!first) w += *reinterpret_cast<const d4u*>(dst);
-              *reinterpret_cast<d4u*>(dst) = w;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 3; ++e)
-                if (e < left) dst[e] = (first ? 0.0 : dst[e]) + (double)v[e];
-            }
-          }
-        }
-      }
-      lds_barrier();
-    }
-  };
-
   if (npr > 0) {
     set_b();
     set_c();
@@ -437,7 +370,8 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& f, Smem& sm, int set
       ++pr;
     }
     // (an empty range writes zeros)
-    if (pr == npr || pr % FLUSH_PAIRS == 0) flush(pr <= FLUSH_PAIRS);
+    if (pr == npr || pr % FLUSH_PAIRS == 0)
+      store_d<TI, TJ, TRI>(D, sm.d, f, set, z, R0, P0, wave, pr <= FLUSH_PAIRS);
   } while (pr < npr);
   // the last (repeated) memory-to-LDS loads land before the workgroup may end
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
