@@ -22,17 +22,30 @@ __device__ __forceinline__ double pow2_scale(const unsigned long long* amax) {
 // ---------------------------------------------------------------------------
 // Small kernels
 // ---------------------------------------------------------------------------
+// Several arrays split in one launch (a launch of a few microseconds is mostly its own
+// latency): blocks first[q] .. first[q + 1] - 1 take job q.  A block takes NT / wide rows of
+// wide >= ldk threads each (one row of NT threads from ldk > NT / 2 on).
+struct SplitJobs {
+  SplitArgs job[SPLIT_JOBS];
+  int first[SPLIT_JOBS];   // blocks before job q
+  int wide[SPLIT_JOBS];
+};
 template <int M>
-__global__ __launch_bounds__(NT) void split_kernel(SplitArgs a) {
+__global__ __launch_bounds__(NT) void split_kernel(SplitJobs jobs, int njobs) {
   using T = typename ModeT<M>::T;
   constexpr int NP = ModeT<M>::NP;
-  const int64_t row = blockIdx.x;
+  int q = 0;
+  while (q + 1 < njobs && (int)blockIdx.x >= jobs.first[q + 1]) ++q;
+  const SplitArgs& a = jobs.job[q];
+  const int wide = jobs.wide[q];
+  const int64_t row = (int64_t)(blockIdx.x - jobs.first[q]) * (NT / wide) + threadIdx.x / wide;
+  if (row >= (int64_t)a.rows1 * a.rows2) return;
   const int64_t r1 = row / a.rows2, r2 = row % a.rows2;
   const double sc = pow2_scale(a.amax ? a.amax + r2 * a.amax_s2 : nullptr);
   T* dst = static_cast<T*>(a.dst);
   const int64_t so = r1 * a.s1 + r2 * a.s2;
   const int64_t dof = r1 * a.d1 + r2 * a.d2;
-  for (int c = threadIdx.x; c < a.ldk; c += NT) {
+  for (int c = threadIdx.x % wide; c < a.ldk; c += wide) {
     double x = 0.0;
     if (c < a.cols) {
       x = a.src_f32 ? (double)static_cast<const float*>(a.src)[so + (int64_t)c * a.sc]
@@ -64,37 +77,50 @@ __global__ __launch_bounds__(NT) void rownorm2_kernel(const double* x, int64_t r
   block_atomic_max<NT / 64>(m, out);
 }
 
-// out[b] = max over columns v < n of sum_{s < n} G_b[s n + v]^2, G_b = G + b stride
-__global__ __launch_bounds__(NT) void colnorm2_kernel(const double* G, int n, int64_t stride,
-                                                      unsigned long long* out) {
-  const double* g = G + (int64_t)blockIdx.x * stride;
+// amax_a[b] = bound_b * 2^-14, bound_b = (1 + 2^-10) |U row|max su |Gb column|max(b) sg(b):
+// by Cauchy-Schwarz |A| <= bound_b for A formed from the scaled planes.  One workgroup per
+// b: 64 columns at a time, their rows dealt to the 16 waves.  (n = 97, 16
+// tau points: 5.9 us; one wave a column block, a clearing launch and one for the scale took
+// 17.)
+constexpr int CW = 16;
+__global__ __launch_bounds__(64 * CW) void ascale_kernel(const unsigned long long* unorm2,
+                                                         const unsigned long long* amax_u,
+                                                         const double* G, int n, int64_t stride,
+                                                         const unsigned long long* amax_gb,
+                                                         int64_t gb_stride, unsigned long long* amax_a) {
+  __shared__ double part[CW][64];
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double* g = G + (int64_t)b * stride;
   double m = 0.0;
-  for (int v = threadIdx.x; v < n; v += NT) {
+  for (int v0 = 0; v0 < n; v0 += 64) {
+    const int v = min(v0 + lane, n - 1);   // (the last column again past the end)
     double s = 0.0;
-    for (int r = 0; r < n; ++r) s = fma(g[(int64_t)r * n + v], g[(int64_t)r * n + v], s);
-    m = fmax(m, s);
+#pragma unroll 4
+    for (int r = wave; r < n; r += CW) s = fma(g[(int64_t)r * n + v], g[(int64_t)r * n + v], s);
+    __syncthreads();
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0) {
+      double t = 0.0;
+      for (int w = 0; w < CW; ++w) t += part[w][lane];
+      m = fmax(m, t);
+    }
   }
-  block_atomic_max<NT / 64>(m, out + blockIdx.x);
-}
-
-// amax_a[b] = bound_b * 2^-14, bound_b = (1 + 2^-10) |U row|max su |Gb row|max(b) sg(b):
-// by Cauchy-Schwarz |A| <= bound_b for A formed from the scaled planes.
-__global__ void ascale_kernel(const unsigned long long* unorm2, const unsigned long long* amax_u,
-                              const unsigned long long* gnorm2, const unsigned long long* amax_gb,
-                              int64_t gb_stride, int nb, unsigned long long* amax_a) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
+  if (wave > 0) return;
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if (lane > 0) return;
   const double un = sqrt(__longlong_as_double((long long)*unorm2));
-  const double gn = sqrt(__longlong_as_double((long long)gnorm2[b]));
-  const double bound = (1.0 + 0x1p-10) * un * pow2_scale(amax_u) * gn *
+  const double bound = (1.0 + 0x1p-10) * un * pow2_scale(amax_u) * sqrt(m) *
                        pow2_scale(amax_gb + (int64_t)b * gb_stride);
   amax_a[b] = (unsigned long long)__double_as_longlong(bound * 0x1p-14);
 }
 
-__global__ __launch_bounds__(NT) void absmax_kernel(const double* x, int64_t len, int64_t stride,
-                                                    unsigned long long* amax) {
+__global__ __launch_bounds__(NT) void absmax_kernel(const double* x, const double* x2, int64_t len,
+                                                    int64_t stride, unsigned long long* amax,
+                                                    unsigned long long* amax2) {
   const int64_t b = blockIdx.y;
-  const double* xb = x + b * stride;
+  const double* xb = (blockIdx.z ? x2 : x) + b * stride;
+  if (blockIdx.z) amax = amax2;
   double m = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < len; i += (int64_t)gridDim.x * NT)
     m = fmax(m, fabs(xb[i]));
@@ -185,18 +211,23 @@ __global__ __launch_bounds__(NT) void dreduce_kernel(DReduceArgs a) {
   }
 }
 
-// max |G[k][i][j] - G[k][j][i]| over j > i; a row of workgroups per k strides over G[k].
-__global__ __launch_bounds__(NT) void asym_kernel(const double* G, int n,
-                                                  unsigned long long* asym) {
+// max |G[k][i][j] - G[k][j][i]| over j > i and max |G[k][i][j]|; a row of workgroups per k
+// strides over G[k].
+__global__ __launch_bounds__(NT) void asym_kernel(const double* G, int n, unsigned long long* asym,
+                                                  unsigned long long* amax) {
   const int k = blockIdx.y;
   const double* g = G + (int64_t)k * n * n;
-  double m = 0.0;
+  double m = 0.0, x = 0.0;
   for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < (int64_t)n * n;
        e += (int64_t)gridDim.x * NT) {
     const int i = (int)(e / n), j = (int)(e % n);
-    if (j > i) m = fmax(m, fabs(g[(int64_t)i * n + j] - g[(int64_t)j * n + i]));
+    const double v = g[e];
+    x = fmax(x, fabs(v));
+    if (j > i) m = fmax(m, fabs(v - g[(int64_t)j * n + i]));
   }
   block_atomic_max<NT / 64>(m, asym + k);
+  __syncthreads();   // (both use the same LDS)
+  block_atomic_max<NT / 64>(x, amax + k);
 }
 
 __global__ void sym_flags_kernel(const unsigned long long* asym, const unsigned long long* amax,
@@ -303,27 +334,40 @@ hipError_t add_identity(double* A, int n, int* clear, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t split_planes(int mode, const SplitArgs& a, hipStream_t s) {
-  const int64_t rows = (int64_t)a.rows1 * a.rows2;
-  if (rows <= 0) return hipSuccess;
-  dim3 grid((unsigned)rows);
+hipError_t split_planes(int mode, const SplitArgs* a, int njobs, hipStream_t s) {
+  if (njobs < 1 || njobs > SPLIT_JOBS) return hipErrorInvalidValue;
+  SplitJobs jobs{};
+  int64_t blocks = 0;
+  for (int q = 0; q < njobs; ++q) {
+    int wide = 32;
+    while (wide < NT && wide < a[q].ldk) wide *= 2;
+    jobs.job[q] = a[q];
+    jobs.first[q] = (int)blocks;
+    jobs.wide[q] = wide;
+    const int64_t rows = (int64_t)a[q].rows1 * a[q].rows2, per = NT / wide;
+    blocks += (rows + per - 1) / per;
+    if (rows < 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
+  }
+  if (blocks == 0) return hipSuccess;
+  const dim3 grid((unsigned)blocks);
   switch (mode) {
-    case MODE_F64: split_kernel<MODE_F64><<<grid, NT, 0, s>>>(a); break;
-    case MODE_F32: split_kernel<MODE_F32><<<grid, NT, 0, s>>>(a); break;
-    case MODE_BF16X3: split_kernel<MODE_BF16X3><<<grid, NT, 0, s>>>(a); break;
-    case MODE_F16X2: split_kernel<MODE_F16X2><<<grid, NT, 0, s>>>(a); break;
+    case MODE_F64: split_kernel<MODE_F64><<<grid, NT, 0, s>>>(jobs, njobs); break;
+    case MODE_F32: split_kernel<MODE_F32><<<grid, NT, 0, s>>>(jobs, njobs); break;
+    case MODE_BF16X3: split_kernel<MODE_BF16X3><<<grid, NT, 0, s>>>(jobs, njobs); break;
+    case MODE_F16X2: split_kernel<MODE_F16X2><<<grid, NT, 0, s>>>(jobs, njobs); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 hipError_t absmax64(const double* x, int64_t len, int64_t stride, int batch,
-                    unsigned long long* amax, hipStream_t s) {
+                    unsigned long long* amax, hipStream_t s, const double* x2,
+                    unsigned long long* amax2) {
   if (len <= 0 || batch <= 0) return hipSuccess;
   // a few workgroups per row: one atomic each
   unsigned bx = cdiv(len, NT);
   if (bx > 64) bx = 64;
-  absmax_kernel<<<dim3(bx, batch), NT, 0, s>>>(x, len, stride, amax);
+  absmax_kernel<<<dim3(bx, batch, x2 != nullptr ? 2 : 1), NT, 0, s>>>(x, x2, len, stride, amax, amax2);
   return hipGetLastError();
 }
 
@@ -336,18 +380,11 @@ hipError_t rownorm2_max(const double* x, int64_t rows, int len, int64_t ld,
   return hipGetLastError();
 }
 
-hipError_t colnorm2_max(const double* G, int n, int64_t stride, int nb, unsigned long long* out,
-                        hipStream_t s) {
-  if (nb <= 0 || n <= 0) return hipSuccess;
-  colnorm2_kernel<<<nb, NT, 0, s>>>(G, n, stride, out);
-  return hipGetLastError();
-}
-
 hipError_t ascale_bound(const unsigned long long* unorm2, const unsigned long long* amax_u,
-                        const unsigned long long* gnorm2, const unsigned long long* amax_gb,
+                        const double* G, int n, int64_t stride, const unsigned long long* amax_gb,
                         int64_t gb_stride, int nb, unsigned long long* amax_a, hipStream_t s) {
-  if (nb <= 0) return hipSuccess;
-  ascale_kernel<<<cdiv(nb, 64), 64, 0, s>>>(unorm2, amax_u, gnorm2, amax_gb, gb_stride, nb, amax_a);
+  if (nb <= 0 || n <= 0) return hipSuccess;
+  ascale_kernel<<<nb, 64 * CW, 0, s>>>(unorm2, amax_u, G, n, stride, amax_gb, gb_stride, amax_a);
   return hipGetLastError();
 }
 
@@ -367,11 +404,12 @@ hipError_t dreduce(const DReduceArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t asym64(const double* G, int n, int m, unsigned long long* asym, hipStream_t s) {
+hipError_t asym64(const double* G, int n, int m, unsigned long long* asym, unsigned long long* amax,
+                  hipStream_t s) {
   if (n <= 0 || m <= 0) return hipSuccess;
   unsigned bx = cdiv((int64_t)n * n, NT);
   if (bx > 256) bx = 256;
-  asym_kernel<<<dim3(bx, m), NT, 0, s>>>(G, n, asym);
+  asym_kernel<<<dim3(bx, m), NT, 0, s>>>(G, n, asym, amax);
   return hipGetLastError();
 }
 

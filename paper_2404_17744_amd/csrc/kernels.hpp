@@ -133,27 +133,28 @@ struct SplitArgs {
   const unsigned long long* amax; int64_t amax_s2;
   bool c32;
 };
-hipError_t split_planes(int mode, const SplitArgs& a, hipStream_t s);
+// Up to SPLIT_JOBS arrays in one launch.
+constexpr int SPLIT_JOBS = 3;
+hipError_t split_planes(int mode, const SplitArgs* a, int njobs, hipStream_t s);
 
-// amax[b] = max |x[b*stride + i]| for i < len, for b < batch (max-reduced).
+// amax[b] = max |x[b*stride + i]| for i < len, for b < batch (max-reduced); with x2 also
+// amax2[b] of x2.
 hipError_t absmax64(const double* x, int64_t len, int64_t stride, int batch,
-                    unsigned long long* amax, hipStream_t s);
+                    unsigned long long* amax, hipStream_t s, const double* x2 = nullptr,
+                    unsigned long long* amax2 = nullptr);
 hipError_t fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipStream_t s);
 // *out = max over rows r < rows of sum_{c < len} x[r ld + c]^2 (max-reduced, bits;
 // *out must hold 0 or an earlier maximum).
 hipError_t rownorm2_max(const double* x, int64_t rows, int len, int64_t ld,
                         unsigned long long* out, hipStream_t s);
-// out[b] = max over columns v of sum_s G_b[s][v]^2 for the n x n matrices
-// G_b = G + b stride, b < nb (stride may be negative; out zeroed by the caller).
-hipError_t colnorm2_max(const double* G, int n, int64_t stride, int nb, unsigned long long* out,
-                        hipStream_t s);
 // The A-stage scale of the fp16x2 mode, before A exists: for b < nb,
-//   amax_a[b] = 2^-14 (1 + 2^-10) sqrt(*unorm2) su sqrt(gnorm2[b]) sg_b
-// with su = 2^-ilogb(*amax_u), sg_b = 2^-ilogb(amax_gb[b gb_stride]): unorm2 and
-// gnorm2 are the largest squared row norms of U and of G(beta - tau)^T, so by
+//   amax_a[b] = 2^-14 (1 + 2^-10) sqrt(*unorm2) su sqrt(gnorm2_b) sg_b
+// with su = 2^-ilogb(*amax_u), sg_b = 2^-ilogb(amax_gb[b gb_stride]): unorm2 is the largest
+// squared row norm of U and gnorm2_b the largest squared column norm of the n x n matrix
+// G_b = G + b stride (stride may be negative), a row of G(beta - tau)^T, so by
 // Cauchy-Schwarz the scale 2^-ilogb(amax_a[b]) keeps every |A| below 2^15.
 hipError_t ascale_bound(const unsigned long long* unorm2, const unsigned long long* amax_u,
-                        const unsigned long long* gnorm2, const unsigned long long* amax_gb,
+                        const double* G, int n, int64_t stride, const unsigned long long* amax_gb,
                         int64_t gb_stride, int nb, unsigned long long* amax_a, hipStream_t s);
 
 // Sthc[R][P] = -factor * sum_z Dpart[z][R][P], factor = product of the inverse
@@ -177,8 +178,10 @@ struct DReduceArgs {
 };
 hipError_t dreduce(const DReduceArgs& a, hipStream_t s);
 
-// asym[k] = max |G[k] - G[k]^T| (max-reduced, as the bits of a non-negative double), k < m.
-hipError_t asym64(const double* G, int n, int m, unsigned long long* asym, hipStream_t s);
+// asym[k] = max |G[k] - G[k]^T| and amax[k] = max |G[k]| (max-reduced, as the bits of a
+// non-negative double), k < m.
+hipError_t asym64(const double* G, int n, int m, unsigned long long* asym, unsigned long long* amax,
+                  hipStream_t s);
 // flag[k] = 1 if both G[k] and G[m-1-k] are symmetric to within rtol of the
 // largest element of G on the whole grid (asym[k] <= rtol * max_j amax[j]), else 0.
 hipError_t sym_flags(const unsigned long long* asym, const unsigned long long* amax, int m,

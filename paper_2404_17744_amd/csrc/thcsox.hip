@@ -285,7 +285,7 @@ int build_u(thcsox_plan_s* p, const double* V, void* Uout, unsigned long long* a
         a.dst = static_cast<char*>(Uout) + (size_t)q0 * lrow * p->esize;
         a.d1 = (int64_t)n * lrow; a.d2 = lrow; a.d_plane = p->u_plane;
         a.amax = amax_slot; a.c32 = c32;
-        HIP_TRY(split_planes(p->mode, a, s));
+        HIP_TRY(split_planes(p->mode, &a, 1, s));
       }
     }
   }
@@ -356,33 +356,31 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
   g.b_k = 1; g.b_j = n;
   g.C = p->GX64;
   HIP_TRY(gemm64(g, s));
-  HIP_TRY(absmax64(p->Gt64, an, an, nb, p->am_gt() + k0, s));
-  HIP_TRY(absmax64(p->GX64, an, an, nb, p->am_gx() + k0, s));
+  HIP_TRY(absmax64(p->Gt64, an, an, nb, p->am_gt() + k0, s, p->GX64, p->am_gx() + k0));
 
   // fp16x2 keeps the two planes of each 32-wide chunk together (c32 rows of 2 ldk)
   const bool c32 = mode == MODE_F16X2;
   const int64_t lrow = c32 ? 2 * (int64_t)ldk : ldk;
-  SplitArgs sa{};
+  SplitArgs sp[3] = {};
+  SplitArgs& sa = sp[0];
   sa.rows1 = naux; sa.rows2 = nb; sa.cols = n; sa.ldk = ldk;
   sa.src_f32 = false; sa.s1 = n; sa.s2 = an; sa.sc = 1;
   sa.d1 = lrow; sa.d2 = (int64_t)naux * lrow; sa.d_plane = p->g_plane; sa.c32 = c32;
   sa.src = p->Gt64; sa.dst = p->Gt; sa.amax = p->am_gt() + k0; sa.amax_s2 = 1;
-  HIP_TRY(split_planes(mode, sa, s));
-  sa.src = p->GX64; sa.dst = p->GX; sa.amax = p->am_gx() + k0;
-  HIP_TRY(split_planes(mode, sa, s));
+  sp[1] = sa;
+  sp[1].src = p->GX64; sp[1].dst = p->GX; sp[1].amax = p->am_gx() + k0;
   // G(beta - tau)^T of each tau of the batch: row v holds G[m-1-k][s][v] over s
-  sa.rows1 = n; sa.src = G + (int64_t)(m - 1 - k0) * nn; sa.s1 = 1; sa.s2 = -nn; sa.sc = n;
-  sa.d2 = (int64_t)n * lrow; sa.dst = p->Gb; sa.d_plane = p->gb_plane;
-  sa.amax = p->am_g() + (m - 1 - k0); sa.amax_s2 = -1;
-  HIP_TRY(split_planes(mode, sa, s));
+  SplitArgs& sb = sp[2];
+  sb = sa;
+  sb.rows1 = n; sb.src = G + (int64_t)(m - 1 - k0) * nn; sb.s1 = 1; sb.s2 = -nn; sb.sc = n;
+  sb.d2 = (int64_t)n * lrow; sb.dst = p->Gb; sb.d_plane = p->gb_plane;
+  sb.amax = p->am_g() + (m - 1 - k0); sb.amax_s2 = -1;
+  HIP_TRY(split_planes(mode, sp, 3, s));
   if (c32) {
     // the A stage's scale for each tau of the batch, from the row norms of U and
     // of G(beta - tau)^T (the columns of G(beta - tau))
-    unsigned long long* gn = p->norm2 + 2;
-    HIP_TRY(fill_u64(gn, nb, 0ull, s));
-    HIP_TRY(colnorm2_max(G + (int64_t)(m - 1 - k0) * nn, n, -nn, nb, gn, s));
-    HIP_TRY(ascale_bound(cores.normA, cores.amaxA, gn, p->am_g() + (m - 1 - k0), -1, nb,
-                         p->am_a() + k0, s));
+    HIP_TRY(ascale_bound(cores.normA, cores.amaxA, G + (int64_t)(m - 1 - k0) * nn, n, -nn,
+                         p->am_g() + (m - 1 - k0), -1, nb, p->am_a() + k0, s));
   }
   HIP_TRY(p->mark(THCSOX_STAGE_PROJECT, false));
 
@@ -595,7 +593,7 @@ int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_b
 // The direct term's batch buffers of naux^2 per entry (also the screened exchange's
 // polarization batches), allocated on first use: about 1 GB per batch at most, and
 // no more than what the workspace limit leaves.  Three per tau point, or four per
-// mirrored pair of them where V is symmetric; under a limit the pairs take no more
+// mirrored pair of them where V is symmetric; the pairs take no more
 // memory than the points would (alloc refuses one point that does not fit with
 // THCSOX_ENOMEM).
 int ensure_direct_buffers(thcsox_plan_s* p) {
@@ -604,8 +602,7 @@ int ensure_direct_buffers(thcsox_plan_s* p) {
   double cap = 1.0e9;
   if (p->limit) cap = std::min(cap, (double)p->limit - (double)p->bytes - 256.0);
   const int points = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / (3.0 * one))));
-  int pairs = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / (4.0 * one))));
-  if (p->limit) pairs = 3 * points / 4;
+  const int pairs = 3 * points / 4;
   const bool use_pairs = p->vsym && p->m > 1 && pairs > 0;
   p->tbd = use_pairs ? std::min(pairs, (p->m + 1) / 2) : points;
   const int bufs = use_pairs ? 4 : 3;
@@ -621,9 +618,10 @@ int prepare_g(thcsox_plan_s* p, const double* G_dev) {
   const hipStream_t s = p->stream;
   const int64_t nn = (int64_t)p->n * p->n;
   HIP_TRY(fill_u64(p->am_gt(), 5 * (int64_t)p->m, 0ull, s));   // every per-tau maximum
-  HIP_TRY(absmax64(G_dev, nn, nn, p->m, p->am_g(), s));
-  if (p->sym_mode == THCSOX_SYM_AUTO) {
-    HIP_TRY(asym64(G_dev, p->n, p->m, p->am_asym(), s));
+  if (p->sym_mode != THCSOX_SYM_AUTO) {
+    HIP_TRY(absmax64(G_dev, nn, nn, p->m, p->am_g(), s));
+  } else {
+    HIP_TRY(asym64(G_dev, p->n, p->m, p->am_asym(), p->am_g(), s));
     HIP_TRY(sym_flags(p->am_asym(), p->am_g(), p->m,
                       p->mode == MODE_F64 ? SYM_RTOL_F64 : SYM_RTOL_MIXED, p->symflag, s));
   }
@@ -818,7 +816,7 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   p->U = tmp;
   if ((rc = p->alloc(&tmp, np * es * (size_t)p->a_plane))) return bail(rc);
   p->A = tmp;
-  if (precision == THCSOX_FP16X2 && (rc = p->alloc(&p->norm2, (size_t)2 + p->tb)))
+  if (precision == THCSOX_FP16X2 && (rc = p->alloc(&p->norm2, 2)))
     return bail(rc);
   if ((rc = p->alloc(&tmp, np * es * (size_t)p->g_plane))) return bail(rc);
   p->Gt = tmp;
@@ -858,8 +856,7 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   // is V symmetric to rounding?  (max |V - V^T| and max |V| in two per-tau slots
   // that every later call clears before it uses them)
   unsigned long long vs[2] = {0, 0};
-  if ((e = fill_u64(p->am_gt(), 2, 0ull, s)) || (e = asym64(p->V, naux, 1, p->am_gt(), s)) ||
-      (e = absmax64(p->V, (int64_t)naux * naux, 0, 1, p->am_gt() + 1, s)))
+  if ((e = fill_u64(p->am_gt(), 2, 0ull, s)) || (e = asym64(p->V, naux, 1, p->am_gt(), p->am_gt() + 1, s)))
     return hip_bail(e, "symmetry of V");
   if ((rc = build_u(p, V_dev, p->U, p->amax, p->norm2))) return bail(rc);
   if ((e = hipMemcpyAsync(vs, p->am_gt(), sizeof(vs), hipMemcpyDeviceToHost, s)))
