@@ -24,11 +24,11 @@ __device__ __forceinline__ double pow2_scale(const unsigned long long* amax) {
 // ---------------------------------------------------------------------------
 // Several arrays split in one launch (a launch of a few microseconds is mostly its own
 // latency): blocks first[q] .. first[q + 1] - 1 take job q.  A block takes NT / wide rows of
-// wide >= ldk threads each (one row of NT threads from ldk > NT / 2 on).
+// wide = 2^lw >= ldk threads each (one row of NT threads from ldk > NT / 2 on).
 struct SplitJobs {
   SplitArgs job[SPLIT_JOBS];
   int first[SPLIT_JOBS];   // blocks before job q
-  int wide[SPLIT_JOBS];
+  int lw[SPLIT_JOBS];
 };
 template <int M>
 __global__ __launch_bounds__(NT) void split_kernel(SplitJobs jobs, int njobs) {
@@ -36,16 +36,16 @@ __global__ __launch_bounds__(NT) void split_kernel(SplitJobs jobs, int njobs) {
   constexpr int NP = ModeT<M>::NP;
   int q = 0;
   while (q + 1 < njobs && (int)blockIdx.x >= jobs.first[q + 1]) ++q;
-  const SplitArgs& a = jobs.job[q];
-  const int wide = jobs.wide[q];
-  const int64_t row = (int64_t)(blockIdx.x - jobs.first[q]) * (NT / wide) + threadIdx.x / wide;
-  if (row >= (int64_t)a.rows1 * a.rows2) return;
-  const int64_t r1 = row / a.rows2, r2 = row % a.rows2;
+  const SplitArgs a = jobs.job[q];
+  const int lw = jobs.lw[q], wide = 1 << lw;
+  const unsigned row = (blockIdx.x - jobs.first[q]) * (NT >> lw) + (threadIdx.x >> lw);
+  if (row >= (unsigned)a.rows1 * (unsigned)a.rows2) return;   // (rows < 2^31)
+  const int64_t r1 = row / (unsigned)a.rows2, r2 = row % (unsigned)a.rows2;
   const double sc = pow2_scale(a.amax ? a.amax + r2 * a.amax_s2 : nullptr);
   T* dst = static_cast<T*>(a.dst);
   const int64_t so = r1 * a.s1 + r2 * a.s2;
   const int64_t dof = r1 * a.d1 + r2 * a.d2;
-  for (int c = threadIdx.x % wide; c < a.ldk; c += wide) {
+  for (int c = threadIdx.x & (wide - 1); c < a.ldk; c += wide) {
     double x = 0.0;
     if (c < a.cols) {
       x = a.src_f32 ? (double)static_cast<const float*>(a.src)[so + (int64_t)c * a.sc]
@@ -339,14 +339,14 @@ hipError_t split_planes(int mode, const SplitArgs* a, int njobs, hipStream_t s) 
   SplitJobs jobs{};
   int64_t blocks = 0;
   for (int q = 0; q < njobs; ++q) {
-    int wide = 32;
-    while (wide < NT && wide < a[q].ldk) wide *= 2;
+    int lw = 5;
+    while ((1 << lw) < NT && (1 << lw) < a[q].ldk) ++lw;
     jobs.job[q] = a[q];
     jobs.first[q] = (int)blocks;
-    jobs.wide[q] = wide;
-    const int64_t rows = (int64_t)a[q].rows1 * a[q].rows2, per = NT / wide;
+    jobs.lw[q] = lw;
+    const int64_t rows = (int64_t)a[q].rows1 * a[q].rows2, per = NT >> lw;
     blocks += (rows + per - 1) / per;
-    if (rows < 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if (rows < 0 || rows > 0x7fffffff || blocks > 0x7fffffff) return hipErrorInvalidValue;
   }
   if (blocks == 0) return hipSuccess;
   const dim3 grid((unsigned)blocks);
