@@ -215,7 +215,11 @@ def main():
         torch.cuda.synchronize()
         ms_d = e0.elapsed_time(e1)
         na, nn_ = float(s.naux), float(s.n)
-        mac_d = 2 * na ** 3 + 3 * na * na * nn_ + 3 * na * nn_ * nn_
+        # with a symmetric V (these inputs) the two products of W = V Pi V and both
+        # points' projections are formed once per mirrored pair of tau points
+        pairs = len({min(k, m - 1 - k) for k in range(k_end)})
+        small = na * na * nn_ + na * nn_ * nn_
+        mac_d = (2 * na ** 3 + 2 * small) * pairs / k_end + small
         direct = {"tau_points_per_s": k_end / (ms_d * 1e-3), "ms_per_step": ms_d,
                   "E_dir": E_dir, "mac_per_tau": mac_d,
                   "tflops": 2 * mac_d * k_end / (ms_d * 1e-3) / 1e12,
@@ -303,8 +307,9 @@ def main():
                      "frac": achieved / peak,
                      "traffic": measured_traffic(args.precision, args.workload, args.symmetry,
                                                  info),
-                     "kernel": ("fused_f16_kernel" if args.precision == "fp16x2"
-                                else f"fused_kernel<{args.precision}>"),
+                     "kernel": {"fp16x2": "fused_f16_kernel", "fp32": "fused_f32_kernel",
+                                "bf16x3": "fused_bf3_kernel",
+                                "fp64": "fused_f64_kernel"}[args.precision],
                      "avg_launch_ms": fused_avg, "launches": fused_n,
                      "algorithmic_flop_per_launch": fused_flop,
                      "symmetric_tau_points": n_sym,
