@@ -206,6 +206,12 @@ struct thcsox_plan_s {
     *p = static_cast<T*>(q);
     return 0;
   }
+  // Gives back the allocations after the first `kept`, which took the workspace from
+  // `bytes_kept` on (the caller has published no pointer to them).
+  void release_from(size_t kept, size_t bytes_kept) {
+    for (; allocs.size() > kept; allocs.pop_back()) (void)hipFree(allocs.back());
+    bytes = bytes_kept;
+  }
   ~thcsox_plan_s() {
     for (auto& t : timers) {
       for (hipEvent_t e : t.start) (void)hipEventDestroy(e);
@@ -611,6 +617,24 @@ int ensure_direct_buffers(thcsox_plan_s* p) {
   return 0;
 }
 
+// The static screening's arrays, allocated on first use, all of them or none: a plan whose
+// workspace limit leaves room for some of them refuses every call with THCSOX_ENOMEM
+// and keeps none.
+int ensure_screening_buffers(thcsox_plan_s* p) {
+  if (p->Pi0 != nullptr) return 0;
+  const size_t kept = p->allocs.size(), bytes = p->bytes, aa = (size_t)p->naux * p->naux;
+  double *Pi0 = nullptr, *Mscr = nullptr, *Minv = nullptr, *gjx = nullptr;
+  int* gj = nullptr;
+  int rc;
+  if ((rc = p->alloc(&Pi0, aa)) || (rc = p->alloc(&Mscr, aa)) || (rc = p->alloc(&Minv, aa)) ||
+      (rc = p->alloc(&gjx, (size_t)32 * p->naux)) || (rc = p->alloc(&gj, (size_t)2 * p->naux + 1))) {
+    p->release_from(kept, bytes);
+    return rc;
+  }
+  p->Pi0 = Pi0; p->Mscr = Mscr; p->Minv = Minv; p->gjx = gjx; p->gj = gj;
+  return 0;
+}
+
 // Per-call preparation of G for the exchange contractions: the per-tau maxima
 // cleared, max |G[k]| of every tau point (the power-of-two scales) and, under
 // THCSOX_SYM_AUTO, the flags of the symmetric-D path.
@@ -934,13 +958,7 @@ int thcsox_static_screening(thcsox_plan_t p, const double* G_dev, double* W_dev)
   const int64_t aa = (int64_t)naux * naux;
   const hipStream_t s = p->stream;
   TRY(ensure_direct_buffers(p));
-  if (p->Pi0 == nullptr) {
-    TRY(p->alloc(&p->Pi0, (size_t)aa));
-    TRY(p->alloc(&p->Mscr, (size_t)aa));
-    TRY(p->alloc(&p->Minv, (size_t)aa));
-    TRY(p->alloc(&p->gjx, (size_t)32 * naux));
-    TRY(p->alloc(&p->gj, (size_t)2 * naux + 1));
-  }
+  TRY(ensure_screening_buffers(p));
   // Pi0 = sum_k w_k Pi(tau_k) over the mirrored pairs, batch by batch: Pi(tau_{m-1-l})
   // is the transpose of Pi(tau_l); the middle point of an odd grid has no partner
   const double* bufC = p->dbuf + 2 * (int64_t)p->tbd * aa;

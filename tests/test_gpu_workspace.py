@@ -1,0 +1,67 @@
+"""Workspace limits of the buffers that a plan allocates on first use: a call that does
+not fit is refused every time it is made, leaves nothing behind, and the plan serves
+the calls that do fit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import direct as od
+from oracle import screened as osc
+from paper_2404_17744_amd import synth, thcsox
+
+pytestmark = pytest.mark.gpu
+BETA = 100.0
+ENOMEM = -2
+
+
+def _inputs(dev, n, naux, m, seed=0):
+    s = synth.make_system(n, naux, seed=seed)
+    tau, w = synth.cheb_tau_grid(m, BETA)
+    G = synth.random_general_g(n, m, seed=seed + 1)
+    on = lambda a: torch.from_numpy(a).to(dev)
+    return s, tau, w, G, on(s.X), on(s.V), on(G)
+
+
+def _bytes_without_limit(X, V, tau, w, precision):
+    """One tau point: the plan takes the same memory with any limit that it fits."""
+    plan = thcsox.Plan(X, V, tau, w, BETA, precision=precision)
+    taken = plan.info()["bytes"]
+    plan.close()
+    return taken
+
+
+def _refused(call):
+    with pytest.raises(thcsox.ThcsoxError) as e:
+        call()
+    assert e.value.code == ENOMEM
+
+
+@pytest.mark.parametrize("left", [3.5, 4.5, 5.5, 6.0])
+def test_static_screening_refuses_each_time(dev, left):
+    """`left` matrices of room: the direct term takes three, the screening needs another
+    three and its Gauss-Jordan work."""
+    n, naux = 6, 640
+    s, tau, w, G, X, V, Gd = _inputs(dev, n, naux, 1)
+    limit = _bytes_without_limit(X, V, tau, w, "fp64") + int(left * 8 * naux * naux)
+    print(f"case screening limit left={left}", flush=True)
+    plan = thcsox.Plan(X, V, tau, w, BETA, workspace_limit=limit)
+    _refused(lambda: plan.static_screening(Gd))
+    taken = plan.info()["bytes"]
+    _refused(lambda: plan.static_screening(Gd))
+    assert plan.info()["bytes"] == taken
+    S = plan.sigma_direct(Gd).cpu().numpy()
+    plan.close()
+    ref = od.sigma_direct_thc(s.X, s.V, G[0], G[0])
+    assert np.abs(S[0] - ref).max() <= 1e-11 * np.abs(ref).max()
+
+
+def test_static_screening_fits(dev):
+    n, naux = 6, 640
+    s, tau, w, G, X, V, Gd = _inputs(dev, n, naux, 1)
+    limit = _bytes_without_limit(X, V, tau, w, "fp64") + int(6.5 * 8 * naux * naux)
+    print("case screening limit fits", flush=True)
+    plan = thcsox.Plan(X, V, tau, w, BETA, workspace_limit=limit)
+    W = plan.static_screening(Gd).cpu().numpy()
+    plan.close()
+    ref = osc.screened_core(s.V, osc.static_polarization(s.X, G, w))
+    assert np.abs(W - ref).max() <= 1e-10 * np.abs(ref).max()
