@@ -635,6 +635,29 @@ int ensure_screening_buffers(thcsox_plan_s* p) {
   return 0;
 }
 
+// The second U (of the screened core) and its largest magnitude, allocated on first use,
+// both or neither.  The operand pads are zeroed once (every build writes only the first n
+// of ldk columns).
+int ensure_screened_u(thcsox_plan_s* p) {
+  if (p->Uw != nullptr) return 0;
+  const size_t kept = p->allocs.size(), bytes = p->bytes;
+  const size_t size = (size_t)p->np * p->esize * (size_t)p->u_plane;
+  char* U = nullptr;
+  unsigned long long* amax = nullptr;
+  int rc;
+  if ((rc = p->alloc(&U, size)) || (rc = p->alloc(&amax, 1))) {
+    p->release_from(kept, bytes);
+    return rc;
+  }
+  const hipError_t e = hipMemsetAsync(U, 0, size, p->stream);
+  if (e != hipSuccess) {
+    p->release_from(kept, bytes);
+    return fail(THCSOX_EDEVICE, std::string("zero the screened U: ") + hipGetErrorString(e));
+  }
+  p->Uw = U; p->amax_w = amax;
+  return 0;
+}
+
 // Per-call preparation of G for the exchange contractions: the per-tau maxima
 // cleared, max |G[k]| of every tau point (the power-of-two scales) and, under
 // THCSOX_SYM_AUTO, the flags of the symmetric-D path.
@@ -1006,14 +1029,7 @@ int thcsox_sigma_screened(thcsox_plan_t p, const double* G_dev, const double* W_
   const char* s0 = reinterpret_cast<const char*>(Sigma_dev);
   if (s0 < g0 + gbytes && g0 < s0 + gbytes) return fail(THCSOX_EINVAL, "Sigma aliases G");
   const hipStream_t s = p->stream;
-  if (p->Uw == nullptr) {
-    char* tmp = nullptr;
-    TRY(p->alloc(&tmp, (size_t)p->np * p->esize * (size_t)p->u_plane));
-    p->Uw = tmp;
-    TRY(p->alloc(&p->amax_w, 1));
-    // the operand pads stay zero (every build writes only the first n of ldk columns)
-    HIP_TRY(hipMemsetAsync(p->Uw, 0, (size_t)p->np * p->esize * (size_t)p->u_plane, s));
-  }
+  TRY(ensure_screened_u(p));
   TRY(build_u(p, W_dev, p->Uw, p->amax_w, p->norm2 ? p->norm2 + 1 : nullptr));
   TRY(prepare_g(p, G_dev));
   const Cores vw{p->U, p->amax, p->Uw, p->amax_w, p->norm2};

@@ -65,3 +65,30 @@ def test_static_screening_fits(dev):
     plan.close()
     ref = osc.screened_core(s.V, osc.static_polarization(s.X, G, w))
     assert np.abs(W - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16x3", "fp16x2"])
+@pytest.mark.parametrize("left", [0, 255, "fits"])
+def test_screened_u_refuses_each_time(dev, precision, left):
+    """Room for the second U but not for its largest magnitude (256 bytes), or for both."""
+    n, naux = 5, 40
+    s, tau, w, G, X, V, Gd = _inputs(dev, n, naux, 1)
+    elem = {"fp64": 8, "fp32": 4, "bf16x3": 6, "fp16x2": 4}[precision]
+    u = naux * n * 32 * elem                          # rows padded to 32 orbitals
+    assert u % 256 == 0
+    temps = 2 * n * n * naux * 8 + 512                # of the build of U
+    limit = _bytes_without_limit(X, V, tau, w, precision) + u + (256 + temps if left == "fits" else left)
+    print(f"case second U limit {precision} left={left}", flush=True)
+    plan = thcsox.Plan(X, V, tau, w, BETA, precision=precision, workspace_limit=limit)
+    W = 0.5 * V
+    if left != "fits":
+        taken = plan.info()["bytes"]
+        _refused(lambda: plan.sigma_screened(Gd, W, "g3w2"))
+        _refused(lambda: plan.sigma_screened(Gd, W, "g3w2"))
+        assert plan.info()["bytes"] == taken
+        plan.close()
+        return
+    S = plan.sigma_screened(Gd, W, "g3w2").cpu().numpy()
+    plan.close()
+    ref = osc.sigma_g3w2(s.X, 0.5 * s.V, G[0], G[0])
+    assert np.abs(S[0] - ref).max() <= (1e-10 if precision == "fp64" else 1e-6) * np.abs(ref).max()
