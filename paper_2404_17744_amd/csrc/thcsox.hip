@@ -249,8 +249,8 @@ namespace {
 // planes Uout (the plan's U, or the second U of a screened core).  Split modes
 // first take max|U| into *amax_slot (pass 0; fp16x2 also the largest squared row
 // norm into *norm_slot), then store (pass 1).
-int build_u(thcsox_plan_s* p, const double* V, void* Uout, unsigned long long* amax_slot,
-            unsigned long long* norm_slot) {
+int build_u_passes(thcsox_plan_s* p, const double* V, void* Uout, unsigned long long* amax_slot,
+                   unsigned long long* norm_slot) {
   const int n = p->n, naux = p->naux, ldk = p->ldk;
   const hipStream_t s = p->stream;
   size_t per_q = (size_t)n * naux * sizeof(double);
@@ -296,15 +296,16 @@ int build_u(thcsox_plan_s* p, const double* V, void* Uout, unsigned long long* a
     }
   }
   HIP_TRY(hipStreamSynchronize(s));
-  // the temporaries are the last two allocations: release them
-  for (int t = 0; t < (p->mode == MODE_F64 ? 1 : 2); ++t) {
-    void* q = p->allocs.back();
-    p->allocs.pop_back();
-    (void)hipFree(q);
-  }
-  p->bytes -= ((size_t)qb * n * naux * sizeof(double) + 255) / 256 * 256 *
-              (p->mode == MODE_F64 ? 1 : 2);
   return 0;
+}
+// The build, whose temporaries (the last allocations) are given back however it ends.
+int build_u(thcsox_plan_s* p, const double* V, void* Uout, unsigned long long* amax_slot,
+            unsigned long long* norm_slot) {
+  const size_t kept = p->allocs.size(), bytes = p->bytes;
+  const int rc = build_u_passes(p, V, Uout, amax_slot, norm_slot);
+  if (rc != 0) (void)hipStreamSynchronize(p->stream);   // launches may still use them
+  p->release_from(kept, bytes);
+  return rc;
 }
 
 // Sigma[b] = X Sig_thc[b] X^T for nb tau points at once (FP64 matrix cores);

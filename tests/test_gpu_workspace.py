@@ -92,3 +92,20 @@ def test_screened_u_refuses_each_time(dev, precision, left):
     plan.close()
     ref = osc.sigma_g3w2(s.X, 0.5 * s.V, G[0], G[0])
     assert np.abs(S[0] - ref).max() <= (1e-10 if precision == "fp64" else 1e-6) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3", "fp16x2"])
+def test_refused_build_keeps_no_temporaries(dev, precision):
+    """Room for the second U and for the first of the build's two temporaries."""
+    n, naux = 5, 40
+    s, tau, w, G, X, V, Gd = _inputs(dev, n, naux, 1)
+    u = naux * n * 32 * (6 if precision == "bf16x3" else 4)
+    temp = (n * n * naux * 8 + 255) // 256 * 256
+    plain = _bytes_without_limit(X, V, tau, w, precision)
+    print(f"case build temporaries limit {precision}", flush=True)
+    plan = thcsox.Plan(X, V, tau, w, BETA, precision=precision,
+                       workspace_limit=plain + u + 256 + temp + temp // 2)
+    for _ in range(3):
+        _refused(lambda: plan.sigma_screened(Gd, 0.5 * V, "g3w2"))
+        assert plan.info()["bytes"] == plain + u + 256
+    plan.close()
