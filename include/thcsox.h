@@ -187,7 +187,7 @@ int thcsox_energy_basis(thcsox_plan_t p, const double* G_dev, const double* Sigm
  * must not alias G).  accumulate = 0 writes Sigma[k]; accumulate = 1 adds to it
  * (e.g. onto the SOX term from thcsox_sigma_sox, giving the full second-order
  * scGF2 self-energy).  Pi(beta - tau) is the transpose of Pi(tau), and where V is
- * symmetric to rounding (2^-50 of its largest element, checked by thcsox_plan) W is
+ * symmetric to rounding (each element to 2^-50 of itself, checked by thcsox_plan) W is
  * too, so a mirrored pair of tau points shares one W.  The first call allocates
  * 4 x 8 naux^2 bytes per pair of its batch (3 x 8 naux^2 per tau point where V is not
  * symmetric or the limit leaves no room for a pair; about 1 GB at most; counted

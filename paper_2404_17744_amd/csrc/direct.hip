@@ -63,7 +63,39 @@ __global__ __launch_bounds__(NT) void hadamard_pair_kernel(const double* __restr
   }
 }
 
+// *flag = 1 if some |V_ij - V_ji| > rtol max(|V_ij|, |V_ji|), or is not a number: one 32 x 32
+// tile on or above the diagonal per workgroup against its mirror, both read along
+// their rows
+__global__ __launch_bounds__(NT) void unsymmetric_kernel(const double* __restrict__ V, int naux,
+                                                         double rtol,
+                                                         unsigned long long* __restrict__ flag) {
+  __shared__ double t[PT][PT + 1];
+  const int i0 = blockIdx.y * PT, j0 = blockIdx.x * PT;
+  if (j0 < i0) return;
+  const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;   // 32 x 8
+#pragma unroll
+  for (int r = ty; r < PT; r += NT / PT)
+    if (j0 + r < naux && i0 + tx < naux) t[r][tx] = V[(int64_t)(j0 + r) * naux + i0 + tx];
+  __syncthreads();
+  bool ok = true;
+#pragma unroll
+  for (int r = ty; r < PT; r += NT / PT)
+    if (i0 + r < naux && j0 + tx < naux) {
+      const double a = V[(int64_t)(i0 + r) * naux + j0 + tx], b = t[tx][r];
+      ok = ok && fabs(a - b) <= rtol * fmax(fabs(a), fabs(b));
+    }
+  if (!ok) *flag = 1ull;
+}
+
 }  // namespace
+
+hipError_t unsymmetric(const double* V, int naux, double rtol, unsigned long long* flag,
+                       hipStream_t s) {
+  if (naux <= 0) return hipSuccess;
+  const unsigned nt = (unsigned)((naux + PT - 1) / PT);
+  unsymmetric_kernel<<<dim3(nt, nt), NT, 0, s>>>(V, naux, rtol, flag);
+  return hipGetLastError();
+}
 
 hipError_t hadamard_pair(const double* W, double* A, double* B, int naux, int nb, hipStream_t s) {
   if (naux <= 0 || nb <= 0 || (A == nullptr && B == nullptr)) return hipSuccess;

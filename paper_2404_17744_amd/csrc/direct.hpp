@@ -16,4 +16,9 @@ hipError_t hadamard64(const double* W, const double* Gt, double* H, int64_t len,
 // A[b] <- W[b] o A[b] and B[b] <- W[b]^T o B[b] for nb matrices [naux][naux] (A or B
 // may be null).
 hipError_t hadamard_pair(const double* W, double* A, double* B, int naux, int nb, hipStream_t s);
+
+// *flag is set to 1 if V [naux][naux] is not symmetric to rtol element by element, |V_ij -
+// V_ji| <= rtol max(|V_ij|, |V_ji|), or holds a value that is not finite.
+hipError_t unsymmetric(const double* V, int naux, double rtol, unsigned long long* flag,
+                       hipStream_t s);
 }  // namespace thcsox

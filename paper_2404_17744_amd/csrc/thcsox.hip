@@ -43,9 +43,11 @@ int fail(int code, const std::string& msg) { return set_error(code, msg); }
 constexpr double SYM_RTOL_F64 = 1e-12;
 constexpr double SYM_RTOL_MIXED = 1e-10;
 
-// V counts as symmetric when max |V - V^T| <= V_RTOL max |V| (a few units in the last
-// place): the direct term then takes W(beta - tau) as the transpose of W(tau), which
-// differs from the product with V as given by no more than the product's own rounding.
+// V counts as symmetric when |V_ij - V_ji| <= V_RTOL max(|V_ij|, |V_ji|) for every element (a
+// few units in its last place): the direct term then takes W(beta - tau) as the transpose
+// of W(tau), which differs from the product with V as given by no more than the product's
+// own rounding.  (Against the largest element of V instead, blocks of small elements would
+// count as symmetric whatever they hold.)
 constexpr double V_RTOL = 0x1p-50;
 
 #define HIP_TRY(expr)                                                                  \
@@ -901,18 +903,16 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   if ((e = hipMemcpyAsync(p->V, V_dev, sizeof(double) * (size_t)naux * naux,
                           hipMemcpyDeviceToDevice, s)))
     return hip_bail(e, "copy V");
-  // is V symmetric to rounding?  (max |V - V^T| and max |V| in two per-tau slots
-  // that every later call clears before it uses them)
-  unsigned long long vs[2] = {0, 0};
-  if ((e = fill_u64(p->am_gt(), 2, 0ull, s)) || (e = asym64(p->V, naux, 1, p->am_gt(), p->am_gt() + 1, s)))
+  // is V symmetric to rounding?  (a flag in a per-tau slot that every later call clears
+  // before it uses it)
+  unsigned long long unsym = 0;
+  if ((e = fill_u64(p->am_gt(), 1, 0ull, s)) || (e = unsymmetric(p->V, naux, V_RTOL, p->am_gt(), s)))
     return hip_bail(e, "symmetry of V");
   if ((rc = build_u(p, V_dev, p->U, p->amax, p->norm2))) return bail(rc);
-  if ((e = hipMemcpyAsync(vs, p->am_gt(), sizeof(vs), hipMemcpyDeviceToHost, s)))
+  if ((e = hipMemcpyAsync(&unsym, p->am_gt(), sizeof(unsym), hipMemcpyDeviceToHost, s)))
     return hip_bail(e, "symmetry of V");
   if ((e = hipStreamSynchronize(s))) return hip_bail(e, "plan synchronise");
-  double vd[2];
-  std::memcpy(vd, vs, sizeof(vd));
-  p->vsym = vd[0] <= V_RTOL * vd[1];
+  p->vsym = unsym == 0;
   *out = p;
   return 0;
 }
