@@ -109,3 +109,29 @@ def test_refused_build_keeps_no_temporaries(dev, precision):
         _refused(lambda: plan.sigma_screened(Gd, 0.5 * V, "g3w2"))
         assert plan.info()["bytes"] == plain + u + 256
     plan.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16x3", "fp16x2"])
+def test_plan_on_a_part_filled_device(dev, precision):
+    """With a third of the device's memory taken a plan does not add the buffers of several
+    tau points per launch, and gives the same bits."""
+    n, naux, m = 24, 130, 16
+    s, tau, w, G, X, V, Gd = _inputs(dev, n, naux, m)
+
+    def run():
+        plan = thcsox.Plan(X, V, tau, w, BETA, precision=precision)
+        S = plan.sigma(Gd)
+        taken = plan.info()["bytes"]
+        plan.close()
+        return S, taken
+
+    print(f"case part-filled device {precision}", flush=True)
+    S0, taken0 = run()
+    held = torch.empty(torch.cuda.mem_get_info()[1] // 3, dtype=torch.uint8, device=dev)
+    S1, taken1 = run()
+    del held
+    torch.cuda.empty_cache()
+    # A and partial tiles of one tau point (two in the fp16x2 A stage) against several
+    one = n * naux * 32 * {"fp64": 8, "fp32": 4, "bf16x3": 6, "fp16x2": 4}[precision]
+    assert taken0 - taken1 >= 2 * one
+    assert torch.equal(S0, S1)
