@@ -357,28 +357,29 @@ __global__ __launch_bounds__(NT) void pair_gather_kernel(const double* __restric
                                                          int64_t npairs, float* __restrict__ x) {
   __shared__ float t[PT][PT + 1];   // [tau][pair]
   const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;
-  const int64_t b0 = (int64_t)blockIdx.x * PT;
-  const int64_t b = b0 + tx;
-  const int64_t pr = b < npairs ? (pairs ? pairs[b] : b) : -1;
-  const bool in = pr >= 0 && pr < aa;   // a pair outside the array reads as zero
-  const double sc = in ? scale[pr] : 1.0;
-  for (int k0 = 0; k0 < m; k0 += PT) {
-    const int nk = min(PT, m - k0);
-    double v[PT / PTS];
+  for (int64_t b0 = (int64_t)blockIdx.x * PT; b0 < npairs; b0 += (int64_t)gridDim.x * PT) {
+    const int64_t b = b0 + tx;
+    const int64_t pr = b < npairs ? (pairs ? pairs[b] : b) : -1;
+    const bool in = pr >= 0 && pr < aa;   // a pair outside the array reads as zero
+    const double sc = in ? scale[pr] : 1.0;
+    for (int k0 = 0; k0 < m; k0 += PT) {
+      const int nk = min(PT, m - k0);
+      double v[PT / PTS];
 #pragma unroll
-    for (int e = 0; e < PT / PTS; ++e)
-      v[e] = S[(int64_t)(k0 + min(ty + e * PTS, nk - 1)) * aa + (in ? pr : 0)];
+      for (int e = 0; e < PT / PTS; ++e)
+        v[e] = S[(int64_t)(k0 + min(ty + e * PTS, nk - 1)) * aa + (in ? pr : 0)];
 #pragma unroll
-    for (int e = 0; e < PT / PTS; ++e)
-      if (ty + e * PTS < nk) t[ty + e * PTS][tx] = in ? (float)(v[e] / sc) : 0.f;
-    __syncthreads();
-    // consecutive threads along tau, then along pairs
-    const int rows = (int)(npairs - b0 < PT ? npairs - b0 : PT);
-    for (int e = threadIdx.x; e < rows * nk; e += NT) {
-      const int r = e / nk, k = e - r * nk;
-      x[(b0 + r) * m + k0 + k] = t[k][r];
+      for (int e = 0; e < PT / PTS; ++e)
+        if (ty + e * PTS < nk) t[ty + e * PTS][tx] = in ? (float)(v[e] / sc) : 0.f;
+      __syncthreads();
+      // consecutive threads along tau, then along pairs
+      const int rows = (int)(npairs - b0 < PT ? npairs - b0 : PT);
+      for (int e = threadIdx.x; e < rows * nk; e += NT) {
+        const int r = e / nk, k = e - r * nk;
+        x[(b0 + r) * m + k0 + k] = t[k][r];
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -389,28 +390,36 @@ __global__ __launch_bounds__(NT) void pair_scatter_kernel(const float* __restric
                                                           double* __restrict__ S) {
   __shared__ float t[PT][PT + 1];   // [tau][pair]
   const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;
-  const int64_t p0 = (int64_t)blockIdx.x * PT;
-  const int rows = (int)(aa - p0 < PT ? aa - p0 : PT);
-  const double sc = tx < rows ? scale[p0 + tx] : 0.0;
-  for (int k0 = 0; k0 < m; k0 += PT) {
-    const int nk = min(PT, m - k0);
-    float v[PT * PT / NT];   // all in flight together (addresses clamped into the block)
+  for (int64_t p0 = (int64_t)blockIdx.x * PT; p0 < aa; p0 += (int64_t)gridDim.x * PT) {
+    const int rows = (int)(aa - p0 < PT ? aa - p0 : PT);
+    const double sc = tx < rows ? scale[p0 + tx] : 0.0;
+    for (int k0 = 0; k0 < m; k0 += PT) {
+      const int nk = min(PT, m - k0);
+      float v[PT * PT / NT];   // all in flight together (addresses clamped into the block)
 #pragma unroll
-    for (int i = 0; i < PT * PT / NT; ++i) {
-      const int e = min((int)threadIdx.x + i * NT, rows * nk - 1), r = e / nk;
-      v[i] = y[(p0 + r) * m + k0 + e - r * nk];
-    }
+      for (int i = 0; i < PT * PT / NT; ++i) {
+        const int e = min((int)threadIdx.x + i * NT, rows * nk - 1), r = e / nk;
+        v[i] = y[(p0 + r) * m + k0 + e - r * nk];
+      }
 #pragma unroll
-    for (int i = 0; i < PT * PT / NT; ++i) {
-      const int e = (int)threadIdx.x + i * NT, r = e / nk;
-      if (e < rows * nk) t[e - r * nk][r] = v[i];
+      for (int i = 0; i < PT * PT / NT; ++i) {
+        const int e = (int)threadIdx.x + i * NT, r = e / nk;
+        if (e < rows * nk) t[e - r * nk][r] = v[i];
+      }
+      __syncthreads();
+      if (tx < rows)
+        for (int k = ty; k < nk; k += PTS)
+          S[(int64_t)(k0 + k) * aa + p0 + tx] = (double)t[k][tx] * sc;
+      __syncthreads();
     }
-    __syncthreads();
-    if (tx < rows)
-      for (int k = ty; k < nk; k += PTS)
-        S[(int64_t)(k0 + k) * aa + p0 + tx] = (double)t[k][tx] * sc;
-    __syncthreads();
   }
+}
+
+// Workgroups of the two kernels above: a block of pairs each, and several where there are
+// more blocks than a launch takes (beyond 2^32 threads it drops the excess without an
+// error).
+unsigned pair_blocks(int64_t npairs) {
+  return (unsigned)std::min<int64_t>((npairs + PT - 1) / PT, 1 << 23);
 }
 
 unsigned blocks_for(int64_t n) {
@@ -840,9 +849,7 @@ int thcsox_pair_gather(int m, int naux, const double* S_dev, const double* scale
       npairs < 0 || (pairs_dev == nullptr && npairs > aa))
     return set_error(THCSOX_EINVAL, "bad argument");
   if (npairs == 0) return 0;
-  const long long blocks = (npairs + PT - 1) / PT;
-  if (blocks > 0x7fffffffLL) return set_error(THCSOX_EINVAL, "too many pairs");
-  pair_gather_kernel<<<(unsigned)blocks, NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
+  pair_gather_kernel<<<pair_blocks(npairs), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
       S_dev, m, aa, scale_dev, reinterpret_cast<const int64_t*>(pairs_dev), npairs, x_dev);
   MTRY(hipGetLastError());
   return 0;
@@ -854,7 +861,7 @@ int thcsox_pair_scatter(int m, int naux, const float* y_dev, const double* scale
   if (m <= 0 || naux <= 0 || S_dev == nullptr || scale_dev == nullptr || y_dev == nullptr)
     return set_error(THCSOX_EINVAL, "bad argument");
   const int64_t aa = (int64_t)naux * naux;
-  pair_scatter_kernel<<<(unsigned)((aa + PT - 1) / PT), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
+  pair_scatter_kernel<<<pair_blocks(aa), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
       y_dev, m, aa, scale_dev, S_dev);
   MTRY(hipGetLastError());
   return 0;
