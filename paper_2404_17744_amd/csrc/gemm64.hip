@@ -33,6 +33,8 @@ namespace {
 constexpr int NT = 256;      // threads per workgroup (4 wavefronts)
 constexpr int NXCD = 8;
 constexpr int BAND = 8;      // row tiles per band of the tile walk
+// a launch of more than 2^32 - 1 threads would be cut short without an error
+constexpr int64_t MAX_GRID = 0xffffffffLL / NT;
 typedef double d2 __attribute__((ext_vector_type(2)));
 
 // An operand's panel in LDS.  Within 16 k lane group g takes k = 2 g, 2 g + 1, 8 + 2 g
@@ -243,7 +245,7 @@ template <int WT, int BK, Access ACC>
 hipError_t launch(const Gemm64Args& g, bool ac, bool bc, hipStream_t s) {
   const int64_t nti = (g.M + 32 * WT - 1) / (32 * WT), ntj = ((int64_t)g.N + 32 * WT - 1) / (32 * WT);
   const int64_t total = nti * ntj * g.batch;
-  if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (total > MAX_GRID) return hipErrorInvalidValue;
   const dim3 grid((unsigned)total);
   const int ni = (int)nti, nj = (int)ntj;
   if (ac && bc) gemm64_kernel<WT, BK, true, true, ACC><<<grid, NT, 0, s>>>(g, ni, nj);

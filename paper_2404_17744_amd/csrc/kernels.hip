@@ -346,7 +346,8 @@ hipError_t split_planes(int mode, const SplitArgs* a, int njobs, hipStream_t s) 
     jobs.lw[q] = lw;
     const int64_t rows = (int64_t)a[q].rows1 * a[q].rows2, per = NT >> lw;
     blocks += (rows + per - 1) / per;
-    if (rows < 0 || rows > 0x7fffffff || blocks > 0x7fffffff) return hipErrorInvalidValue;
+    // (a launch of more than 2^32 - 1 threads would be cut short without an error)
+    if (rows < 0 || rows > 0x7fffffff || blocks > 0xffffffffLL / NT) return hipErrorInvalidValue;
   }
   if (blocks == 0) return hipSuccess;
   const dim3 grid((unsigned)blocks);

@@ -237,7 +237,9 @@ __global__ __launch_bounds__(NT) void gemm32_kernel(G32 g, int ntj) {
   }
 }
 
-int tiles_of(int M, int N, int T) { return ((M + T - 1) / T) * ((N + T - 1) / T); }
+int64_t tiles_of(int M, int N, int T) {
+  return (((int64_t)M + T - 1) / T) * (((int64_t)N + T - 1) / T);
+}
 
 // Tile edge of a product that is not sliced: the least of rounds of tiles over 256
 // compute units x tile area x the cost per element of that tile relative to the
@@ -254,7 +256,7 @@ int tile_edge(int M, int N) {
 // most 64 slices, each of at least two k steps
 constexpr int MAX_SLICES = 64;
 int slices_of(int M, int N, int K) {
-  const int want = std::min(MAX_SLICES, std::max(1, 512 / tiles_of(M, N, 64)));
+  const int want = (int)std::min<int64_t>(MAX_SLICES, std::max<int64_t>(1, 512 / tiles_of(M, N, 64)));
   return std::max(1, std::min(want, K / (2 * GBK)));
 }
 
@@ -266,7 +268,10 @@ hipError_t gemm32(const G32& g, hipStream_t s) {
                   (reinterpret_cast<uintptr_t>(g.A) & 15) == 0 &&
                   (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
   const int T = EPI == GRADIENT ? 64 : tile_edge(g.M, g.N);
-  const dim3 grid(tiles_of(g.M, g.N, T), EPI == GRADIENT ? (g.K + g.kslice - 1) / g.kslice : 1);
+  const int64_t tiles = tiles_of(g.M, g.N, T);
+  // (a launch of more than 2^32 - 1 threads would be cut short without an error)
+  if (tiles > 0xffffffffLL / NT) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)tiles, EPI == GRADIENT ? (g.K + g.kslice - 1) / g.kslice : 1);
   const int ntj = (g.N + T - 1) / T;
   if (T == 64) {
     if (al) gemm32_kernel<2, AC, BC, EPI, true><<<grid, NT, 0, s>>>(g, ntj);
@@ -652,7 +657,7 @@ int backward(thcsox_mlp_s* q, const float* x, int B) {
   MTRY(weights(0, q->DZ1, x));
   ss.out = q->Gr;
   ss.part = q->part;
-  ss.nparts = tiles_of(B, m, tile_edge(B, m));
+  ss.nparts = (int)tiles_of(B, m, tile_edge(B, m));
   ss.loss = q->loss;
   sum_slices<<<blocks_for(q->np) + 1, NT, 0, s>>>(ss, q->np);
   MTRY(hipGetLastError());
