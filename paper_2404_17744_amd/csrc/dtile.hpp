@@ -8,6 +8,9 @@ namespace thcsox {
 namespace {
 
 constexpr int TT = 128;          // tile edge of D (R and P)
+// two waves' 16 x 16 tiles side by side make a strip: a diagonal tile forms the strips' blocks
+// on and above its diagonal
+static_assert(SYM_BLOCK == 32 && TT % SYM_BLOCK == 0, "the strips are the blocks of a symmetric D");
 
 // All but the newest LEFT of this wave's memory loads (including those that write LDS)
 // and all of its LDS accesses complete, then the workgroup barrier.

@@ -32,6 +32,8 @@ namespace {
 constexpr int NXCD = 8;      // accelerator complex dies of an MI355X
 constexpr int TD = 64;       // tile edge of D
 constexpr int DK = 16;       // k per stage
+// two waves' 16 x 16 tiles side by side make a strip (see SYM_BLOCK)
+static_assert(SYM_BLOCK == 32 && TD % SYM_BLOCK == 0, "the strips are the blocks of a symmetric D");
 constexpr int BAND = 1;      // R blocks per band of the tile walk (measured at n = 300: 5 % faster than 4)
 
 // One panel of a stage: 64 rows of 16 k, the eight 16-byte pieces of row r permuted by

@@ -139,6 +139,7 @@ __global__ void fill_u64_kernel(unsigned long long* p, int64_t n, unsigned long 
 // and inside a diagonal tile the entries with R > P come from the mirrored
 // position.
 constexpr int DT = 32;          // reduction tile edge
+static_assert(SYM_BLOCK % DT == 0, "a tile on or above the diagonal lies in blocks that are written");
 constexpr int DRP = NT / DT;    // rows per pass
 constexpr int DEL = DT / DRP;   // elements per thread
 // (vector types of element alignment: rows of any length are read in 16- or 32-byte pieces)

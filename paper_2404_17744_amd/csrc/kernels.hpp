@@ -84,6 +84,10 @@ struct AStageB3Args {
 bool astage_bf3_fits(int n, int naux, int ldk);
 hipError_t astage_bf3(const AStageB3Args& a, hipStream_t s);
 
+// Edge of the blocks in which a symmetric D is formed (the strips of the fused kernels'
+// tiles): the reduction reads no block below the diagonal of this size.
+constexpr int SYM_BLOCK = 32;
+
 // The fused B/C/D stage for nsets tau points (grid.y), each:
 //   Dpart[z][R][P] = sum_{v in split z} (sum_q Gt[R][q] A[v][P][q]) (sum_w U[R][v][w] GXt[P][w])
 // A holds the mode's planes (fp16x2: scaled by the power of two taken from
@@ -103,8 +107,8 @@ struct FusedArgs {
   // partial sum, so storing it as FP32 is exact.
   bool dpart_f32;
   // If sym != nullptr and *sym != 0, D is symmetric (G(tau) and G(beta - tau)
-  // symmetric): tiles lying wholly below the diagonal (every R > every P) are
-  // skipped and their Dpart entries are left untouched.
+  // symmetric): only the SYM_BLOCK x SYM_BLOCK blocks on and above the diagonal are
+  // written; what Dpart holds below them is left from earlier launches.
   const int* sym;
   // set x of the launch: Gt and GXt lie x g_set, A x a_set and Dpart x d_set elements
   // (fp16x2 and FP32: halves; Dpart: of its own type) further, its flag at sym[x]
@@ -159,7 +163,7 @@ hipError_t ascale_bound(const unsigned long long* unorm2, const unsigned long lo
 
 // Sthc[R][P] = -factor * sum_z Dpart[z][R][P], factor = product of the inverse
 // operand scales (see scale_factor in the kernel source).
-// With sym != nullptr and *sym != 0 (symmetric D, lower tiles skipped by the
+// With sym != nullptr and *sym != 0 (symmetric D, lower blocks not written by the
 // fused stage), entries with R > P are taken from the mirrored position P, R.
 struct DReduceArgs {
   int naux, vsplit;
