@@ -493,14 +493,15 @@ int sigma_batch(thcsox_plan_s* p, const double* G, double* Sigma, double* Sthc_o
 }
 
 // Gt = X^T G[k] X into the direct-term buffer A and Gbt = X^T G[m-1-k] X into
-// buffer B for k0 <= k < k1 (k1 - k0 <= tbd), then Pi = Gt o Gbt^T into buffer C.
-int bubble_batch(thcsox_plan_s* p, const double* G, int k0, int k1) {
+// buffer B for k0 <= k < k1 (k1 - k0 <= cap), then Pi = Gt o Gbt^T into buffer C (buffers of
+// cap matrices).
+int bubble_batch(thcsox_plan_s* p, const double* G, int k0, int k1, int cap) {
   const int n = p->n, naux = p->naux, m = p->m, nb = k1 - k0;
   const hipStream_t s = p->stream;
   const int64_t nn = (int64_t)n * n, aa = (int64_t)naux * naux;
   double* bufA = p->dbuf;
-  double* bufB = p->dbuf + (int64_t)p->tbd * aa;
-  double* bufC = bufB + (int64_t)p->tbd * aa;
+  double* bufB = p->dbuf + (int64_t)cap * aa;
+  double* bufC = bufB + (int64_t)cap * aa;
   // T = X^T G for the batch (into Gt64, [nb][naux][n]) and Gt = T X; the same
   // for the mirrored points, walking G backwards
   for (int mirror = 0; mirror < 2; ++mirror) {
@@ -548,7 +549,7 @@ int direct_batch(thcsox_plan_s* p, const double* G, double* Sigma, int k0, int k
   double* bufA = p->dbuf;                          // Gt
   double* bufB = p->dbuf + (int64_t)p->tbd * aa;   // Gbt, then V Pi
   double* bufC = bufB + (int64_t)p->tbd * aa;      // Pi, then W, then W o Gt
-  TRY(bubble_batch(p, G, k0, k1));
+  TRY(bubble_batch(p, G, k0, k1, p->tbd));
   TRY(screen_both_sides(p, bufC, bufB, bufC, nb));
   HIP_TRY(hadamard64(bufC, bufA, bufC, (int64_t)nb * aa, p->stream));
   return backproject_batch(p, bufC, aa, Sigma + (int64_t)k0 * nn, nb, accumulate ? 1.0 : 0.0);
@@ -560,22 +561,24 @@ int direct_batch(thcsox_plan_s* p, const double* G, double* Sigma, int k0, int k
 // grid gives the same bits as the whole; a pair that is only half inside the range goes
 // with the others (a batch of few points takes as long as its launches: n = 79, naux =
 // 439, 7 of 9 points: 227 us, 358 with the half pairs apart, 293 by points).  The two
-// products of W are most of the term's flops: at n = 300, naux = 1800 the 100-point grid takes 33.6 ms by pairs, 61.0 by
-// points.
+// products of W are most of the term's flops: at n = 300, naux = 1800 the 100-point grid
+// takes 33.6 ms by pairs, 61.0 by points.  cap: pairs that the buffers hold; a batch
+// with only lower or only upper points in the range needs three per pair (the other side's
+// Gt makes room for V Pi), else four.
 int direct_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int l0, int l1, int k_begin,
-                 int k_end, bool accumulate) {
+                 int k_end, int cap, bool accumulate) {
   const int n = p->n, naux = p->naux, m = p->m, nb = l1 - l0;
-  const int64_t nn = (int64_t)n * n, aa = (int64_t)naux * naux, step = (int64_t)p->tbd * aa;
-  double* bufA = p->dbuf;          // Gt[l], then W o Gt[l]
-  double* bufB = bufA + step;      // Gt[m-1-l], then W^T o Gt[m-1-l]
-  double* bufC = bufB + step;      // Pi, then W
-  double* bufD = bufC + step;      // V Pi
+  const int64_t nn = (int64_t)n * n, aa = (int64_t)naux * naux, step = (int64_t)cap * aa;
   const double beta = accumulate ? 1.0 : 0.0;
   // the lower and the upper points in the range (the middle point of an odd grid is a
   // lower one)
   const int a0 = std::max(l0, k_begin), a1 = std::min(l1, k_end);
   const int b0 = std::max(l0, m - k_end), b1 = std::min({l1, m - k_begin, m / 2});
-  TRY(bubble_batch(p, G, l0, l1));
+  double* bufA = p->dbuf;          // Gt[l], then W o Gt[l]
+  double* bufB = bufA + step;      // Gt[m-1-l], then W^T o Gt[m-1-l]
+  double* bufC = bufB + step;      // Pi, then W
+  double* bufD = b0 >= b1 ? bufB : a0 >= a1 ? bufA : bufC + step;   // V Pi
+  TRY(bubble_batch(p, G, l0, l1, cap));
   TRY(screen_both_sides(p, bufC, bufD, bufC, nb));
   HIP_TRY(hadamard_pair(bufC, a0 < a1 ? bufA : nullptr, b0 < b1 ? bufB : nullptr, naux, nb,
                         p->stream));
@@ -588,14 +591,22 @@ int direct_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int l0, int l
 }
 
 // All tau points k_begin <= k < k_end by mirrored pairs: the lower points of the pairs that
-// the range touches are consecutive.
+// the range touches are consecutive.  A range on one side of the grid takes as many pairs
+// per batch as three buffers each allow where that saves a batch (n = 8, naux = 32, 16
+// lower points of 64: 41 us in one batch, 77 in batches of 12 and 4; by points 46.  With as
+// many batches either way the tiles decide: n = 160, naux = 800, 20 lower points: 1305 us as
+// 12 and 8, 1333 as 16 and 4, 1405 as 10 and 10).
 int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_begin, int k_end,
                        bool accumulate) {
   const int m = p->m, half = (m + 1) / 2;
-  const int first = k_end <= half ? k_begin : k_begin >= half ? m - k_end : std::min(k_begin, m - k_end);
-  const int end = k_end <= half ? k_end : k_begin >= half ? m - k_begin : half;
-  for (int l = first; l < end; l += p->tbd)
-    TRY(direct_pairs(p, G, Sigma, l, std::min(end, l + p->tbd), k_begin, k_end, accumulate));
+  const bool lower = k_end <= half, upper = k_begin >= half;
+  const int first = lower ? k_begin : upper ? m - k_end : std::min(k_begin, m - k_end);
+  const int end = lower ? k_end : upper ? m - k_begin : half;
+  const int more = lower || upper ? std::min(p->tb, 4 * p->tbd / 3) : p->tbd;
+  auto batches = [&](int per) { return (end - first + per - 1) / per; };
+  const int cap = batches(more) < batches(p->tbd) ? more : p->tbd;
+  for (int l = first; l < end; l += cap)
+    TRY(direct_pairs(p, G, Sigma, l, std::min(end, l + cap), k_begin, k_end, cap, accumulate));
   return 0;
 }
 
@@ -996,7 +1007,7 @@ int thcsox_static_screening(thcsox_plan_t p, const double* G_dev, double* W_dev)
   const int half = (m + 1) / 2;
   for (int l0 = 0; l0 < half; l0 += p->tbd) {
     const int l1 = std::min(half, l0 + p->tbd);
-    TRY(bubble_batch(p, G_dev, l0, l1));
+    TRY(bubble_batch(p, G_dev, l0, l1, p->tbd));
     HIP_TRY(weighted_pair_sum(bufC, p->w, m, l0, l1 - l0, naux, p->Pi0, l0 > 0 ? 1 : 0, s));
   }
   // W = (1 + V Pi0)^-1 V
