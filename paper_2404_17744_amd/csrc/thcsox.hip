@@ -844,27 +844,31 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
     // workgroups leaves compute units idle and a launch of a few microseconds is
     // mostly its own latency, so small systems take several points: about eight
     // workgroups per compute unit, and at least the A stage's sets.  Their A and
-    // partial tiles may add 1.2 times the memory that the plan takes anyway (or 2 MB), as
-    // long as three quarters of the device's memory stay free: plans that fill a device
-    // take what one point per launch needs.  Under a workspace limit they may
-    // only add what the buffers allocated on first use cannot need.
+    // partial tiles may add 1.2 times the memory that the plan takes anyway (or 2 MB), beyond
+    // 32 MB only as long as three quarters of the device's memory stay free: plans that fill
+    // a device take what one point per launch needs (asking the device costs a
+    // small plan a tenth of its construction).  Under a workspace limit they may only add
+    // what the buffers allocated on first use cannot need.
     int TR = 0, TP = 0;
     fused_tile(precision, &TR, &TP);
     const double wgs = std::ceil((double)naux / TR) * std::ceil((double)naux / TP) * p->vsplit;
     const double base = fixed + p->tb * per_tau;
     double room = std::max(1.2 * base, 2.0e6);
+    const double want = std::max((double)p->a_sets, std::ceil(8.0 * 256.0 / wgs));
+    const double extra = std::min(want, (double)p->tb) * (a_bytes + d_bytes);
     size_t free_now = 0, total = 0;
-    if (hipMemGetInfo(&free_now, &total) == hipSuccess)
-      room = std::min(room, (double)free_now - base - 0.75 * (double)total);
-    else
-      (void)hipGetLastError();
+    if (extra > 32.0e6) {
+      if (hipMemGetInfo(&free_now, &total) == hipSuccess)
+        room = std::min(room, std::max(32.0e6, (double)free_now - base - 0.75 * (double)total));
+      else
+        (void)hipGetLastError();
+    }
     if (workspace_limit > 0) {
       const double aa8 = 8.0 * naux * naux;
       const double later = aa8 * (3.0 * p->tb + 5.0) + row_bytes * naux * n * ldk +
                            16.0 * ntau * ((double)n * n + ntau + 1.0) + (1 << 20);
       room = std::min(room, (double)workspace_limit - base - later);
     }
-    const double want = std::max((double)p->a_sets, std::ceil(8.0 * 256.0 / wgs));
     const double fit = 1.0 + std::floor((room + (p->a_sets - 1) * a_bytes) / (a_bytes + d_bytes));
     const int sets = (int)std::min({want, fit, (double)p->tb});
     if (sets > 1 && sets >= p->a_sets) p->a_sets = p->f_sets = sets;
