@@ -350,82 +350,125 @@ __global__ void pair_scale_kernel(const double* S, int m, int64_t aa, double* sc
 // The network's rows x[b][k] and the THC self-energy's slices S[k][pair] are each other's
 // transposes: blocks of 64 pairs x 64 tau points go through LDS, so that both sides
 // are touched in whole lines (S in runs of 64 pairs, x in runs of up to 64 tau points).
-// naux = 505, 64 tau points: 41 us each, 4.9 TB/s (105 and 307 us with one side strided).
+// naux = 505, 64 tau points: 37 us each, 5.3 TB/s (106 and 309 us with one side strided).
+// Few tau points leave most of a block's threads idle, few pairs most of the chip, and
+// listed pairs are scattered anyhow: there one thread per element is faster (the rules
+// are with gather_by_blocks and scatter_by_blocks).
 constexpr int PT = 64;             // pairs and tau points per block
 constexpr int PTS = NT / PT;       // rows of a block per pass
 
-// x[b][k] = S[k][pair_b] / scale[pair_b]; pair_b = pairs[b] (or b if pairs is null)
-__global__ __launch_bounds__(NT) void pair_gather_kernel(const double* __restrict__ S, int m,
+// x[b][k] = S[k][pair_b] / scale[pair_b]; pair_b = pairs[b] (or b if pairs is null): one
+// thread per element, consecutive threads along tau
+__global__ void pair_gather_kernel(const double* S, int m, int64_t aa, const double* scale,
+                                   const int64_t* pairs, int64_t npairs, float* x) {
+  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < npairs * m;
+       e += (int64_t)gridDim.x * NT) {
+    const int64_t b = e / m;
+    const int k = (int)(e % m);
+    const int64_t pr = pairs ? pairs[b] : b;
+    x[e] = (pr >= 0 && pr < aa) ? (float)(S[(int64_t)k * aa + pr] / scale[pr]) : 0.f;
+  }
+}
+
+// the same by blocks
+__global__ __launch_bounds__(NT) void pair_gather_blocks(const double* __restrict__ S, int m,
                                                          int64_t aa,
                                                          const double* __restrict__ scale,
                                                          const int64_t* __restrict__ pairs,
-                                                         int64_t npairs, float* __restrict__ x) {
+                                                         int64_t npairs, int64_t first,
+                                                         float* __restrict__ x) {
   __shared__ float t[PT][PT + 1];   // [tau][pair]
   const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;
-  for (int64_t b0 = (int64_t)blockIdx.x * PT; b0 < npairs; b0 += (int64_t)gridDim.x * PT) {
-    const int64_t b = b0 + tx;
-    const int64_t pr = b < npairs ? (pairs ? pairs[b] : b) : -1;
-    const bool in = pr >= 0 && pr < aa;   // a pair outside the array reads as zero
-    const double sc = in ? scale[pr] : 1.0;
-    for (int k0 = 0; k0 < m; k0 += PT) {
-      const int nk = min(PT, m - k0);
-      double v[PT / PTS];
+  const int64_t b0 = first + (int64_t)blockIdx.x * PT;
+  const int64_t b = b0 + tx;
+  const int64_t pr = b < npairs ? (pairs ? pairs[b] : b) : -1;
+  const bool in = pr >= 0 && pr < aa;   // a pair outside the array reads as zero
+  const double sc = in ? scale[pr] : 1.0;
+  for (int k0 = 0; k0 < m; k0 += PT) {
+    const int nk = min(PT, m - k0);
+    double v[PT / PTS];
 #pragma unroll
-      for (int e = 0; e < PT / PTS; ++e)
-        v[e] = S[(int64_t)(k0 + min(ty + e * PTS, nk - 1)) * aa + (in ? pr : 0)];
+    for (int e = 0; e < PT / PTS; ++e)
+      v[e] = S[(int64_t)(k0 + min(ty + e * PTS, nk - 1)) * aa + (in ? pr : 0)];
 #pragma unroll
-      for (int e = 0; e < PT / PTS; ++e)
-        if (ty + e * PTS < nk) t[ty + e * PTS][tx] = in ? (float)(v[e] / sc) : 0.f;
-      __syncthreads();
-      // consecutive threads along tau, then along pairs
-      const int rows = (int)(npairs - b0 < PT ? npairs - b0 : PT);
-      for (int e = threadIdx.x; e < rows * nk; e += NT) {
-        const int r = e / nk, k = e - r * nk;
-        x[(b0 + r) * m + k0 + k] = t[k][r];
-      }
-      __syncthreads();
+    for (int e = 0; e < PT / PTS; ++e)
+      if (ty + e * PTS < nk) t[ty + e * PTS][tx] = in ? (float)(v[e] / sc) : 0.f;
+    __syncthreads();
+    // consecutive threads along tau, then along pairs
+    const int rows = (int)(npairs - b0 < PT ? npairs - b0 : PT);
+    for (int e = threadIdx.x; e < rows * nk; e += NT) {
+      const int r = e / nk, k = e - r * nk;
+      x[(b0 + r) * m + k0 + k] = t[k][r];
     }
+    __syncthreads();
   }
 }
 
-// S[k][pair] = y[pair][k] * scale[pair] for every pair
-__global__ __launch_bounds__(NT) void pair_scatter_kernel(const float* __restrict__ y, int m,
+// S[k][pair] = y[pair][k] * scale[pair] for every pair: one thread per element, consecutive
+// threads along pairs
+__global__ void pair_scatter_kernel(const float* y, int m, int64_t aa, const double* scale,
+                                    double* S) {
+  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < aa * m; e += (int64_t)gridDim.x * NT) {
+    const int k = (int)(e / aa);
+    const int64_t pr = e % aa;
+    S[e] = (double)y[pr * m + k] * scale[pr];
+  }
+}
+
+// the same by blocks
+__global__ __launch_bounds__(NT) void pair_scatter_blocks(const float* __restrict__ y, int m,
                                                           int64_t aa,
                                                           const double* __restrict__ scale,
-                                                          double* __restrict__ S) {
+                                                          int64_t first, double* __restrict__ S) {
   __shared__ float t[PT][PT + 1];   // [tau][pair]
   const int tx = threadIdx.x % PT, ty = threadIdx.x / PT;
-  for (int64_t p0 = (int64_t)blockIdx.x * PT; p0 < aa; p0 += (int64_t)gridDim.x * PT) {
-    const int rows = (int)(aa - p0 < PT ? aa - p0 : PT);
-    const double sc = tx < rows ? scale[p0 + tx] : 0.0;
-    for (int k0 = 0; k0 < m; k0 += PT) {
-      const int nk = min(PT, m - k0);
-      float v[PT * PT / NT];   // all in flight together (addresses clamped into the block)
+  const int64_t p0 = first + (int64_t)blockIdx.x * PT;
+  const int rows = (int)(aa - p0 < PT ? aa - p0 : PT);
+  const double sc = tx < rows ? scale[p0 + tx] : 0.0;
+  for (int k0 = 0; k0 < m; k0 += PT) {
+    const int nk = min(PT, m - k0);
+    float v[PT * PT / NT];   // all in flight together (addresses clamped into the block)
 #pragma unroll
-      for (int i = 0; i < PT * PT / NT; ++i) {
-        const int e = min((int)threadIdx.x + i * NT, rows * nk - 1), r = e / nk;
-        v[i] = y[(p0 + r) * m + k0 + e - r * nk];
-      }
-#pragma unroll
-      for (int i = 0; i < PT * PT / NT; ++i) {
-        const int e = (int)threadIdx.x + i * NT, r = e / nk;
-        if (e < rows * nk) t[e - r * nk][r] = v[i];
-      }
-      __syncthreads();
-      if (tx < rows)
-        for (int k = ty; k < nk; k += PTS)
-          S[(int64_t)(k0 + k) * aa + p0 + tx] = (double)t[k][tx] * sc;
-      __syncthreads();
+    for (int i = 0; i < PT * PT / NT; ++i) {
+      const int e = min((int)threadIdx.x + i * NT, rows * nk - 1), r = e / nk;
+      v[i] = y[(p0 + r) * m + k0 + e - r * nk];
     }
+#pragma unroll
+    for (int i = 0; i < PT * PT / NT; ++i) {
+      const int e = (int)threadIdx.x + i * NT, r = e / nk;
+      if (e < rows * nk) t[e - r * nk][r] = v[i];
+    }
+    __syncthreads();
+    if (tx < rows)
+      for (int k = ty; k < nk; k += PTS)
+        S[(int64_t)(k0 + k) * aa + p0 + tx] = (double)t[k][tx] * sc;
+    __syncthreads();
   }
 }
 
-// Workgroups of the two kernels above: a block of pairs each, and several where there are
-// more blocks than a launch takes (beyond 2^32 threads it drops the excess without an
-// error).
-unsigned pair_blocks(int64_t npairs) {
-  return (unsigned)std::min<int64_t>((npairs + PT - 1) / PT, 1 << 23);
+// Runs go(first pair, workgroups) for the two kernels by blocks, a workgroup per block of
+// pairs, in as many launches as it takes: one of more than 2^32 threads drops the excess
+// without an error (a loop over blocks in the kernels cost 6 to 9 % at 16 to 32 tau points).
+template <typename Go>
+void by_blocks(int64_t npairs, Go go) {
+  constexpr int64_t MOST = int64_t(1) << 23;
+  for (int64_t first = 0; first < npairs; first += MOST * PT)
+    go(first, (unsigned)std::min(MOST, (npairs - first + PT - 1) / PT));
 }
+
+// Where blocks pay (us, per element against by blocks; aa pairs in S):
+//   all pairs, aa = 255025: m = 16 13.5 / 15.1, 24 23.2 / 18.1; 40000: 32 5.8 / 6.7, 48 10.4 /
+//   8.0; 10201: 64 4.4 / 5.9, 95 9.4 / 8.1; with S beyond the 256 MB cache (aa = 3.24e6):
+//   m = 12 138 / 164, 16 199 / 179
+//   listed pairs (aa = 255025): 4096: m = 64 4.5 / 10.1, 95 9.4 / 16.1; 32768: 64 42 / 41,
+//   95 62 / 57; 262144: 16 75 / 73, 64 318 / 297 (aa = 10201: 16 21 / 30, 64 101 / 97)
+bool gather_by_blocks(bool listed, int64_t npairs, int64_t aa, int m) {
+  if (listed) return (npairs >= 32768 && m > 64) || (npairs >= 131072 && m >= 48);
+  return (m >= 24 && (m > 64 || npairs * m >= 1500000)) || (m >= 16 && aa * m > 32000000);
+}
+//   scatter, aa = 255025: m = 8 12.0 / 19.7, 12 24.9 / 20.7; 40000: 16 4.6 / 6.2, 24 7.4 /
+//   7.0; 10201: 100 7.3 / 8.1
+bool scatter_by_blocks(int64_t aa, int m) { return m >= 12 && aa >= 20000 && aa * m >= 900000; }
 
 unsigned blocks_for(int64_t n) {
   int64_t b = (n + NT - 1) / NT;
@@ -854,8 +897,15 @@ int thcsox_pair_gather(int m, int naux, const double* S_dev, const double* scale
       npairs < 0 || (pairs_dev == nullptr && npairs > aa))
     return set_error(THCSOX_EINVAL, "bad argument");
   if (npairs == 0) return 0;
-  pair_gather_kernel<<<pair_blocks(npairs), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
-      S_dev, m, aa, scale_dev, reinterpret_cast<const int64_t*>(pairs_dev), npairs, x_dev);
+  const int64_t* pairs = reinterpret_cast<const int64_t*>(pairs_dev);
+  const hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if (gather_by_blocks(pairs != nullptr, npairs, aa, m))
+    by_blocks(npairs, [&](int64_t first, unsigned blocks) {
+      pair_gather_blocks<<<blocks, NT, 0, s>>>(S_dev, m, aa, scale_dev, pairs, npairs, first, x_dev);
+    });
+  else
+    pair_gather_kernel<<<blocks_for(npairs * m), NT, 0, s>>>(S_dev, m, aa, scale_dev, pairs, npairs,
+                                                             x_dev);
   MTRY(hipGetLastError());
   return 0;
 }
@@ -866,8 +916,13 @@ int thcsox_pair_scatter(int m, int naux, const float* y_dev, const double* scale
   if (m <= 0 || naux <= 0 || S_dev == nullptr || scale_dev == nullptr || y_dev == nullptr)
     return set_error(THCSOX_EINVAL, "bad argument");
   const int64_t aa = (int64_t)naux * naux;
-  pair_scatter_kernel<<<pair_blocks(aa), NT, 0, static_cast<hipStream_t>(hip_stream)>>>(
-      y_dev, m, aa, scale_dev, S_dev);
+  const hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if (scatter_by_blocks(aa, m))
+    by_blocks(aa, [&](int64_t first, unsigned blocks) {
+      pair_scatter_blocks<<<blocks, NT, 0, s>>>(y_dev, m, aa, scale_dev, first, S_dev);
+    });
+  else
+    pair_scatter_kernel<<<blocks_for(aa * m), NT, 0, s>>>(y_dev, m, aa, scale_dev, S_dev);
   MTRY(hipGetLastError());
   return 0;
 }

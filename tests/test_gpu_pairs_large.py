@@ -51,3 +51,33 @@ def test_more_listed_pairs_than_a_launch_has_threads_for(dev):
     want = torch.cat([torch.zeros(1, device=dev), S.float(), torch.zeros(1, device=dev)])
     for c in _chunks(n):
         assert torch.equal(x[c], want[pairs[c] + 1]), c
+
+
+def test_blocks_in_several_launches(dev):
+    """Sixteen tau points of 2^29 pairs and more, the first size at which the forms by blocks
+    take two launches; values that FP32 holds exactly, so that they come back as they were."""
+    naux, m = 23171, 16
+    aa = naux * naux
+    assert aa > 1 << 29 and aa % 64 != 0
+
+    def values(k, c):
+        i = torch.arange(c.start, c.stop, device=dev)
+        return ((i * 7 + k * 13) % 2047 - 1023).double() * 0.25
+
+    S = torch.empty((m, aa), dtype=torch.float64, device=dev)
+    for k in range(m):
+        for c in _chunks(aa):
+            S[k, c] = values(k, c)
+    scale = torch.full((aa,), 2.0, dtype=torch.float64, device=dev)
+    x = torch.full((aa, m), 9.0, dtype=torch.float32, device=dev)
+    s = torch.cuda.current_stream().cuda_stream
+    print(f"case blocks naux{naux} m{m}", flush=True)
+    thcsox.thcsox_pair_gather(m, naux, S.data_ptr(), scale.data_ptr(), None, aa, x.data_ptr(), s)
+    for k in (0, 7, m - 1):
+        for c in _chunks(aa):
+            assert torch.equal(x[c, k], 0.5 * values(k, c).float()), (k, c)
+    S.zero_()
+    thcsox.thcsox_pair_scatter(m, naux, x.data_ptr(), scale.data_ptr(), S.data_ptr(), s)
+    for k in range(m):
+        for c in _chunks(aa):
+            assert torch.equal(S[k, c], values(k, c)), (k, c)
