@@ -247,6 +247,16 @@ namespace {
     if (rc_ != 0) return rc_; \
   } while (0)
 
+// The U build's chunk of q and the bytes of its temporaries: the Khatri-Rao chunk and, in the
+// split modes, its FP64 result.
+int u_chunk(int n, int naux) {
+  const size_t per_q = (size_t)n * naux * sizeof(double);
+  return (int)std::max<size_t>(1, std::min<size_t>((size_t)n, (size_t(256) << 20) / per_q));
+}
+double u_temps(int mode, int n, int naux) {
+  return (mode == MODE_F64 ? 1.0 : 2.0) * (8.0 * n * naux * u_chunk(n, naux) + 256.0);
+}
+
 // U_Pqs = sum_Q V_PQ X_qQ X_sQ in FP64, chunked over q, stored in the operand
 // planes Uout (the plan's U, or the second U of a screened core).  Split modes
 // first take max|U| into *amax_slot (pass 0; fp16x2 also the largest squared row
@@ -255,8 +265,7 @@ int build_u_passes(thcsox_plan_s* p, const double* V, void* Uout, unsigned long 
                    unsigned long long* norm_slot) {
   const int n = p->n, naux = p->naux, ldk = p->ldk;
   const hipStream_t s = p->stream;
-  size_t per_q = (size_t)n * naux * sizeof(double);
-  int qb = (int)std::max<size_t>(1, std::min<size_t>((size_t)n, (size_t(256) << 20) / per_q));
+  const int qb = u_chunk(n, naux);
   double* KR = nullptr;
   TRY(p->alloc(&KR, (size_t)qb * n * naux));
   double* Uc = nullptr;
@@ -611,16 +620,24 @@ int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_b
 }
 
 // The direct term's batch buffers of naux^2 per entry (also the screened exchange's
-// polarization batches), allocated on first use: about 1 GB per batch at most, and
-// no more than what the workspace limit leaves.  Three per tau point, or four per
-// mirrored pair of them where V is symmetric; the pairs take no more
-// memory than the points would (alloc refuses one point that does not fit with
-// THCSOX_ENOMEM).
+// polarization batches), allocated on first use: about 1 GB per batch at most, and no
+// more than what the workspace limit leaves beside the screened terms' own buffers, down to
+// one point.  Three per tau point, or four per mirrored pair of them where V is
+// symmetric; the pairs take no more memory than the points would (alloc refuses one point
+// that does not fit with THCSOX_ENOMEM).
 int ensure_direct_buffers(thcsox_plan_s* p) {
   if (p->dbuf != nullptr) return 0;
   const double one = 8.0 * (double)p->naux * p->naux;
   double cap = 1.0e9;
-  if (p->limit) cap = std::min(cap, (double)p->limit - (double)p->bytes - 256.0);
+  if (p->limit) {
+    // leave room for what the other terms allocate on first use (the limit's last bytes went
+    // into the batch before, and whether those terms still fitted was a matter of the
+    // remainder)
+    double others = u_temps(p->mode, p->n, p->naux);
+    if (p->Pi0 == nullptr) others += 3.0 * one + 8.0 * 33.0 * p->naux + 5.0 * 256.0;
+    if (p->Uw == nullptr) others += (double)p->np * p->esize * p->u_plane + 2.0 * 256.0;
+    cap = std::min(cap, (double)p->limit - (double)p->bytes - others - 256.0);
+  }
   const int points = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / (3.0 * one))));
   const int pairs = 3 * points / 4;
   const bool use_pairs = p->vsym && p->m > 1 && pairs > 0;
@@ -823,17 +840,18 @@ int thcsox_plan(thcsox_plan_t* out, int n, int naux, int ntau, double beta,
   // while their A arrays take at most 2 GB together
   if (precision == THCSOX_FP16X2 && ntau > 1 && 2.0 * a_bytes <= 2.0e9) p->a_sets = 2;
   // tau batch of the projections and back-projection: up to 16 points within ~2 GB
+  // (under a workspace limit fp16x2 rows count as padded to 64, so that a batch leaves no
+  // less to the buffers allocated on first use than it would with such rows)
+  const double row = workspace_limit > 0 && precision == THCSOX_FP16X2 ? (n + 63) / 64 * 64 : ldk;
   const double per_tau = 8.0 * (2.0 * naux * n + (double)naux * naux + (double)n * naux) +
-                         row_bytes * ((2.0 * naux + n) * ldk);
+                         row_bytes * ((2.0 * naux + n) * row);
   // what the plan keeps besides (X, V and the per-tau scalars in FP64, U, A, the
   // partial tiles), plus 1 MiB of slack; the U build's temporaries (Khatri-Rao
   // chunk, and its FP64 result in the split modes) are allocated last and freed
   // after the build, so they count too
-  const double per_q = 8.0 * n * naux;
-  const double qb = std::max(1.0, std::min((double)n, std::floor((double)(size_t(256) << 20) / per_q)));
-  const double temps = qb * per_q * (precision == THCSOX_FP64 ? 1.0 : 2.0);
   const double fixed = 8.0 * ((double)n * naux + (double)naux * naux + 7.0 * ntau + 2.0) +
-                       row_bytes * naux * n * ldk + p->a_sets * a_bytes + d_bytes + temps + (1 << 20);
+                       (1.0 + p->a_sets) * row_bytes * naux * n * row + d_bytes +
+                       u_temps(precision, n, naux) + (1 << 20);
   {
     double cap = 2.0e9;
     if (workspace_limit > 0) cap = std::min(cap, (double)workspace_limit - fixed);

@@ -1,6 +1,8 @@
 """Workspace limits of the buffers that a plan allocates on first use: a call that does
 not fit is refused every time it is made, leaves nothing behind, and the plan serves
 the calls that do fit."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -135,3 +137,32 @@ def test_plan_on_a_part_filled_device(dev, precision):
     one = n * naux * 96 * {"fp64": 8, "fp32": 4, "bf16x3": 6, "fp16x2": 4}[precision]
     assert taken0 - taken1 >= 2 * one
     assert torch.equal(S0, S1)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp16x2"])
+def test_more_room_refuses_no_term(dev, precision):
+    """A small system under rising limits: once the direct term, the screening and the screened
+    exchange all fit, in whichever order they are called, they fit with every larger limit.
+    (Their buffers, allocated on first use, take less than the megabyte that a plan leaves.)"""
+    n, naux, m = 20, 100, 32
+    s, tau, w, G, X, V, Gd = _inputs(dev, n, naux, m)
+    calls = {"direct": lambda p: p.sigma_direct(Gd), "screening": lambda p: p.static_screening(Gd),
+             "screened": lambda p: p.sigma_screened(Gd, V, "g3w2")}
+    for order in itertools.permutations(calls):
+        fitted = False
+        for limit in range(1500000, 9000000, 60001):
+            try:
+                plan = thcsox.Plan(X, V, tau, w, BETA, precision=precision, workspace_limit=limit)
+            except thcsox.ThcsoxError as e:
+                assert e.code == ENOMEM and not fitted, (order, limit)
+                continue
+            try:
+                for name in order:
+                    calls[name](plan)
+                fitted = True
+            except thcsox.ThcsoxError as e:
+                assert e.code == ENOMEM and not fitted, (order, limit)
+            finally:
+                torch.cuda.synchronize()
+                plan.close()
+        assert fitted, order
