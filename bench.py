@@ -310,8 +310,10 @@ def main():
                      "kernel": {"fp16x2": "fused_f16_kernel", "fp32": "fused_f32_kernel",
                                 "bf16x3": "fused_bf3_kernel",
                                 "fp64": "fused_f64_kernel"}[args.precision],
+                     # (a launch that covers several tau points counts once for each, with its
+                     # share of the time: these three are per tau point)
                      "avg_launch_ms": fused_avg, "launches": fused_n,
-                     "algorithmic_flop_per_launch": fused_flop,
+                     "algorithmic_flop_per_launch": fused_flop, "launch_unit": "one tau point",
                      "symmetric_tau_points": n_sym,
                      "plane_products": PRODUCTS[args.precision],
                      "mfma_busy_frac": achieved * PRODUCTS[args.precision] / peak},

@@ -337,7 +337,12 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nstep = g.naux * KST;
   // block -> (set x, worker y); the sets of worker y are the blocks 8 (X (y / 8) +
-  // x) + y % 8, on one XCD, so U is fetched from HBM once for all of them.  An XCD takes
+  // x) + y % 8, on one XCD, whose L2 serves U to all of them while they keep within the two
+  // steps that it holds beside the lines of A.  Nothing ties them: n = 300, two sets, 0.70
+  // GB fetched a launch where they keep together and 1.27 GB where they drift apart, which
+  // depends on what ran before and costs 1.5 % of the cycles.  (A written past the caches
+  // keeps them together, but takes as long, and the fused stage that reads A 3 to 4 %
+  // longer at n = 60 to 97.)  An XCD takes
   // consecutive steps, so the pieces of a row of A meet in its L2 (n = 97, naux = 485, 8
   // sets: 82 -> 79 us, and the fused stage that reads A 196 -> 191 us)
   const int X = g.nsets;

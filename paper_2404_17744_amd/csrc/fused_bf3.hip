@@ -28,7 +28,8 @@
 // load has two phases to land.  n = 120, naux = 600: 181 -> 146 us a tau point against
 // two buffers with D in LDS and loads one phase ahead.  The first chunk of a v starts the
 // accumulators from zero inside the MFMA.  Past the last chunk the loads repeat it
-// (never used).
+// (never used).  The compiler keeps 635 scalar values of the 14 tile forms in lanes of
+// vector registers (67 with one form).
 #include <type_traits>
 
 #include "dtile.hpp"

@@ -35,15 +35,17 @@
 //
 // What bounds it: the matrix cores run 0.65 of the time; the rest is the LDS writes of the
 // loads and the fragment reads that one wave per SIMD hides only in part (n = 300, naux =
-// 1800, a pair of v of a full tile: 21.3 us; 16.8 without the loads, 13.8 without the
-// reads either).  Two buffers with D in LDS, loads one phase ahead and fragments read a
-// phase ahead (which spilled) took 25.8, and its 64 single-word stores a thread 8.6
-// instead of 3.4 us a tile.  Whole launches: n = 300, symmetric, fp16x2 1.83 -> 1.62 ms a tau
-// point; n = 97, naux = 485 30.2 -> 24.0 us; n = 149, naux = 797, general, FP32 590 -> 555
-// us.  The loads are issued in inline assembly: tracked ones would make the compiler wait
-// before it reads another part of LDS.  The first chunk of a pair starts the accumulators
-// from zero inside the MFMA (no register clearing).  Past the last chunk the loads
-// repeat it (never used).
+// 1800, a pair of v of a full tile: 21.3 us; 19.9 with loads that always hit the L2, 16.8
+// without the loads, 13.8 without the reads either).  The L2 misses come at a plain copy's
+// rate (7.7 GB a tau point in 1.65 ms).  Two buffers with D in LDS, loads one phase ahead and
+// fragments read a phase ahead (which spilled) took 25.8, and its 64 single-word stores a
+// thread 8.6 instead of 3.4 us a tile.  Whole launches: n = 300, symmetric, fp16x2 1.83 ->
+// 1.62 ms a tau point; n = 97, naux = 485 30.2 -> 24.0 us; n = 149, naux = 797, general,
+// FP32 590 -> 555 us.  The loads are issued in inline assembly: tracked ones would make the
+// compiler wait before it reads another part of LDS.  The first chunk of a pair starts the
+// accumulators from zero inside the MFMA (no register clearing).  Past the last chunk the
+// loads repeat it (never used).  The compiler keeps 257 scalar values of the 14 tile forms
+// in lanes of vector registers (FP32: 217, and 9 vector registers in scratch).
 #include <type_traits>
 
 #include "dtile.hpp"

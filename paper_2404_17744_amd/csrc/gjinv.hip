@@ -19,7 +19,7 @@
 // so wide panels pay (32 columns while a thread's row fits its registers), and it
 // keeps the next 16 rows' loads in flight while one group is multiplied (256
 // matrices of n = 300: 199 us a panel, 3.7 TB/s; 245 without).  The panel is a serial
-// chain of n pivot steps (69 us per 32 columns at n = 300, 41 at n = 77).  Together
+// chain of n pivot steps (69 us per 32 columns at n = 300, 49 at n = 77).  Together
 // 2.7 ms per 256 matrices of n = 300; 7.6 ms with panels of 8 columns in LDS, row
 // swaps in memory and the update on the vector units.
 #include <algorithm>

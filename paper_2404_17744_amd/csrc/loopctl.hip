@@ -61,9 +61,11 @@ __global__ __launch_bounds__(NT) void combine_kernel(int64_t n, Entries h, bool 
 // The new residual r = x - z (z null: r = x) into res (res null: it is stored already, at
 // x), a copy of keep into keep_to (len_keep values; null: none), and part[e][block] =
 // the workgroup's part of <r, a_e>, a_e null standing for r itself (fixed order).
-// One pass over everything a new history entry touches: at n = 300, 100 tau and a
-// history of three, 0.3 ms for what a copy, a difference, a dot product per entry
-// (each waited for by the host) and two updates per entry took 0.9 ms for.
+// One pass over everything a new history entry touches.  A whole step at n = 300, 100
+// tau points and a history of six takes 243 us, 398 with a copy, a difference, a dot product
+// per entry (each waited for by the host) and two updates per entry; at n = 77, 64 points
+// 51 and 173.  Bound by its bytes: with commutator residuals (n = 300, 256 frequencies,
+// three entries, 1.5 GB) 0.46 ms, 3.2 TB/s.
 __global__ __launch_bounds__(NT) void push_kernel(int64_t n, const double* x, const double* z,
                                                   double* res, int64_t len_keep, const double* keep,
                                                   double* keep_to, Entries h,

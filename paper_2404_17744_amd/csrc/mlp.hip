@@ -489,9 +489,10 @@ unsigned blocks_for(int64_t n) {
 // lane's results are four consecutive outputs of one row, one 16-byte store.
 // What bounds it: the weights come from L2 for every block of rows, one flop per row
 // and byte, so 128 rows (all of the LDS at H = 512) halve the 17 TB/s that 64 rows
-// need at the matrix cores' rate; the next k step's weights are loaded while one is
-// multiplied.  m = 64, H = 512, 255025 rows: 373 us (563 with 64 rows and no prefetch),
-// about half of it the silu of two hidden layers, which no wave's products overlap.
+// need at the 1127 TFLOP/s of a large library product; the next k step's weights are
+// loaded while one is multiplied.  m = 64, H = 512, 255025 rows: 373 us (563 with 64 rows
+// and no prefetch), about half of it the silu of two hidden layers, which no wave's
+// products overlap.
 constexpr int INW = 8, INTH = 64 * INW;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
