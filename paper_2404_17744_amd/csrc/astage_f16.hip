@@ -325,11 +325,17 @@ template <int KST> struct RBuf {
 // M = MODE_F16X2, or MODE_F32: FP32 K-major rows, whose 32-wide k chunks are
 // 128 bytes as in c32, so the loads, the LDS layout and the stores are the same;
 // a chunk is eight 16x16x4 FP32 MFMAs per tile (lane group g takes k = 8 g + j,
-// 32 contiguous bytes, in both operands), and A is written unscaled as FP32 (n = 149,
-// naux = 797: 132 us per 2 points, 330 us through the general kernel, which larger n take).
+// 32 contiguous bytes, in both operands), and A is written unscaled as FP32.  With
+// an odd number of chunks product j takes k = 4 j + g instead, the order of the
+// general kernel (gemm_kmajor_f32) that these sizes took before: their FP32 results are
+// held bit for bit, where the other order moves Sigma by 9e-8 (n = 149) with the same
+// error against FP64.  The 4-byte reads cost 10.7 us a point against 9.7 (n = 80), 70.8
+// against 65.9 (149; 330 per 2 points through the general kernel), 203 against 185 (210),
+// 401 against 370 (285).
 template <int M, int KST>
 __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0, RBuf<KST>& b1) {
   constexpr bool F32 = M == MODE_F32;
+  constexpr bool SEQ = F32 && KST % 2 == 1;
   constexpr int NCT = (KST + 1) / 2;        // 16-column tiles per wave: 4 waves cover ldk columns
   constexpr int LDK = 32 * KST;
   constexpr int LD2 = 2 * LDK;              // halves per c32 row
@@ -370,6 +376,15 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
   auto gload = [&](int f) {
     const int t = f / (2 * KST), c = (f / 2) % KST, p = f % 2;
     const int v = 16 * (NCT * wave + t) + (lane & 15);
+    if constexpr (SEQ) {   // k = 32 c + 4 (4 p + e) + lane / 16, e < 4
+      const uint32_t gv = (uint32_t)(v * LD2 * 2 + (lane >> 4) * 4);
+      u4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[e] = __builtin_amdgcn_raw_buffer_load_b32(rG, gv, c * 128 + 64 * p + 16 * e, 0);
+      gr[t][c][p] = __builtin_bit_cast(f16x8, x);
+      return;
+    }
     const uint32_t gv = (uint32_t)((v * LD2 + (F32 ? 16 : 8) * (lane >> 4)) * 2);
     gr[t][c][p] = __builtin_bit_cast(
         f16x8, __builtin_amdgcn_raw_buffer_load_b128(rG, gv, (c * 64 + (F32 ? 8 : 32) * p) * 2, 0));
@@ -407,7 +422,14 @@ __device__ __forceinline__ void astage_r_body(const AStageArgs& g, RBuf<KST>& b0
   int uoff[2];
 #pragma unroll
   for (int p = 0; p < 2; ++p) uoff[p] = lr * 64 + sw8a(lr, F32 ? 2 * kc + p : 4 * p + kc) * 8;
-  auto uread = [&](const RBuf<KST>& bf, int c, int a, int p) {
+  auto uread = [&](const RBuf<KST>& bf, int c, int a, int p) -> f16x8 {
+    if constexpr (SEQ) {   // float lane / 16 of the 16-byte pieces 4 p .. 4 p + 3
+      f4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[e] = reinterpret_cast<const float*>(&bf.u[c][(16 * a + lr) * 64 + sw8a(lr, 4 * p + e) * 8])[kc];
+      return __builtin_bit_cast(f16x8, x);
+    }
     return *reinterpret_cast<const f16x8*>(&bf.u[c][uoff[p] + a * 16 * 64]);
   };
   // the two 16-row halves of a step run one after the other on the same
