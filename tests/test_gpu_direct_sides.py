@@ -12,11 +12,11 @@ from paper_2404_17744_amd import synth, thcsox
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("limit_matrices", [0, 7, 13])
+@pytest.mark.parametrize("buffers", [0, 4, 12])
 @pytest.mark.parametrize("m", [44, 45])
-def test_one_sided_ranges(dev, m, limit_matrices):
-    """Without a limit a batch holds 12 pairs or 16 points; with room for 13 matrices 3 pairs
-    or 4 points, for 7 one pair or one point."""
+def test_one_sided_ranges(dev, m, buffers):
+    """Without a limit a batch holds 12 pairs or 16 on one side; with 12 buffers of naux^2 it
+    holds 3 or 4, with 4 one."""
     n, naux = 5, 290
     s = synth.make_system(n, naux, seed=m)
     tau, w = synth.cheb_tau_grid(m, 100.0)
@@ -27,21 +27,32 @@ def test_one_sided_ranges(dev, m, limit_matrices):
     plan = thcsox.Plan(X, V, tau, w, 100.0)
     whole = plan.sigma_direct(Gd)
     assert np.abs(whole.cpu().numpy() - ref).max() <= 1e-11 * np.abs(ref).max()
-    if limit_matrices:
-        # (what the plan takes under a limit depends on it: find one that leaves that room)
-        taken, one = plan.info()["bytes"], 8 * naux * naux
+    if buffers:
+        # (what a plan takes under a limit, and keeps for its other terms, depends on the
+        # limit: find one that leaves the direct term these)
+        one = 8 * naux * naux
+        top = 2 * plan.info()["bytes"]
         plan.close()
-        limit = taken + limit_matrices * one
-        while True:
-            plan = thcsox.Plan(X, V, tau, w, 100.0, workspace_limit=limit)
-            room = limit - plan.info()["bytes"]
-            if room <= (limit_matrices + 0.5) * one:
+        for limit in range(8 * one, top, one // 2):
+            try:
+                plan = thcsox.Plan(X, V, tau, w, 100.0, workspace_limit=limit)
+            except thcsox.ThcsoxError as e:
+                assert e.code == -2   # out of the limit's room
+                continue
+            before = plan.info()["bytes"]
+            try:
+                plan.sigma_direct(Gd)
+            except thcsox.ThcsoxError as e:
+                assert e.code == -2
+                plan.close()
+                continue
+            if round((plan.info()["bytes"] - before) / one) == buffers:
                 break
             plan.close()
-            limit -= max(room - int((limit_matrices + 0.5) * one), 256)
-        assert room >= 3.5 * one
+        else:
+            pytest.fail(f"no limit leaves {buffers} buffers")
     half = (m + 1) // 2
-    print(f"case direct one side m{m} limit {limit_matrices}", flush=True)
+    print(f"case direct one side m{m} buffers {buffers}", flush=True)
     for k in (1, 3, 4, 5, 12, 13, 16, 17, half - 1, half):
         for a, b in ((0, k), (m - k, m), (half - k, half), (half, min(m, half + k))):
             S = torch.full_like(Gd, 3.0)
