@@ -604,14 +604,20 @@ int direct_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int l0, int l
 // per batch as three buffers each allow where that saves a batch (n = 8, naux = 32, 16
 // lower points of 64: 41 us in one batch, 77 in batches of 12 and 4; by points 46.  With as
 // many batches either way the tiles decide: n = 160, naux = 800, 20 lower points: 1305 us as
-// 12 and 8, 1333 as 16 and 4, 1405 as 10 and 10).
+// 12 and 8, 1333 as 16 and 4, 1405 as 10 and 10).  Where the workspace limit leaves
+// no more than one point's three buffers, each side of the grid goes by itself, with the
+// bits of the pairs: a limit does not change the result.
 int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_begin, int k_end,
                        bool accumulate) {
   const int m = p->m, half = (m + 1) / 2;
   const bool lower = k_end <= half, upper = k_begin >= half;
+  if (p->dbufs == 3 && !lower && !upper) {
+    TRY(direct_range_pairs(p, G, Sigma, k_begin, half, accumulate));
+    return direct_range_pairs(p, G, Sigma, half, k_end, accumulate);
+  }
   const int first = lower ? k_begin : upper ? m - k_end : std::min(k_begin, m - k_end);
   const int end = lower ? k_end : upper ? m - k_begin : half;
-  const int more = lower || upper ? std::min(p->tb, 4 * p->tbd / 3) : p->tbd;
+  const int more = p->dbufs == 4 && (lower || upper) ? std::min(p->tb, 4 * p->tbd / 3) : p->tbd;
   auto batches = [&](int per) { return (end - first + per - 1) / per; };
   const int cap = batches(more) < batches(p->tbd) ? more : p->tbd;
   for (int l = first; l < end; l += cap)
@@ -620,27 +626,30 @@ int direct_range_pairs(thcsox_plan_s* p, const double* G, double* Sigma, int k_b
 }
 
 // The direct term's batch buffers of naux^2 per entry (also the screened exchange's
-// polarization batches), allocated on first use: about 1 GB per batch at most, and no
-// more than what the workspace limit leaves beside the screened terms' own buffers, down to
-// one point.  Three per tau point, or four per mirrored pair of them where V is
-// symmetric; the pairs take no more memory than the points would (alloc refuses one point
-// that does not fit with THCSOX_ENOMEM).
+// polarization batches), allocated on first use: about 1 GB per batch at most.  Three per
+// tau point, or four per mirrored pair of them where V is symmetric; the pairs take no
+// more memory than the points would (alloc refuses one point that does not fit with
+// THCSOX_ENOMEM).  Under a workspace limit the batch leaves the screened terms' own buffers
+// their room, down to one pair or point (else the limit's last bytes would go into the
+// batch, and whether those terms still fitted would be a matter of the remainder); a limit
+// that has no room for them beside one point leaves all of it to the batch.
 int ensure_direct_buffers(thcsox_plan_s* p) {
   if (p->dbuf != nullptr) return 0;
   const double one = 8.0 * (double)p->naux * p->naux;
+  const bool by_pairs = p->vsym && p->m > 1;
   double cap = 1.0e9;
+  bool beside = false;   // room for the screened terms beside the batch
   if (p->limit) {
-    // leave room for what the other terms allocate on first use (the limit's last bytes went
-    // into the batch before, and whether those terms still fitted was a matter of the
-    // remainder)
     double others = u_temps(p->mode, p->n, p->naux);
     if (p->Pi0 == nullptr) others += 3.0 * one + 8.0 * 33.0 * p->naux + 5.0 * 256.0;
     if (p->Uw == nullptr) others += (double)p->np * p->esize * p->u_plane + 2.0 * 256.0;
-    cap = std::min(cap, (double)p->limit - (double)p->bytes - others - 256.0);
+    const double left = (double)p->limit - (double)p->bytes - 256.0;
+    beside = left - others >= 3.0 * one;
+    cap = std::min(cap, beside ? left - others : left);
   }
   const int points = (int)std::max(1.0, std::min((double)p->tb, std::floor(cap / (3.0 * one))));
-  const int pairs = 3 * points / 4;
-  const bool use_pairs = p->vsym && p->m > 1 && pairs > 0;
+  const int pairs = std::max(3 * points / 4, beside && p->tb > 1 && cap >= 4.0 * one ? 1 : 0);
+  const bool use_pairs = by_pairs && pairs > 0;
   p->tbd = use_pairs ? std::min(pairs, (p->m + 1) / 2) : points;
   const int bufs = use_pairs ? 4 : 3;
   TRY(p->alloc(&p->dbuf, (size_t)bufs * p->tbd * p->naux * p->naux));
@@ -1005,7 +1014,7 @@ int thcsox_sigma_direct(thcsox_plan_t p, const double* G_dev, double* Sigma_dev,
   const char* s0 = reinterpret_cast<const char*>(Sigma_dev);
   if (s0 < g0 + gbytes && g0 < s0 + gbytes) return fail(THCSOX_EINVAL, "Sigma aliases G");
   TRY(ensure_direct_buffers(p));
-  if (p->dbufs == 4)
+  if (p->vsym && p->m > 1)
     return direct_range_pairs(p, G_dev, Sigma_dev, k_begin, k_end, accumulate != 0);
   for (int k = k_begin; k < k_end; k += p->tbd)
     TRY(direct_batch(p, G_dev, Sigma_dev, k, std::min(k_end, k + p->tbd), accumulate != 0));

@@ -12,11 +12,11 @@ from paper_2404_17744_amd import synth, thcsox
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("buffers", [0, 4, 12])
+@pytest.mark.parametrize("buffers", [0, 3, 4, 12])
 @pytest.mark.parametrize("m", [44, 45])
 def test_one_sided_ranges(dev, m, buffers):
     """Without a limit a batch holds 12 pairs or 16 on one side; with 12 buffers of naux^2 it
-    holds 3 or 4, with 4 one."""
+    holds 3 or 4, with 4 one, with 3 one of one side."""
     n, naux = 5, 290
     s = synth.make_system(n, naux, seed=m)
     tau, w = synth.cheb_tau_grid(m, 100.0)
@@ -54,7 +54,8 @@ def test_one_sided_ranges(dev, m, buffers):
     half = (m + 1) // 2
     print(f"case direct one side m{m} buffers {buffers}", flush=True)
     for k in (1, 3, 4, 5, 12, 13, 16, 17, half - 1, half):
-        for a, b in ((0, k), (m - k, m), (half - k, half), (half, min(m, half + k))):
+        for a, b in ((0, k), (m - k, m), (half - k, half), (half, min(m, half + k)),
+                     (half - k, min(m, half + k)), (0, m)):
             S = torch.full_like(Gd, 3.0)
             plan.sigma_direct(Gd, a, b, out=S)
             assert torch.equal(S[a:b], whole[a:b]), (a, b)
