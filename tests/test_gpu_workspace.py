@@ -128,6 +128,7 @@ def test_plan_on_a_part_filled_device(dev, precision):
         return S, taken
 
     print(f"case part-filled device {precision}", flush=True)
+    torch.cuda.empty_cache()   # (what other tests left cached is not free either)
     S0, taken0 = run()
     held = torch.empty(torch.cuda.mem_get_info()[1] // 3, dtype=torch.uint8, device=dev)
     S1, taken1 = run()
